@@ -143,13 +143,13 @@ size_t ksa_prefill_workspace_bytes(const ksa_layout *layout);
  *   *_strides = {batch, row, head} strides in elements; NULL = contiguous in the order above.
  *   lse: device fp32 [B, Hq, L] contiguous, natural-log sum-exp of the scaled visible scores; may be NULL.
  *   workspace: device memory, 16-byte aligned, at least ksa_prefill_workspace_bytes(layout) bytes, owned by the
- *   caller; the call overwrites it (a preparation pass re-lays V out key-major for the main kernel and takes the
- *   largest K row norm of every KV head, from which the main kernel derives a fixed softmax reference per row
- *   wherever |q| max |k| * scale is small enough to rule out overflow and underflow; other rows keep a running
- *   maximum) and needs it until the work enqueued on `stream` has finished.  Calls that share a workspace must be
- *   stream-ordered.
+ *   caller, and needed until the work enqueued on `stream` has finished.  What the call writes there depends on the
+ *   layout: a key-major copy of V and the largest K row norms (long key runs), the norms alone (short ones), or nothing
+ *   (chunk shapes that are no powers of two).  From the norms the kernels derive a fixed softmax reference per row wherever
+ *   |q| max |k| * scale is small enough to rule out overflow and underflow; other rows keep a running maximum.  Calls that
+ *   share a workspace must be stream-ordered.
  *   stream: hipStream_t (NULL = default stream).
- * The main kernel walks the layout's schedule: bf16 MFMA for Q K^T and P V, fp32 online softmax.
+ * bf16 MFMA for Q K^T and P V over the live key tiles of every query tile, fp32 online softmax.
  * Value range: the weights of a row are kept within [2^-88, 2^32] relative to its reference and summed in fp32, so
  * the output is finite as long as max |v| times the number of visible keys stays below 2^95.
  * Errors: INVALID_ARG (null tensors or workspace, misaligned pointers: 16-byte alignment required),

@@ -98,6 +98,7 @@ int prefill_call(ksa_layout *lay, const void *q, const void *k, const void *v, v
     a.aug_len = lay->aug_len;
     a.workspace = workspace;
     a.workspace_bytes = workspace_bytes;
+    a.direct = lay->direct;
     a.phases = phases;
     return ksa_launch_prefill(a, stream);
 }

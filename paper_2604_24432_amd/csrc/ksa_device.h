@@ -53,6 +53,21 @@ __device__ __forceinline__ void lds_direct_load_16_s(const __bf16 *sbase, unsign
                  : "memory");
 }
 
+// Division of an index x in [0, 2^30) by a fixed d in [1, 2^30] as one multiplication: with 2^(s-1) < d <= 2^s the
+// quotient is (x * M) >> (31 + s), M = floor(2^(31 + s) / d) + 1 < 2^32 (Granlund and Montgomery: exact for x < 2^31,
+// because M d exceeds 2^(31 + s) by at most d <= 2^s).
+struct KsaDivisor {
+    uint32_t mul, shift;
+};
+inline KsaDivisor ksa_divisor(int d) {
+    uint32_t s = 0;
+    while (((int64_t)1 << s) < d) ++s;
+    return {(uint32_t)(((uint64_t)1 << (31 + s)) / (uint64_t)d + 1), s};
+}
+__device__ __forceinline__ int ksa_div(int x, const KsaDivisor &d) {
+    return (int)(__umulhi((unsigned)x * 2u, d.mul) >> d.shift);
+}
+
 inline int log2_exact(int x) {
     if (x <= 0 || (x & (x - 1))) return -1;
     int s = 0;

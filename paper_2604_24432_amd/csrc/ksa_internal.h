@@ -16,6 +16,7 @@ struct ksa_layout {
     int32_t n_pipelined_entries = 0;  // length of the first part (a multiple of 8)
     int32_t n_pipelined_items = 0;    // items with KsaWorkItem::pipelined set
     int32_t head_stack = 1;           // query heads per workgroup (1, 2 or 4)
+    bool direct = false;              // the forward pass takes the kernel for short key runs (see takes_direct)
     int32_t q_tile_rows = KSA_Q_TILE; // rows of a query tile = KSA_Q_TILE / head_stack
     // device copies (owned), valid on `device` once uploaded
     int device = -1;
@@ -41,11 +42,15 @@ struct KsaPrefillLaunch {
     ksa_params p;
     int64_t aug_len;
     void *workspace;          // key-major copy of V, written by the launch itself
+    bool direct;              // run the kernel for short key runs instead (ksa_prefill_direct.hip)
     int32_t phases;           // bit 0: write the key-major copy of V; bit 1: run the attention kernels
     size_t workspace_bytes;
 };
 size_t ksa_prefill_workspace_size(const ksa_params &p);
 int ksa_launch_prefill(const KsaPrefillLaunch &a, void *stream);
+// The kernel for short key runs and chunk shapes that are no powers of two (ksa_prefill_direct.hip).  knorm_tiles, knorm:
+// the row-norm parts of the workspace.
+int ksa_launch_prefill_direct(const KsaPrefillLaunch &a, float *knorm_tiles, float *knorm, int32_t norm_tiles, void *stream);
 
 struct KsaPrefillBwdLaunch {
     const void *q, *k, *v, *o, *d_o;

@@ -111,6 +111,28 @@ bool item_pipelined(const ksa_params &p, const KsaWorkItem &it) {
     return true;
 }
 
+// Which of the two forward kernels a layout takes: true = ksa_prefill_direct.hip.
+//   - Chunk shapes that are no powers of two always (c 48, m 6, 16K tokens, 32/8 heads, d 128: 0.63 -> 0.36 ms; 6K tokens,
+//     12/4 heads, d 64: 124 -> 54 us): the other kernel's pipelined loop maps rows with shifts.
+//   - Otherwise by the mean number of key tiles per query tile.  Up to the line the pipelined kernel's time goes into what
+//     its workgroups, alone on their compute unit, do outside the tile loop; beyond it the direct kernel's doubled operand
+//     traffic costs more.  Measured on both sides (pipelined / direct kernel, us, c 64, m 8 unless stated):
+//       d 128, 4 heads of a group per workgroup: 4K tokens (7 tiles) 134 / 93, 16K (17) 388 / 340, 28K (28) 904 / 873,
+//         32K (31) 1118 / 1105, 64K (60) 3800 / 4030; 32K with c 128, m 16 and outlier keys, where the pipelined kernel
+//         tracks row maxima (33), 1450 / 1300; no summaries: window 2048 (31) 495 / 497, causal 4K (33) 131 / 142;
+//       2 heads: 32K (33) 617 / 570, 64K (62) 1991 / 2053;
+//       1 head, 16 heads: 16K (20) 271 / 195, 48K (52) 1382 / 1285, 64K (66) 2214 / 2173, causal 8K (66) 247 / 263;
+//       d 64: 16K 268 / 218, 64K 2425 / 2275, 128K 9110 / 8728, 256K (8/2 heads, 231) 8550 / 8600, 512K (460) 16560 / 16970.
+bool takes_direct(const ksa_layout &lay) {
+    const ksa_params &p = lay.p;
+    auto pow2 = [](int64_t x) { return x > 0 && (x & (x - 1)) == 0; };
+    if (!pow2(p.chunk_len) || (p.n_summary > 0 && !pow2(p.n_summary))) return true;
+    int64_t tiles = 0;
+    for (const KsaWorkItem &it : lay.items) tiles += it.n_tiles;
+    const int64_t line = p.head_dim == 64 ? 230 : lay.head_stack == 4 ? (p.n_summary > 0 ? 34 : 30) : lay.head_stack == 2 ? 48 : 56;
+    return tiles <= line * (int64_t)lay.items.size();
+}
+
 // Launch order.  Workgroups are dealt to the 8 XCDs round-robin by workgroup id, and each XCD has its
 // own L2: queue q (workgroup ids congruent to q mod 8) is given whole (batch, KV head) groups so that the
 // workgroups running together on one XCD stream the same K/V rows, and items go heaviest first so the
@@ -207,6 +229,7 @@ int ksa_build_layout(const ksa_params *params, ksa_layout **out) {
     std::stable_sort(lay->items.begin(), lay->items.end(), [](const KsaWorkItem &a, const KsaWorkItem &b) {
         return a.pipelined != b.pipelined ? a.pipelined > b.pipelined : a.n_tiles > b.n_tiles;
     });
+    lay->direct = takes_direct(*lay);
     build_entries(*lay, 0, lay->n_pipelined_items);
     lay->n_pipelined_entries = (int32_t)lay->entries.size();
     build_entries(*lay, lay->n_pipelined_items, (int32_t)lay->items.size());

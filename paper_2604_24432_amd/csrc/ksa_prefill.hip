@@ -1317,6 +1317,7 @@ int ksa_launch_prefill(const KsaPrefillLaunch &L, void *stream) {
         // ... and so are the ones into the key-major copy of V (head_dim rows of nt_pad or ns_pad keys)
         if ((int64_t)L.p.head_dim * (a.nt_pad > a.ns_pad ? a.nt_pad : a.ns_pad) >= ((int64_t)1 << 31)) return KSA_ERR_UNSUPPORTED;
     }
+    if (L.phases == 3 && L.direct) return ksa_launch_prefill_direct(L, a.knorm_tiles, a.knorm, (a.nt_pad + a.ns_pad) / 64, stream);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (L.phases & 1) {
         const int tiles_text = a.nt_pad / 64, tiles_sum = a.ns_pad / 64;

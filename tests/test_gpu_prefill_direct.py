@@ -1,0 +1,63 @@
+"""GPU parity of the forward kernel for short key runs and for chunk shapes that are no powers of two
+(csrc/ksa_prefill_direct.hip) at the sizes where it can go wrong: query tiles of 1 to 129 rows, key lists that end on and
+beside a multiple of 64, tiles that hold the last summaries and the first text rows, chunks of 64 and more rows, every head
+stack, and rows so far apart that such mixed tiles are not formed.  Tolerances as in test_gpu_prefill.py."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_24432_amd as K
+from paper_2604_24432_amd import synth
+from oracle import ksa_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+MAX_ABS, MEAN_ABS, LSE_ABS = 2e-2, 2e-3, 4e-3
+
+SHAPES = [
+    # B, Hq, Hkv, d, n, c, m, C
+    *[(1, 4, 1, 128, n, 12, 3, 1) for n in (1, 11, 12, 31, 33, 64, 129)],
+    *[(1, 2, 1, 64, n, 8, 1, 2) for n in (63, 65, 127, 257)],
+    (2, 3, 1, 128, 300, 20, 5, 2),          # three heads per group: one head per workgroup
+    (1, 8, 1, 128, 700, 48, 6, 2),          # two slices of four heads
+    (1, 2, 2, 64, 650, 96, 12, 1),          # chunks longer than a key tile
+    (1, 2, 2, 128, 1100, 192, 64, 0),       # ... with summaries that fill one
+    (1, 2, 1, 128, 700, 100, 0, 3),         # no summaries
+    (1, 4, 2, 128, 1024, 128, 16, 1),       # powers of two: fixed reference
+    (3, 2, 1, 128, 515, 1, 0, 70),          # token window
+]
+
+
+def compare(got, ref, what):
+    o, lse = (x.float().cpu().numpy().astype(np.float64) for x in got)
+    err, lerr = np.abs(o - ref[0]), np.abs(lse - ref[1])
+    print(f"{what}: max-abs {err.max():.3e} mean-abs {err.mean():.3e} lse {lerr.max():.3e}", flush=True)
+    assert np.isfinite(o).all() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS and lerr.max() <= LSE_ABS, what
+
+
+@pytest.mark.parametrize("outliers", [0.0, 0.03])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_edges(shape, outliers):
+    B, Hq, Hkv, d, n, c, m, C = shape
+    cfg = synth.KsaConfig("direct", B, Hq, Hkv, d, n, c, m, C, seed=n + c, key_outlier_frac=outliers)
+    q, k, v = synth.make_prefill_inputs(cfg)
+    flags = K.KSA_FLAG_SUMMARY_SELF_ONLY if m > 1 and n % 2 else 0
+    lay = K.ksa_build_layout(K.make_params(B, n, c, m, C, Hq, Hkv, d, flags=flags))
+    got = K.ksa_prefill_fwd(lay, q.cuda(), k.cuda(), v.cuda())
+    ref = O.prefill(q.float().numpy(), k.float().numpy(), v.float().numpy(), n, c, m, C, flags=flags)
+    compare(got, ref, str(shape))
+
+
+def test_rows_far_apart():
+    """K / V rows 8 MiB apart: the rows of a tile across the border of summaries and text are beyond 32-bit offsets."""
+    n, c, m, C = 95, 20, 5, 1
+    cfg = synth.KsaConfig("far", 1, 2, 1, 64, n, c, m, C, seed=9)
+    q, k, v = synth.make_prefill_inputs(cfg)
+    stride = 1 << 22
+    far = [torch.empty(cfg.aug_len * stride, dtype=torch.bfloat16, device="cuda").as_strided(k.shape, (0, stride, 64, 1)) for _ in "kv"]
+    for x, y in zip(far, (k, v)):
+        x.copy_(y)
+    lay = K.ksa_build_layout(K.make_params(1, n, c, m, C, 2, 1, 64))
+    got = K.ksa_prefill_fwd(lay, q.cuda(), *far)
+    ref = O.prefill(q.float().numpy(), k.float().numpy(), v.float().numpy(), n, c, m, C)
+    compare(got, ref, "rows 8 MiB apart")
