@@ -9,7 +9,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libksa.so")
 PROBE_LIB = os.path.join(HERE, "libksa_probe.so")   # bench.py's measurement probes (csrc/ksa_probe.hip), not the product
-SOURCES = ["ksa_layout.cpp", "ksa_api.cpp", "ksa_prefill.hip", "ksa_prefill_direct.hip", "ksa_prefill_bwd.hip", "ksa_decode.hip", "ksa_cache.hip"]
+SOURCES = ["ksa_layout.cpp", "ksa_api.cpp", "ksa_prefill.hip", "ksa_prefill_direct.hip", "ksa_prefill_bwd.hip", "ksa_prefill_bwd_sum.hip",
+           "ksa_decode.hip", "ksa_cache.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 VALU instructions are kept out of the generated code (hand-written none either)

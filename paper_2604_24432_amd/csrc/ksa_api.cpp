@@ -35,6 +35,7 @@ void ksa_layout_destroy(ksa_layout *lay) {
     if (!lay) return;
     if (lay->d_items) (void)hipFree(lay->d_items);
     if (lay->d_entries) (void)hipFree(lay->d_entries);
+    if (lay->d_dkv) (void)hipFree(lay->d_dkv);
     delete lay;
 }
 
@@ -43,25 +44,24 @@ int ksa_layout_upload(ksa_layout *lay) {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return KSA_ERR_HIP;
     if (lay->d_items && lay->device == dev) return KSA_OK;
-    if (lay->d_items) {
+    auto drop = [&]() {
         (void)hipFree(lay->d_items);
         (void)hipFree(lay->d_entries);
-        lay->d_items = lay->d_entries = nullptr;
-    }
+        (void)hipFree(lay->d_dkv);
+        lay->d_items = lay->d_entries = lay->d_dkv = nullptr;
+        return KSA_ERR_HIP;
+    };
+    if (lay->d_items) (void)drop();
     const size_t ib = lay->items.size() * sizeof(KsaWorkItem), eb = lay->entries.size() * sizeof(KsaWgEntry);
-    if (hipMalloc(&lay->d_items, ib) != hipSuccess) return KSA_ERR_HIP;
-    if (hipMalloc(&lay->d_entries, eb) != hipSuccess) {
-        (void)hipFree(lay->d_items);
-        lay->d_items = nullptr;
-        return KSA_ERR_HIP;
-    }
+    const size_t kb = lay->dkv_entries.size() * sizeof(KsaDkvEntry), sb = lay->dkv_splits.size() * sizeof(KsaDkvSplit);
+    if (hipMalloc(&lay->d_items, ib) != hipSuccess || hipMalloc(&lay->d_entries, eb) != hipSuccess ||
+        hipMalloc(&lay->d_dkv, kb + sb) != hipSuccess)
+        return drop();
     if (hipMemcpy(lay->d_items, lay->items.data(), ib, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(lay->d_entries, lay->entries.data(), eb, hipMemcpyHostToDevice) != hipSuccess) {
-        (void)hipFree(lay->d_items);
-        (void)hipFree(lay->d_entries);
-        lay->d_items = lay->d_entries = nullptr;
-        return KSA_ERR_HIP;
-    }
+        hipMemcpy(lay->d_entries, lay->entries.data(), eb, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(lay->d_dkv, lay->dkv_entries.data(), kb, hipMemcpyHostToDevice) != hipSuccess ||
+        (sb > 0 && hipMemcpy(static_cast<char *>(lay->d_dkv) + kb, lay->dkv_splits.data(), sb, hipMemcpyHostToDevice) != hipSuccess))
+        return drop();
     lay->device = dev;
     return KSA_OK;
 }
@@ -149,6 +149,10 @@ int ksa_prefill_bwd(ksa_layout *lay, const void *q, const void *k, const void *v
     a.entries = static_cast<const KsaWgEntry *>(lay->d_entries);
     a.n_entries = (int32_t)lay->entries.size();
     a.head_stack = lay->head_stack;
+    a.dkv_entries = static_cast<const KsaDkvEntry *>(lay->d_dkv);
+    a.n_dkv_entries = (int32_t)lay->dkv_entries.size();
+    a.dkv_splits = reinterpret_cast<const KsaDkvSplit *>(a.dkv_entries + a.n_dkv_entries);
+    a.n_dkv_splits = (int32_t)lay->dkv_splits.size();
     a.p = p;
     a.aug_len = lay->aug_len;
     a.workspace = workspace;

@@ -18,10 +18,14 @@ struct ksa_layout {
     int32_t head_stack = 1;           // query heads per workgroup (1, 2 or 4)
     bool direct = false;              // the forward pass takes the kernel for short key runs (see takes_direct)
     int32_t q_tile_rows = KSA_Q_TILE; // rows of a query tile = KSA_Q_TILE / head_stack
+    std::vector<KsaDkvEntry> dkv_entries;   // backward dK / dV, per (batch, KV head), longest first
+    std::vector<KsaDkvSplit> dkv_splits;    // the tiles whose work is dealt to several workgroups
+    int32_t dkv_slots = 0;                  // scratch slots per (batch, KV head)
     // device copies (owned), valid on `device` once uploaded
     int device = -1;
     void *d_items = nullptr;
     void *d_entries = nullptr;
+    void *d_dkv = nullptr;            // dkv_entries, then dkv_splits
 };
 
 // Validates the problem statement; returns KSA_OK or the error.
@@ -61,6 +65,9 @@ struct KsaPrefillBwdLaunch {
     const KsaWgEntry *entries;
     int32_t n_entries;
     int32_t head_stack;       // query heads per workgroup of the schedule
+    const KsaDkvEntry *dkv_entries;   // NULL: every key tile is one workgroup
+    const KsaDkvSplit *dkv_splits;
+    int32_t n_dkv_entries, n_dkv_splits;
     ksa_params p;
     int64_t aug_len;
     void *workspace;          // delta_i = dO_i . O_i per (batch, query head, row), fp32
@@ -68,6 +75,16 @@ struct KsaPrefillBwdLaunch {
 };
 size_t ksa_prefill_bwd_workspace_size(const ksa_params &p, int64_t aug_len);
 int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &a, void *stream);
+// Second step of the split dK / dV tiles (ksa_prefill_bwd_sum.hip).
+struct KsaDkvSumArgs {
+    const float *scratch;
+    const KsaDkvSplit *splits;
+    void *dk, *dv;
+    int64_t strides[3];       // of dk and dv, {batch, row, head}
+    int32_t n_splits, sum_tiles, n_text, n_sum, c, m, n_kv_heads, n_bh, head_dim;
+    float scale;
+};
+void ksa_launch_dkv_sum(const KsaDkvSumArgs &a, void *stream);
 
 struct KsaDecodeLaunch {
     const void *q, *k_cache, *v_cache;

@@ -175,6 +175,59 @@ void build_entries(ksa_layout &lay, int32_t item_lo, int32_t item_hi) {
         for (size_t x = 0; x < queue[q].size(); ++x) lay.entries[base + x * KSA_NUM_XCD + q] = queue[q][x];
 }
 
+// Steps of the dK / dV work of the keys [k0, k1) of an index space, per query head: the aligned 64-row query blocks that
+// overlap the two runs of rows that can see one of them (the kernel works the same runs out).
+int64_t dkv_blocks(const ksa_params &p, int space, int64_t k0, int64_t k1) {
+    const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = (int64_t)(p.n_text / c) * m;
+    const int64_t per = space == KSA_SPACE_TEXT ? c : m, jl = k0 / per, jh = (k1 - 1) / per;
+    const int64_t b0 = space == KSA_SPACE_TEXT ? k0 : std::min<int64_t>((jl + C + 1) * c, p.n_text);
+    const int64_t e0 = space == KSA_SPACE_TEXT ? std::min<int64_t>((jh + C + 1) * c, p.n_text) : p.n_text;
+    const int64_t b1 = space == KSA_SPACE_TEXT ? jl * m : k0, e1 = std::min<int64_t>((jh + 1) * m, n_sum);
+    auto blocks = [](int64_t b, int64_t e) { return e > b ? (e - 1) / KSA_K_TILE - b / KSA_K_TILE + 1 : 0; };
+    return blocks(b0, e0) + blocks(b1, e1);
+}
+
+// The backward pass's dK / dV work of one (batch, KV head).  A summary key is seen by every later text row, so the first
+// tile of 128 of them is as long as hundreds of text tiles: on short sequences a few workgroups would run long after the
+// others have finished.  Tiles longer than the launch's mean work per compute unit are therefore dealt to several
+// workgroups, whose fp32 partial sums a second kernel adds up in a fixed order (whole backward pass, c 64, m 8, d 128, before /
+// after: 2 x 4096 tokens, 32/8 heads 723 / 452 us; 16K 2490 / 1472; 32K 6150 / 4800; 16K, 8/1 heads 3600 / 435; pieces of half
+// or a quarter of the mean: 465 / 1480 / 4880 / 433 and 465 / 1530 / 4845 / 477).  A piece is at least 32 steps (a step takes
+// about 1.3 us; writing and adding up a piece's 128 KB of partial sums 5 - 10), and all partial sums have to fit into the
+// memory of dq (see ksa_launch_prefill_bwd), which holds batch * rows * query heads / 512 of them.
+void build_dkv(ksa_layout &lay) {
+    const ksa_params &p = lay.p;
+    const int64_t n_sum = (int64_t)lay.n_chunks * p.n_summary, group = p.n_q_heads / p.n_kv_heads;
+    const int64_t n_bh = (int64_t)p.batch * p.n_kv_heads;
+    const int64_t sum_tiles = (n_sum + KSA_DKV_KEYS - 1) / KSA_DKV_KEYS, text_tiles = (p.n_text + KSA_DKV_KEYS - 1) / KSA_DKV_KEYS;
+    std::vector<int64_t> steps(sum_tiles + text_tiles);
+    int64_t total = 0;
+    for (int64_t t = 0; t < sum_tiles + text_tiles; ++t) {
+        const int space = t < sum_tiles ? KSA_SPACE_SUMMARY : KSA_SPACE_TEXT;
+        const int64_t k0 = (t < sum_tiles ? t : t - sum_tiles) * KSA_DKV_KEYS, n = t < sum_tiles ? n_sum : p.n_text;
+        steps[t] = dkv_blocks(p, space, k0, std::min<int64_t>(k0 + KSA_DKV_KEYS, n)) * group;
+        total += steps[t];
+    }
+    const int64_t capacity = (int64_t)p.batch * lay.aug_len * p.n_q_heads / 512 / n_bh;
+    int64_t longest = std::max<int64_t>(32, total * n_bh / 256);
+    auto slots_at = [&](int64_t most) {
+        int64_t n = 0;
+        for (int64_t x : steps) n += x > most ? (x + most - 1) / most : 0;
+        return n;
+    };
+    while (slots_at(longest) > capacity) longest *= 2;   // (0 once no tile is longer)
+    for (int64_t t = 0; t < (int64_t)steps.size(); ++t) {
+        const int64_t pieces = steps[t] > longest ? (steps[t] + longest - 1) / longest : 1;
+        if (pieces > 1) lay.dkv_splits.push_back({(int32_t)t, lay.dkv_slots, (int32_t)pieces, 0});
+        for (int64_t x = 0; x < pieces; ++x)
+            lay.dkv_entries.push_back({(int32_t)t, (int32_t)(steps[t] * x / pieces), (int32_t)(steps[t] * (x + 1) / pieces),
+                                       pieces > 1 ? lay.dkv_slots++ : -1});
+    }
+    std::stable_sort(lay.dkv_entries.begin(), lay.dkv_entries.end(), [](const KsaDkvEntry &a, const KsaDkvEntry &b) {
+        return a.step_end - a.step_begin > b.step_end - b.step_begin;
+    });
+}
+
 }  // namespace
 
 int ksa_validate_params(const ksa_params *p) {
@@ -233,6 +286,7 @@ int ksa_build_layout(const ksa_params *params, ksa_layout **out) {
     build_entries(*lay, 0, lay->n_pipelined_items);
     lay->n_pipelined_entries = (int32_t)lay->entries.size();
     build_entries(*lay, lay->n_pipelined_items, (int32_t)lay->items.size());
+    build_dkv(*lay);
     } catch (...) {
         delete lay;
         return KSA_ERR_OUT_OF_MEMORY;

@@ -5,11 +5,13 @@
 //   dV_j  = sum_i P_ij G_i
 //   dS_ij = P_ij (G_i.v_j - delta_i),  delta_i = G_i.O_i  (= sum_l P_il G_i.v_l)
 //   dQ_i  = scale sum_j dS_ij k_j,     dK_j = scale sum_i dS_ij q_i
-// Three kernels, no atomics, results independent of the launch order:
+// No atomics, results independent of the launch order:
 //   ksa_bwd_delta_kernel  delta_i and lse_i log2(e) per (batch, head, row), in compact row order, into the workspace;
 //   ksa_bwd_dq_kernel     one workgroup per query tile of the forward schedule walks that tile's key runs;
 //   ksa_bwd_dkv_kernel    one workgroup per 128-key tile of an index space walks the query rows that can see it
-//                         (two runs, closed form from Eq. 3), for every query head of the KV head's group.
+//                         (two runs, closed form from Eq. 3), for every query head of the KV head's group; where that
+//                         would leave the chip waiting for a few long tiles, several workgroups share a tile and
+//                         ksa_bwd_dkv_sum_kernel (ksa_prefill_bwd_sum.hip) adds up their fp32 partial sums.
 // Both main kernels recompute the scores with v_mfma_f32_32x32x16_bf16 and keep the result block in the layout
 // whose registers are the B operand of the next product: dQ works on S^T (keys x queries, the forward kernel's
 // layout, per-lane query statistics), dK/dV on S (queries x keys, per-lane key, per-register query statistics
@@ -32,6 +34,7 @@ constexpr int BN = KSA_K_TILE;                // rows of an LDS tile
 constexpr int RW = BN / NW;                   // rows of a tile each wave fetches
 constexpr int QB = KSA_Q_TILE / (NW * 32);    // 32-row query blocks per wave (dQ kernel)
 constexpr int KEYS_PER_WG = NW * 32;          // dK/dV kernel: 32 keys per wave
+static_assert(KEYS_PER_WG == KSA_DKV_KEYS, "the schedule counts key tiles of this size");
 static_assert(BN == 64, "an LDS tile is two 32-row MFMA blocks");
 
 struct BwdArgs {
@@ -51,7 +54,10 @@ struct BwdArgs {
     int32_t group, n_q_heads, n_kv_heads, self_only, batch;
     int32_t stack, stack_shift;    // dQ kernel: query heads per workgroup of the forward schedule (1, 2 or 4), its log2
     int32_t n_text, n_sum;                    // rows per index space
-    int32_t sum_tiles;                        // dK/dV grid: summary-space key tiles come first (the long ones)
+    int32_t sum_tiles;                        // dK/dV: summary-space key tiles come first in the numbering
+    const KsaDkvEntry *dkv_entries;           // dK/dV: what the workgroups of a (batch, KV head) do
+    const KsaDkvSplit *dkv_splits;            // ... and the tiles whose partial sums are added up afterwards
+    float *scratch;                           // partial sums (the memory of dq, which is written last); NULL: no tile is split
     int64_t aug_len;
     float scale, scale_log2e;
 };
@@ -586,14 +592,20 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
     __shared__ __attribute__((aligned(256))) float st_lse[STAGES][BN], st_dl[STAGES][BN];
     __shared__ __attribute__((aligned(16))) int st_lo[STAGES][BN], st_span[STAGES][BN];   // visible keys: [lo, lo + span)
 
-    // Workgroup index -> (key tile, batch, KV head), the head running fastest: consecutive workgroup ids go to the
+    // Workgroup index -> (entry, batch, KV head), the head running fastest: consecutive workgroup ids go to the
     // XCDs round-robin, so with 8 (batch, KV head) pairs all key tiles of a head share one L2, and they walk the same
-    // query rows at about the same time (see the loop order below).  Summary-space tiles come first, oldest chunks
-    // first: their runs of query rows are the long ones.
+    // query rows at about the same time (see the loop order below).  An entry is a key tile or, where tiles are split, a
+    // piece of its sequence of steps; longest first.  Without a list the tiles follow in their numbering: summary-space
+    // tiles first, oldest chunks first, whose runs of query rows are the long ones.
     const int n_bh = a.n_kv_heads * a.batch;
     const int bh = blockIdx.x % n_bh;
     const int hkv = bh % a.n_kv_heads, b = bh / a.n_kv_heads;
     int t = blockIdx.x / n_bh, space = KSA_SPACE_SUMMARY;
+    int step_begin = 0, step_end = 0x7fffffff, slot = -1;
+    if (a.scratch) {
+        const KsaDkvEntry ent = a.dkv_entries[t];
+        t = ent.tile, step_begin = ent.step_begin, step_end = ent.step_end, slot = ent.slot;
+    }
     if (t >= a.sum_tiles) t -= a.sum_tiles, space = KSA_SPACE_TEXT;
     const int n_space = space == KSA_SPACE_TEXT ? a.n_text : a.n_sum;
     const int k0 = t * KEYS_PER_WG;
@@ -653,7 +665,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
         run_first_blk[x] = run_begin[x] / BN;
         run_tiles[x] = run_end[x] > run_begin[x] ? (run_end[x] - 1) / BN - run_first_blk[x] + 1 : 0;
     }
-    const int n_tiles = (run_tiles[0] + run_tiles[1]) * a.group;   // > 0: a key is seen by its own row at least
+    // > 0: a key is seen by its own row at least
+    const int n_tiles = min((run_tiles[0] + run_tiles[1]) * a.group, step_end) - step_begin;
     // Blocks [full_lo_blk, full_hi_blk) of a run (counted from the run's first block) are seen whole: no row of such
     // a block lies outside the run, and every row sees every key of the workgroup.  Visible ranges are monotone in
     // the row index (Eq. 3: both ends of a row's range never move backwards from one row to the next), so these
@@ -706,7 +719,9 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
     const unsigned q_row_elems = (unsigned)a.qs[1], g_row_elems = (unsigned)a.os[1];
     const unsigned q_head_elems = (unsigned)a.qs[2], g_head_elems = (unsigned)a.os[2];
     // the next tile of the sequence; stays on the last tile once the sequence is exhausted
-    int sq_run = run_tiles[0] > 0 ? 0 : 1, sq_ti = 0, sq_hj = 0;
+    const int steps0 = run_tiles[0] * a.group;   // steps of the text run
+    int sq_run = step_begin < steps0 ? 0 : 1;
+    int sq_ti = (step_begin - (sq_run ? steps0 : 0)) / a.group, sq_hj = step_begin - (sq_run ? steps0 : 0) - sq_ti * a.group;
     struct Request {
         const __bf16 *q_base, *g_base;   // row `first` of the tile (scalar)
         const float *lse_p, *dl_p;       // statistics of row `first` (scalar)
@@ -988,6 +1003,19 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
     // nothing of this workgroup is in flight any more when it leaves (the last requests fetched tiles nobody reads)
     __builtin_amdgcn_s_waitcnt(0x0F70);
     accumulators_settle();
+    if (slot >= 0) {   // a piece: the partial sums as they sit in the registers, one 16-byte store per lane and four of them
+        f32x4 *out = reinterpret_cast<f32x4 *>(a.scratch) + ((int64_t)slot * n_bh + bh) * (KEYS_PER_WG * D / 2) + wave * (D * 16) + lane;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                f32x4 xk, xv;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xk[e] = dkacc[db][g4 * 4 + e], xv[e] = dvacc[db][g4 * 4 + e];
+                out[(db * 4 + g4) * 128] = xk, out[(db * 4 + g4) * 128 + 64] = xv;
+            }
+        return;
+    }
     if (!key_valid) return;
     __bf16 *kp = a.dk + b * a.dks[0] + (int64_t)key_aug * a.dks[1] + hkv * a.dks[2];
     __bf16 *vp = a.dv + b * a.dks[0] + (int64_t)key_aug * a.dks[1] + hkv * a.dks[2];
@@ -1004,6 +1032,27 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
             *reinterpret_cast<bf16x4 *>(kp + db * 32 + g4 * 8 + h * 4) = pk;
             *reinterpret_cast<bf16x4 *>(vp + db * 32 + g4 * 8 + h * 4) = pv;
         }
+}
+
+template <int D, bool POW2>
+void launch_dkv(const BwdArgs &a, int entries, int splits, hipStream_t st) {
+    const int n_bh = a.n_kv_heads * a.batch;
+    hipLaunchKernelGGL((ksa_bwd_dkv_kernel<D, POW2>), dim3((unsigned)(entries * n_bh)), dim3(NW * 64), 0, st, a);
+    if (splits > 0) {
+        const KsaDkvSumArgs sum = {a.scratch, a.dkv_splits, a.dk, a.dv, {a.dks[0], a.dks[1], a.dks[2]}, splits, a.sum_tiles,
+                                   a.n_text, a.n_sum, a.c, a.m, a.n_kv_heads, n_bh, D, a.scale};
+        ksa_launch_dkv_sum(sum, st);
+    }
+}
+
+template <int D, bool POW2>
+void launch_all(const BwdArgs &a, int64_t n_rows, int dq_grid, int entries, int splits, hipStream_t st) {
+    const int64_t delta_blocks = (n_rows * (D / 8) + 255) / 256;
+    hipLaunchKernelGGL(ksa_bwd_delta_kernel<D>, dim3((unsigned)delta_blocks), dim3(256), 0, st, a, n_rows);
+    // with split key tiles dq holds their partial sums until it is written itself
+    if (a.scratch) launch_dkv<D, POW2>(a, entries, splits, st);
+    hipLaunchKernelGGL((ksa_bwd_dq_kernel<D, POW2>), dim3((unsigned)dq_grid), dim3(NW * 64), 0, st, a);
+    if (!a.scratch) launch_dkv<D, POW2>(a, entries, splits, st);
 }
 
 }  // namespace
@@ -1086,27 +1135,30 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
         // ... and the dK/dV kernel multiplies the head strides of q and d_o as unsigned 32-bit numbers
         if (a.qs[2] >= ((int64_t)1 << 32) || a.os[2] >= ((int64_t)1 << 32) || L.aug_len >= ((int64_t)1 << 31)) return KSA_ERR_UNSUPPORTED;
     }
-    const dim3 block(NW * 64), grid_dq(L.n_entries), grid_dkv((unsigned)((a.sum_tiles + text_tiles) * L.p.n_kv_heads * L.p.batch));
-    if (L.p.head_dim == 128) {
-        hipLaunchKernelGGL(ksa_bwd_delta_kernel<128>, dim3((unsigned)delta_blocks), dim3(256), 0, st, a, n_rows);
-        if (pow2)
-            hipLaunchKernelGGL((ksa_bwd_dq_kernel<128, true>), grid_dq, block, 0, st, a);
-        else
-            hipLaunchKernelGGL((ksa_bwd_dq_kernel<128, false>), grid_dq, block, 0, st, a);
-        if (pow2)
-            hipLaunchKernelGGL((ksa_bwd_dkv_kernel<128, true>), grid_dkv, block, 0, st, a);
-        else
-            hipLaunchKernelGGL((ksa_bwd_dkv_kernel<128, false>), grid_dkv, block, 0, st, a);
-    } else {
-        hipLaunchKernelGGL(ksa_bwd_delta_kernel<64>, dim3((unsigned)delta_blocks), dim3(256), 0, st, a, n_rows);
-        if (pow2)
-            hipLaunchKernelGGL((ksa_bwd_dq_kernel<64, true>), grid_dq, block, 0, st, a);
-        else
-            hipLaunchKernelGGL((ksa_bwd_dq_kernel<64, false>), grid_dq, block, 0, st, a);
-        if (pow2)
-            hipLaunchKernelGGL((ksa_bwd_dkv_kernel<64, true>), grid_dkv, block, 0, st, a);
-        else
-            hipLaunchKernelGGL((ksa_bwd_dkv_kernel<64, false>), grid_dkv, block, 0, st, a);
+    // The partial sums of split key tiles live in the memory of dq until dq is written: a dense dq that shares no byte with
+    // the other tensors (a caller may hand over one that does: dq is then written before dK and dV, as ever, and no tile is
+    // split).
+    int entries = a.sum_tiles + text_tiles, splits = 0;
+    a.scratch = nullptr, a.dkv_entries = L.dkv_entries, a.dkv_splits = L.dkv_splits;
+    if (L.n_dkv_splits > 0) {
+        const int64_t B = L.p.batch, Hq = a.n_q_heads, Hkv = a.n_kv_heads, d = L.p.head_dim, rows = L.aug_len;
+        const bool dense = a.dqs[2] == d && a.dqs[1] == Hq * d && (B == 1 || a.dqs[0] == rows * Hq * d);
+        const char *lo = reinterpret_cast<const char *>(a.dq), *hi = lo + B * rows * Hq * d * 2;
+        auto apart = [&](const void *x, int64_t bytes) {
+            const char *p = static_cast<const char *>(x);
+            return p + bytes <= lo || p >= hi;
+        };
+        auto extent = [&](const int64_t st[3], int64_t heads) { return 2 * ((B - 1) * st[0] + (rows - 1) * st[1] + (heads - 1) * st[2] + d); };
+        if (dense && apart(a.q, extent(a.qs, Hq)) && apart(a.k, extent(a.ks, Hkv)) && apart(a.v, extent(a.ks, Hkv)) &&
+            apart(a.o, extent(a.os, Hq)) && apart(a.g, extent(a.os, Hq)) && apart(a.dk, extent(a.dks, Hkv)) &&
+            apart(a.dv, extent(a.dks, Hkv)) && apart(a.lse, 4 * B * Hq * rows) && apart(L.workspace, (int64_t)L.workspace_bytes)) {
+            a.scratch = reinterpret_cast<float *>(a.dq);
+            entries = L.n_dkv_entries, splits = L.n_dkv_splits;
+        }
     }
+    if (L.p.head_dim == 128)
+        pow2 ? launch_all<128, true>(a, n_rows, L.n_entries, entries, splits, st) : launch_all<128, false>(a, n_rows, L.n_entries, entries, splits, st);
+    else
+        pow2 ? launch_all<64, true>(a, n_rows, L.n_entries, entries, splits, st) : launch_all<64, false>(a, n_rows, L.n_entries, entries, splits, st);
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
 }

@@ -41,6 +41,22 @@ struct KsaWorkItem {
     int32_t pad[2];
 };
 
+// Backward dK / dV: keys per workgroup, and what the workgroups of one (batch, KV head) do.  A key tile's work is a
+// sequence of steps (one 64-row query tile of one query head each, see ksa_bwd_dkv_kernel).  Tiles of the summary space
+// come first in the numbering.
+#define KSA_DKV_KEYS 128
+struct KsaDkvEntry {
+    int32_t tile;
+    int32_t step_begin, step_end;
+    int32_t slot;        // >= 0: partial sums go to this scratch slot; -1: the whole tile, results are stored directly
+};
+// A tile in several pieces: partial sums in slots [first_slot, first_slot + n_slots).
+struct KsaDkvSplit {
+    int32_t tile;
+    int32_t first_slot, n_slots;
+    int32_t pad;
+};
+
 // What workgroup blockIdx.x does: item < 0 means nothing.
 struct KsaWgEntry {
     int32_t item;
