@@ -181,8 +181,12 @@ int decode_call(const ksa_params *p, int32_t kind, const void *q, const void *k_
     if (n_splits < 0 || n_splits > 1024) return KSA_ERR_INVALID_ARG;
     if (kind == KSA_ROW_SUMMARY && p->n_summary == 0) return KSA_ERR_INVALID_ARG;
     if (p->n_q_heads / p->n_kv_heads > 8) return KSA_ERR_UNSUPPORTED;
-    if (n_splits == 0) n_splits = ksa_decode_default_splits(p);
+    const bool chosen = n_splits != 0;
+    if (!chosen) n_splits = ksa_decode_default_splits(p);
     if (workspace_bytes < ksa_decode_workspace_bytes(p, n_splits)) return KSA_ERR_WORKSPACE_TOO_SMALL;
+    // a summary token reads at most chunk_len + n_summary rows, whatever the cache holds: one span up to 768 rows (the
+    // shortest span of the default for a text token)
+    if (!chosen && kind == KSA_ROW_SUMMARY && p->chunk_len + p->n_summary <= 768) n_splits = 1;
     KsaDecodeLaunch a;
     default_strides(a.cache_strides, cache_strides, p->n_kv_heads, rows, p->head_dim);
     if (!strides_ok(a.cache_strides)) return KSA_ERR_INVALID_ARG;

@@ -2,13 +2,13 @@
 // (section 2.3.1).  The work is bandwidth bound: every visible K and V row is read from HBM exactly once
 // per KV head and serves all Hq/Hkv query heads of that head.
 //
-// Split-K: workgroup (split, kv head, batch) streams one span of the visible rows.  A cache row of
-// head_dim bf16 is read by head_dim/8 adjacent lanes with one 16-byte load each, so a wavefront load covers
-// 1 KiB of consecutive memory; U such loads of K and of V are in flight per lane.  Each lane keeps the
-// partial dot products of its 8 columns for all query heads of the group, a 4-step DPP all-reduce over the
-// row's lanes finishes the scores, and every lane group runs its own online softmax on the rows it saw.
-// The lane groups of a workgroup are merged through LDS into one partial (max, sum, o) per query head;
-// a second kernel merges the spans of a sequence by log-sum-exp.
+// Split-K: a workgroup streams one span of the visible rows of one (sequence, KV head).  A cache row of head_dim bf16 is
+// read by head_dim/8 adjacent lanes with one 16-byte load each, so a wavefront load covers 1 KiB of consecutive memory; U
+// such loads of K and of V are in flight per lane.  Each lane keeps the partial dot products of its 8 columns for all query
+// heads of the group, a 4-step DPP all-reduce over the row's lanes finishes the scores, and every lane group runs its own
+// online softmax on the rows it saw.  The lane groups of a wave are merged by lane swaps, the waves through LDS, into one
+// partial (max, sum, o) per query head; a second kernel merges the spans of a sequence by log-sum-exp.  With one span per
+// sequence (a summary token's few rows, small caches) the workgroup stores the result itself and there is no second kernel.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -25,7 +25,6 @@ namespace {
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int NT = 256;      // threads per workgroup
 constexpr int U = 4;         // row loads in flight per lane, K and V each
 
 struct DecodeArgs {
@@ -36,6 +35,7 @@ struct DecodeArgs {
     float *ws;
     int64_t cs[3];   // {batch, head, row} strides of the caches in elements
     int32_t n_splits, s_cap;
+    int32_t batch;
     int32_t kind, self_only;   // KSA_ROW_TEXT / KSA_ROW_SUMMARY query; flag bit 0 of the parameters
     int32_t c, m, C, n_text;
     int32_t n_q_heads, n_kv_heads;
@@ -107,13 +107,36 @@ __device__ __forceinline__ void unpack8(const u32x4 &x, float f[8]) {
     }
 }
 
+template <int D>
+__device__ __forceinline__ void store_result(const DecodeArgs &a, int b, int hq, int col, bool valid, float acc, float den, float M) {
+    const float out = valid ? acc / den : __builtin_nanf("");
+    a.o[((int64_t)b * a.n_q_heads + hq) * D + col] = (__bf16)out;
+    if (a.lse && col == 0)
+        a.lse[(int64_t)b * a.n_q_heads + hq] = valid ? M * 0.6931471805599453f + __logf(den) : __builtin_nanf("");
+}
+
+// values of lane l ^ 16 (rows of 16 lanes swapped pairwise) and of lane l ^ 32
+__device__ __forceinline__ float swap16(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __builtin_bit_cast(float, (threadIdx.x & 16) ? r[0] : r[1]);
+}
+__device__ __forceinline__ float swap32(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __builtin_bit_cast(float, (threadIdx.x & 32) ? r[0] : r[1]);
+}
+__device__ __forceinline__ float swap8(float x) {   // lane l ^ 8: row_ror 8
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xf, 0xf, false));
+}
+
 // partial record in the workspace: [D] unnormalised o, then running max (log2 domain), then running sum
-template <int D, int G>
+template <int D, int G, int NT>
 __global__ __launch_bounds__(NT) void ksa_decode_split_kernel(const DecodeArgs a) {
     constexpr int LPR = D / 8;          // lanes per cache row
     constexpr int RPW = 64 / LPR;       // rows per wavefront load
-    constexpr int NG = NT / LPR;        // lane groups per workgroup
-    constexpr int R_IT = (NT / 64) * RPW * U;   // rows per workgroup iteration
+    constexpr int NW = NT / 64;
+    constexpr int R_IT = NW * RPW * U;  // rows per workgroup iteration
 
     const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -199,71 +222,101 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_kernel(const DecodeArgs a
         }
     }
 
-    // ---- merge the NG lane groups of the workgroup ------------------------------------------------
-    __shared__ float sh_o[NG][G][D];
-    __shared__ float sh_m[NG][G], sh_l[NG][G];
-    const int grp = tid / LPR;
+    // ---- merge the lane groups of each wave, then the waves -----------------------------------------
+    __shared__ float sh_o[NW][G][D];
+    __shared__ float sh_m[NW][G], sh_l[NW][G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
+        float M = m_run[g];
+        if (LPR == 8) M = fmaxf(M, swap8(M));
+        M = fmaxf(M, swap16(M));
+        M = fmaxf(M, swap32(M));
+        const float f = __builtin_amdgcn_exp2f(m_run[g] - M);
+        auto merge = [&](float x) {
+            x *= f;
+            if (LPR == 8) x += swap8(x);
+            x += swap16(x);
+            return x + swap32(x);
+        };
+        const float l = merge(l_run[g]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sh_o[grp][g][chunk * 8 + e] = o[g][e];
-        if (chunk == 0) {
-            sh_m[grp][g] = m_run[g];
-            sh_l[grp][g] = l_run[g];
+        for (int e = 0; e < 8; ++e) o[g][e] = merge(o[g][e]);
+        if (gi == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sh_o[wave][g][chunk * 8 + e] = o[g][e];
+            if (chunk == 0) sh_m[wave][g] = M, sh_l[wave][g] = l;
         }
     }
     __syncthreads();
-    for (int x = tid; x < G * (D + 2); x += NT) {
-        const int g = x / (D + 2), col = x % (D + 2);
+    for (int x = tid; x < G * D; x += NT) {
+        const int g = x / D, col = x % D;
         float M = sh_m[0][g];
-        for (int y = 1; y < NG; ++y) M = fmaxf(M, sh_m[y][g]);
-        float acc = 0.f;
-        if (col < D) {
-            for (int y = 0; y < NG; ++y) acc += sh_o[y][g][col] * __builtin_amdgcn_exp2f(sh_m[y][g] - M);
-        } else if (col == D) {
-            acc = M;
-        } else {
-            for (int y = 0; y < NG; ++y) acc += sh_l[y][g] * __builtin_amdgcn_exp2f(sh_m[y][g] - M);
+#pragma unroll
+        for (int y = 1; y < NW; ++y) M = fmaxf(M, sh_m[y][g]);
+        float acc = 0.f, den = 0.f;
+#pragma unroll
+        for (int y = 0; y < NW; ++y) {
+            const float w = __builtin_amdgcn_exp2f(sh_m[y][g] - M);
+            acc += sh_o[y][g][col] * w, den += sh_l[y][g] * w;
         }
-        a.ws[(((int64_t)b * a.n_q_heads + hkv * G + g) * a.n_splits + split) * (D + 2) + col] = acc;
+        const int hq = hkv * G + g;
+        if (a.n_splits == 1) {
+            store_result<D>(a, b, hq, col, valid_pos(a, a.pos[b]), acc, den, M);
+        } else {
+            float *rec = a.ws + (((int64_t)b * a.n_q_heads + hq) * a.n_splits + split) * (D + 2);
+            rec[col] = acc;
+            if (col == 0) rec[D] = M, rec[D + 1] = den;
+        }
     }
 }
 
 // one workgroup of D threads per (batch, query head): log-sum-exp merge of the spans
 template <int D>
 __global__ __launch_bounds__(D) void ksa_decode_merge_kernel(const DecodeArgs a) {
-    const int hq = blockIdx.x, b = blockIdx.y, col = threadIdx.x;
+    const int hq = blockIdx.x, b = blockIdx.y, col = threadIdx.x, lane = threadIdx.x & 63;
     const float *rec = a.ws + ((int64_t)b * a.n_q_heads + hq) * a.n_splits * (D + 2);
     const bool valid = valid_pos(a, a.pos[b]);
     float M = -1e30f;
-    for (int s = 0; s < a.n_splits; ++s) M = fmaxf(M, rec[s * (D + 2) + D]);
+    for (int s = lane; s < a.n_splits; s += 64) M = fmaxf(M, rec[s * (D + 2) + D]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
     float acc = 0.f, den = 0.f;
-    for (int s = 0; s < a.n_splits; ++s) {
+#pragma unroll 8
+    for (int s = 0; s < a.n_splits; ++s) {   // unrolled: the loads of several spans travel together
         const float wgt = __builtin_amdgcn_exp2f(rec[s * (D + 2) + D] - M);
         acc += rec[s * (D + 2) + col] * wgt;
         den += rec[s * (D + 2) + D + 1] * wgt;
     }
-    const float out = valid ? acc / den : __builtin_nanf("");
-    a.o[((int64_t)b * a.n_q_heads + hq) * D + col] = (__bf16)out;
-    if (a.lse && col == 0)
-        a.lse[(int64_t)b * a.n_q_heads + hq] = valid ? M * 0.6931471805599453f + __logf(den) : __builtin_nanf("");
+    store_result<D>(a, b, hq, col, valid, acc, den, M);
 }
 
+template <int D, int G, int NT>
+void launch(const DecodeArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL((ksa_decode_split_kernel<D, G, NT>), dim3(a.n_splits, a.n_kv_heads, a.batch), dim3(NT), 0, st, a);
+    if (a.n_splits > 1) hipLaunchKernelGGL(ksa_decode_merge_kernel<D>, dim3(a.n_q_heads, a.batch), dim3(D), 0, st, a);
+}
+
+// 256 threads per span; with no more spans than compute units 1024 (512 with eight query heads per KV head, whose
+// accumulators take more registers), i.e. four times the loads in flight per unit.  Kernels of one step, 256 / 1024 threads:
+// 128K context, batch 1 (168 spans) 29 / 25 us; 32K, batch 4 (160) 28 / 24; 16K, batch 16 (256) 39 / 31; 128K, batch 2 (336)
+// 41 / 44; 64K, d 64, batch 8 (640) 30 / 42.
 template <int D, int G>
-void launch_split(const DecodeArgs &a, int batch, hipStream_t st) {
-    hipLaunchKernelGGL((ksa_decode_split_kernel<D, G>), dim3(a.n_splits, a.n_kv_heads, batch), dim3(NT), 0, st, a);
+void launch_group(const DecodeArgs &a, hipStream_t st) {
+    if (a.n_splits == 1 || (int64_t)a.batch * a.n_splits * a.n_kv_heads > 256)
+        launch<D, G, 256>(a, st);
+    else
+        launch<D, G, G == 8 ? 512 : 1024>(a, st);
 }
 
 template <int D>
-int launch_all(const DecodeArgs &a, int batch, hipStream_t st) {
+int launch_all(const DecodeArgs &a, hipStream_t st) {
     switch (a.n_q_heads / a.n_kv_heads) {
-        case 1: launch_split<D, 1>(a, batch, st); break;
-        case 2: launch_split<D, 2>(a, batch, st); break;
-        case 4: launch_split<D, 4>(a, batch, st); break;
-        case 8: launch_split<D, 8>(a, batch, st); break;
+        case 1: launch_group<D, 1>(a, st); break;
+        case 2: launch_group<D, 2>(a, st); break;
+        case 4: launch_group<D, 4>(a, st); break;
+        case 8: launch_group<D, 8>(a, st); break;
         default: return KSA_ERR_UNSUPPORTED;
     }
-    hipLaunchKernelGGL(ksa_decode_merge_kernel<D>, dim3(a.n_q_heads, batch), dim3(D), 0, st, a);
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
 }
 
@@ -321,8 +374,9 @@ int ksa_launch_decode(const KsaDecodeLaunch &L, void *stream) {
     a.n_q_heads = L.p.n_q_heads;
     a.n_kv_heads = L.p.n_kv_heads;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
+    a.batch = L.p.batch;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (L.p.head_dim == 128) return launch_all<128>(a, L.p.batch, st);
-    if (L.p.head_dim == 64) return launch_all<64>(a, L.p.batch, st);
+    if (L.p.head_dim == 128) return launch_all<128>(a, st);
+    if (L.p.head_dim == 64) return launch_all<64>(a, st);
     return KSA_ERR_UNSUPPORTED;
 }
