@@ -195,27 +195,34 @@ def ksa_build_layout(params: ksa_params) -> Layout:
 
 # ---- torch-facing wrappers ------------------------------------------------------------------------
 
+# The smallest problems (512 tokens, a summary step) take as long as the host needs to hand them over: addresses go to the
+# library as plain ints, and the raw stream comes from torch's C interface (0.2 us; a torch.cuda.Stream object 3.3 us).
+
+_I64x3 = C.c_int64 * 3
+
+
 def _stream_ptr(stream):
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-def _strides3(t, dims):
-    return (C.c_int64 * 3)(*[t.stride(d) for d in dims])
+def _strides3(t):
+    return _I64x3(*t.stride()[:3])
 
 
 def _require(t, name, dtype, ndim):
     import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
-    if t.dtype != dtype or t.dim() != ndim or t.stride(-1) != 1:
+    if t.dtype is not dtype or t.ndim != ndim or t.stride(-1) != 1:
         raise ValueError(f"{name}: expected {ndim}-d {dtype} with contiguous last dim, got {t.dtype} {tuple(t.shape)}")
 
 
 def _same_strides(x, y) -> bool:
     """Strides agree wherever they matter (a dimension of size 1 may carry any stride)."""
-    return all(sx == sy for n, sx, sy in zip(x.shape, x.stride(), y.stride()) if n > 1)
+    return x.stride() == y.stride() or all(sx == sy for n, sx, sy in zip(x.shape, x.stride(), y.stride()) if n > 1)
 
 
 def prefill_workspace_bytes(layout: Layout) -> int:
@@ -238,15 +245,15 @@ def ksa_prefill_fwd(layout: Layout, q, k, v, o=None, lse=None, return_lse=True, 
     _require(o, "o", torch.bfloat16, 4)
     if lse is None and return_lse:
         lse = torch.empty((p.batch, p.n_q_heads, layout.aug_len), dtype=torch.float32, device=q.device)
-    lse_ptr = C.c_void_p(lse.data_ptr()) if lse is not None else None
+    lse_ptr = lse.data_ptr() if lse is not None else None
     if workspace is None:
         workspace = torch.empty(prefill_workspace_bytes(layout), dtype=torch.uint8, device=q.device)
     if not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous uint8 GPU tensor")
-    rc = lib().ksa_prefill_fwd(layout.handle, C.c_void_p(q.data_ptr()), C.c_void_p(k.data_ptr()),
-                               C.c_void_p(v.data_ptr()), C.c_void_p(o.data_ptr()), lse_ptr,
-                               _strides3(q, (0, 1, 2)), _strides3(k, (0, 1, 2)), _strides3(o, (0, 1, 2)),
-                               C.c_void_p(workspace.data_ptr()), C.c_size_t(workspace.numel()), _stream_ptr(stream))
+    rc = lib().ksa_prefill_fwd(layout.handle, q.data_ptr(), k.data_ptr(),
+                               v.data_ptr(), o.data_ptr(), lse_ptr,
+                               _strides3(q), _strides3(k), _strides3(o),
+                               workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     _check(rc, "ksa_prefill_fwd")
     return o, lse
 
@@ -255,8 +262,8 @@ def ksa_prefill_relayout_v(layout: Layout, v, workspace, stream=None):
     """Only the first kernel of ksa_prefill_fwd (key-major copy of V into the workspace); for timing."""
     import torch
     _require(v, "v", torch.bfloat16, 4)
-    rc = lib().ksa_prefill_relayout_v(layout.handle, C.c_void_p(v.data_ptr()), _strides3(v, (0, 1, 2)),
-                                      C.c_void_p(workspace.data_ptr()), C.c_size_t(workspace.numel()), _stream_ptr(stream))
+    rc = lib().ksa_prefill_relayout_v(layout.handle, v.data_ptr(), _strides3(v),
+                                      workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     _check(rc, "ksa_prefill_relayout_v")
 
 
@@ -291,12 +298,12 @@ def ksa_prefill_bwd(layout: Layout, q, k, v, o, lse, d_o, dq=None, dk=None, dv=N
         workspace = torch.empty(prefill_bwd_workspace_bytes(layout), dtype=torch.uint8, device=q.device)
     if not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous uint8 GPU tensor")
-    rc = lib().ksa_prefill_bwd(layout.handle, C.c_void_p(q.data_ptr()), C.c_void_p(k.data_ptr()),
-                               C.c_void_p(v.data_ptr()), C.c_void_p(o.data_ptr()), C.c_void_p(lse.data_ptr()),
-                               C.c_void_p(d_o.data_ptr()), C.c_void_p(dq.data_ptr()), C.c_void_p(dk.data_ptr()),
-                               C.c_void_p(dv.data_ptr()), _strides3(q, (0, 1, 2)), _strides3(k, (0, 1, 2)),
-                               _strides3(o, (0, 1, 2)), _strides3(dq, (0, 1, 2)), _strides3(dk, (0, 1, 2)),
-                               C.c_void_p(workspace.data_ptr()), C.c_size_t(workspace.numel()), _stream_ptr(stream))
+    rc = lib().ksa_prefill_bwd(layout.handle, q.data_ptr(), k.data_ptr(),
+                               v.data_ptr(), o.data_ptr(), lse.data_ptr(),
+                               d_o.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+                               dv.data_ptr(), _strides3(q), _strides3(k),
+                               _strides3(o), _strides3(dq), _strides3(dk),
+                               workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     _check(rc, "ksa_prefill_bwd")
     return dq, dk, dv
 
@@ -310,7 +317,9 @@ def augmented_rows(params: ksa_params, n_text: int) -> int:
 
 def cache_geometry(params: ksa_params) -> Tuple[int, int]:
     s, r = C.c_int32(), C.c_int32()
-    _check(lib().ksa_cache_geometry(C.byref(params), C.byref(s), C.byref(r)), "ksa_cache_geometry")
+    rc = lib().ksa_cache_geometry(params, s, r)
+    if rc:
+        _check(rc, "ksa_cache_geometry")
     return s.value, r.value
 
 
@@ -354,13 +363,12 @@ def _decode(entry, params: ksa_params, q, k_cache, v_cache, pos, o, lse, return_
         o = torch.empty_like(q)
     if lse is None and return_lse:
         lse = torch.empty((params.batch, params.n_q_heads), dtype=torch.float32, device=q.device)
-    need = decode_workspace_bytes(params, n_splits)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    rc = getattr(lib(), entry)(C.byref(params), C.c_void_p(q.data_ptr()), C.c_void_p(k_cache.data_ptr()),
-                               C.c_void_p(v_cache.data_ptr()), C.c_void_p(pos.data_ptr()), C.c_void_p(o.data_ptr()),
-                               C.c_void_p(lse.data_ptr()) if lse is not None else None,
-                               _strides3(k_cache, (0, 1, 2)), C.c_void_p(workspace.data_ptr()),
+        workspace = torch.empty(decode_workspace_bytes(params, n_splits), dtype=torch.uint8, device=q.device)
+    rc = getattr(lib(), entry)(C.byref(params), q.data_ptr(), k_cache.data_ptr(),
+                               v_cache.data_ptr(), pos.data_ptr(), o.data_ptr(),
+                               lse.data_ptr() if lse is not None else None,
+                               _strides3(k_cache), workspace.data_ptr(),
                                workspace.numel() * workspace.element_size(), n_splits, _stream_ptr(stream))
     _check(rc, entry)
     return o, lse
@@ -392,10 +400,10 @@ def ksa_decode_fwd_static(params: ksa_params, q, k_cache, v_cache, pos, o, lse=N
         _require(lse, "lse", torch.float32, 2)
         if tuple(lse.shape) != (params.batch, params.n_q_heads) or not lse.is_contiguous():
             raise ValueError("lse must be a contiguous [B, Hq] tensor")
-    rc = lib().ksa_decode_fwd_static(C.byref(params), C.c_void_p(q.data_ptr()), C.c_void_p(k_cache.data_ptr()),
-                                     C.c_void_p(v_cache.data_ptr()), C.c_void_p(pos.data_ptr()),
-                                     C.c_void_p(o.data_ptr()), C.c_void_p(lse.data_ptr()) if lse is not None else None,
-                                     _strides3(k_cache, (0, 1, 2)), n_splits, _stream_ptr(stream))
+    rc = lib().ksa_decode_fwd_static(C.byref(params), q.data_ptr(), k_cache.data_ptr(),
+                                     v_cache.data_ptr(), pos.data_ptr(),
+                                     o.data_ptr(), lse.data_ptr() if lse is not None else None,
+                                     _strides3(k_cache), n_splits, _stream_ptr(stream))
     _check(rc, "ksa_decode_fwd_static")
     return o, lse
 
@@ -436,9 +444,9 @@ def ksa_cache_from_prefill(params: ksa_params, n_prefill: int, k, v, k_cache, v_
     if tuple(k.shape) != (params.batch, L, params.n_kv_heads, params.head_dim) or k.shape != v.shape or \
             k.stride() != v.stride() or k.stride(3) != 1:
         raise ValueError(f"k / v shape must be {(params.batch, L, params.n_kv_heads, params.head_dim)}")
-    rc = lib().ksa_cache_from_prefill(C.byref(params), n_prefill, C.c_void_p(k.data_ptr()), C.c_void_p(v.data_ptr()),
-                                      _strides3(k, (0, 1, 2)), C.c_void_p(k_cache.data_ptr()),
-                                      C.c_void_p(v_cache.data_ptr()), _strides3(k_cache, (0, 1, 2)), _stream_ptr(stream))
+    rc = lib().ksa_cache_from_prefill(C.byref(params), n_prefill, k.data_ptr(), v.data_ptr(),
+                                      _strides3(k), k_cache.data_ptr(),
+                                      v_cache.data_ptr(), _strides3(k_cache), _stream_ptr(stream))
     _check(rc, "ksa_cache_from_prefill")
 
 
@@ -452,9 +460,9 @@ def ksa_cache_append(params: ksa_params, kind: int, k_new, v_new, pos, k_cache, 
     if tuple(k_new.shape) != (params.batch, params.n_kv_heads, params.head_dim) or k_new.shape != v_new.shape or \
             not k_new.is_contiguous() or not v_new.is_contiguous() or pos.shape[0] != params.batch:
         raise ValueError("k_new / v_new / pos shape does not match params")
-    rc = lib().ksa_cache_append(C.byref(params), kind, C.c_void_p(k_new.data_ptr()), C.c_void_p(v_new.data_ptr()),
-                                C.c_void_p(pos.data_ptr()), C.c_void_p(k_cache.data_ptr()),
-                                C.c_void_p(v_cache.data_ptr()), _strides3(k_cache, (0, 1, 2)), _stream_ptr(stream))
+    rc = lib().ksa_cache_append(C.byref(params), kind, k_new.data_ptr(), v_new.data_ptr(),
+                                pos.data_ptr(), k_cache.data_ptr(),
+                                v_cache.data_ptr(), _strides3(k_cache), _stream_ptr(stream))
     _check(rc, "ksa_cache_append")
 
 

@@ -34,8 +34,6 @@ extern "C" {
 void ksa_layout_destroy(ksa_layout *lay) {
     if (!lay) return;
     if (lay->d_items) (void)hipFree(lay->d_items);
-    if (lay->d_entries) (void)hipFree(lay->d_entries);
-    if (lay->d_dkv) (void)hipFree(lay->d_dkv);
     delete lay;
 }
 
@@ -44,24 +42,33 @@ int ksa_layout_upload(ksa_layout *lay) {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return KSA_ERR_HIP;
     if (lay->d_items && lay->device == dev) return KSA_OK;
-    auto drop = [&]() {
+    if (lay->d_items) {
         (void)hipFree(lay->d_items);
-        (void)hipFree(lay->d_entries);
-        (void)hipFree(lay->d_dkv);
         lay->d_items = lay->d_entries = lay->d_dkv = nullptr;
-        return KSA_ERR_HIP;
-    };
-    if (lay->d_items) (void)drop();
+    }
+    // the parts follow each other in one allocation (all records are multiples of 16 bytes)
+    static_assert(sizeof(KsaWorkItem) % 16 == 0 && sizeof(KsaWgEntry) % 16 == 0 && sizeof(KsaDkvEntry) % 16 == 0, "alignment of the parts");
     const size_t ib = lay->items.size() * sizeof(KsaWorkItem), eb = lay->entries.size() * sizeof(KsaWgEntry);
     const size_t kb = lay->dkv_entries.size() * sizeof(KsaDkvEntry), sb = lay->dkv_splits.size() * sizeof(KsaDkvSplit);
-    if (hipMalloc(&lay->d_items, ib) != hipSuccess || hipMalloc(&lay->d_entries, eb) != hipSuccess ||
-        hipMalloc(&lay->d_dkv, kb + sb) != hipSuccess)
-        return drop();
-    if (hipMemcpy(lay->d_items, lay->items.data(), ib, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(lay->d_entries, lay->entries.data(), eb, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(lay->d_dkv, lay->dkv_entries.data(), kb, hipMemcpyHostToDevice) != hipSuccess ||
-        (sb > 0 && hipMemcpy(static_cast<char *>(lay->d_dkv) + kb, lay->dkv_splits.data(), sb, hipMemcpyHostToDevice) != hipSuccess))
-        return drop();
+    std::vector<unsigned char> all;
+    try {
+        all.resize(ib + eb + kb + sb);
+    } catch (...) {
+        return KSA_ERR_OUT_OF_MEMORY;
+    }
+    std::memcpy(all.data(), lay->items.data(), ib);
+    std::memcpy(all.data() + ib, lay->entries.data(), eb);
+    std::memcpy(all.data() + ib + eb, lay->dkv_entries.data(), kb);
+    if (sb > 0) std::memcpy(all.data() + ib + eb + kb, lay->dkv_splits.data(), sb);
+    void *dst = nullptr;
+    if (hipMalloc(&dst, all.size()) != hipSuccess) return KSA_ERR_HIP;
+    if (hipMemcpy(dst, all.data(), all.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipFree(dst);
+        return KSA_ERR_HIP;
+    }
+    lay->d_items = dst;
+    lay->d_entries = static_cast<char *>(dst) + ib;
+    lay->d_dkv = static_cast<char *>(dst) + ib + eb;
     lay->device = dev;
     return KSA_OK;
 }

@@ -23,7 +23,7 @@ struct ksa_layout {
     int32_t dkv_slots = 0;                  // scratch slots per (batch, KV head)
     // device copies (owned), valid on `device` once uploaded
     int device = -1;
-    void *d_items = nullptr;
+    void *d_items = nullptr;          // the allocation: items, entries, dkv_entries, dkv_splits
     void *d_entries = nullptr;
     void *d_dkv = nullptr;            // dkv_entries, then dkv_splits
 };
