@@ -160,6 +160,7 @@ int ksa_prefill_bwd(ksa_layout *lay, const void *q, const void *k, const void *v
     a.n_dkv_entries = (int32_t)lay->dkv_entries.size();
     a.dkv_splits = reinterpret_cast<const KsaDkvSplit *>(a.dkv_entries + a.n_dkv_entries);
     a.n_dkv_splits = (int32_t)lay->dkv_splits.size();
+    a.dq_direct = lay->dq_direct;
     a.p = p;
     a.aug_len = lay->aug_len;
     a.workspace = workspace;

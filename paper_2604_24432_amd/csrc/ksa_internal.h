@@ -16,6 +16,7 @@ struct ksa_layout {
     int32_t n_pipelined_entries = 0;  // length of the first part (a multiple of 8)
     int32_t n_pipelined_items = 0;    // items with KsaWorkItem::pipelined set
     int32_t head_stack = 1;           // query heads per workgroup (1, 2 or 4)
+    bool dq_direct = false;           // ... and dQ
     bool direct = false;              // the forward pass takes the kernel for short key runs (see takes_direct)
     int32_t q_tile_rows = KSA_Q_TILE; // rows of a query tile = KSA_Q_TILE / head_stack
     std::vector<KsaDkvEntry> dkv_entries;   // backward dK / dV, per (batch, KV head), longest first
@@ -68,6 +69,7 @@ struct KsaPrefillBwdLaunch {
     const KsaDkvEntry *dkv_entries;   // NULL: every key tile is one workgroup
     const KsaDkvSplit *dkv_splits;
     int32_t n_dkv_entries, n_dkv_splits;
+    bool dq_direct;                   // dQ by the kernel for short key runs (ksa_prefill_direct.hip)
     ksa_params p;
     int64_t aug_len;
     void *workspace;          // delta_i = dO_i . O_i per (batch, query head, row), fp32
@@ -75,6 +77,8 @@ struct KsaPrefillBwdLaunch {
 };
 size_t ksa_prefill_bwd_workspace_size(const ksa_params &p, int64_t aug_len);
 int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &a, void *stream);
+// dQ by the kernel for short key runs and odd chunk shapes (ksa_prefill_direct.hip); lse2c, dlc: the row statistics.
+int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &a, const float *lse2c, const float *dlc, void *stream);
 // Second step of the split dK / dV tiles (ksa_prefill_bwd_sum.hip).
 struct KsaDkvSumArgs {
     const float *scratch;

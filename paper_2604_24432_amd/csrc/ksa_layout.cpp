@@ -133,6 +133,18 @@ bool takes_direct(const ksa_layout &lay) {
     return tiles <= line * (int64_t)lay.items.size();
 }
 
+// Does dQ take the kernel of ksa_prefill_direct.hip?  It does unless every key run is a long stretch of text: with two
+// workgroups per compute unit the other kernel's fixed costs are hidden, and its extra operand reads only show on dense causal
+// attention.  Whole backward pass, ksa_bwd_dq_kernel / direct, ms: 2 x 4096 tokens 0.449 / 0.336, 16K 1.476 / 1.269, 128K 58.3 /
+// 57.0 (c 64, m 8, 32/8 heads, d 128), 20K in the paper's form, 16 heads, 1.646 / 1.401, window 1024 at 16K (17 tiles) 1.227 /
+// 1.071, 64K d 64 9.19 / 8.81; causal 4K (33 tiles) 0.539 / 0.528, causal 8K (65) 1.846 / 1.875, causal 32K, 4 heads 3.53 / 3.63,
+// causal 32K d 64 4.21 / 4.11.
+bool dq_takes_direct(const ksa_layout &lay) {
+    int64_t tiles = 0;
+    for (const KsaWorkItem &it : lay.items) tiles += it.n_tiles;
+    return lay.p.head_dim == 64 || lay.p.n_summary > 0 || tiles <= 48 * (int64_t)lay.items.size();
+}
+
 // Launch order.  Workgroups are dealt to the 8 XCDs round-robin by workgroup id, and each XCD has its
 // own L2: queue q (workgroup ids congruent to q mod 8) is given whole (batch, KV head) groups so that the
 // workgroups running together on one XCD stream the same K/V rows, and items go heaviest first so the
@@ -283,6 +295,7 @@ int ksa_build_layout(const ksa_params *params, ksa_layout **out) {
         return a.pipelined != b.pipelined ? a.pipelined > b.pipelined : a.n_tiles > b.n_tiles;
     });
     lay->direct = takes_direct(*lay);
+    lay->dq_direct = dq_takes_direct(*lay);
     build_entries(*lay, 0, lay->n_pipelined_items);
     lay->n_pipelined_entries = (int32_t)lay->entries.size();
     build_entries(*lay, lay->n_pipelined_items, (int32_t)lay->items.size());

@@ -7,7 +7,8 @@
 //   dQ_i  = scale sum_j dS_ij k_j,     dK_j = scale sum_i dS_ij q_i
 // No atomics, results independent of the launch order:
 //   ksa_bwd_delta_kernel  delta_i and lse_i log2(e) per (batch, head, row), in compact row order, into the workspace;
-//   ksa_bwd_dq_kernel     one workgroup per query tile of the forward schedule walks that tile's key runs;
+//   ksa_bwd_dq_kernel     one workgroup per query tile of the forward schedule walks that tile's key runs (long stretches
+//                         of text; other layouts take ksa_bwd_dq_direct_kernel, ksa_prefill_direct.hip);
 //   ksa_bwd_dkv_kernel    one workgroup per 128-key tile of an index space walks the query rows that can see it
 //                         (two runs, closed form from Eq. 3), for every query head of the KV head's group; where that
 //                         would leave the chip waiting for a few long tiles, several workgroups share a tile and
@@ -1046,13 +1047,19 @@ void launch_dkv(const BwdArgs &a, int entries, int splits, hipStream_t st) {
 }
 
 template <int D, bool POW2>
-void launch_all(const BwdArgs &a, int64_t n_rows, int dq_grid, int entries, int splits, hipStream_t st) {
+int launch_all(const KsaPrefillBwdLaunch &L, const BwdArgs &a, int64_t n_rows, int entries, int splits, hipStream_t st) {
     const int64_t delta_blocks = (n_rows * (D / 8) + 255) / 256;
     hipLaunchKernelGGL(ksa_bwd_delta_kernel<D>, dim3((unsigned)delta_blocks), dim3(256), 0, st, a, n_rows);
     // with split key tiles dq holds their partial sums until it is written itself
     if (a.scratch) launch_dkv<D, POW2>(a, entries, splits, st);
-    hipLaunchKernelGGL((ksa_bwd_dq_kernel<D, POW2>), dim3((unsigned)dq_grid), dim3(NW * 64), 0, st, a);
+    if (L.dq_direct) {
+        const int rc = ksa_launch_dq_direct(L, a.lse2c, a.dlc, st);
+        if (rc != KSA_OK) return rc;
+    } else {
+        hipLaunchKernelGGL((ksa_bwd_dq_kernel<D, POW2>), dim3((unsigned)L.n_entries), dim3(NW * 64), 0, st, a);
+    }
     if (!a.scratch) launch_dkv<D, POW2>(a, entries, splits, st);
+    return KSA_OK;
 }
 
 }  // namespace
@@ -1156,9 +1163,11 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
             entries = L.n_dkv_entries, splits = L.n_dkv_splits;
         }
     }
+    int rc;
     if (L.p.head_dim == 128)
-        pow2 ? launch_all<128, true>(a, n_rows, L.n_entries, entries, splits, st) : launch_all<128, false>(a, n_rows, L.n_entries, entries, splits, st);
+        rc = pow2 ? launch_all<128, true>(L, a, n_rows, entries, splits, st) : launch_all<128, false>(L, a, n_rows, entries, splits, st);
     else
-        pow2 ? launch_all<64, true>(a, n_rows, L.n_entries, entries, splits, st) : launch_all<64, false>(a, n_rows, L.n_entries, entries, splits, st);
+        rc = pow2 ? launch_all<64, true>(L, a, n_rows, entries, splits, st) : launch_all<64, false>(L, a, n_rows, entries, splits, st);
+    if (rc != KSA_OK) return rc;
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
 }

@@ -1,4 +1,5 @@
-// KSA prefill forward for gfx950, the kernel for short key runs and for chunk shapes that are no powers of two.
+// KSA prefill for gfx950 with two workgroups per compute unit: the forward kernel for short key runs and for chunk shapes
+// that are no powers of two, and the dQ kernel of the backward pass.
 //
 // The pipelined kernel (ksa_prefill.hip) owns a whole compute unit per workgroup (one wave per SIMD, 512 registers,
 // 131 KB of LDS): at long key runs its hand-placed MFMA stream is the fastest, but nothing hides what a workgroup does
@@ -13,7 +14,8 @@
 // 1.18 PFLOP/s).  Neither deeper prefetch (5 stages of 32 keys), three workgroups per compute unit, nor the scores of the
 // next tile under the exponentials of this one changed that by more than 3 %; the loads dealt between the MFMAs, the row
 // offsets kept from tile to tile and the order of the query tiles did (together 10 - 30 %).
-// The line between the two kernels: takes_direct() in ksa_layout.cpp.
+// The line between the two kernels: takes_direct() in ksa_layout.cpp.  dQ (three products per visible pair instead of two) is ahead of ksa_bwd_dq_kernel nearly everywhere (dq_takes_direct()): at 2 x 4096
+// tokens 110 against 221 us.
 //
 // The work of a workgroup follows from its index in closed form (Eq. 3): no schedule is read from memory.  The keys of
 // its query tile form one list (summaries, then text) cut into tiles of 64; tile t sits in LDS buffer t % 2, and tile
@@ -61,6 +63,12 @@ struct DirectArgs {
     int32_t mixed_tiles;                // a key tile may hold the last summaries and the first text rows of a list
     int64_t aug_len;
     float scale_log2e;
+    // dQ only: o is dq, the others as in ksa_prefill_bwd.hip
+    const __bf16 *g;                    // dLoss/dO
+    int64_t gs[3];
+    const float *lse2c, *dlc;           // per row, compact order: log-sum-exp times log2(e), minus delta
+    int32_t nt_pad, ns_pad;
+    float scale;
 };
 
 __device__ __forceinline__ float other_half(float x) {
@@ -111,13 +119,20 @@ __device__ __forceinline__ Visible visible(const DirectArgs &a, int q_space, int
     return r;
 }
 
-// Two workgroups per compute unit for head_dim 128 (64 KB of LDS, 256 registers each), three for head_dim 64 (16K tokens,
-// 32/8 heads: 219 us; two: 235, four, with shorter operand read-ahead: 250).
+// The swizzle for tiles that are read both ways (K in the dQ kernel: rows for the scores, columns for dQ): spreads the 16
+// rows of a plain 16-byte read and the 4 rows of a transposing read over different banks.
 template <int D>
-__global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_kernel(const DirectArgs a) {
+__device__ __forceinline__ int both_swz(int row) { return (((row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
+
+// GRAD = false: forward.  GRAD = true: dQ of the backward pass (see ksa_prefill_bwd.hip for the products) on the same key
+// lists: S^T = K Q^T and dP^T = V dO^T, whose accumulator starts from minus delta, dS^T = P^T o dP^T in bf16 as the B operand
+// of dQ^T += K^T dS^T.
+template <int D, bool GRAD>
+__device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) {
     using T = Tile<D>;
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * T::BYTES];
     static_assert(NW * 32 * T::STAGE_ROW <= 4 * T::BYTES, "the epilogue's staging area reuses the tile buffers");
+    auto k_swizzle = [](int row) { return GRAD ? both_swz<D>(row) : k_swz<D>(row); };
+    auto v_swizzle = [](int row) { return GRAD ? both_swz<D>(row) : v_swz<D>(row); };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -157,6 +172,15 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
         const __bf16 *qp = a.q + b * a.qs[0] + (int64_t)q_aug * a.qs[1] + hq * a.qs[2] + h * 8;
 #pragma unroll
         for (int s = 0; s < T::KS; ++s) qreg[s] = *reinterpret_cast<const bf16x8 *>(qp + s * 16);
+    }
+    bf16x8 greg[GRAD ? T::KS : 1];
+    float lse2 = 0.f, minus_delta = 0.f;
+    if constexpr (GRAD) {
+        const __bf16 *gp = a.g + b * a.gs[0] + (int64_t)q_aug * a.gs[1] + hq * a.gs[2] + h * 8;
+#pragma unroll
+        for (int s = 0; s < T::KS; ++s) greg[s] = *reinterpret_cast<const bf16x8 *>(gp + s * 16);
+        const int64_t stat = ((int64_t)b * a.n_q_heads + hq) * (a.nt_pad + a.ns_pad) + (q_space == KSA_SPACE_TEXT ? idx : a.nt_pad + idx);
+        lse2 = a.lse2c[stat], minus_delta = a.dlc[stat];
     }
 
     // ---- the request of a tile, in two parts -------------------------------------------------------------------
@@ -233,8 +257,8 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
             for (int i = 0; i < T::NI; ++i) {
                 const int row = RW * wave + T::RPI * i + lane / T::CH, pch = lane % T::CH;
                 const bool any = t < n_tiles;
-                k_off[i] = row_off[i] + (any ? (pch ^ k_swz<D>(row)) << 4 : 0);
-                v_off[i] = row_off[i] + (any ? (pch ^ v_swz<D>(row)) << 4 : 0);
+                k_off[i] = row_off[i] + (any ? (pch ^ k_swizzle(row)) << 4 : 0);
+                v_off[i] = row_off[i] + (any ? (pch ^ v_swizzle(row)) << 4 : 0);
             }
         }
         off_state = state;
@@ -274,7 +298,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
     const float sl = a.scale_log2e;
     float m_static = 0.f;
     bool static_ok = false;
-    if (a.knorm_tiles) {
+    if (!GRAD && a.knorm_tiles) {
         float kmax2 = 0.f;
         const float *src = a.knorm_tiles + (int64_t)bh * a.norm_tiles;
         bool bad = false;
@@ -301,8 +325,69 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
     // byte addresses inside a buffer, relative to its start: see ksa_prefill.hip
     const int grp = lane >> 4, li = lane & 15;
     const int t_row = 4 * (grp >> 1) + (li >> 2), t_col = 16 * (grp & 1) + 4 * (li & 3);
-    const int ll_k = r * (D * 2) + ((k_swz<D>(r) ^ h) << 4);
-    const int ll_v = T::BYTES + t_row * (D * 2) + (((t_col >> 3) ^ v_swz<D>(t_row)) << 4) + ((t_col & 7) << 1);
+    const int ll_k = r * (D * 2) + ((k_swizzle(r) ^ h) << 4);                                                   // rows
+    const int ll_t = t_row * (D * 2) + (((t_col >> 3) ^ v_swizzle(t_row)) << 4) + ((t_col & 7) << 1);           // columns
+    const int ll_v = T::BYTES + ll_t;
+
+    // dQ: one key tile, 32 keys at a time (the registers of two blocks of S and dP would not fit)
+    auto grad_tile = [&](int t, int buf, const unsigned char *tile_lds, f32x16 (&oacc)[T::DB]) {
+        const int x0 = t * BN;
+        const bool masked = (unsigned)(t - fs_t) >= fs_n && (unsigned)(t - ft_t) >= ft_n;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            f32x16 sacc, gacc;
+#pragma unroll
+            for (int g = 0; g < 16; ++g) sacc[g] = 0.f, gacc[g] = minus_delta;
+            constexpr int AHEAD = 2;   // operands are read AHEAD k steps before the MFMAs that use them
+            bf16x8 ka[T::KS], va[T::KS];
+            auto read_rows = [&](int s) {
+                const unsigned char *at = tile_lds + ((ll_k ^ (s << 5)) + kb * 32 * (D * 2));
+                ka[s] = *reinterpret_cast<const bf16x8 *>(at), va[s] = *reinterpret_cast<const bf16x8 *>(at + T::BYTES);
+            };
+#pragma unroll
+            for (int s = 0; s < AHEAD; ++s) read_rows(s);
+#pragma unroll
+            for (int s = 0; s < T::KS; ++s) {
+                if (s + AHEAD < T::KS) read_rows(s + AHEAD);
+                KSA_FENCE();
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[s], qreg[s], sacc, 0, 0, 0);
+                gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[s], greg[GRAD ? s : 0], gacc, 0, 0, 0);
+                if (kb == 0) issue(buf ^ 1, s);
+                KSA_FENCE();
+            }
+            if (kb == 0) prepare(t + 2);
+            if (masked) {   // as in the forward tile
+                const int y0 = x0 + kb * 32, base_t = y0 + 4 * h - t_lo, base_s = y0 + 4 * h - s_lo;
+                const unsigned span_t = (unsigned)max(t_hi - t_lo, 0), span_s = (unsigned)max(s_hi - s_lo, 0);
+                if (y0 >= t_first || y0 + 32 <= n_s) {
+                    const int base = y0 >= t_first ? base_t : base_s;
+                    const unsigned span = y0 >= t_first ? span_t : span_s;
+#pragma unroll
+                    for (int g = 0; g < 16; ++g) sacc[g] = (unsigned)(base + 8 * (g / 4) + g % 4) < span ? sacc[g] : -INFINITY;
+                } else {
+#pragma unroll
+                    for (int g = 0; g < 16; ++g) {
+                        const int o = 8 * (g / 4) + g % 4;
+                        sacc[g] = ((unsigned)(base_t + o) < span_t || (unsigned)(base_s + o) < span_s) ? sacc[g] : -INFINITY;
+                    }
+                }
+            }
+            bf16x8 ds[2];
+#pragma unroll
+            for (int g = 0; g < 16; ++g) ds[g / 8][g % 8] = (__bf16)(__builtin_amdgcn_exp2f(fmaf(sacc[g], sl, -lse2)) * gacc[g]);
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                for (int db = 0; db < T::DB; ++db) {
+                    // rows R0 + t_row and R0 + 8 + t_row, R0 = 32 kb + 16 hf: the latter's swizzle differs by XOR 2
+                    const unsigned char *at = tile_lds + (kb * 32 + hf * 16) * (D * 2);
+                    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(at + (ll_t ^ (db << 6))));
+                    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(at + ((ll_t ^ (((db * 4) ^ 2) << 4)) + 8 * (D * 2))));
+                    const bf16x8 kt = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, ds[hf], oacc[db], 0, 0, 0);
+                }
+        }
+    };
 
     auto body = [&](auto track_tag) {
         constexpr bool TRACK = decltype(track_tag)::value;
@@ -332,6 +417,10 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
                 continue;
             }
             const unsigned char *tile_lds = lds + buf * 2 * T::BYTES;
+            if constexpr (GRAD) {
+                grad_tile(t, buf, tile_lds, oacc);
+                continue;
+            }
 
             f32x16 sacc[2];
 #pragma unroll
@@ -439,7 +528,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
         unsigned char *stg = lds + wave * (32 * T::STAGE_ROW);
         const float s0 = __shfl(l_sum[0], r & 15), s1 = __shfl(l_sum[1], r & 15);
         const float l_row = (r & 16) ? s1 : s0;
-        const float inv = 1.0f / l_row;
+        const float inv = GRAD ? a.scale : 1.0f / l_row;
 #pragma unroll
         for (int db = 0; db < T::DB; ++db)
 #pragma unroll
@@ -458,6 +547,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
             if (w_begin + row < q_end)
                 *reinterpret_cast<u32x4 *>(obase + (int64_t)row_of(a, q_space, w_begin + row) * a.os[1]) = x;
         }
+        if constexpr (GRAD) return;
         l_exact = TRACK ? l_row : l_exact + other_half(l_exact);
         if (a.lse && h == 0 && w_begin + r < q_end) {
             float msl = m_ref * sl;
@@ -468,10 +558,23 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_
         }
     };
     // both copies meet at the same barriers, so the choice is per wave
-    if (static_ok)
+    if (GRAD || static_ok)
         body(std::false_type{});
-    else
+    else if constexpr (!GRAD)
         body(std::true_type{});
+}
+
+// Two workgroups per compute unit for head_dim 128 (64 KB of LDS, 256 registers each), three for head_dim 64 (16K tokens,
+// 32/8 heads: 219 us; two: 235, four, with shorter operand read-ahead: 250).
+template <int D>
+__global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_kernel(const DirectArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * Tile<D>::BYTES];
+    direct<D, false>(a, lds);
+}
+template <int D>
+__global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dq_direct_kernel(const DirectArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * Tile<D>::BYTES];
+    direct<D, true>(a, lds);
 }
 
 // Largest squared K row norm of every (batch, KV head, 64-key tile), the tiles of the text space first.
@@ -511,6 +614,46 @@ void launch(const DirectArgs &a, float *tiles, int text_key_tiles, int batch, in
     hipLaunchKernelGGL(ksa_prefill_direct_kernel<D>, dim3((unsigned)n_wg), dim3(NW * 64), 0, st, a);
 }
 
+// the parts of the arguments that describe the key lists (the strides are set); returns the number of workgroups
+int64_t fill_lists(DirectArgs &a, const ksa_params &p, int32_t head_stack, int64_t aug_len) {
+    a.n_text = p.n_text;
+    a.n_sum = (p.n_text / p.chunk_len) * p.n_summary;
+    a.c = p.chunk_len, a.m = p.n_summary, a.C = p.window_chunks;
+    a.small_c = (65535 + a.c) / a.c, a.small_m = a.m > 0 ? (65535 + a.m) / a.m : 0;
+    a.by_c = ksa_divisor(a.c), a.by_m = ksa_divisor(a.m > 0 ? a.m : 1);
+    a.n_q_heads = p.n_q_heads, a.n_kv_heads = p.n_kv_heads;
+    a.group = p.n_q_heads / p.n_kv_heads;
+    a.n_bh = p.batch * p.n_kv_heads;
+    a.by_bh = ksa_divisor(a.n_bh), a.by_kv_heads = ksa_divisor(a.n_kv_heads);
+    a.stack = head_stack;
+    a.stack_shift = log2_exact(head_stack);
+    a.slices = a.group / head_stack;
+    a.by_slices = ksa_divisor(a.slices);
+    a.q_rows = WG_PAIRS / head_stack;
+    a.text_tiles = (a.n_text + a.q_rows - 1) / a.q_rows;
+    a.sum_tiles = (a.n_sum + a.q_rows - 1) / a.q_rows;
+    {   // a text tile's list has (chunks before the window) m summaries and at most (C + 1) c + q_rows text rows
+        const int64_t sum_keys = a.m > 0 ? (int64_t)((a.q_rows + a.m - 1) / a.m) * a.c + a.q_rows : 0;
+        auto longer = [&](int64_t tile) {
+            const int64_t row = tile * a.q_rows, j = row / a.c;
+            return (j > a.C ? (j - a.C) * a.m + (int64_t)(a.C + 1) * a.c : row) + a.q_rows > sum_keys;
+        };
+        int32_t lo = 0, hi = a.text_tiles;   // (lists do not get shorter from one text tile to the next)
+        while (lo < hi) {
+            const int32_t mid = lo + (hi - lo) / 2;
+            if (longer(mid)) hi = mid; else lo = mid + 1;
+        }
+        a.text_before = a.text_tiles - lo;
+    }
+    a.self_only = (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY) ? 1 : 0;
+    // rows of a mixed tile: up to 63 summaries and 63 text rows around the border of the list, whose chunks differ by no
+    // more than a query tile's rows span
+    const int64_t span = (63 / (a.m > 0 ? a.m : 1) + (63 + a.q_rows) / a.c + 6) * (int64_t)(a.c + a.m);
+    a.mixed_tiles = span * a.ks[1] * 2 < ((int64_t)1 << 32) ? 1 : 0;
+    a.aug_len = aug_len;
+    return ((int64_t)a.text_tiles + a.sum_tiles) * a.slices * a.n_bh;
+}
+
 }  // namespace
 
 int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_tiles, float *knorm, int32_t norm_tiles, void *stream) {
@@ -528,43 +671,8 @@ int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_tiles, flo
     a.knorm_tiles = fixed ? knorm_tiles : nullptr;
     a.knorm = knorm;
     a.norm_tiles = norm_tiles;
-    a.n_text = L.p.n_text;
-    a.n_sum = (L.p.n_text / L.p.chunk_len) * L.p.n_summary;
-    a.c = L.p.chunk_len, a.m = L.p.n_summary, a.C = L.p.window_chunks;
-    a.small_c = (65535 + a.c) / a.c, a.small_m = a.m > 0 ? (65535 + a.m) / a.m : 0;
-    a.by_c = ksa_divisor(a.c), a.by_m = ksa_divisor(a.m > 0 ? a.m : 1);
-    a.n_q_heads = L.p.n_q_heads, a.n_kv_heads = L.p.n_kv_heads;
-    a.group = L.p.n_q_heads / L.p.n_kv_heads;
-    a.n_bh = L.p.batch * L.p.n_kv_heads;
-    a.by_bh = ksa_divisor(a.n_bh), a.by_kv_heads = ksa_divisor(a.n_kv_heads);
-    a.stack = L.head_stack;
-    a.stack_shift = log2_exact(L.head_stack);
-    a.slices = a.group / L.head_stack;
-    a.by_slices = ksa_divisor(a.slices);
-    a.q_rows = WG_PAIRS / L.head_stack;
-    a.text_tiles = (a.n_text + a.q_rows - 1) / a.q_rows;
-    a.sum_tiles = (a.n_sum + a.q_rows - 1) / a.q_rows;
-    {   // a text tile's list has (chunks before the window) m summaries and at most (C + 1) c + q_rows text rows
-        const int64_t sum_keys = a.m > 0 ? (int64_t)((a.q_rows + a.m - 1) / a.m) * a.c + a.q_rows : 0;
-        auto longer = [&](int64_t tile) {
-            const int64_t row = tile * a.q_rows, j = row / a.c;
-            return (j > a.C ? (j - a.C) * a.m + (int64_t)(a.C + 1) * a.c : row) + a.q_rows > sum_keys;
-        };
-        int32_t lo = 0, hi = a.text_tiles;   // (lists do not get shorter from one text tile to the next)
-        while (lo < hi) {
-            const int32_t mid = lo + (hi - lo) / 2;
-            if (longer(mid)) hi = mid; else lo = mid + 1;
-        }
-        a.text_before = a.text_tiles - lo;
-    }
-    a.self_only = (L.p.flags & KSA_FLAG_SUMMARY_SELF_ONLY) ? 1 : 0;
-    // rows of a mixed tile: up to 63 summaries and 63 text rows around the border of the list, whose chunks differ by no
-    // more than a query tile's rows span
-    const int64_t span = (63 / (a.m > 0 ? a.m : 1) + (63 + a.q_rows) / a.c + 6) * (int64_t)(a.c + a.m);
-    a.mixed_tiles = span * L.kv_strides[1] * 2 < ((int64_t)1 << 32) ? 1 : 0;
-    a.aug_len = L.aug_len;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
-    const int64_t n_wg = ((int64_t)a.text_tiles + a.sum_tiles) * a.slices * a.n_bh;
+    const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);
     if (n_wg >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int text_key_tiles = (a.n_text + BN - 1) / BN;
@@ -575,4 +683,27 @@ int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_tiles, flo
     else
         return KSA_ERR_UNSUPPORTED;
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
+}
+
+int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *lse2c, const float *dlc, void *stream) {
+    DirectArgs a;
+    a.q = static_cast<const __bf16 *>(L.q);
+    a.k = static_cast<const __bf16 *>(L.k);
+    a.v = static_cast<const __bf16 *>(L.v);
+    a.g = static_cast<const __bf16 *>(L.d_o);
+    a.o = static_cast<__bf16 *>(L.dq);
+    a.lse = nullptr, a.knorm_tiles = nullptr, a.knorm = nullptr, a.norm_tiles = 0;
+    for (int x = 0; x < 3; ++x) a.qs[x] = L.q_strides[x], a.ks[x] = L.kv_strides[x], a.gs[x] = L.o_strides[x], a.os[x] = L.dq_strides[x];
+    a.lse2c = lse2c, a.dlc = dlc;
+    const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);
+    if (n_wg >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
+    a.nt_pad = (a.n_text + 63) / 64 * 64, a.ns_pad = (a.n_sum + 63) / 64 * 64;
+    a.scale = L.p.softmax_scale, a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
+    const dim3 grid((unsigned)n_wg), block(NW * 64);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (L.p.head_dim == 128)
+        hipLaunchKernelGGL(ksa_bwd_dq_direct_kernel<128>, grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL(ksa_bwd_dq_direct_kernel<64>, grid, block, 0, st, a);
+    return KSA_OK;
 }
