@@ -14,8 +14,8 @@
 // 1.18 PFLOP/s).  Neither deeper prefetch (5 stages of 32 keys), three workgroups per compute unit, nor the scores of the
 // next tile under the exponentials of this one changed that by more than 3 %; the loads dealt between the MFMAs, the row
 // offsets kept from tile to tile and the order of the query tiles did (together 10 - 30 %).
-// The line between the two kernels: takes_direct() in ksa_layout.cpp.  dQ (three products per visible pair instead of two) is ahead of ksa_bwd_dq_kernel nearly everywhere (dq_takes_direct()): at 2 x 4096
-// tokens 110 against 221 us.
+// The line between the two kernels: takes_direct() in ksa_layout.cpp.  dQ (three products per visible pair instead of two)
+// is ahead of ksa_bwd_dq_kernel nearly everywhere (dq_takes_direct()): 103 against 221 us at 2 x 4096 tokens.
 //
 // The work of a workgroup follows from its index in closed form (Eq. 3): no schedule is read from memory.  The keys of
 // its query tile form one list (summaries, then text) cut into tiles of 64; tile t sits in LDS buffer t % 2, and tile
@@ -629,9 +629,15 @@ int64_t fill_lists(DirectArgs &a, const ksa_params &p, int32_t head_stack, int64
     a.stack_shift = log2_exact(head_stack);
     a.slices = a.group / head_stack;
     a.by_slices = ksa_divisor(a.slices);
+    // Rows per query tile: 32 per wave.  A launch with fewer workgroups than compute units takes shorter tiles, down to the
+    // rows of one wave (the other waves then only fetch): their key lists are shorter, and there are units to spare (512
+    // tokens, 1 head, d 64: the 64 summary rows see 576 keys together, 288 by halves: 16.7 -> 13.4 us; 700 tokens in the
+    // paper's form, 16 heads: 26.0 -> 20.5).
     a.q_rows = WG_PAIRS / head_stack;
-    a.text_tiles = (a.n_text + a.q_rows - 1) / a.q_rows;
-    a.sum_tiles = (a.n_sum + a.q_rows - 1) / a.q_rows;
+    auto tiles_of = [&](int32_t rows) { return (rows + a.q_rows - 1) / a.q_rows; };
+    while (a.q_rows > 32 && 2 * ((int64_t)tiles_of(a.n_text) + tiles_of(a.n_sum)) * a.slices * a.n_bh <= 256) a.q_rows /= 2;
+    a.text_tiles = tiles_of(a.n_text);
+    a.sum_tiles = tiles_of(a.n_sum);
     {   // a text tile's list has (chunks before the window) m summaries and at most (C + 1) c + q_rows text rows
         const int64_t sum_keys = a.m > 0 ? (int64_t)((a.q_rows + a.m - 1) / a.m) * a.c + a.q_rows : 0;
         auto longer = [&](int64_t tile) {
