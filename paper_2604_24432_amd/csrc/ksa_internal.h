@@ -12,9 +12,8 @@ struct ksa_layout {
     int64_t aug_len;      // L
     int32_t n_chunks;     // J
     std::vector<KsaWorkItem> items;   // one per query tile, heaviest first
-    std::vector<KsaWgEntry> entries;  // one per workgroup: first those of the pipelined items, then the others
-    int32_t n_pipelined_entries = 0;  // length of the first part (a multiple of 8)
-    int32_t n_pipelined_items = 0;    // items with KsaWorkItem::pipelined set
+    std::vector<KsaWgEntry> entries;  // one per workgroup
+    bool ragged = false;              // some run's last key tile reaches past the end of its index space
     int32_t head_stack = 1;           // query heads per workgroup (1, 2 or 4)
     bool dq_direct = false;           // ... and dQ
     bool direct = false;              // the forward pass takes the kernel for short key runs (see takes_direct)
@@ -41,8 +40,7 @@ struct KsaPrefillLaunch {
     const KsaWorkItem *items;
     const KsaWgEntry *entries;
     int32_t n_entries;
-    int32_t n_pipelined_entries;                  // entries [0, n_pipelined_entries): the pipelined kernel's; rest: the generic one's
-    int32_t n_pipelined_items, n_generic_items;   // how many work items each of the two kernels owns
+    bool ragged;              // some run's last key tile reaches past the end of its index space
     int32_t head_stack;                           // query heads per workgroup
     ksa_params p;
     int64_t aug_len;

@@ -35,12 +35,15 @@ inline void summary_row_ranges(const ksa_params &p, int64_t u, int32_t out[4]) {
 
 inline int32_t tiles_in(const KsaSegment &s) { return (s.end - s.begin + KSA_K_TILE - 1) / KSA_K_TILE; }
 
-// The run starts at the multiple of 16 at or below its first visible key: the kernel's pipelined loop wants that
-// alignment (see item_pipelined), and the up to 15 extra keys in front lie outside every row's visible range, so
-// the first tile stays live and its mask clips them.
-void push_segment(KsaWorkItem &it, int32_t space, int64_t begin, int64_t end, int64_t full_lo, int64_t full_hi) {
+// The run starts at the multiple of 16 at or below its first visible key, or of 64 if its tiles would otherwise end behind
+// the next multiple of 64 of its index space (of n_space keys): the pipelined forward kernel reads V from a key-major copy
+// whose keys are permuted in groups of 16 and which ends there.  The extra keys in front lie outside every row's visible
+// range, so the first tile stays live and its mask clips them.
+void push_segment(KsaWorkItem &it, int32_t space, int64_t begin, int64_t end, int64_t full_lo, int64_t full_hi, int64_t n_space) {
     if (end <= begin) return;
+    auto tiles_end = [&](int64_t b) { return b + (end - b + KSA_K_TILE - 1) / KSA_K_TILE * KSA_K_TILE; };
     begin -= begin % 16;
+    if (tiles_end(begin) > (n_space + KSA_K_TILE - 1) / KSA_K_TILE * KSA_K_TILE) begin -= begin % KSA_K_TILE;
     KsaSegment &s = it.seg[it.n_seg++];
     s.space = space;
     s.begin = (int32_t)begin;
@@ -64,13 +67,13 @@ KsaWorkItem text_item(const ksa_params &p, int64_t t0, int32_t cnt) {
     it.q_space = KSA_SPACE_TEXT;
     it.q_begin = (int32_t)t0;
     it.q_count = cnt;
-    const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks;
+    const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = p.n_text / c * m;
     const int64_t j0 = t0 / c, j1 = (t0 + cnt - 1) / c;
     // distant summaries: the first row's chunk sees the fewest (those every row sees), the last row's chunk the most
-    if (m > 0) push_segment(it, KSA_SPACE_SUMMARY, 0, pos_part(j1 - C) * m, 0, pos_part(j0 - C) * m);
+    if (m > 0) push_segment(it, KSA_SPACE_SUMMARY, 0, pos_part(j1 - C) * m, 0, pos_part(j0 - C) * m, n_sum);
     // sliding-chunk text: [lo_first, ...) is seen by the first row's chunk, [lo_last, t0) by every row
     const int64_t lo_first = pos_part(j0 - C) * c, lo_last = pos_part(j1 - C) * c;
-    push_segment(it, KSA_SPACE_TEXT, lo_first, t0 + cnt, lo_last, t0);
+    push_segment(it, KSA_SPACE_TEXT, lo_first, t0 + cnt, lo_last, t0, p.n_text);
     return it;
 }
 
@@ -81,34 +84,11 @@ KsaWorkItem summary_item(const ksa_params &p, int64_t u0, int32_t cnt) {
     it.q_space = KSA_SPACE_SUMMARY;
     it.q_begin = (int32_t)u0;
     it.q_count = cnt;
-    const int64_t c = p.chunk_len, m = p.n_summary;
+    const int64_t c = p.chunk_len, m = p.n_summary, n_sum = p.n_text / c * m;
     const int64_t j0 = u0 / m, j1 = (u0 + cnt - 1) / m;
-    push_segment(it, KSA_SPACE_TEXT, j0 * c, (j1 + 1) * c, 0, 0);
-    push_segment(it, KSA_SPACE_SUMMARY, j0 * m, u0 + cnt, 0, 0);
+    push_segment(it, KSA_SPACE_TEXT, j0 * c, (j1 + 1) * c, 0, 0, p.n_text);
+    push_segment(it, KSA_SPACE_SUMMARY, j0 * m, u0 + cnt, 0, 0, n_sum);
     return it;
-}
-
-// Can the kernel walk every key run of the item with its pipelined loop?  That loop computes each lane's row
-// offsets once per run and reads V from a key-major copy whose keys are permuted in groups of 16, so it needs
-//   - tiles that all start at the same phase of the chunk pattern (64 % period == 0) or never cross a chunk
-//     (period % 64 == 0 and an aligned start), period = c for text keys and m for summary keys,
-//   - a run that starts at a multiple of 16,
-//   - a last tile that ends inside the index space (all 64 rows of every tile exist), and
-//   - a chunk length and a summary count that are powers of two.
-bool item_pipelined(const ksa_params &p, const KsaWorkItem &it) {
-    const int64_t n_sum = (int64_t)(p.n_text / p.chunk_len) * p.n_summary;
-    // ... and chunk shapes that are powers of two: that loop maps compact indices to rows with shifts, in scalar code
-    // it can afford inside an MFMA slot
-    auto pow2 = [](int64_t x) { return x > 0 && (x & (x - 1)) == 0; };
-    if (!pow2(p.chunk_len) || (p.n_summary > 0 && !pow2(p.n_summary))) return false;
-    for (int s = 0; s < it.n_seg; ++s) {
-        const KsaSegment &g = it.seg[s];
-        const int64_t period = g.space == KSA_SPACE_TEXT ? p.chunk_len : p.n_summary;
-        const int64_t n_space = g.space == KSA_SPACE_TEXT ? p.n_text : n_sum;
-        const bool invariant = (KSA_K_TILE % period == 0) || (period % KSA_K_TILE == 0 && g.begin % KSA_K_TILE == 0);
-        if (!invariant || g.begin % 16 != 0 || g.begin + (int64_t)tiles_in(g) * KSA_K_TILE > n_space) return false;
-    }
-    return true;
 }
 
 // Which of the two forward kernels a layout takes: true = ksa_prefill_direct.hip.
@@ -148,11 +128,10 @@ bool dq_takes_direct(const ksa_layout &lay) {
 // Launch order.  Workgroups are dealt to the 8 XCDs round-robin by workgroup id, and each XCD has its
 // own L2: queue q (workgroup ids congruent to q mod 8) is given whole (batch, KV head) groups so that the
 // workgroups running together on one XCD stream the same K/V rows, and items go heaviest first so the
-// long tiles start early (longest-processing-time order).  The entries of the items that the forward kernel's
-// pipelined instantiation walks come first, those of the other items after them, each part a launch of its own.
-// Appends the launch entries of items [item_lo, item_hi) to lay.entries (a whole number of rounds of 8).
-void build_entries(ksa_layout &lay, int32_t item_lo, int32_t item_hi) {
+// long tiles start early (longest-processing-time order).  A whole number of rounds of 8.
+void build_entries(ksa_layout &lay) {
     const ksa_params &p = lay.p;
+    const int32_t n_items = (int32_t)lay.items.size();
     const int32_t n_groups = p.batch * p.n_kv_heads;
     const int32_t gsz = p.n_q_heads / p.n_kv_heads;
     std::vector<std::vector<KsaWgEntry>> queue(KSA_NUM_XCD);
@@ -168,7 +147,7 @@ void build_entries(ksa_layout &lay, int32_t item_lo, int32_t item_hi) {
     };
     if (n_groups >= KSA_NUM_XCD) {
         for (int q = 0; q < KSA_NUM_XCD; ++q)
-            for (int32_t it = item_lo; it < item_hi; ++it)
+            for (int32_t it = 0; it < n_items; ++it)
                 for (int32_t grp = q; grp < n_groups; grp += KSA_NUM_XCD) emit(q, it, grp);
     } else {
         // fewer groups than XCDs: the queues congruent to grp mod n_groups share the items of group grp
@@ -176,15 +155,14 @@ void build_entries(ksa_layout &lay, int32_t item_lo, int32_t item_hi) {
             const int32_t grp = q % n_groups;
             const int32_t sharers = (KSA_NUM_XCD - grp + n_groups - 1) / n_groups;  // queues serving grp
             const int32_t rank = q / n_groups;
-            for (int32_t it = item_lo + rank; it < item_hi; it += sharers) emit(q, it, grp);
+            for (int32_t it = rank; it < n_items; it += sharers) emit(q, it, grp);
         }
     }
     size_t longest = 0;
     for (auto &qv : queue) longest = std::max(longest, qv.size());
-    const size_t base = lay.entries.size();
-    lay.entries.resize(base + longest * KSA_NUM_XCD, KsaWgEntry{-1, 0, 0, 0});
+    lay.entries.resize(longest * KSA_NUM_XCD, KsaWgEntry{-1, 0, 0, 0});
     for (int q = 0; q < KSA_NUM_XCD; ++q)
-        for (size_t x = 0; x < queue[q].size(); ++x) lay.entries[base + x * KSA_NUM_XCD + q] = queue[q][x];
+        for (size_t x = 0; x < queue[q].size(); ++x) lay.entries[x * KSA_NUM_XCD + q] = queue[q][x];
 }
 
 // Steps of the dK / dV work of the keys [k0, k1) of an index space, per query head: the aligned 64-row query blocks that
@@ -287,18 +265,16 @@ int ksa_build_layout(const ksa_params *params, ksa_layout **out) {
     const int64_t n_sum = (int64_t)lay->n_chunks * p.n_summary;
     for (int64_t u0 = 0; u0 < n_sum; u0 += qt)
         lay->items.push_back(summary_item(p, u0, (int32_t)std::min<int64_t>(qt, n_sum - u0)));
-    for (KsaWorkItem &it : lay->items) {
-        it.pipelined = item_pipelined(p, it) ? 1 : 0;
-        lay->n_pipelined_items += it.pipelined;
-    }
-    std::stable_sort(lay->items.begin(), lay->items.end(), [](const KsaWorkItem &a, const KsaWorkItem &b) {
-        return a.pipelined != b.pipelined ? a.pipelined > b.pipelined : a.n_tiles > b.n_tiles;
-    });
+    for (const KsaWorkItem &it : lay->items)
+        for (int32_t s = 0; s < it.n_seg; ++s) {
+            const KsaSegment &g = it.seg[s];
+            lay->ragged |= g.begin + (int64_t)tiles_in(g) * KSA_K_TILE > (g.space == KSA_SPACE_TEXT ? (int64_t)p.n_text : n_sum);
+        }
+    std::stable_sort(lay->items.begin(), lay->items.end(),
+                     [](const KsaWorkItem &a, const KsaWorkItem &b) { return a.n_tiles > b.n_tiles; });
     lay->direct = takes_direct(*lay);
     lay->dq_direct = dq_takes_direct(*lay);
-    build_entries(*lay, 0, lay->n_pipelined_items);
-    lay->n_pipelined_entries = (int32_t)lay->entries.size();
-    build_entries(*lay, lay->n_pipelined_items, (int32_t)lay->items.size());
+    build_entries(*lay);
     build_dkv(*lay);
     } catch (...) {
         delete lay;

@@ -13,13 +13,10 @@
 // K tiles (64 keys) go from global memory straight into LDS (global_load_lds_dwordx4, no VGPR staging) with
 // an XOR swizzle of the 16-byte chunks applied on the global side and are read with ds_read_b128.
 //
-// Two kernels come out of one template.  PIPELINED = true (work items all of whose key runs meet the
-// conditions the scheduler checks; every item of the paper's shapes): a software-pipelined loop over 32-key
-// sub-tiles, three LDS buffers per operand, V read from a key-major copy made by ksa_vt_kernel so that the
-// V^T operand is one ds_read_b128 as well; masked runs (window edges, the causal diagonal, summary rows) go
-// through the same loop and clip every score to its row's visible key range.  PIPELINED = false: the
-// remaining items, with a plain load -> compute loop per tile and the gfx950 transposing LDS read
-// (ds_read_b64_tr_b16) for V^T out of the row-major tile.
+// A software-pipelined loop over 32-key sub-tiles, three LDS buffers per operand, V read from a key-major copy made by
+// ksa_vt_kernel so that the V^T operand is one ds_read_b128 as well; masked runs (window edges, the causal diagonal, summary
+// rows) go through the same loop and clip every score to its row's visible key range.  Chunk lengths and summary counts are
+// powers of two here; other shapes, and layouts with short key runs, take ksa_prefill_direct.hip.
 // The running maximum is only raised when a tile exceeds it by more than 2^8 in the exponent domain, so the
 // accumulator rescale almost never runs; results are unchanged because the final 1/l normalisation uses
 // the same reference.
@@ -81,8 +78,6 @@ __device__ __forceinline__ float other_half(float x) {
 // LDS tile: row-major [64][D] bf16, the 16-byte chunk index XORed with a function of the row
 template <int D>
 __device__ __forceinline__ int k_swz(int row) { return row & (D / 8 - 1); }
-template <int D>
-__device__ __forceinline__ int v_swz(int row) { return ((row & 3) << 2) & (D / 8 - 1); }
 
 template <int D>
 struct Tile {
@@ -105,24 +100,20 @@ struct Tile {
 // Per-lane element offsets (relative to the tile's first row) of the 16-byte pieces this lane fetches.
 template <int D>
 struct LaneOffsets {
-    int k[Tile<D>::NI], v[Tile<D>::NI];
+    int k[Tile<D>::NI];
     int vt[Tile<D>::NIV];   // key-major V: offsets relative to (row 0 of the head, first key of the tile)
 };
 
-// Offsets for the tile whose first key is kt; rows beyond `last` (inclusive bound) are clamped to it.
+// Offsets for a tile whose first key is kt.
 template <int D>
-__device__ __forceinline__ void lane_offsets(const PrefillArgs &a, int space, int kt, int last, int wave, int lane,
-                                             int base_aug, LaneOffsets<D> &off) {
+__device__ __forceinline__ void lane_offsets(const PrefillArgs &a, int space, int kt, int wave, int lane, int base_aug, LaneOffsets<D> &off) {
     using T = Tile<D>;
 #pragma unroll
     for (int i = 0; i < T::NI; ++i) {
         const int row = RW * wave + T::RPI * i + lane / T::CH;
         const int pch = lane % T::CH;
-        int kc = kt + row;
-        kc = kc < last ? kc : last;
-        const int rel = (aug_row(a, space, kc) - base_aug) * (int)a.ks[1];
+        const int rel = (aug_row(a, space, kt + row) - base_aug) * (int)a.ks[1];
         off.k[i] = rel + ((pch ^ k_swz<D>(row)) << 3);
-        off.v[i] = rel + ((pch ^ v_swz<D>(row)) << 3);
     }
 }
 
@@ -141,21 +132,10 @@ __device__ __forceinline__ void lane_offsets_vt(int vt_stride, int wave, int lan
     }
 }
 
-template <int D>
-__device__ __forceinline__ void issue_tile_load(const __bf16 *gbase, const int (&off)[Tile<D>::NI], unsigned char *lds,
-                                                int buf_off, int wave) {
-    using T = Tile<D>;
-#pragma unroll
-    for (int i = 0; i < T::NI; ++i) {
-        lds_direct_load_16(gbase + off[i], lds + buf_off + (RW * wave + T::RPI * i) * (D * 2));
-    }
-}
-
 // Byte addresses inside an LDS tile are written as (per-lane constant XOR small constant) + constant, so that
 // a handful of registers plus the instructions' immediate offsets cover every operand read.
 struct LaneLds {
     int k;   // K operand: row r, chunk (swizzle(r) ^ h); XOR (s << 5) selects k step s
-    int v;   // V^T operand: this lane's address row / column of the transposing read; XOR (db << 6) selects the column block
     int vt;  // V^T operand out of a key-major tile: row r, piece (swizzle(r) ^ h); XOR ((2 * sb + hf) << 5) selects the
              // 16-key group, + db * 4096 the block of 32 head-dim rows
 };
@@ -163,112 +143,21 @@ struct LaneLds {
 template <int D>
 __device__ __forceinline__ LaneLds lane_lds(int lane) {
     const int r = lane & 31, h = lane >> 5;
-    const int grp = lane >> 4, li = lane & 15;
-    // transposing read: lane (grp, li) supplies the address of key 4*(grp/2) + li/4, columns 16*(grp%2) + 4*(li%4) .. +3
-    // and receives keys 4*(grp/2) .. +3 of column 16*(grp%2) + li
-    const int t_row = 4 * (grp >> 1) + (li >> 2);
-    const int t_col = 16 * (grp & 1) + 4 * (li & 3);
     LaneLds L;
     L.k = r * (D * 2) + ((k_swz<D>(r) ^ h) << 4);
-    L.v = t_row * (D * 2) + (((t_col >> 3) ^ v_swz<D>(t_row)) << 4) + ((t_col & 7) << 1);
     L.vt = r * 128 + ((h ^ vt_swz(r)) << 4);
     return L;
 }
 
-// S^T (two 32-key blocks) for QB query blocks: sacc[qb][kb] += K[kb] Q[qb]^T
-template <int D>
-__device__ __forceinline__ void score_mfma(const unsigned char *lds, int buf_off, const LaneLds &ll,
-                                           const bf16x8 (&qreg)[QB][Tile<D>::KS], f32x16 (&sacc)[QB][2]) {
-    using T = Tile<D>;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int g = 0; g < 16; ++g) sacc[qb][kb][g] = 0.f;
-#pragma unroll
-    for (int s = 0; s < T::KS; ++s) {
-        const int a_s = ll.k ^ (s << 5);   // logical chunk 2s + h of row r
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(lds + a_s + (buf_off + kb * 32 * (D * 2)));
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-                sacc[qb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[qb][s], sacc[qb][kb], 0, 0, 0);
-        }
-    }
-}
-
-// O^T += V^T P^T
-template <int D>
-__device__ __forceinline__ void pv_mfma(const unsigned char *lds, int buf_off, const LaneLds &ll,
-                                        const bf16x8 (&pb)[QB][2][2], f32x16 (&oacc)[QB][Tile<D>::DB]) {
-    using T = Tile<D>;
-#pragma unroll
-    for (int db = 0; db < T::DB; ++db) {
-        const int a_db = ll.v ^ (db << 6);
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const int o0 = buf_off + (kb * 32 + hf * 16) * (D * 2), o1 = o0 + 8 * (D * 2);
-                const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(lds + a_db + o0));
-                const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(lds + a_db + o1));
-                const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-                    oacc[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[qb][kb][hf], oacc[qb][db], 0, 0, 0);
-            }
-    }
-}
-
 // Online-softmax state of one lane's query rows.  m_ref is the reference maximum (raw score units) the
-// exponentials are taken against; l_part is this lane's part of the row sum (the lane pair is added up at
-// the end).
+// exponentials are taken against.
 struct RowState {
-    float m_ref[QB], l_part[QB];
-    f32x4 l_sum[QB];    // pipelined kernel: row sums kept by sum_half(): lanes 0..15, registers 0 (query = lane) and 1 (+ 16)
+    float m_ref[QB];
+    f32x4 l_sum[QB];    // row sums kept by sum_half(): lanes 0..15, registers 0 (query = lane) and 1 (+ 16)
 };
 
-// Row maxima of a score tile; returns true if some lane's row exceeds its reference by more than the threshold.
-__device__ __forceinline__ bool tile_max(const f32x16 (&sacc)[QB][2], const RowState &st, float sl, float (&tmax)[QB]) {
-    bool raise = false;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        float mx = sacc[qb][0][0];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int g = 0; g < 16; ++g) mx = fmaxf(mx, sacc[qb][kb][g]);
-        mx = fmaxf(mx, other_half(mx));
-        tmax[qb] = mx;
-        raise |= (mx - st.m_ref[qb]) * sl > RESCALE_THRESHOLD_LOG2;
-    }
-    return __builtin_amdgcn_ballot_w64(raise) != 0;   // wave-uniform
-}
-
-// Raises the reference maxima to the tile maxima and rescales the row sums and the output accumulators (generic
-// kernel).  Rarely taken: see RESCALE_THRESHOLD_LOG2.
-template <int D>
-__device__ __forceinline__ void raise_reference(RowState &st, const float (&tmax)[QB], f32x16 (&oacc)[QB][Tile<D>::DB],
-                                                float sl) {
-    using T = Tile<D>;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const float m_new = fmaxf(st.m_ref[qb], tmax[qb]);
-        // (old - new) first: equal references (also the -1e30 start value) must give exactly 2^0
-        const float alpha = __builtin_amdgcn_exp2f((st.m_ref[qb] - m_new) * sl);
-        st.m_ref[qb] = m_new;
-        st.l_part[qb] *= alpha;
-#pragma unroll
-        for (int db = 0; db < T::DB; ++db)
-#pragma unroll
-            for (int g = 0; g < 16; ++g) oacc[qb][db][g] *= alpha;
-    }
-}
-
-// The pipelined kernel's version.  mx are the LANE's maxima of the pending scores; the two lanes of a row are combined
-// here.  The output accumulators live in accumulation registers and are only ever touched by the inline-assembly
+// Raises the reference maxima and rescales the row sums and the output accumulators.  Rarely taken: see
+// RESCALE_THRESHOLD_LOG2.  mx are the LANE's maxima of the pending scores; the two lanes of a row are combined here.  The output accumulators live in accumulation registers and are only ever touched by the inline-assembly
 // MFMAs of pv_mfma_raw() and by this routine, which scales them in place, also in assembly: left to the compiler, the
 // copies to VGPRs that a plain multiply needs get hoisted out of this block into the loop around it, where they would
 // drain the MFMA pipe on every tile.
@@ -339,31 +228,6 @@ __device__ __forceinline__ void accumulators_settle(f32x16 (&oacc)[QB][Tile<D>::
             if (qb + db > 0) asm volatile("" : "+a"(oacc[qb][db]));
 }
 
-// p = 2^((s - m_ref) * scale * log2 e) rounded to bf16 in the B-operand layout of P V.  The row sum adds up the
-// ROUNDED values (v_dot2c_f32_bf16 against (1, 1)), so that O = sum(p v) / sum(p) is normalised by exactly the
-// weights that were multiplied: a row dominated by one key returns that key's V row up to output rounding.
-__device__ __forceinline__ void exp_and_pack(const f32x16 (&sacc)[QB][2], bf16x8 (&pb)[QB][2][2], RowState &st, float sl) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const float msl = st.m_ref[qb] * sl;
-        float rsum = st.l_part[qb];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int g = 0; g < 16; g += 2) {
-                bf16x2 pk;
-                pk[0] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[qb][kb][g], sl, -msl));
-                pk[1] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[qb][kb][g + 1], sl, -msl));
-                rsum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, rsum, false);
-                pb[qb][kb][g / 8][g % 8] = pk[0];
-                pb[qb][kb][g / 8][g % 8 + 1] = pk[1];
-            }
-        st.l_part[qb] = rsum;
-    }
-}
-
 // ---- pieces of the pipelined loop, which advances in sub-tiles of 32 keys -------------------------------------
 // Source order below is the intended issue order: every MFMA group is followed by a slice of independent VALU
 // work, and the order is pinned with scheduling barriers, because one wave per SIMD has nobody else to fill its
@@ -429,11 +293,16 @@ __device__ __forceinline__ void issue_vt_load_part(const __bf16 *gbase, unsigned
 
 // What the synchronising sub-tile of a tile does besides its arithmetic: wait for this wave's pieces of the next
 // tile, meet the other waves, and request the tile after that.
-template <int D>
+// RAGGED: some run's last tile reaches past the end of its index space.  Its K rows do not exist there: the byte offset of
+// a lane is limited to the last 16 bytes of the last row (one v_min per K load; rows are at least head_dim elements apart,
+// the launch checks that, so pieces of rows that exist are never cut).  What is fetched instead is masked.
+template <int D, bool RAGGED>
 struct TileSync {
     const __bf16 *kg, *vg;          // global addresses (wave-uniform) of the first row of the tile to request
     const unsigned *k_off, *v_off;  // the lane's byte offsets from them, one per load instruction
     unsigned k_dst, v_dst;          // LDS byte addresses of this wave's share of the buffers it goes to
+    unsigned k_lim;                 // RAGGED: limit of the K offsets of the tile to request
+    __device__ __forceinline__ unsigned k_offset(int i) const { return RAGGED ? min(k_off[i], k_lim) : k_off[i]; }
 };
 
 // v_max3_f32 without the NaN-quieting self-maxima that fmaxf expands to
@@ -489,12 +358,12 @@ __device__ __forceinline__ unsigned pack_pair(float w0, float w1) {
 // (the lane pair of a row is only combined when a raise happens).
 // TRACK = false: the reference maximum is fixed for the whole work item (see static_reference() in the kernel): no row
 // maxima, no raise decision; a MASKED run still clips the next scores in the same slots.
-template <int D, bool SYNC, bool MASKED, bool TRACK, class Hook>
+template <int D, bool SYNC, bool MASKED, bool TRACK, class Sync, class Hook>
 __device__ __forceinline__ bool subtile(unsigned char *lds, const LaneLds &ll, const bf16x8 (&qreg)[QB][Tile<D>::KS],
                                         f32x16 (&sv_next)[QB], const f32x16 (&sv_cur)[QB], bf16x8 (&ka)[Tile<D>::RING],
                                         int k_off, int v_off, int sb, int k_next_off, f32x16 (&oacc)[QB][Tile<D>::DB],
                                         RowState &st, const u32x4 &ind, float sl, float raise_margin,
-                                        float (&mx_out)[QB], const TileSync<D> &sync, int next_key0, const int (&vis_lo)[QB],
+                                        float (&mx_out)[QB], const Sync &sync, int next_key0, const int (&vis_lo)[QB],
                                         const int (&vis_span)[QB], Hook hook) {
     using T = Tile<D>;
     constexpr int NSTEP = 2 * T::DB;              // (hf, db) pairs of the P V phase
@@ -619,7 +488,7 @@ __device__ __forceinline__ bool subtile(unsigned char *lds, const LaneLds &ll, c
                 asm volatile("s_barrier" ::: "memory");
             }
             // the tile after next, one instruction per slot
-            if (u >= 1 && u - 1 < T::NI) issue_tile_load_part<D>(sync.kg, sync.k_off[u - 1], sync.k_dst, u - 1);
+            if (u >= 1 && u - 1 < T::NI) issue_tile_load_part<D>(sync.kg, sync.k_offset(u - 1), sync.k_dst, u - 1);
             if (u >= 1 + T::NI && u - 1 - T::NI < T::NIV)
                 issue_vt_load_part<D>(sync.vg, sync.v_off[u - 1 - T::NI], sync.v_dst, u - 1 - T::NI);
         }
@@ -652,10 +521,10 @@ __device__ __forceinline__ bool subtile(unsigned char *lds, const LaneLds &ll, c
 // exponential.  It keeps the pipeline state the neighbouring sub-tiles rely on: the next scores are all "masked", the
 // first RING K operands of the following block are read, and with SYNC it waits for its tile loads, meets the other
 // waves at the tile's one barrier and issues its share of the requests for the tile after next.
-template <int D, bool SYNC>
+template <int D, bool SYNC, class Sync>
 __device__ __forceinline__ void idle_subtile(unsigned char *lds, const LaneLds &ll, f32x16 (&sv_next)[QB],
                                              bf16x8 (&ka)[Tile<D>::RING], int k_next_off, float (&mx_out)[QB],
-                                             const TileSync<D> &sync) {
+                                             const Sync &sync) {
     using T = Tile<D>;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -667,7 +536,7 @@ __device__ __forceinline__ void idle_subtile(unsigned char *lds, const LaneLds &
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's pieces of the next tile have landed
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < T::NI; ++i) issue_tile_load_part<D>(sync.kg, sync.k_off[i], sync.k_dst, i);
+        for (int i = 0; i < T::NI; ++i) issue_tile_load_part<D>(sync.kg, sync.k_offset(i), sync.k_dst, i);
 #pragma unroll
         for (int i = 0; i < T::NIV; ++i) issue_vt_load_part<D>(sync.vg, sync.v_off[i], sync.v_dst, i);
     }
@@ -675,10 +544,7 @@ __device__ __forceinline__ void idle_subtile(unsigned char *lds, const LaneLds &
     for (int x = 0; x < T::RING; ++x) ka[x] = read_k_operand<D>(lds, ll.k + k_next_off, x);
 }
 
-// PIPELINED = true: work items all of whose key runs satisfy the conditions of the pipelined loop (the scheduler
-// marks them); false: the remaining items, walked with the plain loop.  Two instantiations rather than one kernel
-// with both loops keep the register allocation of the pipelined loop free of the plain loop's temporaries.
-template <int D, bool PIPELINED>
+template <int D, bool RAGGED>
 __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs a) {
     using T = Tile<D>;
     // three K tiles, then three V tiles: the pipelined loop loads two tiles ahead with one barrier per tile
@@ -689,7 +555,6 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
     const KsaWgEntry ent = a.entries[blockIdx.x];
     if (ent.item < 0) return;
     const KsaWorkItem &item = a.items[ent.item];
-    if ((item.pipelined != 0) != PIPELINED) return;
     // The runs' few words are copied into scalar registers here: read through the reference at the start of each run
     // they would be fetched from memory again (the tile requests are opaque memory operations to the compiler), one
     // more memory round trip in front of every run's first tile request.
@@ -766,17 +631,21 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
     wlo_s = __builtin_amdgcn_readfirstlane(wlo_s), whi_s = __builtin_amdgcn_readfirstlane(whi_s);
 
     const __bf16 *kbase = a.k + b * a.ks[0] + hkv * a.ks[2];
-    const __bf16 *vbase = a.v + b * a.ks[0] + hkv * a.ks[2];
+    // RAGGED: limit of a lane's byte offset into the tile that starts at key u (see TileSync)
+    auto k_limit = [&](int space, int u) {
+        const int last = (space == KSA_SPACE_TEXT ? a.n_text : a.n_sum) - 1;
+        return last - u >= BN - 1 ? ~0u : (unsigned)(aug_row(a, space, last) - aug_row(a, space, u)) * ((unsigned)a.ks[1] * 2u) + (D * 2 - 16);
+    };
     // ---- the first key tiles of the first run are requested right behind the Q rows ----------------------
     // A workgroup owns its compute unit alone (LDS, registers), so nothing hides its start-up: the Q rows come from
     // HBM (about 4 us on the loaded chip), and the first two key tiles another 2 us if they were only requested once
     // the Q rows are there.  Requested here they travel together.  Nothing else touches the LDS ring before the run's
     // own set-up in the loop below, which repeats this arithmetic and skips the requests.
-    if constexpr (PIPELINED) {
+    {
         const int space = run_space[0], seg_begin = run_begin[0], seg_end = run_end[0];
         const int second = seg_end - seg_begin > BN ? 1 : 0;
         LaneOffsets<D> off;
-        lane_offsets<D>(a, space, seg_begin, 0x7fffffff, wave, lane, aug_row(a, space, seg_begin), off);
+        lane_offsets<D>(a, space, seg_begin, wave, lane, aug_row(a, space, seg_begin), off);
         const int vt_stride = space == KSA_SPACE_TEXT ? a.nt_pad : a.ns_pad;
         lane_offsets_vt<D>(vt_stride, wave, lane, off);
         const __bf16 *vtbase = a.vt + (space == KSA_SPACE_TEXT ? 0 : a.vt_sum_off) +
@@ -788,7 +657,11 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
             const int tt = t == 0 ? 0 : second;
             const __bf16 *kg = kbase + (int64_t)aug_row(a, space, seg_begin + tt * BN) * a.ks[1], *vg = vtbase + tt * BN;
 #pragma unroll
-            for (int i = 0; i < T::NI; ++i) issue_tile_load_part<D>(kg, (unsigned)off.k[i] * 2u, k_wave + t * T::BYTES, i);
+            for (int i = 0; i < T::NI; ++i) {
+                unsigned o = (unsigned)off.k[i] * 2u;
+                if constexpr (RAGGED) o = min(o, k_limit(space, seg_begin + tt * BN));
+                issue_tile_load_part<D>(kg, o, k_wave + t * T::BYTES, i);
+            }
 #pragma unroll
             for (int i = 0; i < T::NIV; ++i) issue_vt_load_part<D>(vg, (unsigned)off.vt[i] * 2u, v_wave + t * T::BYTES, i);
         }
@@ -809,8 +682,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
     // queries of unusual size) or not a number take the tracking variant; both variants execute the same barriers,
     // so the waves of a workgroup may differ.
     float m_static[QB];
-    bool static_ok = false;
-    if constexpr (PIPELINED) {
+    bool static_ok;
+    {
         const float kmax2 = a.knorm[b * a.n_kv_heads + hkv];
         bool ok = true;
 #pragma unroll
@@ -826,9 +699,6 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
             m_static[qb] = bound - 32.f / a.scale_log2e;
         }
         static_ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
-    } else {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) m_static[qb] = 0.f;
     }
 
     // Everything from the accumulators to the stores, once per variant (two copies of the code that share nothing but
@@ -841,7 +711,6 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         st.m_ref[qb] = TRACK ? -1e30f : m_static[qb];
-        st.l_part[qb] = 0.f;
         st.l_sum[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int db = 0; db < T::DB; ++db)
@@ -864,25 +733,23 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
         const int full_lo = seg == 0 ? run_full_lo[0] : run_full_lo[1], full_hi = seg == 0 ? run_full_hi[0] : run_full_hi[1];
         auto tile_masked = [&](int key0) { return !(key0 >= full_lo && key0 + BN <= full_hi); };
         const int n_tiles = (seg_end - seg_begin + BN - 1) / BN;
-        // Are the lanes' row offsets the same for every tile of the run?  Yes when every tile starts at the same
-        // phase of the chunk pattern (64 % period == 0), or never crosses a chunk (period % 64 == 0, aligned).
         const int period = space == KSA_SPACE_TEXT ? a.c : a.m;
-        const bool invariant = (BN % period == 0) || (period % BN == 0 && seg_begin % BN == 0);
         LaneOffsets<D> off;
-        if (invariant) lane_offsets<D>(a, space, seg_begin, 0x7fffffff, wave, lane, aug_row(a, space, seg_begin), off);
+        lane_offsets<D>(a, space, seg_begin, wave, lane, aug_row(a, space, seg_begin), off);
 
         // union of the visible ranges of the wave's rows in this index space: a masked tile outside it has nothing for
         // this wave
         const int wlo = space == KSA_SPACE_TEXT ? wlo_t : wlo_s, whi = space == KSA_SPACE_TEXT ? whi_t : whi_s;
-        if constexpr (PIPELINED) {
-            // (the scheduler guarantees: lane offsets invariant over the run, seg_begin % 16 == 0, and the run's last
-            // tile ends inside its index space, so every row of every tile exists)
+        {
+            // (With chunk lengths and summary counts that are powers of two the lane offsets are the same for every tile of a
+            // run: it starts at a multiple of 16 at the beginning of a chunk, or on the 64-key grid.  A run's last tile may end
+            // behind its index space, but not behind the next multiple of 64, up to which the key-major V holds zeros.)
             // ================= pipelined loop over a run of tiles =======================================
             // The loop advances in sub-tiles of 32 keys (2t and 2t+1 for the halves of LDS tile t); see subtile().
             // The accumulators are only touched by VALU in the rare "raise the reference" block between sub-tiles.
             // LDS tile t lives in buffer t % 3; tile t+2 is requested right after the one barrier of tile t.
             // A MASKED run differs in one place: every score is clipped to its row's visible key range when it is
-            // looked at for the row maximum.  (Every row of every tile exists: the run ends inside its index space.)
+            // looked at for the row maximum.
             auto tile_base = [&](int t) { return (int64_t)aug_row(a, space, seg_begin + t * BN) * a.ks[1]; };
             constexpr int HALF = 32 * (D * 2);   // byte offset of the second 32-key block of a tile
             // V comes from the key-major copy: rows of one (batch, KV head, index space), keys contiguous
@@ -901,10 +768,12 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
             auto issue_tile = [&](int t, int buf_off) {
                 const __bf16 *kg = kbase + tile_base(t), *vg = vtbase + t * BN;
 #pragma unroll
-                for (int i = 0; i < T::NI; ++i) issue_tile_load_part<D>(kg, k_offb[i], k_wave + buf_off, i);
+                for (int i = 0; i < T::NI; ++i)
+                    issue_tile_load_part<D>(kg, RAGGED ? min(k_offb[i], k_limit(space, seg_begin + t * BN)) : k_offb[i], k_wave + buf_off, i);
 #pragma unroll
                 for (int i = 0; i < T::NIV; ++i) issue_vt_load_part<D>(vg, v_offb[i], v_wave + buf_off, i);
             };
+            const unsigned last_lim = RAGGED ? k_limit(space, seg_begin + (n_tiles - 1) * BN) : 0u;
             // visible key range of each of the lane's rows inside this run: [lo, lo + span), lo stored minus 4 * h
             int vis_lo[QB], vis_span[QB];
 #pragma unroll
@@ -966,7 +835,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
 #pragma unroll
                 for (int s = 0; s < T::RING; ++s) ka_pre[s] = read_k_operand<D>(lds, ll.k + K0 + HALF, s);
                 int b_cur = 0, b_nxt = T::BYTES, b_ld = 2 * T::BYTES;   // buffer offsets of tiles tn, tn+1, tn+2
-                TileSync<D> sync;
+                TileSync<D, RAGGED> sync;
+                sync.k_lim = ~0u;
                 sync.k_off = k_offb;
                 sync.v_off = v_offb;
                 sync.kg = kbase, sync.vg = vtbase, sync.k_dst = k_wave, sync.v_dst = v_wave;
@@ -986,6 +856,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                     const int row = (u >> r_sh) * a.w + (u & r_msk) + r_add;
                     sync.kg = kbase + (int64_t)row * a.ks[1];
                     sync.vg = vtbase + tt * BN;
+                    if constexpr (RAGGED) sync.k_lim = tt == n_tiles - 1 ? last_lim : ~0u;
                 };
                 auto stretch = [&](auto masked_tag, int tn_begin, int tn_end) {
                     constexpr bool MASKED = decltype(masked_tag)::value;
@@ -1045,45 +916,6 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                 __builtin_amdgcn_s_waitcnt(0x0F70);
                 accumulators_settle<D>(oacc, st);
             }
-        } else {
-        // ================= plain loop: MASKED runs, short runs, odd chunk shapes ============================
-        for (int kt = seg_begin; kt < seg_end; kt += BN) {
-            const int t_lo = kt, t_hi = min(kt + BN, seg_end);
-            // the wave has nothing visible in this tile (block-diagonal summary rows, window edges): skip the math
-            const bool masked = tile_masked(kt);
-            const bool active = !masked || (t_lo < whi && t_hi > wlo);
-            const bool ragged = kt + BN > seg_end;
-            const int base_aug = aug_row(a, space, kt);
-            if (!invariant || ragged) lane_offsets<D>(a, space, kt, seg_end - 1, wave, lane, base_aug, off);
-            __syncthreads();
-            issue_tile_load<D>(kbase + (int64_t)base_aug * a.ks[1], off.k, lds, K0, wave);
-            issue_tile_load<D>(vbase + (int64_t)base_aug * a.ks[1], off.v, lds, V0, wave);
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            if (!active) continue;
-            f32x16 sacc[QB][2];
-            score_mfma<D>(lds, K0, ll, qreg, sacc);
-            if (masked) {
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {
-                    const int lo = space == KSA_SPACE_TEXT ? lo_t[qb] : lo_s[qb];
-                    const int hi = space == KSA_SPACE_TEXT ? hi_t[qb] : hi_s[qb];
-                    const int elo = max(lo, seg_begin), ehi = min(hi, seg_end);
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int g = 0; g < 16; ++g) {
-                            const int key = kt + kb * 32 + 8 * (g / 4) + 4 * h + (g % 4);
-                            if (key < elo || key >= ehi) sacc[qb][kb][g] = -INFINITY;
-                        }
-                }
-            }
-            bf16x8 pb[QB][2][2];
-            float tmax[QB];
-            if (tile_max(sacc, st, sl, tmax)) raise_reference<D>(st, tmax, oacc, sl);
-            exp_and_pack(sacc, pb, st, sl);
-            pv_mfma<D>(lds, V0, ll, pb, oacc);
-        }
         }
     }
 
@@ -1098,13 +930,9 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
         unsigned char *stg = lds + 6 * T::BYTES + wave * (32 * ROWB);
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            float l_row;
-            if (PIPELINED) {   // lane j < 16 holds the sums of queries j (register 0) and j + 16 (register 1)
-                const float s0 = __shfl(st.l_sum[qb][0], r & 15), s1 = __shfl(st.l_sum[qb][1], r & 15);
-                l_row = (r & 16) ? s1 : s0;
-            } else {
-                l_row = st.l_part[qb] + other_half(st.l_part[qb]);
-            }
+            // lane j < 16 holds the sums of queries j (register 0) and j + 16 (register 1)
+            const float s0 = __shfl(st.l_sum[qb][0], r & 15), s1 = __shfl(st.l_sum[qb][1], r & 15);
+            const float l_row = (r & 16) ? s1 : s0;
             const float inv = 1.0f / l_row;   // rows past the end of the tile: never stored
 #pragma unroll
             for (int db = 0; db < T::DB; ++db)
@@ -1117,7 +945,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                 }
             const int row0 = q_begin + (wrow * QB + qb) * 32;
             // the lane's piece of row 0 of its (batch, head); a row's address is this plus augmented row x row stride.
-            // The pipelined instantiation only sees chunk shapes that are powers of two (the scheduler's condition), so
+            // This kernel only sees chunk shapes that are powers of two (the scheduler's condition), so
             // the row map is two shifts and a multiply-add per store rather than the general map with its divisions
             // (60 instructions per store, 16 stores per wave, with the matrix pipe idle).
             const int piece = lane % T::CH;
@@ -1130,7 +958,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                 const u32x4 x = *reinterpret_cast<const u32x4 *>(stg + row * ROWB + piece * 16);
                 const int idx = row0 + row;
                 if (idx < q_end) {
-                    const int arow = PIPELINED ? (idx >> e_sh) * a.w + (idx & e_msk) + e_add : aug_row(a, q_space, idx);
+                    const int arow = (idx >> e_sh) * a.w + (idx & e_msk) + e_add;
                     *reinterpret_cast<u32x4 *>(obase + (int64_t)arow * a.os[1]) = x;
                 }
             }
@@ -1148,14 +976,10 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
         }
     }
     };
-    if constexpr (PIPELINED) {
-        if (static_ok)
-            body(std::false_type{});
-        else
-            body(std::true_type{});
-    } else {
+    if (static_ok)
+        body(std::false_type{});
+    else
         body(std::true_type{});
-    }
 }
 
 // Key-major copy of V for the pipelined loop.  The P V MFMA wants, per lane, eight keys of one head-dim column; V is
@@ -1317,7 +1141,9 @@ int ksa_launch_prefill(const KsaPrefillLaunch &L, void *stream) {
         // ... and so are the ones into the key-major copy of V (head_dim rows of nt_pad or ns_pad keys)
         if ((int64_t)L.p.head_dim * (a.nt_pad > a.ns_pad ? a.nt_pad : a.ns_pad) >= ((int64_t)1 << 31)) return KSA_ERR_UNSUPPORTED;
     }
-    if (L.phases == 3 && L.direct) return ksa_launch_prefill_direct(L, a.knorm_tiles, a.knorm, (a.nt_pad + a.ns_pad) / 64, stream);
+    // (rows that overlap: the limit on the offsets of a ragged last tile would cut into rows that exist)
+    if (L.phases == 3 && (L.direct || (L.ragged && L.kv_strides[1] < L.p.head_dim)))
+        return ksa_launch_prefill_direct(L, a.knorm_tiles, a.knorm, (a.nt_pad + a.ns_pad) / 64, stream);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (L.phases & 1) {
         const int tiles_text = a.nt_pad / 64, tiles_sum = a.ns_pad / 64;
@@ -1333,16 +1159,17 @@ int ksa_launch_prefill(const KsaPrefillLaunch &L, void *stream) {
         if (hipGetLastError() != hipSuccess) return KSA_ERR_HIP;
     }
     if (!(L.phases & 2)) return KSA_OK;
-    // the pipelined items' workgroups first, then those of the remaining items: one launch each
-    const dim3 block(NW * 64), grid_p(L.n_pipelined_entries), grid_g(L.n_entries - L.n_pipelined_entries);
-    PrefillArgs g = a;
-    g.entries = a.entries + L.n_pipelined_entries;
+    const dim3 block(NW * 64), grid(L.n_entries);
     if (L.p.head_dim == 128) {
-        if (grid_p.x > 0) hipLaunchKernelGGL((ksa_prefill_kernel<128, true>), grid_p, block, 0, st, a);
-        if (grid_g.x > 0) hipLaunchKernelGGL((ksa_prefill_kernel<128, false>), grid_g, block, 0, st, g);
+        if (L.ragged)
+            hipLaunchKernelGGL((ksa_prefill_kernel<128, true>), grid, block, 0, st, a);
+        else
+            hipLaunchKernelGGL((ksa_prefill_kernel<128, false>), grid, block, 0, st, a);
     } else if (L.p.head_dim == 64) {
-        if (grid_p.x > 0) hipLaunchKernelGGL((ksa_prefill_kernel<64, true>), grid_p, block, 0, st, a);
-        if (grid_g.x > 0) hipLaunchKernelGGL((ksa_prefill_kernel<64, false>), grid_g, block, 0, st, g);
+        if (L.ragged)
+            hipLaunchKernelGGL((ksa_prefill_kernel<64, true>), grid, block, 0, st, a);
+        else
+            hipLaunchKernelGGL((ksa_prefill_kernel<64, false>), grid, block, 0, st, a);
     } else {
         return KSA_ERR_UNSUPPORTED;
     }

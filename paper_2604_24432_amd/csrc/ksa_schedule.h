@@ -37,8 +37,7 @@ struct KsaWorkItem {
     int32_t n_seg;
     KsaSegment seg[KSA_MAX_SEGMENTS];
     int32_t n_tiles;   // key tiles over all segments (the item's cost)
-    int32_t pipelined; // 1: every segment meets the conditions of the kernel's pipelined loop (see ksa_item_pipelined)
-    int32_t pad[2];
+    int32_t pad[3];
 };
 
 // Backward dK / dV: keys per workgroup, and what the workgroups of one (batch, KV head) do.  A key tile's work is a
