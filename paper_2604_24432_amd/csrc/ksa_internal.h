@@ -51,9 +51,9 @@ struct KsaPrefillLaunch {
 };
 size_t ksa_prefill_workspace_size(const ksa_params &p);
 int ksa_launch_prefill(const KsaPrefillLaunch &a, void *stream);
-// The kernel for short key runs and chunk shapes that are no powers of two (ksa_prefill_direct.hip).  knorm_tiles, knorm:
-// the row-norm parts of the workspace.
-int ksa_launch_prefill_direct(const KsaPrefillLaunch &a, float *knorm_tiles, float *knorm, int32_t norm_tiles, void *stream);
+// The kernel for short key runs and chunk shapes that are no powers of two (ksa_prefill_direct.hip).  knorm_parts, knorm:
+// the row norms in the workspace, of parts of the rows (room for one per 64 rows) and of the whole (batch, KV head).
+int ksa_launch_prefill_direct(const KsaPrefillLaunch &a, float *knorm_parts, float *knorm, void *stream);
 
 struct KsaPrefillBwdLaunch {
     const void *q, *k, *v, *o, *d_o;

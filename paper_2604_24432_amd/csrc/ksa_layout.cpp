@@ -96,20 +96,26 @@ KsaWorkItem summary_item(const ksa_params &p, int64_t u0, int32_t cnt) {
 //     12/4 heads, d 64: 124 -> 54 us): the other kernel's pipelined loop maps rows with shifts.
 //   - Otherwise by the mean number of key tiles per query tile.  Up to the line the pipelined kernel's time goes into what
 //     its workgroups, alone on their compute unit, do outside the tile loop; beyond it the direct kernel's doubled operand
-//     traffic costs more.  Measured on both sides (pipelined / direct kernel, us, c 64, m 8 unless stated):
-//       d 128, 4 heads of a group per workgroup: 4K tokens (7 tiles) 134 / 93, 16K (17) 388 / 340, 28K (28) 904 / 873,
-//         32K (31) 1118 / 1105, 64K (60) 3800 / 4030; 32K with c 128, m 16 and outlier keys, where the pipelined kernel
-//         tracks row maxima (33), 1450 / 1300; no summaries: window 2048 (31) 495 / 497, causal 4K (33) 131 / 142;
-//       2 heads: 32K (33) 617 / 570, 64K (62) 1991 / 2053;
-//       1 head, 16 heads: 16K (20) 271 / 195, 48K (52) 1382 / 1285, 64K (66) 2214 / 2173, causal 8K (66) 247 / 263;
-//       d 64: 16K 268 / 218, 64K 2425 / 2275, 128K 9110 / 8728, 256K (8/2 heads, 231) 8550 / 8600, 512K (460) 16560 / 16970.
+//     traffic costs more.  Measured on both sides (pipelined / direct kernel, us, c 64, m 8 unless stated; cards and runs
+//     differ by 2 % in the comparison):
+//       d 128, 4 heads of a group per workgroup: 4K tokens (7 tiles) 134 / 93, 16K (17) 398 / 356, 28K (28) 906 / 903,
+//         32K (31) 1114 / 1133, 40K (38) 1641 / 1711; 32K with c 128, m 16 and outlier keys, where the pipelined kernel
+//         tracks row maxima (33), 1493 / 1295; no summaries: window 256 at 128K (5) 1347 / 1081, window 1024 (17) 328 / 314
+//         at 16K and 2429 / 2467 at 128K, window 1500 (25) 423 / 399, window 2048 (33) 495 / 511, causal 4K (33) 133 / 148;
+//       2 heads: 32K (33) 635 / 611, 40K (41) 926 / 911, 48K (49) 1209 / 1227, 64K (62) 1999 / 2112; no summaries: window
+//         1500 (25) 934 / 883, causal 4K (33) 107 / 97, window 2048 (33) 1099 / 1128, window 3000 (49) 1408 / 1483;
+//       1 head, 16 heads: 16K (20) 271 / 195, 48K (52) 1382 / 1285, 64K (66) 2219 / 2206, 80K (82) 3305 / 3358; no
+//         summaries: window 2048 (36) 1238 / 1214, window 3000 (51) 1576 / 1587, causal 8K (66) 247 / 270;
+//       d 64: 16K 268 / 218, 64K (60) 2527 / 2527, 128K (117) 9165 / 9659, 256K (8/2 heads, 231) 8360 / 9137, window 4096
+//         (65) 2280 / 2406.
 bool takes_direct(const ksa_layout &lay) {
     const ksa_params &p = lay.p;
     auto pow2 = [](int64_t x) { return x > 0 && (x & (x - 1)) == 0; };
     if (!pow2(p.chunk_len) || (p.n_summary > 0 && !pow2(p.n_summary))) return true;
     int64_t tiles = 0;
     for (const KsaWorkItem &it : lay.items) tiles += it.n_tiles;
-    const int64_t line = p.head_dim == 64 ? 230 : lay.head_stack == 4 ? (p.n_summary > 0 ? 34 : 30) : lay.head_stack == 2 ? 48 : 56;
+    const bool sums = p.n_summary > 0;
+    const int64_t line = p.head_dim == 64 ? 60 : lay.head_stack == 4 ? (sums ? 34 : 30) : lay.head_stack == 2 ? (sums ? 44 : 34) : 56;
     return tiles <= line * (int64_t)lay.items.size();
 }
 

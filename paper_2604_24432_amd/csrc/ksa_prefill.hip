@@ -1143,7 +1143,7 @@ int ksa_launch_prefill(const KsaPrefillLaunch &L, void *stream) {
     }
     // (rows that overlap: the limit on the offsets of a ragged last tile would cut into rows that exist)
     if (L.phases == 3 && (L.direct || (L.ragged && L.kv_strides[1] < L.p.head_dim)))
-        return ksa_launch_prefill_direct(L, a.knorm_tiles, a.knorm, (a.nt_pad + a.ns_pad) / 64, stream);
+        return ksa_launch_prefill_direct(L, a.knorm_tiles, a.knorm, stream);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (L.phases & 1) {
         const int tiles_text = a.nt_pad / 64, tiles_sum = a.ns_pad / 64;

@@ -23,6 +23,7 @@
 // ksa_prefill.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ksa_device.h"
@@ -40,14 +41,22 @@ constexpr int WG_PAIRS = NW * 32;       // (row, head) pairs per workgroup
 // keys); time at 64K, c 48: 4.75 / 4.53 / 4.45 ms.
 constexpr float RESCALE_THRESHOLD_LOG2 = 2.0f;
 
+// Parts the K row norms of a (batch, KV head) are kept in.  Every wave of the forward kernel takes the maximum of them all,
+// so there are few enough for four loads per lane that are in flight together; kept by 64-key tile
+// they were 32 dependent round trips at 128K tokens (32/8 heads, d 128: window 256 1467 -> 1081 us, window 1024 2735 -> 2467;
+// 16K tokens, c 64, m 8: 373 -> 356).
+constexpr int NORM_PARTS = 256;
+
 struct DirectArgs {
     const __bf16 *q, *k, *v;
     __bf16 *o;
     float *lse;
     int64_t qs[3], ks[3], os[3];        // {batch, row, head} strides in elements
-    const float *knorm_tiles;           // largest squared K row norm per (batch, KV head, 64-key tile); NULL: keep running maxima
+    const float *knorm_parts;           // largest squared K row norm per part of a (batch, KV head)'s rows; NULL: keep running maxima
     float *knorm;                       // ... per (batch, KV head): stored by one workgroup of each
-    int32_t norm_tiles;                 // tiles per (batch, KV head)
+    int32_t norm_parts;                 // parts per (batch, KV head), at most NORM_PARTS
+    int32_t norm_text_parts;            // the first so many are text
+    int32_t norm_run;                   // key tiles per part
     int32_t n_text, n_sum;
     int32_t c, m, C;
     uint32_t small_c, small_m;          // 65536 / c and 65536 / m, rounded up (used where c, m < 64)
@@ -298,12 +307,13 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
     const float sl = a.scale_log2e;
     float m_static = 0.f;
     bool static_ok = false;
-    if (!GRAD && a.knorm_tiles) {
+    if (!GRAD && a.knorm_parts) {
         float kmax2 = 0.f;
-        const float *src = a.knorm_tiles + (int64_t)bh * a.norm_tiles;
+        const float *src = a.knorm_parts + (int64_t)bh * a.norm_parts;
         bool bad = false;
-        for (int i = lane; i < a.norm_tiles; i += 64) {
-            const float x = src[i];
+#pragma unroll
+        for (int i = 0; i < NORM_PARTS; i += 64) {
+            const float x = src[min(i + lane, a.norm_parts - 1)];   // (the last one repeats)
             bad |= !(x == x);
             kmax2 = fmaxf(kmax2, x);
         }
@@ -577,40 +587,42 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dq_direct_k
     direct<D, true>(a, lds);
 }
 
-// Largest squared K row norm of every (batch, KV head, 64-key tile), the tiles of the text space first.
+// Largest squared K row norm of norm_run 64-key tiles of a (batch, KV head), the parts of the text space first.
 template <int D>
-__global__ __launch_bounds__(256) void ksa_knorm_tiles_kernel(const DirectArgs a, float *out, int text_key_tiles) {
+__global__ __launch_bounds__(256) void ksa_knorm_parts_kernel(const DirectArgs a, float *out) {
     constexpr int CH = D / 8, ROWS = 256 / CH;
     __shared__ float wave_best[4];
-    const int b = blockIdx.z, hkv = blockIdx.y, tid = threadIdx.x;
-    const int space = (int)blockIdx.x < text_key_tiles ? KSA_SPACE_TEXT : KSA_SPACE_SUMMARY;
-    const int k0 = (space == KSA_SPACE_TEXT ? blockIdx.x : blockIdx.x - text_key_tiles) * BN;
+    const int b = blockIdx.z, hkv = blockIdx.y, tid = threadIdx.x, part = blockIdx.x;
+    const int space = part < a.norm_text_parts ? KSA_SPACE_TEXT : KSA_SPACE_SUMMARY;
+    const int k0 = (space == KSA_SPACE_TEXT ? part : part - a.norm_text_parts) * a.norm_run * BN;
     const int n_space = space == KSA_SPACE_TEXT ? a.n_text : a.n_sum;
+    const int n_tiles = min(a.norm_run, (n_space - k0 + BN - 1) / BN);
     const __bf16 *kb = a.k + b * a.ks[0] + hkv * a.ks[2] + (tid % CH) * 8;
     float best = 0.f;
+    for (int t = 0; t < n_tiles; ++t) {
 #pragma unroll
-    for (int i = 0; i < BN / ROWS; ++i) {
-        const int key = min(k0 + ROWS * i + tid / CH, n_space - 1);
-        const bf16x8 x = *reinterpret_cast<const bf16x8 *>(kb + (int64_t)row_of(a, space, key) * a.ks[1]);
-        float s2 = 0.f;
+        for (int i = 0; i < BN / ROWS; ++i) {
+            const int key = min(k0 + BN * t + ROWS * i + tid / CH, n_space - 1);
+            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(kb + (int64_t)row_of(a, space, key) * a.ks[1]);
+            float s2 = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s2 = fmaf((float)x[e], (float)x[e], s2);
+            for (int e = 0; e < 8; ++e) s2 = fmaf((float)x[e], (float)x[e], s2);
 #pragma unroll
-        for (int d = CH / 2; d > 0; d >>= 1) s2 += __shfl_xor(s2, d);   // the CH lanes of a row are neighbours
-        best = fmaxf(best, s2);
+            for (int d = CH / 2; d > 0; d >>= 1) s2 += __shfl_xor(s2, d);   // the CH lanes of a row are neighbours
+            best = fmaxf(best, s2);
+        }
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) best = fmaxf(best, __shfl_xor(best, d));
     if ((tid & 63) == 0) wave_best[tid >> 6] = best;
     __syncthreads();
     if (tid == 0)
-        out[((int64_t)b * a.n_kv_heads + hkv) * gridDim.x + blockIdx.x] =
-            fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
+        out[((int64_t)b * a.n_kv_heads + hkv) * gridDim.x + part] = fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
 }
 
 template <int D>
-void launch(const DirectArgs &a, float *tiles, int text_key_tiles, int batch, int64_t n_wg, hipStream_t st) {
-    if (a.knorm_tiles) hipLaunchKernelGGL(ksa_knorm_tiles_kernel<D>, dim3(a.norm_tiles, a.n_kv_heads, batch), dim3(256), 0, st, a, tiles, text_key_tiles);
+void launch(const DirectArgs &a, float *parts, int batch, int64_t n_wg, hipStream_t st) {
+    if (a.knorm_parts) hipLaunchKernelGGL(ksa_knorm_parts_kernel<D>, dim3(a.norm_parts, a.n_kv_heads, batch), dim3(256), 0, st, a, parts);
     hipLaunchKernelGGL(ksa_prefill_direct_kernel<D>, dim3((unsigned)n_wg), dim3(NW * 64), 0, st, a);
 }
 
@@ -662,7 +674,7 @@ int64_t fill_lists(DirectArgs &a, const ksa_params &p, int32_t head_stack, int64
 
 }  // namespace
 
-int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_tiles, float *knorm, int32_t norm_tiles, void *stream) {
+int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_parts, float *knorm, void *stream) {
     DirectArgs a;
     a.q = static_cast<const __bf16 *>(L.q);
     a.k = static_cast<const __bf16 *>(L.k);
@@ -674,18 +686,20 @@ int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_tiles, flo
     // longer 1 but any number, rounded to bf16 like the others, and the outputs' error against fp64 would rise (2.15e-3 to
     // 2.26e-3 relative); the other shapes have had the fixed reference all along.
     const bool fixed = log2_exact(L.p.chunk_len) >= 0 && (L.p.n_summary == 0 || log2_exact(L.p.n_summary) >= 0);
-    a.knorm_tiles = fixed ? knorm_tiles : nullptr;
+    a.knorm_parts = fixed ? knorm_parts : nullptr;
     a.knorm = knorm;
-    a.norm_tiles = norm_tiles;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
     const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);
     if (n_wg >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int text_key_tiles = (a.n_text + BN - 1) / BN;
+    const int text_tiles = (a.n_text + BN - 1) / BN, sum_tiles = (a.n_sum + BN - 1) / BN;
+    a.norm_run = std::max(1, (text_tiles + sum_tiles + NORM_PARTS - 3) / (NORM_PARTS - 2));   // (each space may add a short part)
+    a.norm_text_parts = (text_tiles + a.norm_run - 1) / a.norm_run;
+    a.norm_parts = a.norm_text_parts + (sum_tiles + a.norm_run - 1) / a.norm_run;
     if (L.p.head_dim == 128)
-        launch<128>(a, knorm_tiles, text_key_tiles, L.p.batch, n_wg, st);
+        launch<128>(a, knorm_parts, L.p.batch, n_wg, st);
     else if (L.p.head_dim == 64)
-        launch<64>(a, knorm_tiles, text_key_tiles, L.p.batch, n_wg, st);
+        launch<64>(a, knorm_parts, L.p.batch, n_wg, st);
     else
         return KSA_ERR_UNSUPPORTED;
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
@@ -698,7 +712,7 @@ int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *lse2c, const
     a.v = static_cast<const __bf16 *>(L.v);
     a.g = static_cast<const __bf16 *>(L.d_o);
     a.o = static_cast<__bf16 *>(L.dq);
-    a.lse = nullptr, a.knorm_tiles = nullptr, a.knorm = nullptr, a.norm_tiles = 0;
+    a.lse = nullptr, a.knorm_parts = nullptr, a.knorm = nullptr, a.norm_parts = a.norm_text_parts = a.norm_run = 0;
     for (int x = 0; x < 3; ++x) a.qs[x] = L.q_strides[x], a.ks[x] = L.kv_strides[x], a.gs[x] = L.o_strides[x], a.os[x] = L.dq_strides[x];
     a.lse2c = lse2c, a.dlc = dlc;
     const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);

@@ -61,3 +61,26 @@ def test_rows_far_apart():
     got = K.ksa_prefill_fwd(lay, q.cuda(), *far)
     ref = O.prefill(q.float().numpy(), k.float().numpy(), v.float().numpy(), n, c, m, C)
     compare(got, ref, "rows 8 MiB apart")
+
+
+@pytest.mark.parametrize("n,c,m,C", [(64, 1, 0, 63), (64 * 254, 1, 0, 63), (64 * 254 + 1, 1, 0, 63), (64 * 255, 1, 0, 63), (128 * 254 - 127, 1, 0, 63),
+                                     (14464, 64, 8, 1), (14464 + 64, 64, 8, 1), (32768, 128, 1, 1), (50048, 64, 1, 2)])
+def test_norm_parts(n, c, m, C):
+    """The largest K row norm of a head is found wherever that row is: first and last rows of both spaces and of the parts
+    that the norms are kept in, below and above one key tile per part.  Whole-numbered keys: the norm is exact."""
+    d, n_chunks = 64, n // c
+    lay = K.ksa_build_layout(K.make_params(1, n, c, m, C, 1, 1, d))
+    L = lay.aug_len
+    nt, ns = -(-n // 64), -(-n_chunks * m // 64)
+    run = max(1, -(-(nt + ns) // 254))
+    text = {0, n - 1, min(64 * run, n) - 1, min(64 * run, n - 1), (nt - 1) // run * run * 64}
+    rows = [t + t // c * m for t in text] + [u + (u // m + 1) * c for u in ({0, n_chunks * m - 1, (ns - 1) // run * run * 64} if m else ())]
+    ws = torch.empty(K.prefill_workspace_bytes(lay), dtype=torch.uint8, device="cuda")
+    at = 2 * d * 64 * (nt + ns) + 4 * (nt + ns)     # behind the key-major V and the norms of the parts
+    q, v = torch.zeros(1, L, 1, d, dtype=torch.bfloat16, device="cuda"), torch.ones(1, L, 1, d, dtype=torch.bfloat16, device="cuda")
+    for row in rows:
+        k = torch.ones_like(v)
+        k[0, row, 0, 1] = 16
+        o, _ = K.ksa_prefill_fwd(lay, q, k, v, workspace=ws)
+        assert ws[at:at + 4].view(torch.float32).item() == d - 1 + 256, row
+        assert bool((o == 1).all())
