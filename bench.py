@@ -277,12 +277,12 @@ def main():
         "decode": {"ms": round(dec_avg, 5), "ms_min": round(float(np.min(dec_ms)), 5), "bytes": dec_bytes,
                    "gbs": round(dec_gbs, 1), "frac_hbm_peak": round(dec_gbs / HBM_PEAK_GBS, 4),
                    "visible_rows_per_kv_head": vis_rows},
-        "roofline": {"bound": "mfma", "kernel": "ksa_prefill_kernel<128, true>", "achieved": round(attn_tflops, 2),
+        "roofline": {"bound": "mfma", "kernel": "ksa_prefill_kernel<128, false>", "achieved": round(attn_tflops, 2),
                      "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(attn_tflops / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": pre_traffic,
                      "traffic_source": pre_traffic_note,
                      "frac_of_mfma_only_loop": round(attn_tflops / ach["mfma_only_tflops_1_wave_per_simd"], 4)},
-        "roofline_decode": {"bound": "hbm", "kernel": "ksa_decode_split_kernel<128,4>", "achieved": round(dec_gbs, 1),
+        "roofline_decode": {"bound": "hbm", "kernel": "ksa_decode_split_kernel<128,4,256>", "achieved": round(dec_gbs, 1),
                             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(dec_gbs / HBM_PEAK_GBS, 4),
                             "traffic": dec_traffic,
                             "frac_of_stream_read": round(dec_gbs / ach["stream_read_gbs"], 4)},
@@ -374,7 +374,7 @@ def prefill_backward(cfg, lay, q, k, v, o, lse, steps):
     tf = flops / (avg * 1e-3) / 1e12
     return {"ms": round(avg, 3), "ms_min": round(float(np.min(ms)), 3), "live_flops": flops, "live_tflops": round(tf, 1),
             "frac_mfma_peak": round(tf / MFMA_BF16_PEAK_TFLOPS, 4),
-            "kernels": "ksa_bwd_delta_kernel, ksa_bwd_dq_kernel, ksa_bwd_dkv_kernel (split in profiles/)"}
+            "kernels": "ksa_bwd_delta_kernel, ksa_bwd_dq_direct_kernel, ksa_bwd_dkv_kernel (split in profiles/)"}
 
 
 def backward_of(lay, q, k, v, o, lse, seed, calls=2):

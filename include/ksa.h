@@ -111,7 +111,8 @@ int ksa_layout_row_ranges(const ksa_layout *layout, int64_t aq, int32_t out[4]);
 /* Row aq of M_KSA expanded from the row ranges: row_out[ak] = 1 iff visible, ak in [0, L). */
 int ksa_layout_mask_row(const ksa_layout *layout, int64_t aq, uint8_t *row_out);
 /*
- * The (query tile, key tile) pairs the prefill kernel visits, for one (batch, head).  Pass NULL arrays to
+ * The (query tile, key tile) pairs of the schedule, for one (batch, head): what the prefill kernel for long key runs
+ * visits (the one for short runs and odd chunk shapes works its key lists out by itself).  Pass NULL arrays to
  * get *n_pairs only.  Pair x: query rows [q_begin[x], q_begin[x]+q_count[x]) of space q_space[x], key rows
  * [k_begin[x], k_begin[x]+k_count[x]) of space k_space[x], kind[x] = KSA_TILE_FULL or KSA_TILE_MASKED.
  */
@@ -119,7 +120,7 @@ int ksa_layout_tile_pairs(const ksa_layout *layout, int64_t *n_pairs, uint8_t *q
                           int32_t *q_count, uint8_t *k_space, int32_t *k_begin, int32_t *k_count, uint8_t *kind);
 
 /*
- * The prefill launch order: entry x is what workgroup x does -- the query tile (q_space[x], q_begin[x]) for
+ * The launch order of the prefill kernel for long key runs: entry x is what workgroup x does -- the query tile (q_space[x], q_begin[x]) for
  * batch[x] and the query heads q_head[x] .. q_head[x] + heads_per_workgroup - 1 (ksa_layout_dims);
  * q_begin[x] = -1 marks a padding workgroup that does nothing.  Consecutive workgroup
  * ids are dealt to the 8 XCDs round-robin, so entries congruent mod 8 share an L2.  NULL arrays: count only.
