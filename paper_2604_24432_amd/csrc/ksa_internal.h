@@ -54,6 +54,17 @@ int ksa_launch_prefill(const KsaPrefillLaunch &a, void *stream);
 // The kernel for short key runs and chunk shapes that are no powers of two (ksa_prefill_direct.hip).  knorm_parts, knorm:
 // the row norms in the workspace, of parts of the rows (room for one per 64 rows) and of the whole (batch, KV head).
 int ksa_launch_prefill_direct(const KsaPrefillLaunch &a, float *knorm_parts, float *knorm, void *stream);
+// How many rows of the augmented sequence the rows of one key tile of that kernel may span where the tile holds the last
+// summaries and the first text rows of a query tile's key list (at most 63 of each; q_rows rows per query tile).  A text
+// tile's summaries end, and its text begins, C chunks before chunks that lie at most ceil((q_rows - 1) / c) apart.  A summary
+// tile's text begins in the chunk of its first row while its last summaries lie in the chunk of its last row, up to
+// ceil((q_rows - 1) / m) chunks later, whatever the number of summaries in the key tile.
+inline int64_t ksa_mixed_tile_rows(int64_t c, int64_t m, int64_t q_rows) {
+    if (m <= 0) return 0;   // no summaries, no such tile
+    auto chunks = [&](int64_t rows, int64_t per) { return (rows + per - 1) / per; };
+    const int64_t text = chunks(63, m) + chunks(63, c) + chunks(q_rows, c), sums = chunks(q_rows, m) + chunks(63, c);
+    return ((text > sums ? text : sums) + 1) * (c + m);
+}
 
 struct KsaPrefillBwdLaunch {
     const void *q, *k, *v, *o, *d_o;

@@ -664,10 +664,7 @@ int64_t fill_lists(DirectArgs &a, const ksa_params &p, int32_t head_stack, int64
         a.text_before = a.text_tiles - lo;
     }
     a.self_only = (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY) ? 1 : 0;
-    // rows of a mixed tile: up to 63 summaries and 63 text rows around the border of the list, whose chunks differ by no
-    // more than a query tile's rows span
-    const int64_t span = (63 / (a.m > 0 ? a.m : 1) + (63 + a.q_rows) / a.c + 6) * (int64_t)(a.c + a.m);
-    a.mixed_tiles = span * a.ks[1] * 2 < ((int64_t)1 << 32) ? 1 : 0;
+    a.mixed_tiles = ksa_mixed_tile_rows(a.c, a.m, a.q_rows) * a.ks[1] * 2 < ((int64_t)1 << 32) ? 1 : 0;   // 32-bit byte offsets
     a.aug_len = aug_len;
     return ((int64_t)a.text_tiles + a.sum_tiles) * a.slices * a.n_bh;
 }

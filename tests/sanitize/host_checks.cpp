@@ -3,10 +3,12 @@
 // of the entry points (HIP stubbed out: hip_stub/) -- over a spread of shapes, and cross-checks the library's mask and
 // tile schedule against the oracle's predicate on the way.  Exit status 0 = all checks passed; the sanitizers abort
 // the run on any finding.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "ksa.h"
@@ -136,6 +138,36 @@ static void layout_against_oracle(int n, int c, int m, int C, unsigned flags, in
     ksa_layout_destroy(lay);
 }
 
+// The bound that decides whether summaries and text share a key tile of the direct kernels, against the rows such tiles hold:
+// the keys of a query tile are one list (the summaries that some row of it sees, then the text), cut every 64 positions.
+static void mixed_tiles(int n, int c, int m, int C, unsigned flags) {
+    ksa_params p = make(1, n, c, m, C, 1, 1, 64, flags);
+    ksa_layout *lay = nullptr;
+    CHECK(ksa_build_layout(&p, &lay) == KSA_OK && lay);
+    if (!lay) return;
+    const int n_sum = n / c * m, w = c + m;
+    auto text_row = [&](int i) { return (int64_t)(i / c) * w + i % c; };
+    auto sum_row = [&](int u) { return (int64_t)(u / m) * w + c + u % m; };
+    for (int q_rows : {32, 64, 128})
+        for (int space : {KSA_SPACE_TEXT, KSA_SPACE_SUMMARY})
+            for (int q0 = 0; q0 < (space == KSA_SPACE_TEXT ? n : n_sum); q0 += q_rows) {
+                const int q1 = std::min(q0 + q_rows, space == KSA_SPACE_TEXT ? n : n_sum) - 1;
+                int32_t first[4], last[4];   // summaries [0], [1]; text [2], [3]
+                CHECK(ksa_layout_row_ranges(lay, space == KSA_SPACE_TEXT ? text_row(q0) : sum_row(q0), first) == KSA_OK);
+                CHECK(ksa_layout_row_ranges(lay, space == KSA_SPACE_TEXT ? text_row(q1) : sum_row(q1), last) == KSA_OK);
+                const int s0 = first[0], s1 = std::max(last[1], s0), t0 = first[2], t1 = last[3];
+                const int sums = (s1 - s0) % 64;   // in the tile that holds the border
+                if (sums == 0) continue;
+                const int text = std::min(64 - sums, t1 - t0);
+                int64_t lo = std::min(sum_row(s1 - sums), text_row(t0)), hi = std::max(sum_row(s1 - 1), text_row(t0 + text - 1));
+                if (hi - lo + 1 > ksa_mixed_tile_rows(c, m, q_rows))
+                    std::printf("n %d c %d m %d C %d q_rows %d: %s tile at %d spans %lld rows\n", n, c, m, C, q_rows,
+                                space == KSA_SPACE_TEXT ? "text" : "summary", q0, (long long)(hi - lo + 1));
+                CHECK(hi - lo + 1 <= ksa_mixed_tile_rows(c, m, q_rows));
+            }
+    ksa_layout_destroy(lay);
+}
+
 static void oracle_numerics(int n, int c, int m, int C, unsigned flags) {
     const int B = 2, Hq = 4, Hkv = 2, d = 8;
     const int64_t L = ksa_oracle_aug_len(n, c, m);
@@ -217,6 +249,11 @@ int main() {
         layout_against_oracle(s[0], s[1], s[2], s[3], (unsigned)s[4], 4, 1);   // four heads stacked per workgroup
         layout_against_oracle(s[0], s[1], s[2], s[3], (unsigned)s[4], 2, 2);   // one head per workgroup
     }
+    for (const auto &s : {std::make_pair(64, 1), std::make_pair(64, 2), std::make_pair(6000, 1), std::make_pair(63, 3), std::make_pair(20, 5),
+                          std::make_pair(8, 1), std::make_pair(1, 1), std::make_pair(4, 4), std::make_pair(192, 64), std::make_pair(64, 8)})
+        for (int C : {0, 1, 5, 128})
+            for (int chunks : {1, 50, 127, 200})
+                for (unsigned flags : {0u, 1u}) mixed_tiles(chunks * s.first + s.first / 2, s.first, s.second, C, flags);
     const int small[][5] = {{24, 4, 2, 1, 0}, {24, 4, 2, 1, 1}, {19, 4, 1, 2, 0}, {16, 16, 0, 0, 0}, {30, 1, 0, 6, 0}};
     for (const auto &s : small) oracle_numerics(s[0], s[1], s[2], s[3], (unsigned)s[4]);
     decode_checks(640, 64, 8, 1);

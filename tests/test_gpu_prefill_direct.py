@@ -63,6 +63,32 @@ def test_rows_far_apart():
     compare(got, ref, "rows 8 MiB apart")
 
 
+def test_summary_rows_whose_chunks_lie_far_apart():
+    """One summary per chunk, a query tile of 128 summaries, K / V rows 512 KiB apart: the text of the tile's first chunk and
+    its last summary are more than 4 GiB apart (forward and dQ), while the rows of either kind stay within it."""
+    B, H, d, n, c, m, C = 1, 4, 128, 8128, 64, 1, 0
+    cfg = synth.KsaConfig("far", B, H, H, d, n, c, m, C, seed=3)
+    q, k, v = synth.make_prefill_inputs(cfg)
+    g = synth.make_upstream_gradient(cfg)
+    stride = 1 << 18
+    both = torch.empty(cfg.aug_len * stride, dtype=torch.bfloat16, device="cuda")
+    kf, vf = (both[at:].as_strided(k.shape, (0, stride, d, 1)) for at in (0, H * d))
+    kf.copy_(k), vf.copy_(v)
+    lay = K.ksa_build_layout(K.make_params(B, n, c, m, C, H, H, d))
+    o, lse = K.ksa_prefill_fwd(lay, q.cuda(), kf, vf)
+    dq, dk, dv = (torch.empty_like(x, device="cuda") for x in (q, k, v))
+    K.ksa_prefill_bwd(lay, q.cuda(), kf, vf, o, lse, g.cuda(), dq=dq, dk=dk, dv=dv)
+    near = K.ksa_prefill_fwd(lay, q.cuda(), k.cuda(), v.cuda())
+    grads = K.ksa_prefill_bwd(lay, q.cuda(), k.cuda(), v.cuda(), *near, g.cuda())
+    rows = np.concatenate([np.arange(64, 8255, 65), np.arange(100, 140)])      # every summary, some text
+    ref = O.prefill(*(x.float().numpy() for x in (q, k, v)), n, c, m, C, rows=rows)
+    compare((o[:, rows], lse[:, :, rows]), ref, "summaries 4 GiB behind their tile's text")
+    # contiguous tensors: the same up to the order of the keys in a list (weights against another reference, one bf16
+    # rounding of the result: 2^-9 each)
+    for x, y in ((o, near[0]), (dq, grads[0]), (dk, grads[1]), (dv, grads[2])):
+        assert (x.float() - y.float()).norm() <= 5e-3 * y.float().norm()
+
+
 @pytest.mark.parametrize("n,c,m,C", [(64, 1, 0, 63), (64 * 254, 1, 0, 63), (64 * 254 + 1, 1, 0, 63), (64 * 255, 1, 0, 63), (128 * 254 - 127, 1, 0, 63),
                                      (14464, 64, 8, 1), (14464 + 64, 64, 8, 1), (32768, 128, 1, 1), (50048, 64, 1, 2)])
 def test_norm_parts(n, c, m, C):
