@@ -1143,22 +1143,27 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
         if (a.qs[2] >= ((int64_t)1 << 32) || a.os[2] >= ((int64_t)1 << 32) || L.aug_len >= ((int64_t)1 << 31)) return KSA_ERR_UNSUPPORTED;
     }
     // The partial sums of split key tiles live in the memory of dq until dq is written: a dense dq that shares no byte with
-    // the other tensors (a caller may hand over one that does: dq is then written before dK and dV, as ever, and no tile is
-    // split).
+    // the other tensors.  dK and dV are then written first, so they have to be apart from K and V, which dQ still reads.  (A
+    // caller may hand over tensors that do share memory: dq is then written before dK and dV, and no tile is split.)
     int entries = a.sum_tiles + text_tiles, splits = 0;
     a.scratch = nullptr, a.dkv_entries = L.dkv_entries, a.dkv_splits = L.dkv_splits;
     if (L.n_dkv_splits > 0) {
         const int64_t B = L.p.batch, Hq = a.n_q_heads, Hkv = a.n_kv_heads, d = L.p.head_dim, rows = L.aug_len;
         const bool dense = a.dqs[2] == d && a.dqs[1] == Hq * d && (B == 1 || a.dqs[0] == rows * Hq * d);
-        const char *lo = reinterpret_cast<const char *>(a.dq), *hi = lo + B * rows * Hq * d * 2;
-        auto apart = [&](const void *x, int64_t bytes) {
-            const char *p = static_cast<const char *>(x);
-            return p + bytes <= lo || p >= hi;
+        auto apart = [](const void *x, int64_t x_bytes, const void *y, int64_t y_bytes) {
+            const char *p = static_cast<const char *>(x), *r = static_cast<const char *>(y);
+            return p + x_bytes <= r || p >= r + y_bytes;
         };
         auto extent = [&](const int64_t st[3], int64_t heads) { return 2 * ((B - 1) * st[0] + (rows - 1) * st[1] + (heads - 1) * st[2] + d); };
-        if (dense && apart(a.q, extent(a.qs, Hq)) && apart(a.k, extent(a.ks, Hkv)) && apart(a.v, extent(a.ks, Hkv)) &&
-            apart(a.o, extent(a.os, Hq)) && apart(a.g, extent(a.os, Hq)) && apart(a.dk, extent(a.dks, Hkv)) &&
-            apart(a.dv, extent(a.dks, Hkv)) && apart(a.lse, 4 * B * Hq * rows) && apart(L.workspace, (int64_t)L.workspace_bytes)) {
+        auto apart_dq = [&](const void *x, int64_t bytes) { return apart(x, bytes, a.dq, B * rows * Hq * d * 2); };
+        const int64_t q_bytes = extent(a.qs, Hq), kv_bytes = extent(a.ks, Hkv), o_bytes = extent(a.os, Hq), dkv_bytes = extent(a.dks, Hkv);
+        bool ok = dense && apart_dq(a.q, q_bytes) && apart_dq(a.o, o_bytes) && apart_dq(a.g, o_bytes) &&
+                  apart_dq(a.lse, 4 * B * Hq * rows) && apart_dq(L.workspace, (int64_t)L.workspace_bytes);
+        for (const void *in : {(const void *)a.k, (const void *)a.v}) {
+            ok = ok && apart_dq(in, kv_bytes);
+            for (const void *out : {(const void *)a.dk, (const void *)a.dv}) ok = ok && apart_dq(out, dkv_bytes) && apart(out, dkv_bytes, in, kv_bytes);
+        }
+        if (ok) {
             a.scratch = reinterpret_cast<float *>(a.dq);
             entries = L.n_dkv_entries, splits = L.n_dkv_splits;
         }

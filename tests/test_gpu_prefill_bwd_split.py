@@ -1,6 +1,6 @@
 """GPU parity of ksa_prefill_bwd where the dK / dV work of a key tile is dealt to several workgroups: pieces that begin
 inside either run of query rows and between the heads of a group, an incomplete last tile, and outputs whose memory cannot
-hold the partial sums (strided dq, dq sharing memory with an input), which take the unsplit order and must agree with it up
+hold the partial sums (strided dq, dq sharing memory with an input) or that replace K and V, which take the unsplit order and must agree with it up
 to the order of the fp32 sums."""
 import numpy as np
 import pytest
@@ -49,4 +49,9 @@ def test_outputs_that_cannot_hold_partial_sums():
         assert torch.equal(a, dq), what                          # dQ does not depend on the split
         for x, y in ((b, dk), (c, dv)):                          # fp32 sums in another order, one bf16 rounding
             assert (x.float() - y.float()).norm() <= 1e-3 * y.float().norm(), what
+    k_in, v_in = k.clone(), v.clone()
+    a, b, c = K.ksa_prefill_bwd(lay, q, k_in, v_in, o, lse, g, dk=k_in, dv=v_in)     # in the memory of k and v
+    assert torch.equal(a, dq)
+    for x, y in ((b, dk), (c, dv)):
+        assert (x.float() - y.float()).norm() <= 1e-3 * y.float().norm()
     assert bool((wide[:, :, 0] == 0).all()) and bool((wide[:, :, 5] == 0).all())
