@@ -150,6 +150,8 @@ size_t ksa_prefill_workspace_bytes(const ksa_layout *layout);
  *   |q| max |k| * scale is small enough to rule out overflow and underflow; other rows keep a running maximum.  Calls that
  *   share a workspace must be stream-ordered.
  *   stream: hipStream_t (NULL = default stream).
+ * o may be the memory of q (same strides), or that of v where chunk_len and n_summary are powers of two; otherwise outputs
+ * share no memory with inputs.
  * bf16 MFMA for Q K^T and P V over the live key tiles of every query tile, fp32 online softmax.
  * Value range: the weights of a row are kept within [2^-88, 2^32] relative to its reference and summed in fp32, so
  * the output is finite as long as max |v| times the number of visible keys stays below 2^95.

@@ -32,6 +32,16 @@ struct ksa_layout {
 int ksa_validate_params(const ksa_params *p);
 
 // Launchers implemented in the .hip files.  All pointers device, strides in elements.
+// Bytes from the first to behind the last element of a [batch, rows, heads, d] bf16 tensor with these {batch, row, head}
+// strides, and whether two ranges of memory share no byte.
+inline int64_t ksa_extent(const int64_t strides[3], int64_t batch, int64_t rows, int64_t heads, int64_t d) {
+    return 2 * ((batch - 1) * strides[0] + (rows - 1) * strides[1] + (heads - 1) * strides[2] + d);
+}
+inline bool ksa_apart(const void *x, int64_t x_bytes, const void *y, int64_t y_bytes) {
+    const char *p = static_cast<const char *>(x), *r = static_cast<const char *>(y);
+    return p + x_bytes <= r || p >= r + y_bytes;
+}
+
 struct KsaPrefillLaunch {
     const void *q, *k, *v;
     void *o;

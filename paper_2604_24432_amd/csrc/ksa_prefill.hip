@@ -1141,8 +1141,14 @@ int ksa_launch_prefill(const KsaPrefillLaunch &L, void *stream) {
         // ... and so are the ones into the key-major copy of V (head_dim rows of nt_pad or ns_pad keys)
         if ((int64_t)L.p.head_dim * (a.nt_pad > a.ns_pad ? a.nt_pad : a.ns_pad) >= ((int64_t)1 << 31)) return KSA_ERR_UNSUPPORTED;
     }
-    // (rows that overlap: the limit on the offsets of a ragged last tile would cut into rows that exist)
-    if (L.phases == 3 && (L.direct || (L.ragged && L.kv_strides[1] < L.p.head_dim)))
+    // Two reasons to leave the layout's choice of a kernel: an o in the memory of v is right only in this file's kernel, which
+    // reads V from a copy that is complete before the first output row is stored; and with K rows that overlap the limit on
+    // the offsets of a ragged last tile would cut into rows that exist.
+    const bool pow2 = a.c_shift >= 0 && (a.m == 0 || a.m_shift >= 0);
+    const bool o_is_v = !ksa_apart(L.o, ksa_extent(L.o_strides, L.p.batch, L.aug_len, L.p.n_q_heads, L.p.head_dim), L.v,
+                                   ksa_extent(L.kv_strides, L.p.batch, L.aug_len, L.p.n_kv_heads, L.p.head_dim));
+    const bool direct = (L.direct && !(pow2 && o_is_v)) || (L.ragged && L.kv_strides[1] < L.p.head_dim);
+    if (L.phases == 3 && direct)
         return ksa_launch_prefill_direct(L, a.knorm_tiles, a.knorm, stream);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (L.phases & 1) {

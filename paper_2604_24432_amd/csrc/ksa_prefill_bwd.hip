@@ -1150,18 +1150,14 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
     if (L.n_dkv_splits > 0) {
         const int64_t B = L.p.batch, Hq = a.n_q_heads, Hkv = a.n_kv_heads, d = L.p.head_dim, rows = L.aug_len;
         const bool dense = a.dqs[2] == d && a.dqs[1] == Hq * d && (B == 1 || a.dqs[0] == rows * Hq * d);
-        auto apart = [](const void *x, int64_t x_bytes, const void *y, int64_t y_bytes) {
-            const char *p = static_cast<const char *>(x), *r = static_cast<const char *>(y);
-            return p + x_bytes <= r || p >= r + y_bytes;
-        };
-        auto extent = [&](const int64_t st[3], int64_t heads) { return 2 * ((B - 1) * st[0] + (rows - 1) * st[1] + (heads - 1) * st[2] + d); };
-        auto apart_dq = [&](const void *x, int64_t bytes) { return apart(x, bytes, a.dq, B * rows * Hq * d * 2); };
+        auto extent = [&](const int64_t st[3], int64_t heads) { return ksa_extent(st, B, rows, heads, d); };
+        auto apart_dq = [&](const void *x, int64_t bytes) { return ksa_apart(x, bytes, a.dq, B * rows * Hq * d * 2); };
         const int64_t q_bytes = extent(a.qs, Hq), kv_bytes = extent(a.ks, Hkv), o_bytes = extent(a.os, Hq), dkv_bytes = extent(a.dks, Hkv);
         bool ok = dense && apart_dq(a.q, q_bytes) && apart_dq(a.o, o_bytes) && apart_dq(a.g, o_bytes) &&
                   apart_dq(a.lse, 4 * B * Hq * rows) && apart_dq(L.workspace, (int64_t)L.workspace_bytes);
         for (const void *in : {(const void *)a.k, (const void *)a.v}) {
             ok = ok && apart_dq(in, kv_bytes);
-            for (const void *out : {(const void *)a.dk, (const void *)a.dv}) ok = ok && apart_dq(out, dkv_bytes) && apart(out, dkv_bytes, in, kv_bytes);
+            for (const void *out : {(const void *)a.dk, (const void *)a.dv}) ok = ok && apart_dq(out, dkv_bytes) && ksa_apart(out, dkv_bytes, in, kv_bytes);
         }
         if (ok) {
             a.scratch = reinterpret_cast<float *>(a.dq);

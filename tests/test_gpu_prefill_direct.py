@@ -63,6 +63,20 @@ def test_rows_far_apart():
     compare(got, ref, "rows 8 MiB apart")
 
 
+@pytest.mark.parametrize("n,c,m,C,d", [(2048, 64, 8, 1, 128), (512, 64, 8, 1, 64), (4096, 8, 1, 32, 128), (1000, 64, 0, 3, 64), (37, 16, 2, 1, 128)])
+def test_output_in_the_memory_of_an_input(n, c, m, C, d):
+    """o = q and, with chunk shapes that are powers of two, o = v on layouts whose key runs are short."""
+    B, H = 2, 4
+    cfg = synth.KsaConfig("inplace", B, H, H, d, n, c, m, C, seed=n)
+    q, k, v = (x.cuda() for x in synth.make_prefill_inputs(cfg))
+    ref = O.prefill(*(x.float().cpu().numpy() for x in (q, k, v)), n, c, m, C)
+    lay = K.ksa_build_layout(K.make_params(B, n, c, m, C, H, H, d))
+    x = q.clone()
+    compare(K.ksa_prefill_fwd(lay, x, k, v, o=x), ref, "o = q")
+    x = v.clone()
+    compare(K.ksa_prefill_fwd(lay, q, k, x, o=x), ref, "o = v")
+
+
 def test_summary_rows_whose_chunks_lie_far_apart():
     """One summary per chunk, a query tile of 128 summaries, K / V rows 512 KiB apart: the text of the tile's first chunk and
     its last summary are more than 4 GiB apart (forward and dQ), while the rows of either kind stay within it."""
