@@ -310,16 +310,10 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
     if (!GRAD && a.knorm_parts) {
         float kmax2 = 0.f;
         const float *src = a.knorm_parts + (int64_t)bh * a.norm_parts;
-        bool bad = false;
 #pragma unroll
-        for (int i = 0; i < NORM_PARTS; i += 64) {
-            const float x = src[min(i + lane, a.norm_parts - 1)];   // (the last one repeats)
-            bad |= !(x == x);
-            kmax2 = fmaxf(kmax2, x);
-        }
+        for (int i = 0; i < NORM_PARTS; i += 64) kmax2 = fmaxf(kmax2, src[min(i + lane, a.norm_parts - 1)]);   // (the last one repeats)
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) kmax2 = fmaxf(kmax2, __shfl_xor(kmax2, d));
-        if (__builtin_amdgcn_ballot_w64(bad) != 0) kmax2 = __builtin_nanf("");
         if (rest == 0 && tid == 0) a.knorm[bh] = kmax2;
         float n2 = 0.f;
 #pragma unroll
@@ -403,9 +397,13 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         constexpr bool TRACK = decltype(track_tag)::value;
         f32x16 oacc[T::DB];
         f32x4 l_sum = {0.f, 0.f, 0.f, 0.f};   // row sums: lane j < 16, register 0 (query j) and 1 (query j + 16)
-        // Fixed reference: the lane's part of the row sum of the weights before rounding, for the log-sum-exp.  (A running
-        // maximum makes a row's largest weight 1, or close to it; against a fixed reference it is any number, and a row of one
-        // or two keys would hand the backward pass a log-sum-exp that is off by up to 2^-9.  3 % of the time.)
+        // l_sum comes from products in which the weights of row j + 16 are multiplied by zero, so one that is no number (a NaN
+        // or an infinity in the query or in a key it sees) would reach row j.  With running maxima such a row is taken out
+        // (m_ref = infinity, weights 0) and its result set to NaN at the end: 1 % of the time, a sum per lane takes 3 %.
+        // Fixed reference: the lane's part of the row sum of the weights before rounding, for the log-sum-exp, and for the row
+        // itself where l_sum is not a number and this sum is.  (A running maximum makes a row's largest weight 1, or close to
+        // it; against a fixed reference it is any number, and a row of one or two keys would hand the backward pass a
+        // log-sum-exp that is off by up to 2^-9.  3 % of the time.)
         float l_exact = 0.f;
         float m_ref = TRACK ? -1e30f : m_static;
 #pragma unroll
@@ -485,10 +483,15 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int g = 0; g < 16; ++g) mx = fmaxf(mx, sacc[kb][g]);
-                mx = fmaxf(mx, other_half(mx));
-                if (__builtin_amdgcn_ballot_w64((mx - m_ref) * sl > RESCALE_THRESHOLD_LOG2) != 0) {
-                    const float m_new = fmaxf(m_ref, mx);
+                    for (int g = 0; g < 16; ++g) mx = __builtin_elementwise_maximum(mx, sacc[kb][g]);   // NaN if one of them is
+                mx = __builtin_elementwise_maximum(mx, other_half(mx));
+                if (__builtin_amdgcn_ballot_w64(!((mx - m_ref) * sl <= RESCALE_THRESHOLD_LOG2)) != 0) {
+                    const bool lost = !(mx < INFINITY);
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int g = 0; g < 16; ++g) sacc[kb][g] = lost ? -INFINITY : sacc[kb][g];
+                    const float m_new = lost ? INFINITY : fmaxf(m_ref, mx);
                     // (old - new) first: equal references (also the -1e30 start value) must give exactly 2^0
                     const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * sl);
                     m_ref = m_new;
@@ -537,7 +540,14 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         if (!w_any) return;
         unsigned char *stg = lds + wave * (32 * T::STAGE_ROW);
         const float s0 = __shfl(l_sum[0], r & 15), s1 = __shfl(l_sum[1], r & 15);
-        const float l_row = (r & 16) ? s1 : s0;
+        float l_row = (r & 16) ? s1 : s0;
+        if constexpr (TRACK) {
+            l_row = m_ref < INFINITY ? l_row : __builtin_nanf("");
+            l_exact = l_row;
+        } else {
+            l_exact += other_half(l_exact);
+            l_row = l_row == l_row ? l_row : l_exact;
+        }
         const float inv = GRAD ? a.scale : 1.0f / l_row;
 #pragma unroll
         for (int db = 0; db < T::DB; ++db)
@@ -558,7 +568,6 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 *reinterpret_cast<u32x4 *>(obase + (int64_t)row_of(a, q_space, w_begin + row) * a.os[1]) = x;
         }
         if constexpr (GRAD) return;
-        l_exact = TRACK ? l_row : l_exact + other_half(l_exact);
         if (a.lse && h == 0 && w_begin + r < q_end) {
             float msl = m_ref * sl;
             asm volatile("" : "+v"(msl));   // (not contracted with the sum below; split as in ksa_prefill.hip)

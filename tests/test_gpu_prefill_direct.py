@@ -77,6 +77,33 @@ def test_output_in_the_memory_of_an_input(n, c, m, C, d):
     compare(K.ksa_prefill_fwd(lay, q, k, x, o=x), ref, "o = v")
 
 
+@pytest.mark.parametrize("what,value", [("q", np.nan), ("k", np.nan), ("k", np.inf)])
+@pytest.mark.parametrize("shape", [(1, 4, 2, 64, 700, 48, 6, 2), (1, 4, 1, 128, 700, 20, 5, 2), (1, 4, 1, 128, 700, 64, 8, 1), (1, 3, 1, 64, 640, 8, 1, 16)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_no_number_reaches_the_rows_that_see_it_alone(shape, what, value):
+    """A NaN or an infinity in a query row or a key row: rows that do not see it keep their results."""
+    B, Hq, Hkv, d, n, c, m, C = shape
+    cfg = synth.KsaConfig("nan", B, Hq, Hkv, d, n, c, m, C, seed=n)
+    t = dict(zip("qkv", (x.cuda() for x in synth.make_prefill_inputs(cfg))))
+    lay = K.ksa_build_layout(K.make_params(B, n, c, m, C, Hq, Hkv, d))
+    clean, clean_lse = K.ksa_prefill_fwd(lay, t["q"], t["k"], t["v"])
+    rows = [20, 45, cfg.aug_len // 2 + 3, cfg.aug_len - 30]
+    t[what][:, rows, :, 5] = value
+    o, lse = K.ksa_prefill_fwd(lay, t["q"], t["k"], t["v"])
+    sees = torch.zeros(cfg.aug_len, dtype=torch.bool)
+    if what == "q":
+        sees[rows] = True
+    else:
+        sees = torch.from_numpy(np.stack([lay.mask_row(a)[rows].any() for a in range(cfg.aug_len)]))
+    sees = sees.cuda()
+    if value != value:
+        assert bool(torch.isnan(o[:, sees]).all()) and bool(torch.isnan(lse[:, :, sees]).all())
+    assert bool(sees.any()) and not bool(sees.all())
+    # against other references a weight is rounded differently: 2^-9 of an output of about 1, twice
+    assert (o[:, ~sees].float() - clean[:, ~sees].float()).abs().max() <= MAX_ABS
+    assert (lse[:, :, ~sees] - clean_lse[:, :, ~sees]).abs().max() <= LSE_ABS
+
+
 def test_summary_rows_whose_chunks_lie_far_apart():
     """One summary per chunk, a query tile of 128 summaries, K / V rows 512 KiB apart: the text of the tile's first chunk and
     its last summary are more than 4 GiB apart (forward and dQ), while the rows of either kind stay within it."""
