@@ -98,6 +98,7 @@ int prefill_call(ksa_layout *lay, const void *q, const void *k, const void *v, v
     a.entries = static_cast<const KsaWgEntry *>(lay->d_entries);
     a.n_entries = (int32_t)lay->entries.size();
     a.ragged = lay->ragged;
+    a.running_text = lay->running_text, a.running_sum = lay->running_sum;
     a.head_stack = lay->head_stack;
     a.p = p;
     a.aug_len = lay->aug_len;

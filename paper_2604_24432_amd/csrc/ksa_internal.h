@@ -14,6 +14,7 @@ struct ksa_layout {
     std::vector<KsaWorkItem> items;   // one per query tile, heaviest first
     std::vector<KsaWgEntry> entries;  // one per workgroup
     bool ragged = false;              // some run's last key tile reaches past the end of its index space
+    int32_t running_text = INT32_MAX, running_sum = INT32_MAX;   // first row of the first text / summary item with running_max
     int32_t head_stack = 1;           // query heads per workgroup (1, 2 or 4)
     bool dq_direct = false;           // ... and dQ
     bool direct = false;              // the forward pass takes the kernel for short key runs (see takes_direct)
@@ -51,6 +52,7 @@ struct KsaPrefillLaunch {
     const KsaWgEntry *entries;
     int32_t n_entries;
     bool ragged;              // some run's last key tile reaches past the end of its index space
+    int32_t running_text, running_sum;   // first row of the first text / summary work item with KsaWorkItem::running_max
     int32_t head_stack;                           // query heads per workgroup
     ksa_params p;
     int64_t aug_len;

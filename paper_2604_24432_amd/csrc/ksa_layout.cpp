@@ -43,6 +43,7 @@ void push_segment(KsaWorkItem &it, int32_t space, int64_t begin, int64_t end, in
     if (end <= begin) return;
     auto tiles_end = [&](int64_t b) { return b + (end - b + KSA_K_TILE - 1) / KSA_K_TILE * KSA_K_TILE; };
     begin -= begin % 16;
+    it.running_max |= tiles_end(begin) > n_space;
     if (tiles_end(begin) > (n_space + KSA_K_TILE - 1) / KSA_K_TILE * KSA_K_TILE) begin -= begin % KSA_K_TILE;
     KsaSegment &s = it.seg[it.n_seg++];
     s.space = space;
@@ -271,11 +272,14 @@ int ksa_build_layout(const ksa_params *params, ksa_layout **out) {
     const int64_t n_sum = (int64_t)lay->n_chunks * p.n_summary;
     for (int64_t u0 = 0; u0 < n_sum; u0 += qt)
         lay->items.push_back(summary_item(p, u0, (int32_t)std::min<int64_t>(qt, n_sum - u0)));
-    for (const KsaWorkItem &it : lay->items)
+    for (const KsaWorkItem &it : lay->items) {
+        int32_t &from = it.q_space == KSA_SPACE_TEXT ? lay->running_text : lay->running_sum;
+        if (it.running_max) from = std::min(from, it.q_begin);
         for (int32_t s = 0; s < it.n_seg; ++s) {
             const KsaSegment &g = it.seg[s];
             lay->ragged |= g.begin + (int64_t)tiles_in(g) * KSA_K_TILE > (g.space == KSA_SPACE_TEXT ? (int64_t)p.n_text : n_sum);
         }
+    }
     std::stable_sort(lay->items.begin(), lay->items.end(),
                      [](const KsaWorkItem &a, const KsaWorkItem &b) { return a.n_tiles > b.n_tiles; });
     lay->direct = takes_direct(*lay);

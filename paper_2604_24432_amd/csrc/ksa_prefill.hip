@@ -559,6 +559,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
     // they would be fetched from memory again (the tile requests are opaque memory operations to the compiler), one
     // more memory round trip in front of every run's first tile request.
     static_assert(KSA_MAX_SEGMENTS == 2, "run fields are selected with one compare");
+    const int running_max = item.running_max;
     int run_space[KSA_MAX_SEGMENTS], run_begin[KSA_MAX_SEGMENTS], run_end[KSA_MAX_SEGMENTS];
     int run_full_lo[KSA_MAX_SEGMENTS], run_full_hi[KSA_MAX_SEGMENTS];
 #pragma unroll
@@ -679,8 +680,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
     // p v can only be lost to underflow where |v| < 2^-38 -- and there are no row maxima, no raise decision and no
     // rescale in the loop (3 - 4 % of the time of the 128K workload).  The result is the same softmax: the reference
     // cancels in O = sum(p v) / sum(p) and is added back in the log-sum-exp.  Waves whose bound is larger (keys or
-    // queries of unusual size) or not a number take the tracking variant; both variants execute the same barriers,
-    // so the waves of a workgroup may differ.
+    // queries of unusual size) or not a number take the tracking variant, and so do work items with running_max set;
+    // both variants execute the same barriers, so the waves of a workgroup may differ.
     float m_static[QB];
     bool static_ok;
     {
@@ -698,7 +699,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
             ok &= bound * a.scale_log2e <= 60.f;                         // false for NaN
             m_static[qb] = bound - 32.f / a.scale_log2e;
         }
-        static_ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
+        static_ok = running_max == 0 && __builtin_amdgcn_ballot_w64(!ok) == 0;
     }
 
     // Everything from the accumulators to the stores, once per variant (two copies of the code that share nothing but

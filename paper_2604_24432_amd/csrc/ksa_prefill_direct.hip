@@ -54,6 +54,7 @@ struct DirectArgs {
     int64_t qs[3], ks[3], os[3];        // {batch, row, head} strides in elements
     const float *knorm_parts;           // largest squared K row norm per part of a (batch, KV head)'s rows; NULL: keep running maxima
     float *knorm;                       // ... per (batch, KV head): stored by one workgroup of each
+    int32_t running_text, running_sum;  // query tiles from these rows on keep running maxima whatever the norms say
     int32_t norm_parts;                 // parts per (batch, KV head), at most NORM_PARTS
     int32_t norm_text_parts;            // the first so many are text
     int32_t norm_run;                   // key tiles per part
@@ -305,6 +306,11 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
 
     // ---- the softmax reference: fixed where |q| max |k| rules out overflow and underflow (see ksa_prefill.hip) -----
     const float sl = a.scale_log2e;
+    // The last query tiles of either space keep running maxima if their key runs reach past the end of the index space
+    // (KsaWorkItem::running_max): short texts consist of such tiles, whose rows see few keys, and the rounding of a row's
+    // largest weight shows there.  Relative error of the outputs against fp64, running / fixed (d 128): 37 tokens 1.76e-3 /
+    // 1.93e-3, 500 tokens with c 8, m 1, C 32 2.00e-3 / 2.12e-3.  Their log-sum-exp still comes from unrounded weights.
+    const bool running_max = q_begin >= (q_space == KSA_SPACE_TEXT ? a.running_text : a.running_sum);
     float m_static = 0.f;
     bool static_ok = false;
     if (!GRAD && a.knorm_parts) {
@@ -323,7 +329,7 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         n2 += other_half(n2);
         const float bound = __builtin_sqrtf(n2 * kmax2) * 1.002f;
         m_static = bound - 32.f / sl;
-        static_ok = __builtin_amdgcn_ballot_w64(!(bound * sl <= 60.f)) == 0;
+        static_ok = !running_max && __builtin_amdgcn_ballot_w64(!(bound * sl <= 60.f)) == 0;
     }
 
     // byte addresses inside a buffer, relative to its start: see ksa_prefill.hip
@@ -393,8 +399,8 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         }
     };
 
-    auto body = [&](auto track_tag) {
-        constexpr bool TRACK = decltype(track_tag)::value;
+    auto body = [&](auto track_tag, auto exact_tag) {
+        constexpr bool TRACK = decltype(track_tag)::value, EXACT = decltype(exact_tag)::value;   // EXACT: l_exact is kept
         f32x16 oacc[T::DB];
         f32x4 l_sum = {0.f, 0.f, 0.f, 0.f};   // row sums: lane j < 16, register 0 (query j) and 1 (query j + 16)
         // l_sum comes from products in which the weights of row j + 16 are multiplied by zero, so one that is no number (a NaN
@@ -497,6 +503,7 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                     m_ref = m_new;
                     const float alpha_lo = __shfl(alpha, lane & 15), alpha_hi = __shfl(alpha, (lane & 15) + 16);
                     l_sum[0] *= alpha_lo, l_sum[1] *= alpha_hi;
+                    if constexpr (EXACT) l_exact *= alpha;
 #pragma unroll
                     for (int db = 0; db < T::DB; ++db)
 #pragma unroll
@@ -514,7 +521,7 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         const float w = __builtin_amdgcn_exp2f(fmaf(sacc[kb][8 * hf + e], sl, -msl));
-                        if constexpr (!TRACK) l_exact += w;
+                        if constexpr (EXACT) l_exact += w;
                         pb[kb][hf][e] = (__bf16)w;
                     }
                     l_sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ind, pb[kb][hf], l_sum, 0, 0, 0);
@@ -541,11 +548,11 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         unsigned char *stg = lds + wave * (32 * T::STAGE_ROW);
         const float s0 = __shfl(l_sum[0], r & 15), s1 = __shfl(l_sum[1], r & 15);
         float l_row = (r & 16) ? s1 : s0;
+        l_exact += other_half(l_exact);
         if constexpr (TRACK) {
             l_row = m_ref < INFINITY ? l_row : __builtin_nanf("");
-            l_exact = l_row;
+            l_exact = EXACT && m_ref < INFINITY ? l_exact : l_row;
         } else {
-            l_exact += other_half(l_exact);
             l_row = l_row == l_row ? l_row : l_exact;
         }
         const float inv = GRAD ? a.scale : 1.0f / l_row;
@@ -576,11 +583,15 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 fmaf(t, 0.6931471805599453f, __logf(__builtin_amdgcn_frexp_mantf(l_exact)));
         }
     };
-    // both copies meet at the same barriers, so the choice is per wave
+    // the copies meet at the same barriers, so the choice is per wave
     if (GRAD || static_ok)
-        body(std::false_type{});
-    else if constexpr (!GRAD)
-        body(std::true_type{});
+        body(std::false_type{}, std::true_type{});
+    else if constexpr (!GRAD) {
+        if (running_max && a.knorm_parts)
+            body(std::true_type{}, std::true_type{});
+        else
+            body(std::true_type{}, std::false_type{});
+    }
 }
 
 // Two workgroups per compute unit for head_dim 128 (64 KB of LDS, 256 registers each), three for head_dim 64 (16K tokens,
@@ -693,6 +704,7 @@ int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_parts, flo
     // 2.26e-3 relative); the other shapes have had the fixed reference all along.
     const bool fixed = log2_exact(L.p.chunk_len) >= 0 && (L.p.n_summary == 0 || log2_exact(L.p.n_summary) >= 0);
     a.knorm_parts = fixed ? knorm_parts : nullptr;
+    a.running_text = L.running_text, a.running_sum = L.running_sum;
     a.knorm = knorm;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
     const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);
@@ -718,7 +730,7 @@ int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *lse2c, const
     a.v = static_cast<const __bf16 *>(L.v);
     a.g = static_cast<const __bf16 *>(L.d_o);
     a.o = static_cast<__bf16 *>(L.dq);
-    a.lse = nullptr, a.knorm_parts = nullptr, a.knorm = nullptr, a.norm_parts = a.norm_text_parts = a.norm_run = 0;
+    a.lse = nullptr, a.knorm_parts = nullptr, a.knorm = nullptr, a.running_text = a.running_sum = a.norm_parts = a.norm_text_parts = a.norm_run = 0;
     for (int x = 0; x < 3; ++x) a.qs[x] = L.q_strides[x], a.ks[x] = L.kv_strides[x], a.gs[x] = L.o_strides[x], a.os[x] = L.dq_strides[x];
     a.lse2c = lse2c, a.dlc = dlc;
     const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);

@@ -37,7 +37,9 @@ struct KsaWorkItem {
     int32_t n_seg;
     KsaSegment seg[KSA_MAX_SEGMENTS];
     int32_t n_tiles;   // key tiles over all segments (the item's cost)
-    int32_t pad[3];
+    int32_t running_max;   // 1: a key run, walked from the multiple of 16 at or below its first key, reaches past the end of its
+                           // index space; such query tiles keep running maxima (see ksa_prefill_direct.hip)
+    int32_t pad[2];
 };
 
 // Backward dK / dV: keys per workgroup, and what the workgroups of one (batch, KV head) do.  A key tile's work is a
