@@ -33,19 +33,13 @@ __device__ __forceinline__ int aug_row(const Args &a, int space, int idx) {
     return j * a.w + a.c + (idx - j * a.m);
 }
 
-// global -> LDS without VGPR staging: every lane fetches 16 bytes from its own global address and the wave's 64
-// pieces land back to back (lane order) from the wave-uniform LDS address `dst`.
+// global -> LDS without VGPR staging: every lane fetches 16 bytes from the wave-uniform base address plus its own unsigned byte
+// offset (nothing but the load itself goes through the vector issue port), and the wave's 64 pieces land back to back (lane
+// order) from the wave-uniform LDS address.
 // Written as inline assembly on purpose: for the builtin the compiler assumes that any later LDS read may alias the
 // data in flight and puts s_waitcnt vmcnt(0) in front of it, which serialises the loads with the MFMA work they are
 // meant to overlap.  Here the waits are explicit (s_waitcnt before the workgroup barrier that publishes a tile).
 // M0 carries the LDS address; no other code of these kernels uses M0.
-__device__ __forceinline__ void lds_direct_load_16(const __bf16 *src, const unsigned char *dst) {
-    const unsigned lds_addr = __builtin_amdgcn_readfirstlane((unsigned)(size_t)dst);
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds_addr) : "memory");
-}
-
-// lds_direct_load_16() with a wave-uniform base address in scalar registers plus a per-lane unsigned byte offset:
-// nothing but the load itself goes through the vector issue port.
 __device__ __forceinline__ void lds_direct_load_16_s(const __bf16 *sbase, unsigned voff_bytes, unsigned lds_addr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :

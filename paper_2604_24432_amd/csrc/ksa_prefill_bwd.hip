@@ -7,8 +7,9 @@
 //   dQ_i  = scale sum_j dS_ij k_j,     dK_j = scale sum_i dS_ij q_i
 // No atomics, results independent of the launch order:
 //   ksa_bwd_delta_kernel  delta_i and lse_i log2(e) per (batch, head, row), in compact row order, into the workspace;
-//   ksa_bwd_dq_kernel     one workgroup per query tile of the forward schedule walks that tile's key runs (long stretches
-//                         of text; other layouts take ksa_bwd_dq_direct_kernel, ksa_prefill_direct.hip);
+//   ksa_bwd_dq_kernel     one workgroup per query tile of the forward schedule walks that tile's key run (long stretches of
+//                         text, no summaries, head_dim 128; other layouts take ksa_bwd_dq_direct_kernel,
+//                         ksa_prefill_direct.hip);
 //   ksa_bwd_dkv_kernel    one workgroup per 128-key tile of an index space walks the query rows that can see it
 //                         (two runs, closed form from Eq. 3), for every query head of the KV head's group; where that
 //                         would leave the chip waiting for a few long tiles, several workgroups share a tile and
@@ -68,29 +69,8 @@ struct BwdArgs {
 template <int D>
 __device__ __forceinline__ int swz(int row) { return (((row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
 
-// Rows first .. first + 63 (clamped to `last`) of one index space, of two tensors that share the row map (K and V, or
-// Q and G) -> two LDS tiles.  The bases point at (batch, head).
-template <int D>
-__device__ __forceinline__ void load_tile_pair(const BwdArgs &a, const __bf16 *base0, int64_t row_stride0,
-                                               const __bf16 *base1, int64_t row_stride1, int space, int first, int last,
-                                               unsigned char *tile0, unsigned char *tile1, int wave, int lane) {
-    constexpr int CH = D / 8, RPI = 64 / CH, NI = RW / RPI;
-    static_assert(RW % RPI == 0 && NI >= 1, "a wave's share of a tile is a whole number of load instructions");
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int row = RW * wave + RPI * i + lane / CH;
-        const int pch = lane % CH;
-        int idx = first + row;
-        idx = idx < last ? idx : last;
-        const int64_t arow = aug_row(a, space, idx);
-        const int col = (pch ^ swz<D>(row)) << 3;
-        lds_direct_load_16(base0 + arow * row_stride0 + col, tile0 + (RW * wave + RPI * i) * (D * 2));
-        lds_direct_load_16(base1 + arow * row_stride1 + col, tile1 + (RW * wave + RPI * i) * (D * 2));
-    }
-}
-
 // global -> LDS, 4 bytes per lane: the wave's 64 pieces land back to back (lane order) from the wave-uniform LDS
-// address dst.  Inline assembly for the same reason as lds_direct_load_16().
+// address dst.  Inline assembly for the same reason as lds_direct_load_16_s().
 __device__ __forceinline__ void lds_direct_load_4(const float *src, const unsigned char *dst) {
     const unsigned lds_addr = __builtin_amdgcn_readfirstlane((unsigned)(size_t)dst);
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(lds_addr) : "memory");
@@ -223,12 +203,10 @@ __global__ __launch_bounds__(256) void ksa_bwd_delta_kernel(const BwdArgs a, int
 }
 
 // ---- dQ -----------------------------------------------------------------------------------------------------
-// POW2: chunk_len and n_summary are powers of two, so that the row maps are shifts and the bookkeeping of the next
-// tile request is short straight-line code that can sit between the MFMAs of the tile in work.  Otherwise the same
-// statements run in one block after the barrier.
-template <int D, bool POW2>
+// For long runs of text without summaries at head_dim 128 (dq_takes_direct() in ksa_layout.cpp): rows of the sequence are
+// text indices, and a work item has one key run.
 __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
-    constexpr int KS = D / 16, DB = D / 32, BYTES = BN * D * 2;
+    constexpr int D = 128, KS = D / 16, DB = D / 32, BYTES = BN * D * 2;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * BYTES];   // two buffers of a K and a V tile
 
     const KsaWgEntry ent = a.entries[blockIdx.x];
@@ -237,16 +215,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
     // would be fetched from memory again after every tile request (the requests are opaque memory operations to the
     // compiler), each fetch followed by a wait for ALL outstanding loads, the tile in flight included.
     const KsaWorkItem *item_p = a.items + ent.item;
-    const int n_seg = item_p->n_seg;
-    int seg_space[KSA_MAX_SEGMENTS], seg_begin[KSA_MAX_SEGMENTS], seg_end[KSA_MAX_SEGMENTS];
-    int seg_full_lo[KSA_MAX_SEGMENTS], seg_full_hi[KSA_MAX_SEGMENTS];
-    static_assert(KSA_MAX_SEGMENTS == 2, "segment fields are selected with one compare");
-#pragma unroll
-    for (int x = 0; x < KSA_MAX_SEGMENTS; ++x) {
-        seg_space[x] = item_p->seg[x].space, seg_begin[x] = item_p->seg[x].begin, seg_end[x] = item_p->seg[x].end;
-        seg_full_lo[x] = item_p->seg[x].full_lo, seg_full_hi[x] = item_p->seg[x].full_hi;
-    }
-#define KSA_SEG(field, sg) ((sg) == 0 ? field[0] : field[1])
+    const int run_begin = item_p->seg[0].begin, run_end = item_p->seg[0].end;
+    const int full_lo = item_p->seg[0].full_lo, full_hi = item_p->seg[0].full_hi;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // as in the forward kernel: wave w takes query head w % stack and row block w / stack of the query tile
@@ -254,9 +224,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
     const int wrow = wave >> a.stack_shift;
     const int r = lane & 31, h = lane >> 5;
     const LaneLds ll = lane_lds<D>(lane);
-    const int q_space = item_p->q_space, q_begin = item_p->q_begin, q_end = item_p->q_begin + item_p->q_count;
+    const int q_begin = item_p->q_begin, q_end = item_p->q_begin + item_p->q_count;
 
-    int q_aug[QB];
     bool q_valid[QB];
     int idc[QB];
     float lse2[QB], dl[QB];
@@ -266,16 +235,14 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
         const int idx = q_begin + (wrow * QB + qb) * 32 + r;
         q_valid[qb] = idx < q_end;
         idc[qb] = q_valid[qb] ? idx : q_end - 1;
-        q_aug[qb] = aug_row(a, q_space, idc[qb]);
-        const __bf16 *qp = a.q + b * a.qs[0] + (int64_t)q_aug[qb] * a.qs[1] + hq * a.qs[2] + h * 8;
-        const __bf16 *gp = a.g + b * a.os[0] + (int64_t)q_aug[qb] * a.os[1] + hq * a.os[2] + h * 8;
+        const __bf16 *qp = a.q + b * a.qs[0] + (int64_t)idc[qb] * a.qs[1] + hq * a.qs[2] + h * 8;
+        const __bf16 *gp = a.g + b * a.os[0] + (int64_t)idc[qb] * a.os[1] + hq * a.os[2] + h * 8;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             qreg[qb][s] = *reinterpret_cast<const bf16x8 *>(qp + s * 16);
             greg[qb][s] = *reinterpret_cast<const bf16x8 *>(gp + s * 16);
         }
-        const int64_t stat = ((int64_t)b * a.n_q_heads + hq) * (a.nt_pad + a.ns_pad) +
-                             (q_space == KSA_SPACE_TEXT ? idc[qb] : a.nt_pad + idc[qb]);
+        const int64_t stat = ((int64_t)b * a.n_q_heads + hq) * a.nt_pad + idc[qb];
         lse2[qb] = a.lse2c[stat];
         dl[qb] = a.dlc[stat];
     }
@@ -289,70 +256,37 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
     const __bf16 *vbase = a.v + b * a.ks[0] + hkv * a.ks[2];
     const float sl = a.scale_log2e;
 
-    // The key tiles of all runs form one sequence; tile t sits in LDS buffer t % 2, and the loads of tile t + 1 go out
-    // during the step of tile t, after the barrier that publishes tile t.
-    int n_tiles = 0;
-#pragma unroll
-    for (int x = 0; x < KSA_MAX_SEGMENTS; ++x)
-        if (x < n_seg && seg_end[x] > seg_begin[x]) n_tiles += (seg_end[x] - seg_begin[x] + BN - 1) / BN;
+    // Tile t of the run sits in LDS buffer t % 2, and the loads of tile t + 1 go out during the step of tile t, after the
+    // barrier that publishes tile t.
+    const int n_tiles = run_end > run_begin ? (run_end - run_begin + BN - 1) / BN : 0;
 
     // ---- the request of a tile, in two parts (as in the dK/dV kernel) ------------------------------------------
-    // prepare: advances the sequence and works out where the tile's rows are; issue: the wave's 2 NI loads.  Once
-    // the sequence is exhausted prepare stays on the last tile, which is then fetched again into the buffer nobody
-    // reads: every step issues the same loads, and the tile loop carries no branch.
+    // prepare: advances to the next tile and works out where its rows are; issue: the wave's 2 NI loads.  At the end of
+    // the run prepare stays on the last tile, which is then fetched again into the buffer nobody reads: every step
+    // issues the same loads, and the tile loop carries no branch.
     constexpr int CH = D / 8, RPI = 64 / CH, NI = RW / RPI;
     static_assert(RW % RPI == 0 && NI >= 1, "a wave's share of a tile is a whole number of load instructions");
     const unsigned kv_row_bytes = (unsigned)a.ks[1] * 2u;
-    // the next tile of the sequence (an empty first run is skipped; the host schedule has no item without tiles)
-    const int second_run = (n_seg > 1 && seg_end[1] > seg_begin[1]) ? 1 : 0;
-    int sq_seg = (n_seg > 1 && seg_end[0] <= seg_begin[0]) ? 1 : 0;
-    int sq_kt = KSA_SEG(seg_begin, sq_seg);
+    int next_kt = run_begin;   // the next tile
     struct Request {
         const __bf16 *k_base, *v_base;   // row `first` of the tile (scalar)
         unsigned off[NI];                // per lane: byte offset of the 16 bytes it fetches, per load instruction
-        int seg, first;
+        int first;
         bool full;                       // every row of the query tile sees every key of the tile
     } rq;
-    rq.k_base = kbase, rq.v_base = vbase, rq.seg = 0, rq.first = 0, rq.full = false;
+    rq.k_base = kbase, rq.v_base = vbase, rq.first = 0, rq.full = false;
 #pragma unroll
     for (int i = 0; i < NI; ++i) rq.off[i] = 0;
-    // Both shift counts in one scalar register, byte `sp` that of index space sp (a shift takes its count modulo 32).
-    // Opaque to the compiler: a select between two kernel arguments is otherwise compiled into a scalar load of the
-    // selected argument inside the tile loop, and the wait for it drains every LDS operand read in flight.
-    unsigned shifts = ((unsigned)a.c_shift & 31u) | (((unsigned)a.m_shift & 31u) << 8);
-    asm volatile("" : "+s"(shifts));
-    auto chunk_of = [&](int sp, int idx) {
-        if constexpr (POW2) return idx >> (shifts >> (sp * 8));
-        return idx / (sp == KSA_SPACE_TEXT ? a.c : a.m);
-    };
     auto prepare_tile = [&]() {   // scalar part
-        const int sg = sq_seg, first = sq_kt;
-        const int space = KSA_SEG(seg_space, sg);
-        {   // advance, unless this is the last tile
-            const int nk = first + BN;
-            const int run_done = nk >= KSA_SEG(seg_end, sg) ? 1 : 0;
-            const int more = (run_done ^ 1) | ((sg == 0 ? 1 : 0) & second_run);   // bitwise: no short-circuit branches
-            const int ns = sg + run_done, nkt = run_done ? seg_begin[1] : nk;
-            sq_seg = more ? ns : sq_seg, sq_kt = more ? nkt : sq_kt;
-        }
-        const int per = space == KSA_SPACE_TEXT ? a.m : a.c;   // rows of the other kind per chunk
-        const int add = space == KSA_SPACE_TEXT ? 0 : a.c;
-        const int64_t arow = (int64_t)first + (int64_t)chunk_of(space, first) * per + add;
-        rq.k_base = kbase + arow * a.ks[1], rq.v_base = vbase + arow * a.ks[1];
-        rq.seg = sg, rq.first = first;
-        rq.full = first >= KSA_SEG(seg_full_lo, sg) && first + BN <= KSA_SEG(seg_full_hi, sg);
+        const int first = next_kt;
+        next_kt = first + BN < run_end ? first + BN : first;
+        rq.k_base = kbase + (int64_t)first * a.ks[1], rq.v_base = vbase + (int64_t)first * a.ks[1];
+        rq.first = first;
+        rq.full = first >= full_lo && first + BN <= full_hi;
     };
-    auto prepare_row = [&](int i) {   // per-lane part of load instruction i
-        const int sg = rq.seg, first = rq.first;
-        const int space = KSA_SEG(seg_space, sg);
-        const int row = RW * wave + RPI * i + lane / CH;
-        int idx = first + row;
-        const int last = KSA_SEG(seg_end, sg) - 1;
-        idx = idx < last ? idx : last;
-        const int per = space == KSA_SPACE_TEXT ? a.m : a.c;
-        // augmented row of idx minus that of `first`: the index distance plus the other kind's rows in between
-        const int d_rows = (idx - first) + (chunk_of(space, idx) - chunk_of(space, first)) * per;
-        rq.off[i] = (unsigned)d_rows * kv_row_bytes + (unsigned)(((lane % CH) ^ swz<D>(row)) << 4);
+    auto prepare_row = [&](int i) {   // per-lane part of load instruction i; keys past the end of the run: its last one, masked
+        const int row = RW * wave + RPI * i + lane / CH, last = run_end - 1 - rq.first;
+        rq.off[i] = (unsigned)(row < last ? row : last) * kv_row_bytes + (unsigned)(((lane % CH) ^ swz<D>(row)) << 4);
     };
     auto prepare_all = [&]() {
         prepare_tile();
@@ -369,17 +303,17 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
     // the wave's own rows and statistics have arrived before the first tile request: from here on only tile requests
     // are outstanding, and the waits in the loop count those alone
     __builtin_amdgcn_s_waitcnt(0x0F70);
-    int fly_seg = 0, fly_kt = 0;   // the tile whose loads went out last: the next one to work on
+    int fly_kt = 0;   // the tile whose loads went out last: the next one to work on
     bool fly_full = false;
     if (n_tiles > 0) {   // (the host schedule has no item without tiles; nothing is requested for one)
         prepare_all();
-        fly_seg = rq.seg, fly_kt = rq.first, fly_full = rq.full;
+        fly_kt = rq.first, fly_full = rq.full;
 #pragma unroll
         for (int x = 0; x < 2 * NI; ++x) issue_load(0, x);
         prepare_all();
     }
     int buf = 0;
-    int elo[QB], espan[QB], range_seg = -1;
+    int elo[QB] = {}, espan[QB] = {}, known = 0;   // visible keys of the lane's rows: [elo, elo + espan)
 
     // One tile: publish it, request the next one, compute.  The tile's work is a stream of MFMAs -- scores of key
     // block 0 (S and dO V^T of both query blocks of the wave, k step by k step: every operand read from LDS feeds
@@ -396,8 +330,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();   // the tile in work is complete in buffer buf; everybody is done with the other buffer
-        const int cur_seg = fly_seg, cur_kt = fly_kt;
-        fly_seg = rq.seg, fly_kt = rq.first, fly_full = rq.full;   // the tile whose loads go out during this step
+        const int cur_kt = fly_kt;
+        fly_kt = rq.first, fly_full = rq.full;   // the tile whose loads go out during this step
         const int k_rows = buf * 2 * BYTES + ll.rows, v_rows = k_rows + BYTES, k_cols = buf * 2 * BYTES + ll.cols;
         const int req_buf = buf ^ 1;
         constexpr int NU = 2 * KS + 4 * DB;   // operand steps: K and V rows per k step, then K columns per dQ product
@@ -413,23 +347,14 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
         };
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) read_ops(u);
-        if (range_seg != cur_seg) {
-            range_seg = cur_seg;
-            const int space = KSA_SEG(seg_space, cur_seg), run_begin = KSA_SEG(seg_begin, cur_seg), run_end = KSA_SEG(seg_end, cur_seg);
+        if (MASKED && known == 0) {   // (once, in a block of its own: in front of the loop its registers spill into the loop)
+            known = 1;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                int lo, hi;
-                visible_range(a, q_space, idc[qb], space, lo, hi);
-                elo[qb] = lo > run_begin ? lo : run_begin;
-                const int ehi = hi < run_end ? hi : run_end;
-                espan[qb] = ehi > elo[qb] ? ehi - elo[qb] : 0;
-                if (!q_valid[qb]) elo[qb] = 0x7fffffff, espan[qb] = 0;
+                int hi;
+                visible_range(a, KSA_SPACE_TEXT, idc[qb], KSA_SPACE_TEXT, elo[qb], hi);
+                espan[qb] = hi - elo[qb];
             }
-        }
-        if constexpr (!POW2) {
-#pragma unroll
-            for (int x = 0; x < 2 * NI; ++x) issue_load(req_buf, x);
-            prepare_all();
         }
         KSA_FENCE();
 
@@ -470,7 +395,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
                         mfma_score<true>(acc, a_op, b_op);
                     else
                         mfma_score<false>(acc, a_op, b_op);
-                    if constexpr (POW2 && kb == 0) {
+                    if constexpr (kb == 0) {
                         if (slot < 2 * NI) issue_load(req_buf, slot);
                     }
                     if constexpr (kb == 1) {
@@ -531,10 +456,8 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
 #pragma unroll
                             for (int e = slot * (8 * QB / HALF); e < (slot + 1) * (8 * QB / HALF); ++e) weight_of_half(1, 1, e);
                         }
-                        if constexpr (POW2) {
-                            if (slot == HALF) prepare_tile();
-                            if (slot > HALF && slot - HALF - 1 < NI) prepare_row(slot - HALF - 1);
-                        }
+                        if (slot == HALF) prepare_tile();
+                        if (slot > HALF && slot - HALF - 1 < NI) prepare_row(slot - HALF - 1);
                     }
                     KSA_FENCE();
                 }
@@ -556,7 +479,6 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
             while (left > 0 && !fly_full);
         }
     }
-#undef KSA_SEG
 
     // nothing of this workgroup is in flight any more when it leaves (the last request fetched a tile nobody reads)
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -564,7 +486,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         if (!q_valid[qb]) continue;
-        __bf16 *op = a.dq + b * a.dqs[0] + (int64_t)q_aug[qb] * a.dqs[1] + hq * a.dqs[2];
+        __bf16 *op = a.dq + b * a.dqs[0] + (int64_t)idc[qb] * a.dqs[1] + hq * a.dqs[2];
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1055,8 +977,10 @@ int launch_all(const KsaPrefillBwdLaunch &L, const BwdArgs &a, int64_t n_rows, i
     if (L.dq_direct) {
         const int rc = ksa_launch_dq_direct(L, a.lse2c, a.dlc, st);
         if (rc != KSA_OK) return rc;
+    } else if constexpr (D == 128) {
+        hipLaunchKernelGGL(ksa_bwd_dq_kernel, dim3((unsigned)L.n_entries), dim3(NW * 64), 0, st, a);
     } else {
-        hipLaunchKernelGGL((ksa_bwd_dq_kernel<D, POW2>), dim3((unsigned)L.n_entries), dim3(NW * 64), 0, st, a);
+        return KSA_ERR_UNSUPPORTED;   // (no such layout: dq_takes_direct())
     }
     if (!a.scratch) launch_dkv<D, POW2>(a, entries, splits, st);
     return KSA_OK;

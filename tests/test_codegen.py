@@ -20,7 +20,8 @@ import pytest
 
 from paper_2604_24432_amd import build as B
 
-DEVICE_SOURCES = ["ksa_prefill.hip", "ksa_prefill_bwd.hip", "ksa_decode.hip", "ksa_cache.hip"]
+DEVICE_SOURCES = ["ksa_prefill.hip", "ksa_prefill_direct.hip", "ksa_prefill_bwd.hip", "ksa_prefill_bwd_sum.hip", "ksa_decode.hip",
+                  "ksa_cache.hip"]
 MFMA_STREAM = 16          # a block with at least this many MFMAs is a stretch of a tile loop
 
 
@@ -75,34 +76,39 @@ def _is_plain_vector_memory(ins: str) -> bool:
     return False
 
 
-@pytest.mark.parametrize("source,kernel_names", [
-    ("ksa_prefill.hip", ["ksa_prefill_kernel"]),
-    ("ksa_prefill_bwd.hip", ["ksa_bwd_dq_kernel", "ksa_bwd_dkv_kernel"]),
-])
-def test_tile_loops_hold_only_their_own_tile_loads(assembly, source, kernel_names):
-    kernels = _kernels(assembly[source])
-    seen = 0
-    for name, blocks in kernels.items():
-        if not any(k in name for k in kernel_names):
+# source, kernel -> instantiations, MFMAs of a stretch
+TILE_LOOPS = [
+    ("ksa_prefill.hip", {"ksa_prefill_kernel": 4}, MFMA_STREAM),
+    ("ksa_prefill_bwd.hip", {"ksa_bwd_dq_kernel": 1, "ksa_bwd_dkv_kernel": 4}, MFMA_STREAM),
+    # (these wait for all their loads; a spill inside the loop would cost time only)
+    ("ksa_prefill_direct.hip", {"ksa_prefill_direct_kernel": 2, "ksa_bwd_dq_direct_kernel": 2}, 8),
+]
+
+
+@pytest.mark.parametrize("source,expected,stream", TILE_LOOPS, ids=[t[0] for t in TILE_LOOPS])
+def test_tile_loops_hold_only_their_own_tile_loads(assembly, source, expected, stream):
+    seen = dict.fromkeys(expected, 0)
+    for name, blocks in _kernels(assembly[source]).items():
+        kernel = next((k for k in expected if k in name), None)
+        if kernel is None:
             continue
-        hot = {lab: ins for lab, ins in blocks.items() if sum("v_mfma" in i for i in ins) >= MFMA_STREAM}
+        hot = {lab: ins for lab, ins in blocks.items() if sum("v_mfma" in i for i in ins) >= stream}
         assert hot, f"{name}: no MFMA stream found"
-        seen += 1
+        seen[kernel] += 1
         for lab, ins in hot.items():
             foreign = [i for i in ins if _is_plain_vector_memory(i)]
             assert not foreign, f"{name} {lab}: {foreign[:4]}"
-    # head dims 64 and 128, two instantiations each
-    assert seen == 4 * len(kernel_names)
+    assert seen == expected
 
 
 def test_tile_loops_load_their_tiles_through_lds_direct_loads(assembly):
     """The check above would pass vacuously if the tile loads were not where it looks."""
-    for source in ("ksa_prefill.hip", "ksa_prefill_bwd.hip"):
+    for source, expected, stream in TILE_LOOPS:
         for name, blocks in _kernels(assembly[source]).items():
-            if "delta" in name or "vt_kernel" in name or "knorm" in name:
+            if not any(k in name for k in expected):
                 continue
             n = sum(i.startswith("global_load_lds_dwordx4") for lab, ins in blocks.items()
-                    if sum("v_mfma" in j for j in ins) >= MFMA_STREAM for i in ins)
+                    if sum("v_mfma" in j for j in ins) >= stream for i in ins)
             assert n > 0, name
 
 
