@@ -99,10 +99,14 @@ KsaWorkItem summary_item(const ksa_params &p, int64_t u0, int32_t cnt) {
 //     its workgroups, alone on their compute unit, do outside the tile loop; beyond it the direct kernel's doubled operand
 //     traffic costs more.  Measured on both sides (pipelined / direct kernel, us, c 64, m 8 unless stated; cards and runs
 //     differ by 2 % in the comparison):
-//       d 128, 4 heads of a group per workgroup: 4K tokens (7 tiles) 134 / 93, 16K (17) 398 / 356, 28K (28) 906 / 903,
-//         32K (31) 1114 / 1133, 40K (38) 1641 / 1711; 32K with c 128, m 16 and outlier keys, where the pipelined kernel
-//         tracks row maxima (33), 1493 / 1295; no summaries: window 256 at 128K (5) 1347 / 1081, window 1024 (17) 328 / 314
-//         at 16K and 2429 / 2467 at 128K, window 1500 (25) 423 / 399, window 2048 (33) 495 / 511, causal 4K (33) 133 / 148;
+//       d 128, 4 heads of a group per workgroup: 4K tokens (7 tiles) 134 / 93, 16K (17) 398 / 356, 24K (24) 710 / 685, 28K
+//         (28) 898 / 890, 30K (30) 1015 / 1015, 32K (31) 1112 / 1138, 34K (33) 1257 / 1280, 36K (35) 1378 / 1415; c 128, m 16
+//         28K (29) 922 / 937, 32K (33) 1157 / 1189.  With outlier keys (1 % of the K rows eight times larger), where both keep
+//         running maxima, 28K 1103 / 948, 32K 1404 / 1195, c 128, m 16, 32K 1448 / 1246.  On ordinary keys the two are level
+//         at 30 tiles; the line lies at 34 because between the two the direct kernel loses 2 - 3 % on those and gains 14 % on
+//         the others.  No summaries (the line is at 30): window 256 at 128K (5) 1347 / 1081, window 700 (12) 1982 / 1878, window
+//         1024 (17) 320 / 307 at 16K, 622 / 613 at 32K, 2456 / 2450 at 128K, window 1500 (25) 430 / 406 at 16K, 3318 / 3290 at
+//         128K, window 2048 (33) 497 / 515, causal 4K (33) 133 / 148;
 //       2 heads: 32K (33) 635 / 611, 40K (41) 926 / 911, 48K (49) 1209 / 1227, 64K (62) 1999 / 2112; no summaries: window
 //         1500 (25) 934 / 883, causal 4K (33) 107 / 97, window 2048 (33) 1099 / 1128, window 3000 (49) 1408 / 1483;
 //       1 head, 16 heads: 16K (20) 271 / 195, 48K (52) 1382 / 1285, 64K (66) 2219 / 2206, 80K (82) 3305 / 3358; no
