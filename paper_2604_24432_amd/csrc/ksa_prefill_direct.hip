@@ -9,13 +9,15 @@
 // written first.  What it costs: every operand read from LDS feeds one MFMA instead of two, and V^T comes from
 // transposing reads.
 // What bounds it: 4K tokens (2 x 4096, 32/8 heads, d 128: 190 MB, 47 GFLOP) take 90 us (before: 135) of which about 40 are
-// the start and end of the workgroups (Q rows from HBM, stores; 1 tile per workgroup alone: 48 us) and 50 the tiles; long
-// runs are held by the board's power cap like the pipelined kernel, at 15 % more energy per product (64K: 1.09 against
-// 1.18 PFLOP/s).  Neither deeper prefetch (5 stages of 32 keys), three workgroups per compute unit, nor the scores of the
-// next tile under the exponentials of this one changed that by more than 3 %; the loads dealt between the MFMAs, the row
-// offsets kept from tile to tile and the order of the query tiles did (together 10 - 30 %).
+// the start and end of the workgroups (Q rows from HBM, stores; 1 tile per workgroup alone: 48 us) and 50 the tiles: the
+// matrix unit is busy 39 % of the time that both waves of a SIMD are there.  At 17 and more tiles per workgroup it is 55 %, at
+// 2.0 of 2.4 GHz under the board's power cap (1370 - 1385 of 1400 W), at 15 % more energy per product than the pipelined kernel
+// (64K: 1.09 against 1.18 PFLOP/s).  Neither deeper prefetch (5 stages of 32 keys), three workgroups per compute unit, nor the
+// scores of the next tile under the exponentials of this one changed the time by more than 3 %; the loads dealt between the
+// MFMAs, the row offsets kept from tile to tile and the order of the query tiles did (together 10 - 30 %).
 // The line between the two kernels: takes_direct() in ksa_layout.cpp.  dQ (three products per visible pair instead of two)
-// is ahead of ksa_bwd_dq_kernel nearly everywhere (dq_takes_direct()): 103 against 221 us at 2 x 4096 tokens.
+// is ahead of ksa_bwd_dq_kernel nearly everywhere (dq_takes_direct()): 103 against 221 us at 2 x 4096 tokens.  It spills 2
+// registers (d 64: 7), outside the blocks that hold its MFMAs.
 //
 // The work of a workgroup follows from its index in closed form (Eq. 3): no schedule is read from memory.  The keys of
 // its query tile form one list (summaries, then text) cut into tiles of 64; tile t sits in LDS buffer t % 2, and tile
