@@ -495,10 +495,12 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 mx = __builtin_elementwise_maximum(mx, other_half(mx));
                 if (__builtin_amdgcn_ballot_w64(!((mx - m_ref) * sl <= RESCALE_THRESHOLD_LOG2)) != 0) {
                     const bool lost = !(mx < INFINITY);
+                    if (__builtin_amdgcn_ballot_w64(lost) != 0) {
 #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
+                        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int g = 0; g < 16; ++g) sacc[kb][g] = lost ? -INFINITY : sacc[kb][g];
+                            for (int g = 0; g < 16; ++g) sacc[kb][g] = lost ? -INFINITY : sacc[kb][g];
+                    }
                     const float m_new = lost ? INFINITY : fmaxf(m_ref, mx);
                     // (old - new) first: equal references (also the -1e30 start value) must give exactly 2^0
                     const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * sl);
