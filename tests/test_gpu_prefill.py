@@ -108,8 +108,8 @@ def test_effective_mask_of_the_kernel_is_bit_exact_on_tiny():
 
 
 def test_fixed_and_running_reference_side_by_side():
-    """The pipelined kernel fixes the softmax reference per row from |q| max |k| where that bound is small and keeps a
-    running maximum elsewhere, wave by wave.  Here one query head of every group is scaled by 4 (its bound, about 80
+    """The forward kernels fix the softmax reference per row from |q| max |k| where that bound is small and keep a
+    running maximum elsewhere, wave by wave (short key runs here, long ones in test_gpu_prefill_long_runs.py).  Here one query head of every group is scaled by 4 (its bound, about 80
     in the exponent domain, is above the limit of 60; the plain heads are at about 20), so the waves of one workgroup
     take different variants and meet at the same barriers; a second case scales a range of rows of all heads, which
     sends whole workgroups one way or the other."""
@@ -445,8 +445,8 @@ def test_preparation_pass_takes_the_largest_key_norm():
 
 
 def test_repeatable_32k_outlier_keys():
-    """The pipelined loop with its hand-placed MFMA wait states on the 32K workload (outlier keys: the rescale path
-    runs): two calls give identical bits."""
+    """The 32K workload with outlier keys (running maxima: the rescale path runs): two calls give identical bits.  (The
+    kernel for long key runs, with its hand-placed MFMA wait states: test_gpu_prefill_long_runs.py.)"""
     cfg = synth.CONFIGS["prefill_32k"]
     q, k, v = (x.cuda() for x in synth.make_prefill_inputs(cfg))
     lay = K.ksa_build_layout(params_of(cfg))
