@@ -161,9 +161,13 @@ struct RowState {
 // MFMAs of pv_mfma_raw() and by this routine, which scales them in place, also in assembly: left to the compiler, the
 // copies to VGPRs that a plain multiply needs get hoisted out of this block into the loop around it, where they would
 // drain the MFMA pipe on every tile.
+// A row one of whose pending scores is no number (a NaN or an infinity in the query or in a key it sees) is taken out here: its
+// reference becomes LOST, its weights are 0 from then on and its result is set to NaN at the end.  Left in, its weights
+// would reach the row 16 before or behind it, whose sum they enter times zero (see sum_half()).
+constexpr float LOST = 3e38f;
 template <int D>
 __device__ __forceinline__ void raise_reference_pl(RowState &st, const float (&mx)[QB], f32x16 (&oacc)[QB][Tile<D>::DB],
-                                                   float sl) {
+                                                   float sl, f32x16 (&pending)[QB]) {
     using T = Tile<D>;
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // the last MFMA results reach the register file
     // The accumulators are re-defined here as far as the compiler can tell: the per-register copies it makes for the
@@ -177,7 +181,13 @@ __device__ __forceinline__ void raise_reference_pl(RowState &st, const float (&m
     }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        const float m_new = fmaxf(st.m_ref[qb], fmaxf(mx[qb], other_half(mx[qb])));
+        const float m_row = __builtin_elementwise_maximum(mx[qb], other_half(mx[qb]));   // NaN if one of the two is
+        const bool lost = !(m_row < LOST);
+        if (__builtin_amdgcn_ballot_w64(lost) != 0) {
+#pragma unroll
+            for (int g = 0; g < 16; ++g) pending[qb][g] = lost ? -INFINITY : pending[qb][g];
+        }
+        const float m_new = lost ? LOST : fmaxf(st.m_ref[qb], m_row);
         // (old - new) first: equal references (also the -1e30 start value) must give exactly 2^0
         const float alpha = __builtin_amdgcn_exp2f((st.m_ref[qb] - m_new) * sl);
         st.m_ref[qb] = m_new;
@@ -305,10 +315,10 @@ struct TileSync {
     __device__ __forceinline__ unsigned k_offset(int i) const { return RAGGED ? min(k_off[i], k_lim) : k_off[i]; }
 };
 
-// v_max3_f32 without the NaN-quieting self-maxima that fmaxf expands to
+// the largest of three, NaN if one of them is (no NaN-quieting self-maxima, which fmaxf expands to)
 __device__ __forceinline__ float max3(float a, float b, float c) {
     float x;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(x) : "v"(a), "v"(b), "v"(c));
+    asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(x) : "v"(a), "v"(b), "v"(c));
     return x;
 }
 
@@ -507,7 +517,7 @@ __device__ __forceinline__ bool subtile(unsigned char *lds, const LaneLds &ll, c
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 mx_out[qb] = mx[qb];
-                raise |= mx[qb] > st.m_ref[qb] + raise_margin;   // (mx - m_ref) * sl > threshold
+                raise |= !(mx[qb] <= st.m_ref[qb] + raise_margin);   // (mx - m_ref) * sl > threshold, or no number
             }
             raise_any = __builtin_amdgcn_ballot_w64(raise) != 0;
         }
@@ -818,7 +828,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                     if constexpr (TRACK) {
 #pragma unroll
                         for (int g = 0; g < 16; g += 2) mx = max3(mx, sv_a[qb][g], sv_a[qb][g + 1]);
-                        raise |= mx > st.m_ref[qb] + raise_margin;
+                        raise |= seg == 0 ? !(mx < LOST) : !(mx <= st.m_ref[qb] + raise_margin);
                     }
                     mxl[qb] = mx;
                 }
@@ -828,8 +838,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                     // keeps its start value and is raised by the first block it does see.
 #pragma unroll
                     for (int qb = 0; qb < QB; ++qb)
-                        st.m_ref[qb] = fmaxf(st.m_ref[qb], fmaxf(mxl[qb], other_half(mxl[qb])));
-                    raise = false;
+                        if (!raise) st.m_ref[qb] = fmaxf(st.m_ref[qb], fmaxf(mxl[qb], other_half(mxl[qb])));
                 }
                 if constexpr (TRACK) raise = __builtin_amdgcn_ballot_w64(raise) != 0;
                 bf16x8 ka_pre[T::RING];
@@ -878,7 +887,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                                 prepare_request();
                                 raise = false;
                             } else {
-                                if (TRACK && raise) raise_reference_pl<D>(st, mxl, oacc, sl);
+                                if (TRACK && raise) raise_reference_pl<D>(st, mxl, oacc, sl, sv_b);
                                 raise = subtile<D, false, MASKED, TRACK>(lds, ll, qreg, sv_a, sv_b, ka_pre, K0 + b_nxt, V0 + b_cur,
                                                                   1, K0 + b_nxt + HALF, oacc, st, ind, sl, raise_margin, mxl,
                                                                   sync, key0, vis_lo, vis_span, prepare_request) &&
@@ -896,7 +905,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
                                 idle_subtile<D, true>(lds, ll, sv_b, ka_pre, K0 + b_nxt, mxl, sync);
                                 raise = false;
                             } else {
-                                if (TRACK && raise) raise_reference_pl<D>(st, mxl, oacc, sl);
+                                if (TRACK && raise) raise_reference_pl<D>(st, mxl, oacc, sl, sv_a);
                                 raise = subtile<D, true, MASKED, TRACK>(lds, ll, qreg, sv_b, sv_a, ka_pre, K0 + b_cur + HALF,
                                                                  V0 + b_cur, 0, K0 + b_nxt, oacc, st, ind, sl, raise_margin,
                                                                  mxl, sync, key0 + 32, vis_lo, vis_span, [] {});
@@ -933,7 +942,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_prefill_kernel(const PrefillArgs 
         for (int qb = 0; qb < QB; ++qb) {
             // lane j < 16 holds the sums of queries j (register 0) and j + 16 (register 1)
             const float s0 = __shfl(st.l_sum[qb][0], r & 15), s1 = __shfl(st.l_sum[qb][1], r & 15);
-            const float l_row = (r & 16) ? s1 : s0;
+            const float l_sum = (r & 16) ? s1 : s0, l_row = TRACK && st.m_ref[qb] >= LOST ? __builtin_nanf("") : l_sum;
             const float inv = 1.0f / l_row;   // rows past the end of the tile: never stored
 #pragma unroll
             for (int db = 0; db < T::DB; ++db)
@@ -1038,15 +1047,16 @@ __global__ __launch_bounds__(256) void ksa_vt_kernel(const PrefillArgs a, int ti
             }
 #pragma unroll
             for (int dd = CH / 2; dd > 0; dd >>= 1) s2 += __shfl_xor(s2, dd);   // the CH lanes of a row are neighbours
-            best = fmaxf(best, s2);
+            best = __builtin_elementwise_maximum(best, s2);   // NaN if a row holds one
         }
 #pragma unroll
-        for (int dd = 32; dd > 0; dd >>= 1) best = fmaxf(best, __shfl_xor(best, dd));
+        for (int dd = 32; dd > 0; dd >>= 1) best = __builtin_elementwise_maximum(best, __shfl_xor(best, dd));
         if ((tid & 63) == 0) wave_best[tid >> 6] = best;
         __syncthreads();
         if (tid == 0)
             a.knorm_tiles[((int64_t)(b * a.n_kv_heads + hkv)) * gridDim.x + blockIdx.x] =
-                fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
+                __builtin_elementwise_maximum(__builtin_elementwise_maximum(wave_best[0], wave_best[1]),
+                                              __builtin_elementwise_maximum(wave_best[2], wave_best[3]));
     }
 }
 

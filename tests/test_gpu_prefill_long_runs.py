@@ -74,6 +74,35 @@ def test_forward(shape, inputs):
     assert np.isfinite(got).all() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS and lerr.max() <= LSE_ABS
 
 
+@pytest.mark.parametrize("what,value", [("q", np.nan), ("k", np.nan), ("k", np.inf)])
+@pytest.mark.parametrize("shape", [(4, 1, 128, 5003, 64, 0, 4096), (2, 2, 128, 12032, 64, 8, 128), (4, 1, 64, 8192, 64, 0, 4096)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_no_number_reaches_the_rows_that_see_it_alone(shape, what, value):
+    """A NaN or an infinity in a query row or a key row: rows that do not see it keep their results."""
+    Hq, Hkv, d, n, c, m, C = shape
+    cfg = synth.KsaConfig("nan", 1, Hq, Hkv, d, n, c, m, C, seed=n)
+    t = dict(zip("qkv", (x.cuda() for x in synth.make_prefill_inputs(cfg))))
+    lay = K.ksa_build_layout(K.make_params(1, n, c, m, C, Hq, Hkv, d))
+    ws = torch.full((K.prefill_workspace_bytes(lay),), 255, dtype=torch.uint8, device="cuda")
+    clean, clean_lse = K.ksa_prefill_fwd(lay, t["q"], t["k"], t["v"], workspace=ws)
+    assert bool((ws[:2 * d * 64] != 255).any())
+    rows = [1500, cfg.aug_len // 2 + 3, cfg.aug_len - 30] + ([cfg.aug_len - 5] if what == "q" else [])
+    t[what][:, rows, :, 5] = value
+    o, lse = K.ksa_prefill_fwd(lay, t["q"], t["k"], t["v"])
+    sees = torch.zeros(cfg.aug_len, dtype=torch.bool)
+    if what == "q":
+        sees[rows] = True
+    else:
+        sees = torch.from_numpy(np.stack([lay.mask_row(a)[rows].any() for a in range(cfg.aug_len)]))
+    sees = sees.cuda()
+    if value != value:
+        assert bool(torch.isnan(o[:, sees]).all()) and bool(torch.isnan(lse[:, :, sees]).all())
+    assert bool(sees.any()) and not bool(sees.all())
+    # against other references a weight is rounded differently: 2^-9 of an output of about 1, twice
+    assert (o[:, ~sees].float() - clean[:, ~sees].float()).abs().max() <= MAX_ABS
+    assert (lse[:, :, ~sees] - clean_lse[:, :, ~sees]).abs().max() <= LSE_ABS
+
+
 BACKWARD = [
     # B, Hq, Hkv, n, c, C: head_dim 128, no summaries, more than 48 key tiles per query tile
     (1, 4, 1, 6500, 64, 4096),
