@@ -9,8 +9,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libksa.so")
 PROBE_LIB = os.path.join(HERE, "libksa_probe.so")   # bench.py's measurement probes (csrc/ksa_probe.hip), not the product
-SOURCES = ["ksa_layout.cpp", "ksa_api.cpp", "ksa_prefill.hip", "ksa_prefill_direct.hip", "ksa_prefill_bwd.hip", "ksa_prefill_bwd_sum.hip",
-           "ksa_decode.hip", "ksa_cache.hip"]
+SOURCES = ["ksa_layout.cpp", "ksa_api.cpp", "ksa_prefill.hip", "ksa_prefill_direct.hip", "ksa_prefill_bwd.hip",
+           "ksa_prefill_bwd_dkv.hip", "ksa_prefill_bwd_sum.hip", "ksa_decode.hip", "ksa_cache.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 VALU instructions are kept out of the generated code (hand-written none either)
@@ -19,7 +19,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 # MFMA results and accumulator inputs in VGPRs: the forward prefill kernel post-processes them with VALU code.  The
 # backward kernels hold more accumulators than there are VGPRs and leave the choice to the compiler.
-PER_SOURCE = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for s in ("ksa_prefill.hip", "ksa_prefill_direct.hip")}
+PER_SOURCE = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for s in ("ksa_prefill.hip", "ksa_prefill_direct.hip", "ksa_prefill_bwd_dkv.hip")}
 OBJ_DIR = os.path.join(HERE, "_build")
 
 

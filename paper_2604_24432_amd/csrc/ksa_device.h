@@ -62,6 +62,12 @@ __device__ __forceinline__ int ksa_div(int x, const KsaDivisor &d) {
     return (int)(__umulhi((unsigned)x * 2u, d.mul) >> d.shift);
 }
 
+// Backward pass: where the log-sum-exp of row statistics slot x is kept; KSA_STAT_ROWS further the same row's delta.  32 rows of
+// the one, then of the other: what a 32-row query tile needs is 256 consecutive bytes.
+#define KSA_STAT_ROWS 32
+template <class T>
+__device__ __forceinline__ T ksa_stat_at(T x) { return x + (x & ~(T)(KSA_STAT_ROWS - 1)); }
+
 inline int log2_exact(int x) {
     if (x <= 0 || (x & (x - 1))) return -1;
     int s = 0;

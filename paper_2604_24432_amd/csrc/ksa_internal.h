@@ -17,6 +17,7 @@ struct ksa_layout {
     int32_t running_text = INT32_MAX, running_sum = INT32_MAX;   // first row of the first text / summary item with running_max
     int32_t head_stack = 1;           // query heads per workgroup (1, 2 or 4)
     bool dq_direct = false;           // ... and dQ
+    bool dkv_direct = false;          // dK and dV take the kernel of ksa_prefill_bwd_dkv.hip
     bool direct = false;              // the forward pass takes the kernel for short key runs (see takes_direct)
     int32_t q_tile_rows = KSA_Q_TILE; // rows of a query tile = KSA_Q_TILE / head_stack
     std::vector<KsaDkvEntry> dkv_entries;   // backward dK / dV, per (batch, KV head), longest first
@@ -90,6 +91,7 @@ struct KsaPrefillBwdLaunch {
     const KsaDkvEntry *dkv_entries;   // NULL: every key tile is one workgroup
     const KsaDkvSplit *dkv_splits;
     int32_t n_dkv_entries, n_dkv_splits;
+    bool dkv_direct;                  // dK and dV by the kernel of ksa_prefill_bwd_dkv.hip
     bool dq_direct;                   // dQ by the kernel for short key runs (ksa_prefill_direct.hip)
     ksa_params p;
     int64_t aug_len;
@@ -98,8 +100,11 @@ struct KsaPrefillBwdLaunch {
 };
 size_t ksa_prefill_bwd_workspace_size(const ksa_params &p, int64_t aug_len);
 int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &a, void *stream);
-// dQ by the kernel for short key runs and odd chunk shapes (ksa_prefill_direct.hip); lse2c, dlc: the row statistics.
-int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &a, const float *lse2c, const float *dlc, void *stream);
+// dQ by the kernel for short key runs and odd chunk shapes (ksa_prefill_direct.hip); stats: the row statistics.
+int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &a, const float *stats, void *stream);
+// dK and dV (ksa_prefill_bwd_dkv.hip); scratch: where the partial sums of split key tiles go, NULL: no tile is split; entries:
+// workgroups per (batch, KV head).
+int ksa_launch_dkv_direct(const KsaPrefillBwdLaunch &a, const float *stats, float *scratch, int entries, void *stream);
 // Second step of the split dK / dV tiles (ksa_prefill_bwd_sum.hip).
 struct KsaDkvSumArgs {
     const float *scratch;

@@ -4,8 +4,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <numeric>
+#include <queue>
 
 #include "ksa_internal.h"
 
@@ -176,57 +178,108 @@ void build_entries(ksa_layout &lay) {
         for (size_t x = 0; x < queue[q].size(); ++x) lay.entries[x * KSA_NUM_XCD + q] = queue[q][x];
 }
 
-// Steps of the dK / dV work of the keys [k0, k1) of an index space, per query head: the aligned 64-row query blocks that
-// overlap the two runs of rows that can see one of them (the kernel works the same runs out).
+// Steps of the dK / dV work of the keys [k0, k1) of an index space, per query head: the aligned blocks of KSA_DKV_ROWS query rows
+// that overlap the two runs of rows that can see one of them (the kernel works the same runs out).
 int64_t dkv_blocks(const ksa_params &p, int space, int64_t k0, int64_t k1) {
     const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = (int64_t)(p.n_text / c) * m;
     const int64_t per = space == KSA_SPACE_TEXT ? c : m, jl = k0 / per, jh = (k1 - 1) / per;
     const int64_t b0 = space == KSA_SPACE_TEXT ? k0 : std::min<int64_t>((jl + C + 1) * c, p.n_text);
     const int64_t e0 = space == KSA_SPACE_TEXT ? std::min<int64_t>((jh + C + 1) * c, p.n_text) : p.n_text;
-    const int64_t b1 = space == KSA_SPACE_TEXT ? jl * m : k0, e1 = std::min<int64_t>((jh + 1) * m, n_sum);
-    auto blocks = [](int64_t b, int64_t e) { return e > b ? (e - 1) / KSA_K_TILE - b / KSA_K_TILE + 1 : 0; };
+    const bool self_only = space == KSA_SPACE_SUMMARY && (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY);
+    const int64_t b1 = space == KSA_SPACE_TEXT ? jl * m : k0, e1 = self_only ? k1 : std::min<int64_t>((jh + 1) * m, n_sum);
+    auto blocks = [](int64_t b, int64_t e) { return e > b ? (e - 1) / KSA_DKV_ROWS - b / KSA_DKV_ROWS + 1 : 0; };
     return blocks(b0, e0) + blocks(b1, e1);
 }
 
 // The backward pass's dK / dV work of one (batch, KV head).  A summary key is seen by every later text row, so the first
-// tile of 128 of them is as long as hundreds of text tiles: on short sequences a few workgroups would run long after the
-// others have finished.  Tiles longer than the launch's mean work per compute unit are therefore dealt to several
-// workgroups, whose fp32 partial sums a second kernel adds up in a fixed order (whole backward pass, c 64, m 8, d 128, before /
-// after: 2 x 4096 tokens, 32/8 heads 723 / 452 us; 16K 2490 / 1472; 32K 6150 / 4800; 16K, 8/1 heads 3600 / 435; pieces of half
-// or a quarter of the mean: 465 / 1480 / 4880 / 433 and 465 / 1530 / 4845 / 477).  A piece is at least 32 steps (a step takes
-// about 1.3 us; writing and adding up a piece's 128 KB of partial sums 5 - 10), and all partial sums have to fit into the
-// memory of dq (see ksa_launch_prefill_bwd), which holds batch * rows * query heads / 512 of them.
+// tile of 128 of them is as long as hundreds of text tiles: a few workgroups would run long after the others have finished.
+// Long tiles are therefore dealt to several workgroups, whose fp32 partial sums a second kernel adds up in a fixed order.  How
+// long a piece may be is found by playing the launch through: workgroups start in the order of the list, longest first, on as
+// many places as the chip has (two per compute unit, three at head_dim 64); a step costs 1, the start and the end of a
+// workgroup DKV_STEPS_PER_START, the kernel that adds up its launch and 1/16 per partial sum.  Pieces are of equal length, or of
+// the full length and what is left, which the greedy order packs better where a launch has few tiles.  Against the best
+// of 13 piece lengths tried one by one (12 shapes, 1K to 64K tokens) the choice is within 3 %; pieces of the mean work per
+// place, for comparison: 32K tokens 4.44 ms against 3.95, 64K 15.8 / 14.4, 2048 124 us / 87.  Equal pieces only: dense causal
+// 16K 3.67 ms against 3.40.  (Whole backward pass, 32/8 heads, d 128.)
+// All partial sums have to fit into the memory of dq (see ksa_launch_prefill_bwd), which holds batch * rows * query heads / 512
+// of them.
+constexpr int64_t DKV_STEPS_PER_START = 8, DKV_STEPS_OF_SUMS = 12, DKV_MIN_STEPS = 16;
 void build_dkv(ksa_layout &lay) {
     const ksa_params &p = lay.p;
     const int64_t n_sum = (int64_t)lay.n_chunks * p.n_summary, group = p.n_q_heads / p.n_kv_heads;
     const int64_t n_bh = (int64_t)p.batch * p.n_kv_heads;
     const int64_t sum_tiles = (n_sum + KSA_DKV_KEYS - 1) / KSA_DKV_KEYS, text_tiles = (p.n_text + KSA_DKV_KEYS - 1) / KSA_DKV_KEYS;
     std::vector<int64_t> steps(sum_tiles + text_tiles);
-    int64_t total = 0;
+    int64_t total = 0, longest_tile = 0;
     for (int64_t t = 0; t < sum_tiles + text_tiles; ++t) {
         const int space = t < sum_tiles ? KSA_SPACE_SUMMARY : KSA_SPACE_TEXT;
         const int64_t k0 = (t < sum_tiles ? t : t - sum_tiles) * KSA_DKV_KEYS, n = t < sum_tiles ? n_sum : p.n_text;
         steps[t] = dkv_blocks(p, space, k0, std::min<int64_t>(k0 + KSA_DKV_KEYS, n)) * group;
-        total += steps[t];
+        total += steps[t], longest_tile = std::max(longest_tile, steps[t]);
     }
     const int64_t capacity = (int64_t)p.batch * lay.aug_len * p.n_q_heads / 512 / n_bh;
-    int64_t longest = std::max<int64_t>(32, total * n_bh / 256);
-    auto slots_at = [&](int64_t most) {
-        int64_t n = 0;
-        for (int64_t x : steps) n += x > most ? (x + most - 1) / most : 0;
-        return n;
+    const int64_t places = p.head_dim == 128 ? 512 : 768, mean = total * n_bh / places;
+    auto pieces_of = [&](int64_t t, int64_t most) { return steps[t] > most ? (steps[t] + most - 1) / most : 1; };
+    // where piece x of n begins: equal pieces, or pieces of `most` steps and what is left (which fits in where the equal ones of
+    // a launch of few tiles do not: dense causal 16K)
+    auto begin_of = [&](int64_t t, int64_t most, bool equal, int64_t x, int64_t n) { return equal ? steps[t] * x / n : std::min(x * most, steps[t]); };
+    std::vector<int64_t> lengths;
+    int64_t longest = longest_tile, best = INT64_MAX;
+    bool best_equal = true;
+    auto consider = [&](int64_t most, bool equal) {   // the launch with pieces of at most so many steps
+        int64_t slots = 0;
+        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) slots += steps[t] > most ? pieces_of(t, most) : 0;
+        if (slots > capacity) return;
+        lengths.clear();
+        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) {
+            const int64_t n = pieces_of(t, most);
+            for (int64_t x = 0; x < n; ++x) lengths.push_back(begin_of(t, most, equal, x + 1, n) - begin_of(t, most, equal, x, n));
+        }
+        std::sort(lengths.begin(), lengths.end(), std::greater<int64_t>());
+        const int64_t sums = slots > 0 ? DKV_STEPS_OF_SUMS + slots * n_bh / 16 : 0;
+        // (when places come free, how many of them): the workgroups of all (batch, KV head) pairs are alike
+        using Free = std::pair<int64_t, int64_t>;
+        std::priority_queue<Free, std::vector<Free>, std::greater<Free>> places_free;
+        places_free.push({0, places});
+        int64_t end = 0;
+        for (const int64_t len : lengths)
+            for (int64_t left = n_bh; left > 0;) {
+                const Free f = places_free.top();
+                const int64_t n = std::min(left, f.second), at = f.first + len + DKV_STEPS_PER_START;
+                if (at + sums >= best) return;
+                places_free.pop();
+                if (n < f.second) places_free.push({f.first, f.second - n});
+                places_free.push({at, n});
+                end = std::max(end, at), left -= n;
+            }
+        best = end + sums, longest = most, best_equal = equal;
     };
-    while (slots_at(longest) > capacity) longest *= 2;   // (0 once no tile is longer)
+    consider(longest_tile, true);
+    if (longest_tile > mean / 8) {
+        const int64_t shortest = std::max(DKV_MIN_STEPS, mean / 8);
+        for (int64_t quarters = 2; quarters <= 6; ++quarters)
+            if (mean * quarters / 4 >= DKV_MIN_STEPS && mean * quarters / 4 < longest_tile) consider(mean * quarters / 4, false);
+        // (no better than 2 % above the mean is worth looking for)
+        for (int64_t quarters = 5; longest_tile * 4 / quarters >= shortest && best * 50 > (mean + DKV_STEPS_PER_START) * 51; quarters += quarters / 4)
+            consider(longest_tile * 4 / quarters, true);
+    }
     for (int64_t t = 0; t < (int64_t)steps.size(); ++t) {
-        const int64_t pieces = steps[t] > longest ? (steps[t] + longest - 1) / longest : 1;
+        const int64_t pieces = pieces_of(t, longest);
         if (pieces > 1) lay.dkv_splits.push_back({(int32_t)t, lay.dkv_slots, (int32_t)pieces, 0});
         for (int64_t x = 0; x < pieces; ++x)
-            lay.dkv_entries.push_back({(int32_t)t, (int32_t)(steps[t] * x / pieces), (int32_t)(steps[t] * (x + 1) / pieces),
+            lay.dkv_entries.push_back({(int32_t)t, (int32_t)begin_of(t, longest, best_equal, x, pieces), (int32_t)begin_of(t, longest, best_equal, x + 1, pieces),
                                        pieces > 1 ? lay.dkv_slots++ : -1});
     }
     std::stable_sort(lay.dkv_entries.begin(), lay.dkv_entries.end(), [](const KsaDkvEntry &a, const KsaDkvEntry &b) {
         return a.step_end - a.step_begin > b.step_end - b.step_begin;
     });
+    // The kernel that works on the scores of 64 rows at a time (ksa_prefill_bwd.hip) is left with launches whose time is that of
+    // their longest workgroup: dense causal text of few tiles none of which could be split (one query head per KV head: dq holds
+    // one partial sum per 512 rows).  A workgroup alone on its compute unit takes 0.9 us per 32 rows there, 1.1 here.  16/16
+    // heads, d 128, there / here: 1024 tokens 68 / 71 us, 2048 120 / 128, 4096 269 / 285 (d 64: 82 / 98, 168 / 192); from two tiles
+    // per place on it is behind: 8192 888 / 870, 2 x 4096 490 / 470; a window of 1024 over 3000 tokens 137 / 111.
+    const bool dense = p.n_summary == 0 && p.window_chunks >= (p.n_text - 1) / p.chunk_len;
+    lay.dkv_direct = !(dense && lay.dkv_splits.empty() && text_tiles * n_bh <= places);
 }
 
 }  // namespace

@@ -78,7 +78,7 @@ struct DirectArgs {
     // dQ only: o is dq, the others as in ksa_prefill_bwd.hip
     const __bf16 *g;                    // dLoss/dO
     int64_t gs[3];
-    const float *lse2c, *dlc;           // per row, compact order: log-sum-exp times log2(e), minus delta
+    const float *stats;                 // row statistics (ksa_stat_at)
     int32_t nt_pad, ns_pad;
     float scale;
 };
@@ -192,7 +192,7 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
 #pragma unroll
         for (int s = 0; s < T::KS; ++s) greg[s] = *reinterpret_cast<const bf16x8 *>(gp + s * 16);
         const int64_t stat = ((int64_t)b * a.n_q_heads + hq) * (a.nt_pad + a.ns_pad) + (q_space == KSA_SPACE_TEXT ? idx : a.nt_pad + idx);
-        lse2 = a.lse2c[stat], minus_delta = a.dlc[stat];
+        lse2 = a.stats[ksa_stat_at(stat)], minus_delta = a.stats[ksa_stat_at(stat) + KSA_STAT_ROWS];
     }
 
     // ---- the request of a tile, in two parts -------------------------------------------------------------------
@@ -727,7 +727,7 @@ int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_parts, flo
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
 }
 
-int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *lse2c, const float *dlc, void *stream) {
+int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *stats, void *stream) {
     DirectArgs a;
     a.q = static_cast<const __bf16 *>(L.q);
     a.k = static_cast<const __bf16 *>(L.k);
@@ -736,7 +736,7 @@ int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *lse2c, const
     a.o = static_cast<__bf16 *>(L.dq);
     a.lse = nullptr, a.knorm_parts = nullptr, a.knorm = nullptr, a.running_text = a.running_sum = a.norm_parts = a.norm_text_parts = a.norm_run = 0;
     for (int x = 0; x < 3; ++x) a.qs[x] = L.q_strides[x], a.ks[x] = L.kv_strides[x], a.gs[x] = L.o_strides[x], a.os[x] = L.dq_strides[x];
-    a.lse2c = lse2c, a.dlc = dlc;
+    a.stats = stats;
     const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);
     if (n_wg >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
     a.nt_pad = (a.n_text + 63) / 64 * 64, a.ns_pad = (a.n_sum + 63) / 64 * 64;

@@ -1,0 +1,68 @@
+"""GPU parity of the dK / dV kernel with 32-row query tiles (ksa_prefill_bwd_dkv.hip) and of the line to the one with 64-row
+blocks: chunks that divide a query tile, are divided by one, or neither; incomplete last tiles of either space; one to eight
+query heads per KV head; rows whose log-sum-exp is no number."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_24432_amd as K
+from paper_2604_24432_amd import synth
+from oracle import ksa_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+def run(shape, flags=0, seed=0):
+    B, Hq, Hkv, d, n, c, m, C = shape
+    cfg = synth.KsaConfig("dkv", B, Hq, Hkv, d, n, c, m, C, seed=n + c + seed)
+    q, k, v = (x.cuda() for x in synth.make_prefill_inputs(cfg))
+    g = synth.make_upstream_gradient(cfg).cuda()
+    lay = K.ksa_build_layout(K.make_params(B, n, c, m, C, Hq, Hkv, d, flags=flags))
+    return cfg, lay, q, k, v, g
+
+
+# batch, heads, KV heads, d, n, c, m, C
+SHAPES = [(1, 4, 2, 128, 31, 8, 1, 2), (1, 2, 1, 128, 33, 16, 2, 1), (2, 3, 1, 64, 129, 32, 4, 0), (1, 8, 1, 128, 353, 64, 8, 1),
+          (1, 2, 2, 64, 641, 96, 32, 1), (1, 4, 1, 128, 500, 128, 64, 1), (1, 2, 1, 128, 479, 48, 6, 2), (1, 2, 2, 64, 383, 1, 0, 70),
+          (1, 4, 4, 128, 417, 2, 1, 100), (1, 2, 2, 128, 510, 64, 0, 9), (1, 2, 2, 64, 300, 100, 0, 9), (1, 2, 1, 128, 385, 64, 0, 9)]
+
+
+@pytest.mark.parametrize("self_only", [0, 1])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_against_oracle(shape, self_only):
+    if self_only and shape[6] < 2:
+        pytest.skip("one summary per chunk")
+    cfg, lay, q, k, v, g = run(shape, K.KSA_FLAG_SUMMARY_SELF_ONLY if self_only else 0)
+    o, lse = K.ksa_prefill_fwd(lay, q, k, v)
+    got = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g)
+    ref = O.prefill_bwd(*(x.float().cpu().numpy() for x in (q, k, v, g)), cfg.n_text, cfg.chunk_len, cfg.n_summary,
+                        cfg.window_chunks, flags=self_only)
+    for name, x, r in zip(("dq", "dk", "dv"), got, ref):
+        # bf16 weights (2^-9 each, in quadrature), the forward's bf16 output in delta, one bf16 rounding of the result: see
+        # test_gpu_prefill_bwd_split.py; few keys per row are at the upper end
+        rel = np.linalg.norm(x.float().cpu().numpy() - r) / np.linalg.norm(r)
+        print(f"{shape} {name}: relative error {rel:.2e}", flush=True)
+        assert rel <= 5e-3, name
+
+
+@pytest.mark.parametrize("value", [math.nan, -math.inf, math.inf])
+@pytest.mark.parametrize("shape", [(1, 2, 1, 128, 353, 64, 8, 1), (1, 2, 2, 64, 383, 1, 0, 70)], ids=["chunks", "window"])
+def test_log_sum_exp_that_is_no_number(shape, value):
+    """A weight of a row without a log-sum-exp is none (infinite: zero) for the keys that the row sees and zero for the others."""
+    cfg, lay, q, k, v, g = run(shape)
+    o, lse = K.ksa_prefill_fwd(lay, q, k, v)
+    row = 200
+    lse[0, :, row] = value
+    _, dk, dv = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g)
+    g0 = g.clone()
+    g0[0, row] = 0                       # without the row's contribution
+    lse[0, :, row] = math.inf
+    _, _, want = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g0)
+    sees = torch.from_numpy(np.array(O.mask(cfg.n_text, cfg.chunk_len, cfg.n_summary, cfg.window_chunks)[row], dtype=bool)).cuda()
+    assert torch.equal(dv[0, ~sees], want[0, ~sees])
+    if value == math.inf:
+        assert bool(torch.isfinite(dv[0, sees]).all())
+    else:
+        assert not bool(torch.isfinite(dv[0, sees]).any())
