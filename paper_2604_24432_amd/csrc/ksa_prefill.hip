@@ -75,9 +75,10 @@ __device__ __forceinline__ float other_half(float x) {
     return __builtin_bit_cast(float, (threadIdx.x & 32) ? r[0] : r[1]);
 }
 
-// LDS tile: row-major [64][D] bf16, the 16-byte chunk index XORed with a function of the row
+// LDS tile: row-major [64][D] bf16, the 16-byte chunk index XORed with a function of the row.  At head_dim 64 two rows share the
+// 256 bytes that all banks hold, so the rows of one parity have to differ (1 % of the time: see ksa_prefill_direct.hip).
 template <int D>
-__device__ __forceinline__ int k_swz(int row) { return row & (D / 8 - 1); }
+__device__ __forceinline__ int k_swz(int row) { return D == 64 ? (row >> 1) & 7 : row & (D / 8 - 1); }
 
 template <int D>
 struct Tile {

@@ -64,9 +64,10 @@ struct BwdArgs {
 };
 
 // LDS tile: row-major [64][D] bf16; the 16-byte chunk index is XORed with a function of the row that spreads both
-// the 16 rows of a plain 16-byte operand read and the 4 rows of a transposing read over different banks.
+// the 16 rows of a plain 16-byte operand read and the 4 rows of a transposing read over different banks (head_dim 64:
+// two rows share the 256 bytes of all banks, so the rows of one parity have to differ).
 template <int D>
-__device__ __forceinline__ int swz(int row) { return (((row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
+__device__ __forceinline__ int swz(int row) { return ((D == 64 ? (row & 2) << 1 : (row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
 
 // global -> LDS, 4 bytes per lane: the wave's 64 pieces land back to back (lane order) from the wave-uniform LDS
 // address dst.  Inline assembly for the same reason as lds_direct_load_16_s().

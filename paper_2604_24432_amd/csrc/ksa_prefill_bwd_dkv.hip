@@ -72,9 +72,10 @@ __device__ __forceinline__ void lds_direct_load_4_s(const float *sbase, unsigned
 }
 
 // LDS tile: row-major [32][D] bf16, the 16-byte piece index XORed with a function of the row that spreads both the 16 rows
-// of a plain 16-byte read and the 4 rows of a transposing read over different banks.
+// of a plain 16-byte read and the 4 rows of a transposing read over different banks (head_dim 64:
+// two rows share the 256 bytes of all banks, so the rows of one parity have to differ).
 template <int D>
-__device__ __forceinline__ int swz(int row) { return (((row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
+__device__ __forceinline__ int swz(int row) { return ((D == 64 ? (row & 2) << 1 : (row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
 
 // Query rows [lo, hi) of index space q_space that see key `key` of index space `space` (Eq. 3 read from the key's side).  A
 // row's visible ranges never move backwards from one row to the next, so these are consecutive rows, and lo and hi do
