@@ -2,16 +2,27 @@
 // (section 2.3.1).  The work is bandwidth bound: every visible K and V row is read from HBM exactly once
 // per KV head and serves all Hq/Hkv query heads of that head.
 //
-// Split-K: a workgroup streams one span of the visible rows of one (sequence, KV head).  A cache row of head_dim bf16 is
-// read by head_dim/8 adjacent lanes with one 16-byte load each, so a wavefront load covers 1 KiB of consecutive memory; U
-// such loads of K and of V are in flight per lane.  Each lane keeps the partial dot products of its 8 columns for all query
-// heads of the group, a 4-step DPP all-reduce over the row's lanes finishes the scores, and every lane group runs its own
-// online softmax on the rows it saw.  The lane groups of a wave are merged by lane swaps, the waves through LDS, into one
-// partial (max, sum, o) per query head; a second kernel merges the spans of a sequence by log-sum-exp.  With one span per
-// sequence (a summary token's few rows, small caches) the workgroup stores the result itself and there is no second kernel.
+// Split-K: a workgroup streams one span of the visible rows of one (sequence, KV head).  Of head_dim bf16 a V row is read by
+// head_dim / 8 adjacent lanes with one 16-byte load each; U such loads of K and of V are in flight per lane.  Each lane keeps
+// its 8 columns of the output for all query heads of the group, and every lane group runs its own online softmax on the rows
+// it saw.  The lane groups of a wave are merged by lane swaps, the waves through LDS, into one partial (max, sum, o) per query
+// head; a second kernel merges the spans of a sequence by log-sum-exp.  With one span per sequence (a summary token's few
+// rows, small caches) the workgroup stores the result itself and there is no second kernel.
+//
+// Scores: with four and eight query heads per KV head from the matrix unit, S^T = K Q^T with v_mfma_f32_16x16x32_bf16: 16 cache
+// rows by G heads (repeated over the 16 columns), fp32 sums of exact products.  Lane l receives the scores of rows
+// 4 (l / 16) + i, i < 4, for head l % G; the V rows it loads are dealt so that they are these same rows, and the (fp32) weights
+// of the other heads are a DPP move away.  With one and two heads they are dot products on the vector unit, 8 columns per lane
+// and a 4-step DPP all-reduce over the row's lanes.
+// What bounds it: HBM reads where the launch fills the chip (batch 64 at a 128K context, 4.33 GB: 655 us, 6.6 TB/s; scores on the
+// vector unit 670).  With eight heads the vector unit was the bound: batch 32, 64K context, 8/1 heads 58.1 / 37.2 us, window
+// 1024 with batch 64 41.1 / 28.2; batch 3, 20K, d 64 22.3 / 16.6.  With four: 32K, batch 4 and append 26.1 / 24.7, 128K, batch 1
+// 23.9 / 22.6.  With one head the matrix unit's operand reads (64 bytes of 16 rows instead of four whole rows) lost: batch 32,
+// 32K, 16/16 heads 163.9 us on the vector unit, 169.0.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <utility>
 
 #include "ksa_internal.h"
 
@@ -24,6 +35,8 @@ static __device__ __align__(256) unsigned char scratch[KSA_DECODE_STATIC_SCRATCH
 namespace {
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int U = 4;         // row loads in flight per lane, K and V each
 
@@ -98,6 +111,34 @@ __device__ __forceinline__ float row_allreduce(float x) {
     return x;
 }
 
+// how far behind its position v among the visible rows a row lies in the cache
+__device__ __forceinline__ int row_shift(const Ranges &R, int v) {
+    const int ring = v < R.n0 + R.n1 ? R.off1 - R.n0 : R.off2 - R.n0 - R.n1;
+    return v < R.n0 ? R.off0 : ring;
+}
+
+// A score lives in the lane of its query head: lane l holds head l % G.  The value of head g among a lane's neighbours that hold
+// the same rows: the 16 lanes of a row of lanes, with D = 64 its halves.
+template <int D, int G, int g>
+__device__ __forceinline__ float of_head(float x) {
+    const int u = __builtin_bit_cast(int, x);
+    if constexpr (G == 1) return x;
+    else if constexpr (G <= 4) return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, u, g * 0x55, 0xf, 0xf, true));   // quad_perm [g,g,g,g]
+    else {
+        const int lo = __builtin_amdgcn_update_dpp(0, u, 0x150 + g, 0xf, 0xf, true);   // row_newbcast: lane g of the 16
+        if constexpr (D == 128) return __builtin_bit_cast(float, lo);
+        else return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(lo, u, 0x158 + g, 0xf, 0xc, false));   // ... 8 + g for the upper 8
+    }
+}
+template <int D, int G, typename F, int... g>
+__device__ __forceinline__ void heads_of(float x, F &&use, std::integer_sequence<int, g...>) {
+    (use(g, of_head<D, G, g>(x)), ...);
+}
+template <int D, int G, typename F>
+__device__ __forceinline__ void for_heads(float x, F &&use) {   // use(g, value of head g)
+    heads_of<D, G>(x, use, std::make_integer_sequence<int, G>{});
+}
+
 // eight bf16 -> eight fp32 (a bf16 is the high half of an fp32)
 __device__ __forceinline__ void unpack8(const u32x4 &x, float f[8]) {
 #pragma unroll
@@ -128,6 +169,34 @@ __device__ __forceinline__ float swap32(float x) {
 }
 __device__ __forceinline__ float swap8(float x) {   // lane l ^ 8: row_ror 8
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xf, 0xf, false));
+}
+
+// the waves' partial results -> the workgroup's: its record in the workspace, or with one span per sequence the result
+template <int D, int G, int NT>
+__device__ __forceinline__ void merge_waves(const DecodeArgs &a, int split, int hkv, int b, const float (&sh_o)[NT / 64][G][D],
+                                            const float (&sh_m)[NT / 64][G], const float (&sh_l)[NT / 64][G]) {
+    constexpr int NW = NT / 64;
+    __syncthreads();
+    for (int x = (int)threadIdx.x; x < G * D; x += NT) {
+        const int g = x / D, col = x % D;
+        float M = sh_m[0][g];
+#pragma unroll
+        for (int y = 1; y < NW; ++y) M = fmaxf(M, sh_m[y][g]);
+        float acc = 0.f, den = 0.f;
+#pragma unroll
+        for (int y = 0; y < NW; ++y) {
+            const float w = __builtin_amdgcn_exp2f(sh_m[y][g] - M);
+            acc += sh_o[y][g][col] * w, den += sh_l[y][g] * w;
+        }
+        const int hq = hkv * G + g;
+        if (a.n_splits == 1) {
+            store_result<D>(a, b, hq, col, valid_pos(a, a.pos[b]), acc, den, M);
+        } else {
+            float *rec = a.ws + (((int64_t)b * a.n_q_heads + hq) * a.n_splits + split) * (D + 2);
+            rec[col] = acc;
+            if (col == 0) rec[D] = M, rec[D + 1] = den;
+        }
+    }
 }
 
 // partial record in the workspace: [D] unnormalised o, then running max (log2 domain), then running sum
@@ -247,27 +316,132 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_kernel(const DecodeArgs a
             if (chunk == 0) sh_m[wave][g] = M, sh_l[wave][g] = l;
         }
     }
-    __syncthreads();
-    for (int x = tid; x < G * D; x += NT) {
-        const int g = x / D, col = x % D;
-        float M = sh_m[0][g];
+    merge_waves<D, G, NT>(a, split, hkv, b, sh_o, sh_m, sh_l);
+}
+
+// the same with scores from the matrix unit: four and eight query heads per KV head
+template <int D, int G, int NT>
+__global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const DecodeArgs a) {
+    constexpr int LPR = D / 8;          // lanes per V row
+    constexpr int RPW = 64 / LPR;       // V rows per wavefront load
+    constexpr int KB = RPW * U / 16;    // blocks of 16 rows per wavefront and iteration
+    constexpr int KS = D / 32;          // k steps of the score MFMA
+    constexpr int NW = NT / 64;
+    constexpr int R_IT = NW * RPW * U;  // rows per workgroup iteration
+    static_assert(KB * KS == U && U == 4, "as many loads of K as of V");
+
+    const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int chunk = lane % LPR, gi = lane / LPR;
+    const int v_row = (D == 64 ? 16 * (gi & 1) : 0) + 4 * (lane >> 4);   // the lane's V rows: v_row .. v_row + 3
+
+    const Ranges R = visible_rows(a, a.pos[b]);
+    const int N = R.n0 + R.n1 + R.n2;
+    const int per = (N + a.n_splits - 1) / a.n_splits;
+    const int v0 = split * per, v1 = min(N, v0 + per);
+
+    bf16x8 qreg[KS];
+    {
+        const __bf16 *qp = a.q + ((int64_t)b * a.n_q_heads + hkv * G + lane % G) * D + (lane >> 4) * 8;
 #pragma unroll
-        for (int y = 1; y < NW; ++y) M = fmaxf(M, sh_m[y][g]);
-        float acc = 0.f, den = 0.f;
+        for (int s = 0; s < KS; ++s) qreg[s] = *reinterpret_cast<const bf16x8 *>(qp + s * 32);
+    }
+    float m_run = -1e30f, l_run = 0.f, o[G][8];
 #pragma unroll
-        for (int y = 0; y < NW; ++y) {
-            const float w = __builtin_amdgcn_exp2f(sh_m[y][g] - M);
-            acc += sh_o[y][g][col] * w, den += sh_l[y][g] * w;
-        }
-        const int hq = hkv * G + g;
-        if (a.n_splits == 1) {
-            store_result<D>(a, b, hq, col, valid_pos(a, a.pos[b]), acc, den, M);
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[g][e] = 0.f;
+
+    const __bf16 *kb = a.k + b * a.cs[0] + hkv * a.cs[1] + (lane >> 4) * 8;
+    const __bf16 *vb = a.v + b * a.cs[0] + hkv * a.cs[1] + chunk * 8;
+
+    const int64_t row = a.cs[2];
+    for (int base = v0 + wave * (RPW * U); base < v1; base += R_IT) {
+        // Nearly all blocks lie in one piece of the cache and before the end: then a scalar offset moves the lane's addresses.
+        // (The shift never decreases from one visible row to the next, so equal ends mean one piece.)
+        const int end = base + RPW * U, shift = row_shift(R, base);
+        const bool whole = end <= v1 && row_shift(R, end - 1) == shift;
+        int64_t k_at[KB], v_at[U];
+        if (whole) {
+            const int64_t first = (int64_t)(base + shift) * row;
+#pragma unroll
+            for (int x = 0; x < KB; ++x) k_at[x] = (lane & 15) * row + (first + 16 * x * row);
+#pragma unroll
+            for (int u = 0; u < U; ++u) v_at[u] = v_row * row + (first + u * row);
         } else {
-            float *rec = a.ws + (((int64_t)b * a.n_q_heads + hq) * a.n_splits + split) * (D + 2);
-            rec[col] = acc;
-            if (col == 0) rec[D] = M, rec[D + 1] = den;
+            auto offset = [&](int v) { v = min(v, v1 - 1); return (int64_t)(v + row_shift(R, v)) * row; };
+#pragma unroll
+            for (int x = 0; x < KB; ++x) k_at[x] = offset(base + 16 * x + (lane & 15));
+#pragma unroll
+            for (int u = 0; u < U; ++u) v_at[u] = offset(base + v_row + u);
+        }
+        u32x4 kk[KB][KS], vv[U];
+#pragma unroll
+        for (int x = 0; x < KB; ++x)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) kk[x][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(kb + k_at[x] + s * 32));
+#pragma unroll
+        for (int u = 0; u < U; ++u) vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + v_at[u]));
+        __builtin_amdgcn_sched_barrier(0);   // all loads of the block are on their way
+        f32x4 acc[KB];
+#pragma unroll
+        for (int x = 0; x < KB; ++x) {
+            acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kk[x][s]), qreg[s], acc[x], 0, 0, 0);
+        }
+        float p[U], mx = m_run;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float s = (KB == 1 || !(gi & 1) ? acc[0][u] : acc[KB - 1][u]) * a.scale_log2e;
+            p[u] = base + v_row + u < v1 ? s : -INFINITY;
+            mx = fmaxf(mx, p[u]);
+        }
+        if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
+            const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
+            l_run *= alpha, m_run = mx;
+            for_heads<D, G>(alpha, [&](int g, float x) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[g][e] *= x;
+            });
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            p[u] = __builtin_amdgcn_exp2f(p[u] - m_run);
+            l_run += p[u];
+            float vf[8];
+            unpack8(vv[u], vf);
+            for_heads<D, G>(p[u], [&](int g, float x) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[g][e] = fmaf(x, vf[e], o[g][e]);
+            });
         }
     }
+
+    // ---- merge the lane groups of each wave, then the waves -----------------------------------------
+    __shared__ float sh_o[NW][G][D];
+    __shared__ float sh_m[NW][G], sh_l[NW][G];
+    float M = m_run;
+    if (LPR == 8) M = fmaxf(M, swap8(M));
+    M = fmaxf(M, swap16(M));
+    M = fmaxf(M, swap32(M));
+    const float f = __builtin_amdgcn_exp2f(m_run - M);
+    auto merge = [&](float x) {
+        if (LPR == 8) x += swap8(x);
+        x += swap16(x);
+        return x + swap32(x);
+    };
+    const float l = merge(l_run * f);
+    if (lane < G) sh_m[wave][lane] = M, sh_l[wave][lane] = l;
+    for_heads<D, G>(f, [&](int g, float x) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float sum = merge(o[g][e] * x);
+            if (gi == 0) sh_o[wave][g][chunk * 8 + e] = sum;
+        }
+    });
+    merge_waves<D, G, NT>(a, split, hkv, b, sh_o, sh_m, sh_l);
 }
 
 // one workgroup of D threads per (batch, query head): log-sum-exp merge of the spans
@@ -292,12 +466,16 @@ __global__ __launch_bounds__(D) void ksa_decode_merge_kernel(const DecodeArgs a)
 
 template <int D, int G, int NT>
 void launch(const DecodeArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL((ksa_decode_split_kernel<D, G, NT>), dim3(a.n_splits, a.n_kv_heads, a.batch), dim3(NT), 0, st, a);
+    const dim3 grid(a.n_splits, a.n_kv_heads, a.batch);
+    if constexpr (G >= 4)
+        hipLaunchKernelGGL((ksa_decode_split_matrix_kernel<D, G, NT>), grid, dim3(NT), 0, st, a);
+    else
+        hipLaunchKernelGGL((ksa_decode_split_kernel<D, G, NT>), grid, dim3(NT), 0, st, a);
     if (a.n_splits > 1) hipLaunchKernelGGL(ksa_decode_merge_kernel<D>, dim3(a.n_q_heads, a.batch), dim3(D), 0, st, a);
 }
 
 // 256 threads per span; with no more spans than compute units 1024 (512 with eight query heads per KV head, whose
-// accumulators take more registers), i.e. four times the loads in flight per unit.  Kernels of one step, 256 / 1024 threads:
+// accumulators take more registers), i.e. four times the loads in flight per unit.  Kernels of one step, 256 / 1024 threads (scores on the vector unit):
 // 128K context, batch 1 (168 spans) 29 / 25 us; 32K, batch 4 (160) 28 / 24; 16K, batch 16 (256) 39 / 31; 128K, batch 2 (336)
 // 41 / 44; 64K, d 64, batch 8 (640) 30 / 42.
 template <int D, int G>
