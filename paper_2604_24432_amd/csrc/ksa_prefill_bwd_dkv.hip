@@ -162,13 +162,14 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
         for (int e = 0; e < 16; ++e) dk[db][e] = 0.f, dv[db][e] = 0.f;
 
     // ---- the sequence of query tiles: run 0 is the text rows, run 1 the summary rows, a step one head of one block ------
-    int blk_end[2], blk_n[2];      // blocks [blk_end - blk_n, blk_end) of the index space
+    int run_end[2], blk_n[2];      // rows before run_end, the last blk_n blocks of them
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         const int lo = seen_by(view, space, k0, x).lo, hi = seen_by(view, space, k_last, x).hi;
-        blk_end[x] = (hi + BM - 1) / BM;
-        blk_n[x] = hi > lo ? blk_end[x] - lo / BM : 0;
+        run_end[x] = hi;
+        blk_n[x] = hi > lo ? (hi + BM - 1) / BM - lo / BM : 0;
     }
+    auto last_block = [&](int x) { return (int)((unsigned)((x ? run_end[1] : run_end[0]) - 1) / BM); };   // (of a run that has rows)
     const int steps0 = blk_n[0] * a.group;
     const int n_steps = min(steps0 + blk_n[1] * a.group, step_end) - step_begin;   // > 0: a key is seen by its own row
 
@@ -185,9 +186,9 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
     int alike, gap, gap_every, gap_in;
     auto open_block = [&](int x, int blk, int head) {   // block blk of run x, worked out from the start
         const auto *p = args_again();
-        const int per = x ? p->view.m : p->view.c, other = x ? p->view.c : p->view.m, n_q = x ? p->view.n_sum : p->view.n_text;
+        const int per = x ? p->view.m : p->view.c, other = x ? p->view.c : p->view.m, end = x ? run_end[1] : run_end[0];
         rq_run = x, rq_first = blk * BM, rq_head = head;
-        run_lo = (x ? blk_end[1] - blk_n[1] : blk_end[0] - blk_n[0]) * BM;
+        run_lo = (last_block(x) + 1 - (x ? blk_n[1] : blk_n[0])) * BM;
         const int j0 = ksa_div(rq_first, KsaDivisor{x ? p->view.by_m.mul : p->view.by_c.mul, x ? p->view.by_m.shift : p->view.by_c.shift});
         const int phase = rq_first - j0 * per;
         const int64_t row0 = (int64_t)rq_first + (x ? p->view.c : 0) + (int64_t)j0 * other;
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
         rq_q = (const char *)(p->q + b * p->qs[0] + row0 * p->qs[1] + hq * p->qs[2]);
         rq_g = (const char *)(p->g + b * p->gs[0] + row0 * p->gs[1] + hq * p->gs[2]);
         rq_st = (const char *)(p->stats + 2 * ((int64_t)(b * p->n_q_heads + hq) * (p->nt_pad + p->ns_pad) + (x ? p->nt_pad : 0) + rq_first));
-        alike = rq_first + BM <= n_q ? (x ? p->alike_m : p->alike_c) : 0;
+        alike = rq_first + BM <= end ? (x ? p->alike_m : p->alike_c) : 0;
         gap = (x ? p->gap_m : p->gap_c), gap_every = max(per - BM, 0), gap_in = per < BM ? 0 : phase;
         // row k of the tile lies k + (chunk borders in between) * other rows behind the first: see ksa_prefill_direct.hip
         const unsigned mul = per < 64 ? (x ? p->small_m : p->small_c) : 1024u;
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int row = RW * wave + RPI * i + lane / CH;
-            const unsigned k = min(row, n_q - 1 - rq_first);   // rows past the end of the index space: its last one, masked
+            const unsigned k = min(row, end - 1 - rq_first);   // rows behind the run: its last one, masked (they may hold NaN)
             const unsigned d_rows = k + ((__umul24(k, mul) + add) >> 16) * (unsigned)other;
             const unsigned col = (unsigned)(((lane % CH) ^ swz<D>(row)) << 4);
             q_off[i] = d_rows * q_row_bytes + col, g_off[i] = d_rows * g_row_bytes + col;
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
             rq_st -= 8 * BM + (a.group - 1) * st_head_bytes;
             return;
         }
-        open_block(first_run_ends ? 1 : rq_run, first_run_ends ? blk_end[1] - 1 : rq_first / BM - 1, 0);
+        open_block(first_run_ends ? 1 : rq_run, first_run_ends ? last_block(1) : rq_first / BM - 1, 0);
     };
     constexpr int LOADS = 2 * NI + 1;
     auto issue = [&](int stage, int x) {   // load x of the prepared tile: Q and G by turns, then the statistics
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
     };
     {
         const int x = step_begin < steps0 ? 0 : 1, in_run = step_begin - (x ? steps0 : 0), ti = ksa_div(in_run, a.by_group);
-        open_block(x, (x ? blk_end[1] : blk_end[0]) - 1 - ti, in_run - ti * a.group);
+        open_block(x, last_block(x) - ti, in_run - ti * a.group);
     }
     int tile_first[STAGES - 1];    // first rows of the tiles that are on their way, with the run in bit 0 (rows are multiples of BM)
     // K and V have arrived before the first request: the counted waits below are about tile requests only

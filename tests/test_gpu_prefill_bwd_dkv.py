@@ -66,3 +66,35 @@ def test_log_sum_exp_that_is_no_number(shape, value):
         assert bool(torch.isfinite(dv[0, sees]).all())
     else:
         assert not bool(torch.isfinite(dv[0, sees]).any())
+
+
+@pytest.mark.parametrize("shape,space,at", [((1, 8, 2, 128, 1024, 64, 8, 1), 1, 16), ((1, 8, 2, 128, 960, 48, 6, 1), 1, 20),
+                                            ((1, 4, 4, 128, 2048, 8, 1, 128), 1, 17), ((1, 4, 2, 64, 1024, 128, 16, 1), 1, 16),
+                                            ((1, 4, 4, 128, 1024, 1, 0, 199), 0, 330), ((1, 4, 4, 64, 1024, 1, 0, 199), 0, 330)],
+                         ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
+def test_row_behind_those_that_see_a_key_tile(shape, space, at):
+    """A NaN or infinity in a row behind the last one that sees any of a tile's 128 keys changes nothing in the tile's gradients,
+    also where the row shares a query tile with that last one.  (dO itself enters every row's delta, which dK of a query tile's
+    keys takes whole: there only dV is asked.)"""
+    cfg, lay, q, k, v, g = run(shape)
+    n, c, m = cfg.n_text, cfg.chunk_len, cfg.n_summary
+    o, lse = K.ksa_prefill_fwd(lay, q, k, v)
+    _, dk, dv = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g)
+    rows = [np.array([i // c * (c + m) + i % c for i in range(n)]),
+            np.array([u // m * (c + m) + c + u % m for u in range(n // c * m)], dtype=int)]
+    mask = np.array(O.mask(n, c, m, cfg.window_chunks), dtype=bool)
+    behind = []                          # keys of the tiles whose rows of this space all lie in front of row `at`
+    for keys in rows:
+        for t in range(0, len(keys), 128):
+            sees = mask[np.ix_(rows[space], keys[t:t + 128])].any(1).nonzero()[0]
+            if len(sees) == 0 or sees[-1] < at:
+                behind.append(keys[t:t + 128])
+    behind = torch.from_numpy(np.concatenate(behind)).cuda()
+    for name, x, value in (("dO", g, math.nan), ("dO", g, math.inf), ("q", q, math.nan), ("q", q, math.inf)):
+        keep = x.clone()
+        x[0, int(rows[space][at])] = value
+        _, dk1, dv1 = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g)
+        x.copy_(keep)
+        assert torch.equal(dv1[0, behind], dv[0, behind]), (name, value)
+        assert name == "dO" or torch.equal(dk1[0, behind], dk[0, behind]), (name, value)
+        assert not bool(torch.isfinite(dk1).all()), (name, value)   # it reached those that see it
