@@ -160,7 +160,7 @@ int ksa_prefill_bwd(ksa_layout *lay, const void *q, const void *k, const void *v
     a.dkv_splits = reinterpret_cast<const KsaDkvSplit *>(a.dkv_entries + a.n_dkv_entries);
     a.n_dkv_splits = (int32_t)lay->dkv_splits.size();
     a.dq_direct = lay->dq_direct;
-    a.dkv_direct = lay->dkv_direct;
+    a.dkv_direct = lay->dkv_direct, a.dkv_unsplit_direct = lay->dkv_unsplit_direct;
     a.p = p;
     a.aug_len = lay->aug_len;
     a.workspace = workspace;

@@ -17,7 +17,8 @@ struct ksa_layout {
     int32_t running_text = INT32_MAX, running_sum = INT32_MAX;   // first row of the first text / summary item with running_max
     int32_t head_stack = 1;           // query heads per workgroup (1, 2 or 4)
     bool dq_direct = false;           // ... and dQ
-    bool dkv_direct = false;          // dK and dV take the kernel of ksa_prefill_bwd_dkv.hip
+    bool dkv_direct = false;          // dK and dV take the kernel of ksa_prefill_bwd_dkv.hip where tiles are split
+    bool dkv_unsplit_direct = false;  // ... and where none is
     bool direct = false;              // the forward pass takes the kernel for short key runs (see takes_direct)
     int32_t q_tile_rows = KSA_Q_TILE; // rows of a query tile = KSA_Q_TILE / head_stack
     std::vector<KsaDkvEntry> dkv_entries;   // backward dK / dV, per (batch, KV head), longest first
@@ -91,7 +92,7 @@ struct KsaPrefillBwdLaunch {
     const KsaDkvEntry *dkv_entries;   // NULL: every key tile is one workgroup
     const KsaDkvSplit *dkv_splits;
     int32_t n_dkv_entries, n_dkv_splits;
-    bool dkv_direct;                  // dK and dV by the kernel of ksa_prefill_bwd_dkv.hip
+    bool dkv_direct, dkv_unsplit_direct;   // dK and dV by the kernel of ksa_prefill_bwd_dkv.hip: with split tiles, without
     bool dq_direct;                   // dQ by the kernel for short key runs (ksa_prefill_direct.hip)
     ksa_params p;
     int64_t aug_len;

@@ -178,18 +178,72 @@ void build_entries(ksa_layout &lay) {
         for (size_t x = 0; x < queue[q].size(); ++x) lay.entries[x * KSA_NUM_XCD + q] = queue[q][x];
 }
 
-// Steps of the dK / dV work of the keys [k0, k1) of an index space, per query head: the aligned blocks of KSA_DKV_ROWS query rows
-// that overlap the two runs of rows that can see one of them (the kernel works the same runs out).
-int64_t dkv_blocks(const ksa_params &p, int space, int64_t k0, int64_t k1) {
+// Steps of the dK / dV work of the keys [k0, k1) of an index space, per query head: the aligned blocks of `rows` query rows that
+// overlap the two runs of rows that can see one of them.  The kernels work the same runs out; the one with 64-row blocks counts
+// all summary rows of the keys' chunks whatever the self-only flag says.
+int64_t dkv_blocks(const ksa_params &p, int64_t rows, int space, int64_t k0, int64_t k1) {
     const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = (int64_t)(p.n_text / c) * m;
     const int64_t per = space == KSA_SPACE_TEXT ? c : m, jl = k0 / per, jh = (k1 - 1) / per;
     const int64_t b0 = space == KSA_SPACE_TEXT ? k0 : std::min<int64_t>((jl + C + 1) * c, p.n_text);
     const int64_t e0 = space == KSA_SPACE_TEXT ? std::min<int64_t>((jh + C + 1) * c, p.n_text) : p.n_text;
-    const bool self_only = space == KSA_SPACE_SUMMARY && (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY);
+    const bool self_only = rows == KSA_DKV_ROWS && space == KSA_SPACE_SUMMARY && (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY);
     const int64_t b1 = space == KSA_SPACE_TEXT ? jl * m : k0, e1 = self_only ? k1 : std::min<int64_t>((jh + 1) * m, n_sum);
-    auto blocks = [](int64_t b, int64_t e) { return e > b ? (e - 1) / KSA_DKV_ROWS - b / KSA_DKV_ROWS + 1 : 0; };
+    auto blocks = [&](int64_t b, int64_t e) { return e > b ? (e - 1) / rows - b / rows + 1 : 0; };
     return blocks(b0, e0) + blocks(b1, e1);
 }
+
+// The dK / dV key tiles of one (batch, KV head) for the kernel with query tiles of `rows` rows, and a launch of them.
+struct DkvTiles {
+    int64_t rows, places, start;     // workgroups that the chip holds at once; what starting and ending one costs, in steps
+    std::vector<int64_t> steps;      // per tile, the summary-space ones first
+    int64_t total = 0, longest = 0, n_bh, mean;   // (mean: steps per place of the whole launch)
+
+    DkvTiles(const ksa_params &p, int64_t rows_, int64_t places_, int64_t start_) : rows(rows_), places(places_), start(start_) {
+        const int64_t n_sum = (int64_t)(p.n_text / p.chunk_len) * p.n_summary, group = p.n_q_heads / p.n_kv_heads;
+        for (const int space : {KSA_SPACE_SUMMARY, KSA_SPACE_TEXT}) {
+            const int64_t n = space == KSA_SPACE_SUMMARY ? n_sum : p.n_text;
+            for (int64_t k0 = 0; k0 < n; k0 += KSA_DKV_KEYS)
+                steps.push_back(dkv_blocks(p, rows, space, k0, std::min<int64_t>(k0 + KSA_DKV_KEYS, n)) * group);
+        }
+        for (const int64_t x : steps) total += x, longest = std::max(longest, x);
+        n_bh = (int64_t)p.batch * p.n_kv_heads, mean = total * n_bh / places;
+    }
+    int64_t pieces(int64_t t, int64_t most) const { return steps[t] > most ? (steps[t] + most - 1) / most : 1; }
+    // where piece x of n begins: equal pieces, or pieces of `most` steps and what is left
+    int64_t begin(int64_t t, int64_t most, bool equal, int64_t x, int64_t n) const { return equal ? steps[t] * x / n : std::min(x * most, steps[t]); }
+    int64_t slots(int64_t most) const {   // partial sums with pieces of at most so many steps
+        int64_t n = 0;
+        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) n += steps[t] > most ? pieces(t, most) : 0;
+        return n;
+    }
+    // When the last workgroup ends if they start in the order of their lengths, longest first; INT64_MAX if not before `limit`.
+    int64_t makespan(int64_t most, bool equal, int64_t limit) const {
+        std::vector<int64_t> lengths;
+        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) {
+            const int64_t n = pieces(t, most);
+            for (int64_t x = 0; x < n; ++x) lengths.push_back(begin(t, most, equal, x + 1, n) - begin(t, most, equal, x, n));
+        }
+        std::sort(lengths.begin(), lengths.end(), std::greater<int64_t>());
+        // (when places come free, how many of them): the workgroups of all (batch, KV head) pairs are alike
+        using Free = std::pair<int64_t, int64_t>;
+        std::priority_queue<Free, std::vector<Free>, std::greater<Free>> places_free;
+        places_free.push({0, places});
+        int64_t end = 0;
+        for (const int64_t len : lengths)
+            for (int64_t left = n_bh; left > 0;) {
+                const Free f = places_free.top();
+                const int64_t n = std::min(left, f.second), at = f.first + len + start;
+                if (at >= limit) return INT64_MAX;
+                places_free.pop();
+                if (n < f.second) places_free.push({f.first, f.second - n});
+                places_free.push({at, n});
+                end = std::max(end, at), left -= n;
+            }
+        return end;
+    }
+    // ... if no tile is split: the longest one, or as long as the mean place is busy
+    int64_t unsplit() const { return std::max(longest + start, mean + start * (int64_t)steps.size() * n_bh / places); }
+};
 
 // The backward pass's dK / dV work of one (batch, KV head).  A summary key is seen by every later text row, so the first
 // tile of 128 of them is as long as hundreds of text tiles: a few workgroups would run long after the others have finished.
@@ -203,83 +257,71 @@ int64_t dkv_blocks(const ksa_params &p, int space, int64_t k0, int64_t k1) {
 // 16K 3.67 ms against 3.40.  (Whole backward pass, 32/8 heads, d 128.)
 // All partial sums have to fit into the memory of dq (see ksa_launch_prefill_bwd), which holds batch * rows * query heads / 512
 // of them.
+//
+// The kernel that works on blocks of 64 rows (ksa_prefill_bwd.hip) takes the launches whose time is that of their longest
+// workgroup: alone on its compute unit a workgroup takes 0.9 us per 32 rows there, 1.1 in ksa_prefill_bwd_dkv.hip (head_dim 64
+// 0.6 / 0.75), which is ahead where its two or three workgroups per unit all have work.  Its pieces are of at least 32 steps and
+// of the mean work per unit, longer while dq cannot hold them.  Both launches are played through and the 64-row kernel is taken
+// where it ends first; likewise for launches in which no tile can be split (few tiles, or a dq that is strided or shares memory).
+// Its step counts as 1.75 of the other's (head_dim 64: 1.6), the start of a workgroup as 7 of its steps (6); where c or m is no
+// power of two its rows cost divisions (a fifth), and where c neither divides a tile of 32 rows nor is divided by it the other
+// kernel works every tile's rows out anew, once for the heads of the group (0.4 of a step).  Dense causal text with no more tiles
+// than places, none of them split, is the 64-row kernel's, too: its tiles' lengths run from one block to the whole text, and the
+// long ones share their units with others for most of their time (4096 tokens, 16/16 heads 273 / 291).  Whole backward pass, us, 64-row /
+// 32-row kernel: window 1024 over 2048 tokens, 16/4 heads, d 64 115 / 141, 8/1 heads, d 128 162 / 186; paper's form 2048 tokens
+// 16/4 heads 211 / 226, dense causal 4096 tokens 358 / 379; 8192 tokens in chunks, gradients packed into one tensor, 32/8
+// heads 1049 / 1168, d 64 703 / 856; but chunks of 64, 1000 tokens, 16/16 heads 84 / 70, 2 x 4096, 32/8 347 / 292, 20003 in the
+// paper's form 1460 / 1318.  Over 848 layouts, each dense and packed (200 - 32K tokens, ten chunk shapes, of one to eight heads
+// per KV head), the choice costs 0.1 % against the better kernel of each, 5.7 % at most.
 constexpr int64_t DKV_STEPS_PER_START = 8, DKV_STEPS_OF_SUMS = 12, DKV_MIN_STEPS = 16;
 void build_dkv(ksa_layout &lay) {
     const ksa_params &p = lay.p;
-    const int64_t n_sum = (int64_t)lay.n_chunks * p.n_summary, group = p.n_q_heads / p.n_kv_heads;
-    const int64_t n_bh = (int64_t)p.batch * p.n_kv_heads;
-    const int64_t sum_tiles = (n_sum + KSA_DKV_KEYS - 1) / KSA_DKV_KEYS, text_tiles = (p.n_text + KSA_DKV_KEYS - 1) / KSA_DKV_KEYS;
-    std::vector<int64_t> steps(sum_tiles + text_tiles);
-    int64_t total = 0, longest_tile = 0;
-    for (int64_t t = 0; t < sum_tiles + text_tiles; ++t) {
-        const int space = t < sum_tiles ? KSA_SPACE_SUMMARY : KSA_SPACE_TEXT;
-        const int64_t k0 = (t < sum_tiles ? t : t - sum_tiles) * KSA_DKV_KEYS, n = t < sum_tiles ? n_sum : p.n_text;
-        steps[t] = dkv_blocks(p, space, k0, std::min<int64_t>(k0 + KSA_DKV_KEYS, n)) * group;
-        total += steps[t], longest_tile = std::max(longest_tile, steps[t]);
-    }
-    const int64_t capacity = (int64_t)p.batch * lay.aug_len * p.n_q_heads / 512 / n_bh;
-    const int64_t places = p.head_dim == 128 ? 512 : 768, mean = total * n_bh / places;
-    auto pieces_of = [&](int64_t t, int64_t most) { return steps[t] > most ? (steps[t] + most - 1) / most : 1; };
-    // where piece x of n begins: equal pieces, or pieces of `most` steps and what is left (which fits in where the equal ones of
-    // a launch of few tiles do not: dense causal 16K)
-    auto begin_of = [&](int64_t t, int64_t most, bool equal, int64_t x, int64_t n) { return equal ? steps[t] * x / n : std::min(x * most, steps[t]); };
-    std::vector<int64_t> lengths;
-    int64_t longest = longest_tile, best = INT64_MAX;
-    bool best_equal = true;
-    auto consider = [&](int64_t most, bool equal) {   // the launch with pieces of at most so many steps
-        int64_t slots = 0;
-        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) slots += steps[t] > most ? pieces_of(t, most) : 0;
+    DkvTiles tiles(p, KSA_DKV_ROWS, p.head_dim == 128 ? 512 : 768, DKV_STEPS_PER_START);
+    const int64_t n_bh = tiles.n_bh, capacity = (int64_t)p.batch * lay.aug_len * p.n_q_heads / 512 / n_bh;
+    int64_t most = tiles.longest, best = INT64_MAX, end = INT64_MAX;
+    bool equal = true;
+    auto consider = [&](int64_t most_, bool equal_) {   // the launch with pieces of at most so many steps
+        const int64_t slots = tiles.slots(most_);
         if (slots > capacity) return;
-        lengths.clear();
-        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) {
-            const int64_t n = pieces_of(t, most);
-            for (int64_t x = 0; x < n; ++x) lengths.push_back(begin_of(t, most, equal, x + 1, n) - begin_of(t, most, equal, x, n));
-        }
-        std::sort(lengths.begin(), lengths.end(), std::greater<int64_t>());
-        const int64_t sums = slots > 0 ? DKV_STEPS_OF_SUMS + slots * n_bh / 16 : 0;
-        // (when places come free, how many of them): the workgroups of all (batch, KV head) pairs are alike
-        using Free = std::pair<int64_t, int64_t>;
-        std::priority_queue<Free, std::vector<Free>, std::greater<Free>> places_free;
-        places_free.push({0, places});
-        int64_t end = 0;
-        for (const int64_t len : lengths)
-            for (int64_t left = n_bh; left > 0;) {
-                const Free f = places_free.top();
-                const int64_t n = std::min(left, f.second), at = f.first + len + DKV_STEPS_PER_START;
-                if (at + sums >= best) return;
-                places_free.pop();
-                if (n < f.second) places_free.push({f.first, f.second - n});
-                places_free.push({at, n});
-                end = std::max(end, at), left -= n;
-            }
-        best = end + sums, longest = most, best_equal = equal;
+        const int64_t sums = slots > 0 ? DKV_STEPS_OF_SUMS + slots * n_bh / 16 : 0, at = tiles.makespan(most_, equal_, best - sums);
+        if (at == INT64_MAX) return;
+        best = at + sums, end = at, most = most_, equal = equal_;
     };
-    consider(longest_tile, true);
-    if (longest_tile > mean / 8) {
-        const int64_t shortest = std::max(DKV_MIN_STEPS, mean / 8);
+    consider(tiles.longest, true);
+    if (tiles.longest > tiles.mean / 8) {
+        const int64_t shortest = std::max(DKV_MIN_STEPS, tiles.mean / 8);
         for (int64_t quarters = 2; quarters <= 6; ++quarters)
-            if (mean * quarters / 4 >= DKV_MIN_STEPS && mean * quarters / 4 < longest_tile) consider(mean * quarters / 4, false);
+            if (tiles.mean * quarters / 4 >= DKV_MIN_STEPS && tiles.mean * quarters / 4 < tiles.longest) consider(tiles.mean * quarters / 4, false);
         // (no better than 2 % above the mean is worth looking for)
-        for (int64_t quarters = 5; longest_tile * 4 / quarters >= shortest && best * 50 > (mean + DKV_STEPS_PER_START) * 51; quarters += quarters / 4)
-            consider(longest_tile * 4 / quarters, true);
+        for (int64_t quarters = 5; tiles.longest * 4 / quarters >= shortest && best * 50 > (tiles.mean + DKV_STEPS_PER_START) * 51; quarters += quarters / 4)
+            consider(tiles.longest * 4 / quarters, true);
     }
-    for (int64_t t = 0; t < (int64_t)steps.size(); ++t) {
-        const int64_t pieces = pieces_of(t, longest);
+
+    const bool d128 = p.head_dim == 128;
+    DkvTiles wide(p, KSA_K_TILE, 256, d128 ? 7 : 6);
+    int64_t wide_most = std::max<int64_t>(32, wide.mean);
+    while (wide.slots(wide_most) > capacity) wide_most *= 2;   // (0 once no tile is longer)
+    auto divides = [](int64_t x, int64_t y) { return x % y == 0 || y % x == 0; };
+    const bool pow2 = (p.chunk_len & (p.chunk_len - 1)) == 0 && (p.n_summary & (p.n_summary - 1)) == 0;
+    const double wide_step = (d128 ? 1.75 : 1.6) * (pow2 ? 1. : 1.2);
+    const double step = 1. + (divides(p.chunk_len, KSA_DKV_ROWS) ? 0. : 0.4 * p.n_kv_heads / p.n_q_heads);
+    const bool dense = p.n_summary == 0 && p.window_chunks >= (p.n_text - 1) / p.chunk_len && (int64_t)tiles.steps.size() * n_bh <= tiles.places;
+    lay.dkv_unsplit_direct = !dense && wide.unsplit() * wide_step >= tiles.unsplit() * step;
+    lay.dkv_direct = !(dense && tiles.slots(most) == 0) &&
+                     wide.makespan(wide_most, true, end) * wide_step >= end * step;   // (its steps are longer: no need to look behind `end` of them)
+    if (!lay.dkv_direct) tiles = std::move(wide), most = wide_most, equal = true;
+
+    for (int64_t t = 0; t < (int64_t)tiles.steps.size(); ++t) {
+        const int64_t pieces = tiles.pieces(t, most);
         if (pieces > 1) lay.dkv_splits.push_back({(int32_t)t, lay.dkv_slots, (int32_t)pieces, 0});
         for (int64_t x = 0; x < pieces; ++x)
-            lay.dkv_entries.push_back({(int32_t)t, (int32_t)begin_of(t, longest, best_equal, x, pieces), (int32_t)begin_of(t, longest, best_equal, x + 1, pieces),
+            lay.dkv_entries.push_back({(int32_t)t, (int32_t)tiles.begin(t, most, equal, x, pieces), (int32_t)tiles.begin(t, most, equal, x + 1, pieces),
                                        pieces > 1 ? lay.dkv_slots++ : -1});
     }
     std::stable_sort(lay.dkv_entries.begin(), lay.dkv_entries.end(), [](const KsaDkvEntry &a, const KsaDkvEntry &b) {
         return a.step_end - a.step_begin > b.step_end - b.step_begin;
     });
-    // The kernel that works on the scores of 64 rows at a time (ksa_prefill_bwd.hip) is left with launches whose time is that of
-    // their longest workgroup: dense causal text of few tiles none of which could be split (one query head per KV head: dq holds
-    // one partial sum per 512 rows).  A workgroup alone on its compute unit takes 0.9 us per 32 rows there, 1.1 here.  16/16
-    // heads, d 128, there / here: 1024 tokens 68 / 71 us, 2048 120 / 128, 4096 269 / 285 (d 64: 82 / 98, 168 / 192); from two tiles
-    // per place on it is behind: 8192 888 / 870, 2 x 4096 490 / 470; a window of 1024 over 3000 tokens 137 / 111.
-    const bool dense = p.n_summary == 0 && p.window_chunks >= (p.n_text - 1) / p.chunk_len;
-    lay.dkv_direct = !(dense && lay.dkv_splits.empty() && text_tiles * n_bh <= places);
+    if (lay.dkv_splits.empty()) lay.dkv_unsplit_direct = lay.dkv_direct;
 }
 
 }  // namespace

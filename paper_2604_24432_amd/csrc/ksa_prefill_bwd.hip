@@ -11,10 +11,11 @@
 //                         text, no summaries, head_dim 128; other layouts take ksa_bwd_dq_direct_kernel,
 //                         ksa_prefill_direct.hip);
 //   ksa_bwd_dkv_kernel    one workgroup per 128-key tile of an index space walks the query rows that can see it
-//                         (two runs, closed form from Eq. 3), for every query head of the KV head's group (dense causal
-//                         text of few tiles; other layouts take ksa_bwd_dkv_direct_kernel, ksa_prefill_bwd_dkv.hip, where
-//                         several workgroups may share a long tile and ksa_bwd_dkv_sum_kernel, ksa_prefill_bwd_sum.hip,
-//                         adds up their fp32 partial sums: see build_dkv in ksa_layout.cpp).
+//                         (two runs, closed form from Eq. 3), for every query head of the KV head's group; where that
+//                         would leave the chip waiting for a few long tiles, several workgroups share a tile and
+//                         ksa_bwd_dkv_sum_kernel (ksa_prefill_bwd_sum.hip) adds up their fp32 partial sums.  Launches whose
+//                         time is that of their longest workgroup; others take ksa_bwd_dkv_direct_kernel
+//                         (ksa_prefill_bwd_dkv.hip): see build_dkv in ksa_layout.cpp.
 // Both main kernels recompute the scores with v_mfma_f32_32x32x16_bf16 and keep the result block in the layout
 // whose registers are the B operand of the next product: dQ works on S^T (keys x queries, the forward kernel's
 // layout, per-lane query statistics), dK/dV on S (queries x keys, per-lane key, per-register query statistics
@@ -59,6 +60,8 @@ struct BwdArgs {
     int32_t stack, stack_shift;    // dQ kernel: query heads per workgroup of the forward schedule (1, 2 or 4), its log2
     int32_t n_text, n_sum;                    // rows per index space
     int32_t sum_tiles;                        // dK/dV: summary-space key tiles come first in the numbering
+    const KsaDkvEntry *dkv_entries;           // dK/dV: what the workgroups of a (batch, KV head) do
+    float *scratch;                           // partial sums (the memory of dq, which is written last); NULL: no tile is split
     int64_t aug_len;
     float scale, scale_log2e;
 };
@@ -517,12 +520,18 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
 
     // Workgroup index -> (entry, batch, KV head), the head running fastest: consecutive workgroup ids go to the
     // XCDs round-robin, so with 8 (batch, KV head) pairs all key tiles of a head share one L2, and they walk the same
-    // query rows at about the same time (see the loop order below).  The tiles follow in their numbering: summary-space
+    // query rows at about the same time (see the loop order below).  An entry is a key tile or, where tiles are split, a
+    // piece of its sequence of steps; longest first.  Without a list the tiles follow in their numbering: summary-space
     // tiles first, oldest chunks first, whose runs of query rows are the long ones.
     const int n_bh = a.n_kv_heads * a.batch;
     const int bh = blockIdx.x % n_bh;
     const int hkv = bh % a.n_kv_heads, b = bh / a.n_kv_heads;
     int t = blockIdx.x / n_bh, space = KSA_SPACE_SUMMARY;
+    int step_begin = 0, step_end = 0x7fffffff, slot = -1;
+    if (a.scratch) {
+        const KsaDkvEntry ent = a.dkv_entries[t];
+        t = ent.tile, step_begin = ent.step_begin, step_end = ent.step_end, slot = ent.slot;
+    }
     if (t >= a.sum_tiles) t -= a.sum_tiles, space = KSA_SPACE_TEXT;
     const int n_space = space == KSA_SPACE_TEXT ? a.n_text : a.n_sum;
     const int k0 = t * KEYS_PER_WG;
@@ -583,7 +592,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
         run_tiles[x] = run_end[x] > run_begin[x] ? (run_end[x] - 1) / BN - run_first_blk[x] + 1 : 0;
     }
     // > 0: a key is seen by its own row at least
-    const int n_tiles = (run_tiles[0] + run_tiles[1]) * a.group;
+    const int n_tiles = min((run_tiles[0] + run_tiles[1]) * a.group, step_end) - step_begin;
     // Blocks [full_lo_blk, full_hi_blk) of a run (counted from the run's first block) are seen whole: no row of such
     // a block lies outside the run, and every row sees every key of the workgroup.  Visible ranges are monotone in
     // the row index (Eq. 3: both ends of a row's range never move backwards from one row to the next), so these
@@ -636,7 +645,9 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
     const unsigned q_row_elems = (unsigned)a.qs[1], g_row_elems = (unsigned)a.os[1];
     const unsigned q_head_elems = (unsigned)a.qs[2], g_head_elems = (unsigned)a.os[2];
     // the next tile of the sequence; stays on the last tile once the sequence is exhausted
-    int sq_run = run_tiles[0] > 0 ? 0 : 1, sq_ti = 0, sq_hj = 0;
+    const int steps0 = run_tiles[0] * a.group;   // steps of the text run
+    int sq_run = step_begin < steps0 ? 0 : 1;
+    int sq_ti = (step_begin - (sq_run ? steps0 : 0)) / a.group, sq_hj = step_begin - (sq_run ? steps0 : 0) - sq_ti * a.group;
     struct Request {
         const __bf16 *q_base, *g_base;   // row `first` of the tile (scalar)
         const float *lse_p, *dl_p;       // statistics of row `first` (scalar)
@@ -918,6 +929,19 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
     // nothing of this workgroup is in flight any more when it leaves (the last requests fetched tiles nobody reads)
     __builtin_amdgcn_s_waitcnt(0x0F70);
     accumulators_settle();
+    if (slot >= 0) {   // a piece: the partial sums as they sit in the registers, one 16-byte store per lane and four of them
+        f32x4 *out = reinterpret_cast<f32x4 *>(a.scratch) + ((int64_t)slot * n_bh + bh) * (KEYS_PER_WG * D / 2) + wave * (D * 16) + lane;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                f32x4 xk, xv;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xk[e] = dkacc[db][g4 * 4 + e], xv[e] = dvacc[db][g4 * 4 + e];
+                out[(db * 4 + g4) * 128] = xk, out[(db * 4 + g4) * 128 + 64] = xv;
+            }
+        return;
+    }
     if (!key_valid) return;
     __bf16 *kp = a.dk + b * a.dks[0] + (int64_t)key_aug * a.dks[1] + hkv * a.dks[2];
     __bf16 *vp = a.dv + b * a.dks[0] + (int64_t)key_aug * a.dks[1] + hkv * a.dks[2];
@@ -936,18 +960,18 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
         }
 }
 
-// scratch: the memory of dq, which is written last, for the partial sums of split dK / dV tiles; NULL: no tile is split
 template <int D, bool POW2>
-int launch_dkv(const KsaPrefillBwdLaunch &L, const BwdArgs &a, float *scratch, hipStream_t st) {
-    const int n_bh = a.n_kv_heads * a.batch, tiles = a.sum_tiles + (a.n_text + KEYS_PER_WG - 1) / KEYS_PER_WG;
-    if (!L.dkv_direct) {
-        hipLaunchKernelGGL((ksa_bwd_dkv_kernel<D, POW2>), dim3((unsigned)(tiles * n_bh)), dim3(NW * 64), 0, st, a);
-        return KSA_OK;
+int launch_dkv(const KsaPrefillBwdLaunch &L, const BwdArgs &a, hipStream_t st) {
+    const int n_bh = a.n_kv_heads * a.batch;
+    const int entries = a.scratch ? L.n_dkv_entries : a.sum_tiles + (a.n_text + KEYS_PER_WG - 1) / KEYS_PER_WG;
+    if (a.scratch ? L.dkv_direct : L.dkv_unsplit_direct) {
+        const int rc = ksa_launch_dkv_direct(L, a.stats, a.scratch, entries, st);
+        if (rc != KSA_OK) return rc;
+    } else {
+        hipLaunchKernelGGL((ksa_bwd_dkv_kernel<D, POW2>), dim3((unsigned)(entries * n_bh)), dim3(NW * 64), 0, st, a);
     }
-    const int rc = ksa_launch_dkv_direct(L, a.stats, scratch, scratch ? L.n_dkv_entries : tiles, st);
-    if (rc != KSA_OK) return rc;
-    if (scratch) {
-        const KsaDkvSumArgs sum = {scratch, L.dkv_splits, a.dk, a.dv, {a.dks[0], a.dks[1], a.dks[2]}, L.n_dkv_splits, a.sum_tiles,
+    if (a.scratch) {
+        const KsaDkvSumArgs sum = {a.scratch, L.dkv_splits, a.dk, a.dv, {a.dks[0], a.dks[1], a.dks[2]}, L.n_dkv_splits, a.sum_tiles,
                                    a.n_text, a.n_sum, a.c, a.m, a.n_kv_heads, n_bh, D, a.scale};
         ksa_launch_dkv_sum(sum, st);
     }
@@ -955,11 +979,11 @@ int launch_dkv(const KsaPrefillBwdLaunch &L, const BwdArgs &a, float *scratch, h
 }
 
 template <int D, bool POW2>
-int launch_all(const KsaPrefillBwdLaunch &L, const BwdArgs &a, int64_t n_rows, float *scratch, hipStream_t st) {
+int launch_all(const KsaPrefillBwdLaunch &L, const BwdArgs &a, int64_t n_rows, hipStream_t st) {
     const int64_t delta_blocks = (n_rows * (D / 8) + 255) / 256;
     hipLaunchKernelGGL(ksa_bwd_delta_kernel<D>, dim3((unsigned)delta_blocks), dim3(256), 0, st, a, n_rows);
     // with split key tiles dq holds their partial sums until it is written itself
-    int rc = scratch ? launch_dkv<D, POW2>(L, a, scratch, st) : KSA_OK;
+    int rc = a.scratch ? launch_dkv<D, POW2>(L, a, st) : KSA_OK;
     if (rc != KSA_OK) return rc;
     if (L.dq_direct) {
         rc = ksa_launch_dq_direct(L, a.stats, st);
@@ -969,7 +993,7 @@ int launch_all(const KsaPrefillBwdLaunch &L, const BwdArgs &a, int64_t n_rows, f
     } else {
         return KSA_ERR_UNSUPPORTED;   // (no such layout: dq_takes_direct())
     }
-    return scratch ? KSA_OK : launch_dkv<D, POW2>(L, a, nullptr, st);
+    return a.scratch ? KSA_OK : launch_dkv<D, POW2>(L, a, st);
 }
 
 }  // namespace
@@ -1054,7 +1078,7 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
     // The partial sums of split key tiles live in the memory of dq until dq is written: a dense dq that shares no byte with
     // the other tensors.  dK and dV are then written first, so they have to be apart from K and V, which dQ still reads.  (A
     // caller may hand over tensors that do share memory: dq is then written before dK and dV, and no tile is split.)
-    float *scratch = nullptr;
+    a.scratch = nullptr, a.dkv_entries = L.dkv_entries;
     if (L.n_dkv_splits > 0) {
         const int64_t B = L.p.batch, Hq = a.n_q_heads, Hkv = a.n_kv_heads, d = L.p.head_dim, rows = L.aug_len;
         const bool dense = a.dqs[2] == d && a.dqs[1] == Hq * d && (B == 1 || a.dqs[0] == rows * Hq * d);
@@ -1067,13 +1091,13 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
             ok = ok && apart_dq(in, kv_bytes);
             for (const void *out : {(const void *)a.dk, (const void *)a.dv}) ok = ok && apart_dq(out, dkv_bytes) && ksa_apart(out, dkv_bytes, in, kv_bytes);
         }
-        if (ok) scratch = reinterpret_cast<float *>(a.dq);
+        if (ok) a.scratch = reinterpret_cast<float *>(a.dq);
     }
     int rc;
     if (L.p.head_dim == 128)
-        rc = pow2 ? launch_all<128, true>(L, a, n_rows, scratch, st) : launch_all<128, false>(L, a, n_rows, scratch, st);
+        rc = pow2 ? launch_all<128, true>(L, a, n_rows, st) : launch_all<128, false>(L, a, n_rows, st);
     else
-        rc = pow2 ? launch_all<64, true>(L, a, n_rows, scratch, st) : launch_all<64, false>(L, a, n_rows, scratch, st);
+        rc = pow2 ? launch_all<64, true>(L, a, n_rows, st) : launch_all<64, false>(L, a, n_rows, st);
     if (rc != KSA_OK) return rc;
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
 }

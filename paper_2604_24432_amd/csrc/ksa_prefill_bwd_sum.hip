@@ -1,5 +1,5 @@
 // KSA prefill backward, split dK / dV key tiles: adds up the fp32 partial sums that the pieces of a tile left behind
-// (ksa_bwd_dkv_direct_kernel) in the order of the pieces and stores dK and dV.
+// (ksa_bwd_dkv_kernel, ksa_bwd_dkv_direct_kernel) in the order of the pieces and stores dK and dV.
 // Bound by memory: 2 x 4096 tokens, 32/8 heads, d 128 read 19 MB of partial sums.  The records are laid out as the pieces'
 // registers sit in their lanes (16 bytes per lane, 1 KiB per wavefront access), so both sides move whole lines; a
 // workgroup takes one 32-column block of a tile, which gives the few split tiles enough workgroups.

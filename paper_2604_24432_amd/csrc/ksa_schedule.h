@@ -43,8 +43,8 @@ struct KsaWorkItem {
 };
 
 // Backward dK / dV: keys per workgroup, and what the workgroups of one (batch, KV head) do.  A key tile's work is a
-// sequence of steps (one tile of KSA_DKV_ROWS query rows of one query head each, see ksa_bwd_dkv_direct_kernel).  Tiles of the
-// summary space come first in the numbering.
+// sequence of steps (one tile of KSA_DKV_ROWS query rows of one query head each, see ksa_bwd_dkv_direct_kernel; or of
+// KSA_K_TILE rows: ksa_bwd_dkv_kernel).  Tiles of the summary space come first in the numbering.
 #define KSA_DKV_KEYS 128
 #define KSA_DKV_ROWS 32
 struct KsaDkvEntry {

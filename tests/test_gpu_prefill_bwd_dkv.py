@@ -47,6 +47,34 @@ def test_against_oracle(shape, self_only):
         assert rel <= 5e-3, name
 
 
+# launches that the kernel with 64-row blocks takes, with split tiles
+WIDE = [(1, 8, 1, 64, 700, 1, 0, 400), (1, 3, 1, 128, 1060, 100, 4, 4), (1, 8, 1, 64, 536, 48, 6, 1), (2, 3, 1, 64, 585, 8, 1, 60),
+        (2, 3, 1, 128, 1146, 64, 8, 4), (2, 8, 1, 64, 640, 1, 0, 500)]
+
+
+@pytest.mark.parametrize("packed", [False, True], ids=["dense", "packed"])
+@pytest.mark.parametrize("self_only", [0, 1])
+@pytest.mark.parametrize("shape", WIDE + [(1, 8, 2, 128, 1300, 64, 8, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_split_tiles_of_64_row_blocks_and_packed_gradients(shape, self_only, packed):
+    """packed: gradients in one tensor, whose dq cannot hold partial sums, so that no tile is split."""
+    if self_only and shape[6] < 2:
+        pytest.skip("one summary per chunk")
+    cfg, lay, q, k, v, g = run(shape, K.KSA_FLAG_SUMMARY_SELF_ONLY if self_only else 0)
+    o, lse = K.ksa_prefill_fwd(lay, q, k, v)
+    Hq, Hkv = shape[1], shape[2]
+    out = {}
+    if packed:
+        both = torch.empty((shape[0], q.shape[1], Hq + 2 * Hkv, shape[3]), dtype=torch.bfloat16, device="cuda")
+        out = dict(dq=both[:, :, :Hq], dk=both[:, :, Hq:Hq + Hkv], dv=both[:, :, Hq + Hkv:])
+    got = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g, **out)
+    ref = O.prefill_bwd(*(x.float().cpu().numpy() for x in (q, k, v, g)), cfg.n_text, cfg.chunk_len, cfg.n_summary,
+                        cfg.window_chunks, flags=self_only)
+    for name, x, r in zip(("dq", "dk", "dv"), got, ref):
+        rel = np.linalg.norm(x.float().cpu().numpy() - r) / np.linalg.norm(r)   # bound: see test_against_oracle
+        print(f"{shape} {name}: relative error {rel:.2e}", flush=True)
+        assert rel <= 5e-3, name
+
+
 @pytest.mark.parametrize("value", [math.nan, -math.inf, math.inf])
 @pytest.mark.parametrize("shape", [(1, 2, 1, 128, 353, 64, 8, 1), (1, 2, 2, 64, 383, 1, 0, 70)], ids=["chunks", "window"])
 def test_log_sum_exp_that_is_no_number(shape, value):
