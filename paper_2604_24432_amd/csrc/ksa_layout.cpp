@@ -70,8 +70,8 @@ KsaWorkItem text_item(const ksa_params &p, int64_t t0, int32_t cnt) {
     it.q_space = KSA_SPACE_TEXT;
     it.q_begin = (int32_t)t0;
     it.q_count = cnt;
-    const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = p.n_text / c * m;
-    const int64_t j0 = t0 / c, j1 = (t0 + cnt - 1) / c;
+    const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = (int64_t)(p.n_text / p.chunk_len) * m;
+    const int32_t j0 = (int32_t)t0 / p.chunk_len, j1 = (int32_t)(t0 + cnt - 1) / p.chunk_len;
     // distant summaries: the first row's chunk sees the fewest (those every row sees), the last row's chunk the most
     if (m > 0) push_segment(it, KSA_SPACE_SUMMARY, 0, pos_part(j1 - C) * m, 0, pos_part(j0 - C) * m, n_sum);
     // sliding-chunk text: [lo_first, ...) is seen by the first row's chunk, [lo_last, t0) by every row
@@ -87,11 +87,28 @@ KsaWorkItem summary_item(const ksa_params &p, int64_t u0, int32_t cnt) {
     it.q_space = KSA_SPACE_SUMMARY;
     it.q_begin = (int32_t)u0;
     it.q_count = cnt;
-    const int64_t c = p.chunk_len, m = p.n_summary, n_sum = p.n_text / c * m;
-    const int64_t j0 = u0 / m, j1 = (u0 + cnt - 1) / m;
+    const int64_t c = p.chunk_len, m = p.n_summary, n_sum = (int64_t)(p.n_text / p.chunk_len) * m;
+    const int64_t j0 = (int32_t)u0 / p.n_summary, j1 = (int32_t)(u0 + cnt - 1) / p.n_summary;
     push_segment(it, KSA_SPACE_TEXT, j0 * c, (j1 + 1) * c, 0, 0, p.n_text);
     push_segment(it, KSA_SPACE_SUMMARY, j0 * m, u0 + cnt, 0, 0, n_sum);
     return it;
+}
+
+// Items in the order of their key tiles, most first, equal ones as they were.  (A counting sort: an item has at most four key
+// tiles per item of the layout, and a few.)
+void heaviest_first(std::vector<KsaWorkItem> &items) {
+    int32_t most = 0;
+    for (const KsaWorkItem &it : items) most = std::max(most, it.n_tiles);
+    std::vector<int32_t> at(most + 2, 0);   // at[most - n]: where the next item of n tiles goes
+    for (const KsaWorkItem &it : items) ++at[most - it.n_tiles + 1];
+    for (int32_t x = 0; x < most; ++x) at[x + 1] += at[x];
+    std::vector<int32_t> to(items.size());
+    for (size_t x = 0; x < items.size(); ++x) to[x] = at[most - items[x].n_tiles]++;
+    for (int32_t x = 0; x < (int32_t)items.size(); ++x)
+        while (to[x] != x) {
+            const int32_t y = to[x];
+            std::swap(items[x], items[y]), std::swap(to[x], to[y]);
+        }
 }
 
 // Which of the two forward kernels a layout takes: true = ksa_prefill_direct.hip.
@@ -147,103 +164,142 @@ void build_entries(ksa_layout &lay) {
     const int32_t n_items = (int32_t)lay.items.size();
     const int32_t n_groups = p.batch * p.n_kv_heads;
     const int32_t gsz = p.n_q_heads / p.n_kv_heads;
-    std::vector<std::vector<KsaWgEntry>> queue(KSA_NUM_XCD);
-    auto emit = [&](int q, int32_t item, int32_t grp) {
-        for (int32_t x = 0; x < gsz; x += lay.head_stack) {
-            KsaWgEntry e;
-            e.item = item;
-            e.batch = grp / p.n_kv_heads;
-            e.q_head = (grp % p.n_kv_heads) * gsz + x;
-            e.pad = 0;
-            queue[q].push_back(e);
-        }
+    // entry x of queue q is workgroup x * KSA_NUM_XCD + q
+    auto fill = [&](int q, int32_t first_item, int32_t item_step, int32_t first_grp, int32_t grp_step) {
+        size_t at = q;
+        for (int32_t it = first_item; it < n_items; it += item_step)
+            for (int32_t grp = first_grp; grp < n_groups; grp += grp_step) {
+                const int32_t b = grp / p.n_kv_heads, head = (grp - b * p.n_kv_heads) * gsz;
+                for (int32_t x = 0; x < gsz; x += lay.head_stack, at += KSA_NUM_XCD) lay.entries[at] = {it, b, head + x, 0};
+            }
     };
-    if (n_groups >= KSA_NUM_XCD) {
-        for (int q = 0; q < KSA_NUM_XCD; ++q)
-            for (int32_t it = 0; it < n_items; ++it)
-                for (int32_t grp = q; grp < n_groups; grp += KSA_NUM_XCD) emit(q, it, grp);
-    } else {
-        // fewer groups than XCDs: the queues congruent to grp mod n_groups share the items of group grp
-        for (int q = 0; q < KSA_NUM_XCD; ++q) {
+    auto chunks = [](int64_t x, int64_t per) { return (x + per - 1) / per; };
+    // (the first queue is the longest: it has the most groups, or the fewest to share its own with)
+    const int64_t sharers0 = n_groups >= KSA_NUM_XCD ? 1 : chunks(KSA_NUM_XCD, n_groups), last = std::min(n_groups, KSA_NUM_XCD) - 1;
+    const int64_t per_queue = n_groups >= KSA_NUM_XCD ? n_items * chunks(n_groups, KSA_NUM_XCD) : chunks(n_items, std::min(sharers0, chunks(KSA_NUM_XCD - last, n_groups)));
+    lay.entries.resize((size_t)(per_queue * (gsz / lay.head_stack) * KSA_NUM_XCD), KsaWgEntry{-1, 0, 0, 0});
+    for (int q = 0; q < KSA_NUM_XCD; ++q) {
+        if (n_groups >= KSA_NUM_XCD) {
+            fill(q, 0, 1, q, KSA_NUM_XCD);
+        } else {
+            // fewer groups than XCDs: the queues congruent to grp mod n_groups share the items of group grp
             const int32_t grp = q % n_groups;
             const int32_t sharers = (KSA_NUM_XCD - grp + n_groups - 1) / n_groups;  // queues serving grp
-            const int32_t rank = q / n_groups;
-            for (int32_t it = rank; it < n_items; it += sharers) emit(q, it, grp);
+            fill(q, q / n_groups, sharers, grp, n_groups);
         }
     }
-    size_t longest = 0;
-    for (auto &qv : queue) longest = std::max(longest, qv.size());
-    lay.entries.resize(longest * KSA_NUM_XCD, KsaWgEntry{-1, 0, 0, 0});
-    for (int q = 0; q < KSA_NUM_XCD; ++q)
-        for (size_t x = 0; x < queue[q].size(); ++x) lay.entries[x * KSA_NUM_XCD + q] = queue[q][x];
 }
 
-// Steps of the dK / dV work of the keys [k0, k1) of an index space, per query head: the aligned blocks of `rows` query rows that
-// overlap the two runs of rows that can see one of them.  The kernels work the same runs out; the one with 64-row blocks counts
-// all summary rows of the keys' chunks whatever the self-only flag says.
-int64_t dkv_blocks(const ksa_params &p, int64_t rows, int space, int64_t k0, int64_t k1) {
-    const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = (int64_t)(p.n_text / c) * m;
-    const int64_t per = space == KSA_SPACE_TEXT ? c : m, jl = k0 / per, jh = (k1 - 1) / per;
-    const int64_t b0 = space == KSA_SPACE_TEXT ? k0 : std::min<int64_t>((jl + C + 1) * c, p.n_text);
-    const int64_t e0 = space == KSA_SPACE_TEXT ? std::min<int64_t>((jh + C + 1) * c, p.n_text) : p.n_text;
-    const bool self_only = rows == KSA_DKV_ROWS && space == KSA_SPACE_SUMMARY && (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY);
-    const int64_t b1 = space == KSA_SPACE_TEXT ? jl * m : k0, e1 = self_only ? k1 : std::min<int64_t>((jh + 1) * m, n_sum);
-    auto blocks = [&](int64_t b, int64_t e) { return e > b ? (e - 1) / rows - b / rows + 1 : 0; };
-    return blocks(b0, e0) + blocks(b1, e1);
-}
-
-// The dK / dV key tiles of one (batch, KV head) for the kernel with query tiles of `rows` rows, and a launch of them.
+// The dK / dV key tiles of one (batch, KV head) for a kernel that walks query rows in aligned blocks, and a launch of them.
 struct DkvTiles {
-    int64_t rows, places, start;     // workgroups that the chip holds at once; what starting and ending one costs, in steps
-    std::vector<int64_t> steps;      // per tile, the summary-space ones first
-    int64_t total = 0, longest = 0, n_bh, mean;   // (mean: steps per place of the whole launch)
+    const int64_t places, start;     // workgroups that the chip holds at once; what starting and ending one costs, in steps
+    std::vector<int32_t> steps;      // per tile, the summary-space ones first: blocks times query heads per KV head
+    struct Run {
+        int64_t steps, count;
+        bool operator<(const Run &x) const { return steps > x.steps; }   // longest first
+    };
+    std::vector<Run> runs;           // tiles of equal length
+    int64_t total = 0, longest = 0, n_bh = 1, mean = 0;   // (mean: steps per place of the whole launch)
+    DkvTiles(int64_t places_, int64_t start_) : places(places_), start(start_) {}
 
-    DkvTiles(const ksa_params &p, int64_t rows_, int64_t places_, int64_t start_) : rows(rows_), places(places_), start(start_) {
-        const int64_t n_sum = (int64_t)(p.n_text / p.chunk_len) * p.n_summary, group = p.n_q_heads / p.n_kv_heads;
-        for (const int space : {KSA_SPACE_SUMMARY, KSA_SPACE_TEXT}) {
-            const int64_t n = space == KSA_SPACE_SUMMARY ? n_sum : p.n_text;
-            for (int64_t k0 = 0; k0 < n; k0 += KSA_DKV_KEYS)
-                steps.push_back(dkv_blocks(p, rows, space, k0, std::min<int64_t>(k0 + KSA_DKV_KEYS, n)) * group);
+    static void merge(std::vector<Run> &x) {   // equal lengths in one
+        std::sort(x.begin(), x.end());
+        size_t n = 0;
+        for (const Run &r : x) {
+            if (n > 0 && x[n - 1].steps == r.steps) x[n - 1].count += r.count; else x[n++] = r;
         }
-        for (const int64_t x : steps) total += x, longest = std::max(longest, x);
-        n_bh = (int64_t)p.batch * p.n_kv_heads, mean = total * n_bh / places;
+        x.resize(n);
     }
-    int64_t pieces(int64_t t, int64_t most) const { return steps[t] > most ? (steps[t] + most - 1) / most : 1; }
-    // where piece x of n begins: equal pieces, or pieces of `most` steps and what is left
-    int64_t begin(int64_t t, int64_t most, bool equal, int64_t x, int64_t n) const { return equal ? steps[t] * x / n : std::min(x * most, steps[t]); }
-    int64_t slots(int64_t most) const {   // partial sums with pieces of at most so many steps
-        int64_t n = 0;
-        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) n += steps[t] > most ? pieces(t, most) : 0;
-        return n;
+    void add(int64_t blocks, int64_t group) {
+        const int64_t x = blocks * group;
+        steps.push_back((int32_t)x), total += x;
+        if (runs.empty() || runs.back().steps != x) runs.push_back({x, 0});
+        ++runs.back().count;
     }
-    // When the last workgroup ends if they start in the order of their lengths, longest first; INT64_MAX if not before `limit`.
-    int64_t makespan(int64_t most, bool equal, int64_t limit) const {
-        std::vector<int64_t> lengths;
-        for (int64_t t = 0; t < (int64_t)steps.size(); ++t) {
-            const int64_t n = pieces(t, most);
-            for (int64_t x = 0; x < n; ++x) lengths.push_back(begin(t, most, equal, x + 1, n) - begin(t, most, equal, x, n));
-        }
-        std::sort(lengths.begin(), lengths.end(), std::greater<int64_t>());
-        // (when places come free, how many of them): the workgroups of all (batch, KV head) pairs are alike
-        using Free = std::pair<int64_t, int64_t>;
-        std::priority_queue<Free, std::vector<Free>, std::greater<Free>> places_free;
-        places_free.push({0, places});
-        int64_t end = 0;
-        for (const int64_t len : lengths)
-            for (int64_t left = n_bh; left > 0;) {
-                const Free f = places_free.top();
-                const int64_t n = std::min(left, f.second), at = f.first + len + start;
-                if (at >= limit) return INT64_MAX;
-                places_free.pop();
-                if (n < f.second) places_free.push({f.first, f.second - n});
-                places_free.push({at, n});
-                end = std::max(end, at), left -= n;
+    void complete(int64_t n_bh_) {
+        merge(runs);
+        longest = runs.front().steps, n_bh = n_bh_, mean = total * n_bh / places;
+    }
+    static int64_t pieces(int64_t x, int64_t most) { return x > most ? ((uint32_t)x - 1) / (uint32_t)most + 1 : 1; }   // (32-bit divisions: this is what the search spends its time on)
+    // A launch with pieces of at most so many steps: its workgroups and partial sums per (batch, KV head), its longest piece.
+    struct Pieces { int64_t jobs, slots, longest; };
+    Pieces cut(int64_t most, bool equal) const {
+        Pieces x = {(int64_t)steps.size(), 0, 0};
+        for (const Run &r : runs) {
+            if (r.steps <= most) {
+                x.longest = std::max(x.longest, r.steps);
+                break;
             }
-        return end;
+            const int64_t n = pieces(r.steps, most);
+            x.jobs += (n - 1) * r.count, x.slots += n * r.count, x.longest = std::max(x.longest, equal ? ((uint32_t)r.steps - 1) / (uint32_t)n + 1 : most);
+        }
+        return x;
+    }
+    // When its last workgroup ends if they start in the order of their lengths, longest first; INT64_MAX if not before `limit`.
+    int64_t makespan(const Pieces &cut, int64_t most, bool equal, int64_t limit) {
+        // no launch ends before the mean place or the longest workgroup does, and none that starts one as soon as a place is
+        // free after both
+        const int64_t busy = ((total + start * cut.jobs) * n_bh + places - 1) / places, most_ = cut.longest + start;
+        if (busy >= limit || most_ >= limit) return INT64_MAX;
+        lengths.clear();
+        size_t split = 0;
+        for (; split < runs.size() && runs[split].steps > most; ++split) {
+            const Run &r = runs[split];
+            const int64_t n = pieces(r.steps, most), len = equal ? (uint32_t)r.steps / (uint32_t)n : r.steps - (n - 1) * most, rest = equal ? r.steps - len * n : n - 1;
+            if (rest > 0) lengths.push_back({equal ? len + 1 : most, rest * r.count});   // the longer pieces
+            if (n > rest) lengths.push_back({len, (n - rest) * r.count});
+        }
+        lengths.insert(lengths.end(), runs.begin() + split, runs.end());
+        merge(lengths);
+        // (in coarser time each of a place's workgroups may end a unit later)
+        const int64_t unit = (busy + most_) / MAX_TIMES + 1, late = unit > 1 ? cut.jobs * n_bh / places + 1 : 0;
+        const int64_t end_by = std::min((busy + most_) / unit + late, limit / unit) + 1;
+        free_at.assign(end_by + 1, 0);   // how many places come free when (the workgroups of all (batch, KV head) pairs are alike)
+        free_at[0] = (int32_t)places;
+        int64_t t = 0, end = 0;
+        for (const Run &r : lengths) {
+            const int64_t len = std::max<int64_t>((r.steps + start + unit / 2) / unit, 1);
+            for (int64_t left = r.count * n_bh; left > 0;) {
+                while (free_at[t] == 0) ++t;
+                const int64_t n = std::min<int64_t>(left, free_at[t]), at = t + len;
+                if (at * unit >= limit || at > end_by) return INT64_MAX;
+                free_at[t] -= (int32_t)n, free_at[at] += (int32_t)n, left -= n, end = at > end ? at : end;
+            }
+        }
+        return end * unit;
     }
     // ... if no tile is split: the longest one, or as long as the mean place is busy
     int64_t unsplit() const { return std::max(longest + start, mean + start * (int64_t)steps.size() * n_bh / places); }
+
+private:
+    static constexpr int64_t MAX_TIMES = 1 << 22;   // longer launches (some millions of tokens) are played in coarser time
+    std::vector<Run> lengths;
+    std::vector<int32_t> free_at;
 };
+
+// Fills in the steps of both kernels' launches: per tile of keys [k0, k1) the blocks that overlap the two runs of query rows that
+// can see one of them.  The kernels work the same runs out; the one with 64-row blocks counts all summary rows of the keys' chunks
+// whatever the self-only flag says.
+void dkv_steps(const ksa_params &p, DkvTiles &tiles, DkvTiles &wide) {
+    const int64_t c = p.chunk_len, m = p.n_summary, C = p.window_chunks, n_sum = (int64_t)(p.n_text / c) * m, group = p.n_q_heads / p.n_kv_heads;
+    const bool self_only = p.flags & KSA_FLAG_SUMMARY_SELF_ONLY;
+    auto blocks = [](int64_t b, int64_t e, int shift) { return e > b ? ((e - 1) >> shift) - (b >> shift) + 1 : 0; };
+    constexpr int SHIFT = 5, WIDE_SHIFT = 6;
+    static_assert(KSA_DKV_ROWS == 1 << SHIFT && KSA_K_TILE == 1 << WIDE_SHIFT, "rows per block");
+    for (const int space : {KSA_SPACE_SUMMARY, KSA_SPACE_TEXT}) {
+        const int64_t n = space == KSA_SPACE_SUMMARY ? n_sum : p.n_text;
+        const uint32_t per = (uint32_t)(space == KSA_SPACE_TEXT ? c : m);
+        for (int64_t k0 = 0; k0 < n; k0 += KSA_DKV_KEYS) {
+            const int64_t k1 = std::min<int64_t>(k0 + KSA_DKV_KEYS, n), jl = (uint32_t)k0 / per, jh = (uint32_t)(k1 - 1) / per;
+            const int64_t b0 = space == KSA_SPACE_TEXT ? k0 : std::min<int64_t>((jl + C + 1) * c, p.n_text);
+            const int64_t e0 = space == KSA_SPACE_TEXT ? std::min<int64_t>((jh + C + 1) * c, p.n_text) : p.n_text;
+            const int64_t b1 = space == KSA_SPACE_TEXT ? jl * m : k0, e1 = std::min<int64_t>((jh + 1) * m, n_sum);
+            tiles.add(blocks(b0, e0, SHIFT) + blocks(b1, space == KSA_SPACE_SUMMARY && self_only ? k1 : e1, SHIFT), group);
+            wide.add(blocks(b0, e0, WIDE_SHIFT) + blocks(b1, e1, WIDE_SHIFT), group);
+        }
+    }
+    tiles.complete((int64_t)p.batch * p.n_kv_heads), wide.complete((int64_t)p.batch * p.n_kv_heads);
+}
 
 // The backward pass's dK / dV work of one (batch, KV head).  A summary key is seen by every later text row, so the first
 // tile of 128 of them is as long as hundreds of text tiles: a few workgroups would run long after the others have finished.
@@ -276,16 +332,19 @@ struct DkvTiles {
 constexpr int64_t DKV_STEPS_PER_START = 8, DKV_STEPS_OF_SUMS = 12, DKV_MIN_STEPS = 16;
 void build_dkv(ksa_layout &lay) {
     const ksa_params &p = lay.p;
-    DkvTiles tiles(p, KSA_DKV_ROWS, p.head_dim == 128 ? 512 : 768, DKV_STEPS_PER_START);
+    const bool d128 = p.head_dim == 128;
+    DkvTiles tiles(d128 ? 512 : 768, DKV_STEPS_PER_START), wide(256, d128 ? 7 : 6);
+    dkv_steps(p, tiles, wide);
     const int64_t n_bh = tiles.n_bh, capacity = (int64_t)p.batch * lay.aug_len * p.n_q_heads / 512 / n_bh;
     int64_t most = tiles.longest, best = INT64_MAX, end = INT64_MAX;
     bool equal = true;
+    DkvTiles::Pieces chosen = {};
     auto consider = [&](int64_t most_, bool equal_) {   // the launch with pieces of at most so many steps
-        const int64_t slots = tiles.slots(most_);
-        if (slots > capacity) return;
-        const int64_t sums = slots > 0 ? DKV_STEPS_OF_SUMS + slots * n_bh / 16 : 0, at = tiles.makespan(most_, equal_, best - sums);
+        const DkvTiles::Pieces cut = tiles.cut(most_, equal_);
+        if (cut.slots > capacity) return;
+        const int64_t sums = cut.slots > 0 ? DKV_STEPS_OF_SUMS + cut.slots * n_bh / 16 : 0, at = tiles.makespan(cut, most_, equal_, best - sums);
         if (at == INT64_MAX) return;
-        best = at + sums, end = at, most = most_, equal = equal_;
+        best = at + sums, end = at, most = most_, equal = equal_, chosen = cut;
     };
     consider(tiles.longest, true);
     if (tiles.longest > tiles.mean / 8) {
@@ -297,26 +356,29 @@ void build_dkv(ksa_layout &lay) {
             consider(tiles.longest * 4 / quarters, true);
     }
 
-    const bool d128 = p.head_dim == 128;
-    DkvTiles wide(p, KSA_K_TILE, 256, d128 ? 7 : 6);
     int64_t wide_most = std::max<int64_t>(32, wide.mean);
-    while (wide.slots(wide_most) > capacity) wide_most *= 2;   // (0 once no tile is longer)
+    DkvTiles::Pieces wide_cut = wide.cut(wide_most, true);
+    while (wide_cut.slots > capacity) wide_cut = wide.cut(wide_most *= 2, true);   // (0 once no tile is longer)
     auto divides = [](int64_t x, int64_t y) { return x % y == 0 || y % x == 0; };
     const bool pow2 = (p.chunk_len & (p.chunk_len - 1)) == 0 && (p.n_summary & (p.n_summary - 1)) == 0;
     const double wide_step = (d128 ? 1.75 : 1.6) * (pow2 ? 1. : 1.2);
     const double step = 1. + (divides(p.chunk_len, KSA_DKV_ROWS) ? 0. : 0.4 * p.n_kv_heads / p.n_q_heads);
     const bool dense = p.n_summary == 0 && p.window_chunks >= (p.n_text - 1) / p.chunk_len && (int64_t)tiles.steps.size() * n_bh <= tiles.places;
     lay.dkv_unsplit_direct = !dense && wide.unsplit() * wide_step >= tiles.unsplit() * step;
-    lay.dkv_direct = !(dense && tiles.slots(most) == 0) &&
-                     wide.makespan(wide_most, true, end) * wide_step >= end * step;   // (its steps are longer: no need to look behind `end` of them)
-    if (!lay.dkv_direct) tiles = std::move(wide), most = wide_most, equal = true;
-
-    for (int64_t t = 0; t < (int64_t)tiles.steps.size(); ++t) {
-        const int64_t pieces = tiles.pieces(t, most);
+    lay.dkv_direct = !(dense && chosen.slots == 0) &&
+                     wide.makespan(wide_cut, wide_most, true, end) * wide_step >= end * step;   // (its steps are longer: no need to look behind `end` of them)
+    if (!lay.dkv_direct) most = wide_most, equal = true, chosen = wide_cut;
+    lay.dkv_entries.reserve(chosen.jobs);
+    const std::vector<int32_t> &steps = (lay.dkv_direct ? tiles : wide).steps;
+    for (size_t t = 0; t < steps.size(); ++t) {
+        const int64_t pieces = DkvTiles::pieces(steps[t], most);
         if (pieces > 1) lay.dkv_splits.push_back({(int32_t)t, lay.dkv_slots, (int32_t)pieces, 0});
-        for (int64_t x = 0; x < pieces; ++x)
-            lay.dkv_entries.push_back({(int32_t)t, (int32_t)tiles.begin(t, most, equal, x, pieces), (int32_t)tiles.begin(t, most, equal, x + 1, pieces),
-                                       pieces > 1 ? lay.dkv_slots++ : -1});
+        int32_t at = 0;
+        for (int64_t x = 1; x <= pieces; ++x) {   // equal pieces, or pieces of `most` steps and what is left
+            const int32_t end = (int32_t)(equal ? steps[t] * x / pieces : std::min<int64_t>(x * most, steps[t]));
+            lay.dkv_entries.push_back({(int32_t)t, at, end, pieces > 1 ? lay.dkv_slots++ : -1});
+            at = end;
+        }
     }
     std::stable_sort(lay.dkv_entries.begin(), lay.dkv_entries.end(), [](const KsaDkvEntry &a, const KsaDkvEntry &b) {
         return a.step_end - a.step_begin > b.step_end - b.step_begin;
@@ -366,6 +428,7 @@ int ksa_build_layout(const ksa_params *params, ksa_layout **out) {
     static_assert(KSA_MAX_HEAD_STACK == 4, "head stacks are 1, 2 or 4");
     lay->q_tile_rows = KSA_Q_TILE / lay->head_stack;
     const int64_t qt = lay->q_tile_rows;
+    lay->items.reserve((p.n_text + qt - 1) / qt + ((int64_t)lay->n_chunks * p.n_summary + qt - 1) / qt);
     for (int64_t t0 = 0; t0 < p.n_text; t0 += qt)
         lay->items.push_back(text_item(p, t0, (int32_t)std::min<int64_t>(qt, p.n_text - t0)));
     const int64_t n_sum = (int64_t)lay->n_chunks * p.n_summary;
@@ -379,8 +442,7 @@ int ksa_build_layout(const ksa_params *params, ksa_layout **out) {
             lay->ragged |= g.begin + (int64_t)tiles_in(g) * KSA_K_TILE > (g.space == KSA_SPACE_TEXT ? (int64_t)p.n_text : n_sum);
         }
     }
-    std::stable_sort(lay->items.begin(), lay->items.end(),
-                     [](const KsaWorkItem &a, const KsaWorkItem &b) { return a.n_tiles > b.n_tiles; });
+    heaviest_first(lay->items);
     lay->direct = takes_direct(*lay);
     lay->dq_direct = dq_takes_direct(*lay);
     build_entries(*lay);

@@ -61,3 +61,20 @@ def test_pieces_are_the_steps_of_the_kernel(plan, shape, flags):
             want.append(blocks * (Hq // Hkv))
     assert got["steps"] == want
     assert got["slots"] <= B * mask.shape[0] * Hq // 512 // (B * Hkv)   # one partial sum (128 KiB per 128 x d) per 512 rows of dq
+
+
+@pytest.mark.parametrize("shape", [(1, 8, 1, 128, 131072, 64, 8, 1), (1, 8, 1, 64, 131072, 8, 1, 128)], ids=lambda s: "x".join(map(str, s)))
+def test_building_a_layout_stays_cheap(shape):
+    """Every caller pays for the plan, also one that only runs the forward pass.  0.2 - 0.25 ms on the machine where playing every
+    candidate launch through piece by piece took 1.9 - 2.1 ms; the bar leaves a slower one a factor of four."""
+    import time
+
+    import paper_2604_24432_amd as K
+    B, Hq, Hkv, d, n, c, m, C = shape
+    p, best = K.make_params(B, n, c, m, C, Hq, Hkv, d), 1.0
+    for _ in range(20):
+        t = time.perf_counter()
+        lay = K.ksa_build_layout(p)
+        best = min(best, time.perf_counter() - t)
+        del lay
+    assert best < 1e-3
