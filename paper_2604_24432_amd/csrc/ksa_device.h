@@ -47,7 +47,7 @@ __device__ __forceinline__ void lds_direct_load_16_s(const __bf16 *sbase, unsign
                  : "memory");
 }
 
-// Division of an index x in [0, 2^30) by a fixed d in [1, 2^30] as one multiplication: with 2^(s-1) < d <= 2^s the
+// Division of an index x in [0, 2^31) by a fixed d in [1, 2^31) as one multiplication: with 2^(s-1) < d <= 2^s the
 // quotient is (x * M) >> (31 + s), M = floor(2^(31 + s) / d) + 1 < 2^32 (Granlund and Montgomery: exact for x < 2^31,
 // because M d exceeds 2^(31 + s) by at most d <= 2^s).
 struct KsaDivisor {

@@ -104,8 +104,8 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &a, void *stream);
 // dQ by the kernel for short key runs and odd chunk shapes (ksa_prefill_direct.hip); stats: the row statistics.
 int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &a, const float *stats, void *stream);
 // dK and dV (ksa_prefill_bwd_dkv.hip); scratch: where the partial sums of split key tiles go, NULL: no tile is split; entries:
-// workgroups per (batch, KV head).
-int ksa_launch_dkv_direct(const KsaPrefillBwdLaunch &a, const float *stats, float *scratch, int entries, void *stream);
+// workgroups per (batch, KV head), whose number the caller has checked to be a grid's.
+void ksa_launch_dkv_direct(const KsaPrefillBwdLaunch &a, const float *stats, float *scratch, int entries, void *stream);
 // Second step of the split dK / dV tiles (ksa_prefill_bwd_sum.hip).
 struct KsaDkvSumArgs {
     const float *scratch;

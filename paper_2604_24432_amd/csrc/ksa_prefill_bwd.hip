@@ -26,6 +26,7 @@
 // Tiles that every row sees whole skip the visibility test (Eq. 3); the others clip each score to its row's range.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ksa_device.h"
@@ -961,21 +962,18 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
 }
 
 template <int D, bool POW2>
-int launch_dkv(const KsaPrefillBwdLaunch &L, const BwdArgs &a, hipStream_t st) {
+void launch_dkv(const KsaPrefillBwdLaunch &L, const BwdArgs &a, hipStream_t st) {
     const int n_bh = a.n_kv_heads * a.batch;
     const int entries = a.scratch ? L.n_dkv_entries : a.sum_tiles + (a.n_text + KEYS_PER_WG - 1) / KEYS_PER_WG;
-    if (a.scratch ? L.dkv_direct : L.dkv_unsplit_direct) {
-        const int rc = ksa_launch_dkv_direct(L, a.stats, a.scratch, entries, st);
-        if (rc != KSA_OK) return rc;
-    } else {
+    if (a.scratch ? L.dkv_direct : L.dkv_unsplit_direct)
+        ksa_launch_dkv_direct(L, a.stats, a.scratch, entries, st);
+    else
         hipLaunchKernelGGL((ksa_bwd_dkv_kernel<D, POW2>), dim3((unsigned)(entries * n_bh)), dim3(NW * 64), 0, st, a);
-    }
     if (a.scratch) {
         const KsaDkvSumArgs sum = {a.scratch, L.dkv_splits, a.dk, a.dv, {a.dks[0], a.dks[1], a.dks[2]}, L.n_dkv_splits, a.sum_tiles,
                                    a.n_text, a.n_sum, a.c, a.m, a.n_kv_heads, n_bh, D, a.scale};
         ksa_launch_dkv_sum(sum, st);
     }
-    return KSA_OK;
 }
 
 template <int D, bool POW2>
@@ -983,17 +981,17 @@ int launch_all(const KsaPrefillBwdLaunch &L, const BwdArgs &a, int64_t n_rows, h
     const int64_t delta_blocks = (n_rows * (D / 8) + 255) / 256;
     hipLaunchKernelGGL(ksa_bwd_delta_kernel<D>, dim3((unsigned)delta_blocks), dim3(256), 0, st, a, n_rows);
     // with split key tiles dq holds their partial sums until it is written itself
-    int rc = a.scratch ? launch_dkv<D, POW2>(L, a, st) : KSA_OK;
-    if (rc != KSA_OK) return rc;
+    if (a.scratch) launch_dkv<D, POW2>(L, a, st);
     if (L.dq_direct) {
-        rc = ksa_launch_dq_direct(L, a.stats, st);
+        const int rc = ksa_launch_dq_direct(L, a.stats, st);
         if (rc != KSA_OK) return rc;
     } else if constexpr (D == 128) {
         hipLaunchKernelGGL(ksa_bwd_dq_kernel, dim3((unsigned)L.n_entries), dim3(NW * 64), 0, st, a);
     } else {
         return KSA_ERR_UNSUPPORTED;   // (no such layout: dq_takes_direct())
     }
-    return a.scratch ? KSA_OK : launch_dkv<D, POW2>(L, a, st);
+    if (!a.scratch) launch_dkv<D, POW2>(L, a, st);
+    return KSA_OK;
 }
 
 }  // namespace
@@ -1059,8 +1057,8 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
     const int64_t n_rows = stat_slots(L.p);
     const int64_t delta_blocks = (n_rows * (L.p.head_dim / 8) + 255) / 256;
     const int text_tiles = (a.n_text + KEYS_PER_WG - 1) / KEYS_PER_WG;
-    if (delta_blocks >= ((int64_t)1 << 31) || L.p.batch > 65535 ||
-        ((int64_t)a.sum_tiles + text_tiles) * L.p.n_kv_heads * L.p.batch >= ((int64_t)1 << 31))
+    const int64_t dkv_entries = std::max((int64_t)a.sum_tiles + text_tiles, (int64_t)L.n_dkv_entries);
+    if (delta_blocks >= ((int64_t)1 << 31) || L.p.batch > 65535 || dkv_entries * L.p.n_kv_heads * L.p.batch >= ((int64_t)1 << 31))
         return KSA_ERR_UNSUPPORTED;
     const bool pow2 = a.c_shift >= 0 && (a.m == 0 || a.m_shift >= 0);
     {   // both kernels address the rows of a streamed tile (Q and dO in the dK/dV kernel, K and V in the dQ kernel) by

@@ -438,7 +438,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
 
 }  // namespace
 
-int ksa_launch_dkv_direct(const KsaPrefillBwdLaunch &L, const float *stats, float *scratch, int entries, void *stream) {
+void ksa_launch_dkv_direct(const KsaPrefillBwdLaunch &L, const float *stats, float *scratch, int entries, void *stream) {
     DkvArgs a;
     a.q = static_cast<const __bf16 *>(L.q);
     a.k = static_cast<const __bf16 *>(L.k);
@@ -464,12 +464,10 @@ int ksa_launch_dkv_direct(const KsaPrefillBwdLaunch &L, const float *stats, floa
     a.view.by_c = ksa_divisor(a.view.c), a.view.by_m = ksa_divisor(a.view.m > 0 ? a.view.m : 1);
     a.by_bh = ksa_divisor(a.n_bh), a.by_kv_heads = ksa_divisor(a.n_kv_heads), a.by_group = ksa_divisor(a.group);
     a.scale = p.softmax_scale, a.scale_log2e = p.softmax_scale * 1.4426950408889634f;
-    if ((int64_t)entries * a.n_bh >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(entries * a.n_bh)), block(NW * 64);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (p.head_dim == 128)
         hipLaunchKernelGGL(ksa_bwd_dkv_direct_kernel<128>, grid, block, 0, st, a);
     else
         hipLaunchKernelGGL(ksa_bwd_dkv_direct_kernel<64>, grid, block, 0, st, a);
-    return KSA_OK;
 }
