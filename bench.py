@@ -282,7 +282,7 @@ def main():
                      "frac": round(attn_tflops / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": pre_traffic,
                      "traffic_source": pre_traffic_note,
                      "frac_of_mfma_only_loop": round(attn_tflops / ach["mfma_only_tflops_1_wave_per_simd"], 4)},
-        "roofline_decode": {"bound": "hbm", "kernel": "ksa_decode_split_kernel<128,4,256>", "achieved": round(dec_gbs, 1),
+        "roofline_decode": {"bound": "hbm", "kernel": "ksa_decode_split_matrix_kernel<128, 4, 256>", "achieved": round(dec_gbs, 1),
                             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(dec_gbs / HBM_PEAK_GBS, 4),
                             "traffic": dec_traffic,
                             "frac_of_stream_read": round(dec_gbs / ach["stream_read_gbs"], 4)},
@@ -374,7 +374,7 @@ def prefill_backward(cfg, lay, q, k, v, o, lse, steps):
     tf = flops / (avg * 1e-3) / 1e12
     return {"ms": round(avg, 3), "ms_min": round(float(np.min(ms)), 3), "live_flops": flops, "live_tflops": round(tf, 1),
             "frac_mfma_peak": round(tf / MFMA_BF16_PEAK_TFLOPS, 4),
-            "kernels": "ksa_bwd_delta_kernel, ksa_bwd_dq_direct_kernel, ksa_bwd_dkv_kernel (split in profiles/)"}
+            "kernels": "ksa_bwd_delta_kernel, ksa_bwd_dq_direct_kernel, ksa_bwd_dkv_direct_kernel (split in profiles/)"}
 
 
 def backward_of(lay, q, k, v, o, lse, seed, calls=2):

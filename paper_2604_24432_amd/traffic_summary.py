@@ -21,6 +21,8 @@ import re
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+# what the benchmark workload launches (head_dim 128, four query heads per KV head)
+KERNELS = (("prefill", "ksa_prefill_kernel<128, false>"), ("decode", "ksa_decode_split_matrix_kernel<128, 4, 256>"))
 
 
 def per_kernel(folder: str, counter: str):
@@ -61,7 +63,7 @@ def main():
              "scaling reference (one device-to-device copy of 1 GiB = 1 048 576 KiB):",
              f"  FETCH_SIZE {max(copy_f):12.1f} KiB -> factor {f_factor:.3f}",
              f"  WRITE_SIZE {max(copy_w):12.1f} KiB -> factor {w_factor:.3f}", ""]
-    for key, needle in (("prefill", "ksa_prefill_kernel"), ("decode", "ksa_decode_split_kernel")):
+    for key, needle in KERNELS:
         name, fv = pick(fetch, needle)
         _, wv = pick(write, needle)
         f_kib, w_kib = sum(fv) / len(fv), sum(wv) / len(wv)
