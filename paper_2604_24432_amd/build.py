@@ -17,8 +17,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
-# MFMA results and accumulator inputs in VGPRs: the forward prefill kernel post-processes them with VALU code.  The
-# backward kernels hold more accumulators than there are VGPRs and leave the choice to the compiler.
+# MFMA results and accumulator inputs in VGPRs: the forward prefill kernels, the dK / dV kernel with two workgroups per compute
+# unit and the decode kernel post-process them with VALU code.  The kernels of ksa_prefill_bwd.hip hold more accumulators than
+# there are VGPRs and leave the choice to the compiler.
 PER_SOURCE = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for s in ("ksa_prefill.hip", "ksa_prefill_direct.hip", "ksa_prefill_bwd_dkv.hip",
                                                               "ksa_decode.hip")}
 OBJ_DIR = os.path.join(HERE, "_build")

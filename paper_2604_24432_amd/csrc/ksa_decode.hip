@@ -18,7 +18,9 @@
 // vector unit 670).  With eight heads the vector unit was the bound: batch 32, 64K context, 8/1 heads 58.1 / 37.2 us, window
 // 1024 with batch 64 41.1 / 28.2; batch 3, 20K, d 64 22.3 / 16.6.  With four: 32K, batch 4 and append 26.1 / 24.7, 128K, batch 1
 // 23.9 / 22.6.  With one head the matrix unit's operand reads (64 bytes of 16 rows instead of four whole rows) lost: batch 32,
-// 32K, 16/16 heads 163.9 us on the vector unit, 169.0.
+// 32K, 16/16 heads 163.9 us on the vector unit, 169.0.  With two heads likewise where there are few spans (vector / matrix unit,
+// 64K, batch 8 30.4 / 32.9, d 64, batch 16 27.9 / 30.6, 128K in the paper's form, batch 1 17.2 / 18.8); level or behind on full
+// launches (64K, batch 32 86.7 / 87.3, 128K, batch 16 176.5 / 171.9, window 1024, batch 64 29.8 / 24.1).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -475,9 +477,10 @@ void launch(const DecodeArgs &a, hipStream_t st) {
 }
 
 // 256 threads per span; with no more spans than compute units 1024 (512 with eight query heads per KV head, whose
-// accumulators take more registers), i.e. four times the loads in flight per unit.  Kernels of one step, 256 / 1024 threads (scores on the vector unit):
-// 128K context, batch 1 (168 spans) 29 / 25 us; 32K, batch 4 (160) 28 / 24; 16K, batch 16 (256) 39 / 31; 128K, batch 2 (336)
-// 41 / 44; 64K, d 64, batch 8 (640) 30 / 42.
+// accumulators take more registers), i.e. four times the loads in flight per unit.  Kernels of one step, 256 / 1024 threads, 32/8
+// heads: 128K context, batch 1 (168 spans) 24.9 / 22.7 us; 32K, batch 4 (160) 25.2 / 22.3; 16K, batch 16 (256) 30.2 / 28.7; 128K,
+// batch 2 (336) 35.3 / 39.9; 64K, d 64, batch 8 (640) 30.6 / 37.0.  8/1 heads, 256 / 512: 128K, batch 4 (84) 29.2 / 24.2; 64K,
+// batch 32 (320) 39.0 / 42.4.  16/16 heads: 64K, batch 2 (320) 27.2 / 30.0; 8/4: 64K, batch 8 (320) 31.1 / 33.0.
 template <int D, int G>
 void launch_group(const DecodeArgs &a, hipStream_t st) {
     if (a.n_splits == 1 || (int64_t)a.batch * a.n_splits * a.n_kv_heads > 256)
@@ -500,9 +503,11 @@ int launch_all(const DecodeArgs &a, hipStream_t st) {
 
 }  // namespace
 
-// Enough spans that the launch has about six workgroups per compute unit (1536 in all: measured best at batch 16 to
-// 128 on the 128K cache, where 2048 workgroups run 4 to 12 % longer), but no span shorter than 768 rows (shorter
-// spans are dominated by the workgroup's fixed costs: measured at batch 1 and 4).
+// Enough spans that the launch has about six workgroups per compute unit (1536 in all; 128K cache, 32/8 heads, batch 16:
+// 768 workgroups 172.6 us, 1024 182.3, 1536 173.7, 2048 185.3, 3072 178.4; batch 64: 1024 702, 1536 656, 2048 775, 2560 659), but
+// no span shorter than 768 rows, whose fixed costs the workgroups would repeat: 64K, batch 8, 640 workgroups 54.5, 1280 52.7;
+// 128K, batch 2, 336 35.8, 672 33.0.  With few sequences the numbers of rounds count more than the spans' length: 128K, batch 1, 168
+// workgroups 23.2, 224 20.3, 272 24.6; 32K, batch 4, 160 23.3, 256 18.1, 320 22.0.
 int ksa_decode_default_splits(const ksa_params *p) {
     const int64_t groups = (int64_t)p->batch * p->n_kv_heads;
     const int64_t rows = (int64_t)(p->n_text / p->chunk_len) * p->n_summary + (int64_t)(p->window_chunks + 1) * p->chunk_len;

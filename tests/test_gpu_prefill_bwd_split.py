@@ -22,7 +22,7 @@ def problem(B, Hq, Hkv, d, n, c, m, C):
     return cfg, lay, q, k, v, o, lse, g
 
 
-# one KV head: a tile's work against the whole chip's makes every longer tile split (at least 32 steps)
+# one KV head: a tile's work against the whole chip's makes every longer tile split (how far: build_dkv in ksa_layout.cpp)
 @pytest.mark.parametrize("shape", [(1, 4, 1, 128, 2100, 64, 8, 1), (1, 3, 1, 64, 2090, 20, 5, 1), (1, 1, 1, 128, 4200, 8, 1, 16),
                                    (2, 8, 2, 64, 1500, 300, 0, 9)], ids=lambda s: "x".join(map(str, s)))
 def test_split_tiles(shape):
