@@ -68,6 +68,13 @@ __device__ __forceinline__ int ksa_div(int x, const KsaDivisor &d) {
 template <class T>
 __device__ __forceinline__ T ksa_stat_at(T x) { return x + (x & ~(T)(KSA_STAT_ROWS - 1)); }
 
+// An LDS tile of row-major bf16 rows that is read both ways (rows as one product's operand, columns as another's): the 16-byte
+// piece index is XORed with this function of the row, which spreads the 16 rows of a plain 16-byte read and the 4 rows of a
+// transposing read over different banks.  At head_dim 64 two rows share the 256 bytes of all banks, so the rows of one parity
+// have to differ.
+template <int D>
+__device__ __forceinline__ int ksa_swz(int row) { return ((D == 64 ? (row & 2) << 1 : (row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
+
 inline int log2_exact(int x) {
     if (x <= 0 || (x & (x - 1))) return -1;
     int s = 0;

@@ -67,12 +67,6 @@ struct BwdArgs {
     float scale, scale_log2e;
 };
 
-// LDS tile: row-major [64][D] bf16; the 16-byte chunk index is XORed with a function of the row that spreads both
-// the 16 rows of a plain 16-byte operand read and the 4 rows of a transposing read over different banks (head_dim 64:
-// two rows share the 256 bytes of all banks, so the rows of one parity have to differ).
-template <int D>
-__device__ __forceinline__ int swz(int row) { return ((D == 64 ? (row & 2) << 1 : (row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
-
 // global -> LDS, 4 bytes per lane: the wave's 64 pieces land back to back (lane order) from the wave-uniform LDS
 // address dst.  Inline assembly for the same reason as lds_direct_load_16_s().
 __device__ __forceinline__ void lds_direct_load_4(const float *src, const unsigned char *dst) {
@@ -80,8 +74,8 @@ __device__ __forceinline__ void lds_direct_load_4(const float *src, const unsign
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(lds_addr) : "memory");
 }
 
-// Byte addresses inside an LDS tile are written as (per-lane constant XOR small constant) + constant, so that one
-// register per tile plus the instructions' immediate offsets cover every operand read.
+// Byte addresses inside an LDS tile (row-major [64][D] bf16, swizzled by ksa_swz) are written as (per-lane constant XOR small
+// constant) + constant, so that one register per tile plus the instructions' immediate offsets cover every operand read.
 struct LaneLds {
     int rows;   // plain operand read: row r, chunk (h ^ swizzle(r)); XOR (s << 5) selects k step s
     int cols;   // transposing read: row t_row, the 8 bytes at column t_col of chunk (t_col / 8 ^ swizzle(t_row))
@@ -94,8 +88,8 @@ __device__ __forceinline__ LaneLds lane_lds(int lane) {
     // 16 (grp % 2) + 4 (li % 4) .. + 3, and receives rows 4 (grp / 2) .. + 3 of column 16 (grp % 2) + li
     const int t_row = 4 * (grp >> 1) + (li >> 2), t_col = 16 * (grp & 1) + 4 * (li & 3);
     LaneLds L;
-    L.rows = r * (D * 2) + ((h ^ swz<D>(r)) << 4);
-    L.cols = t_row * (D * 2) + (((t_col >> 3) ^ swz<D>(t_row)) << 4) + ((t_col & 7) << 1);
+    L.rows = r * (D * 2) + ((h ^ ksa_swz<D>(r)) << 4);
+    L.cols = t_row * (D * 2) + (((t_col >> 3) ^ ksa_swz<D>(t_row)) << 4) + ((t_col & 7) << 1);
     return L;
 }
 
@@ -290,7 +284,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dq_kernel(const BwdArgs a) {
     };
     auto prepare_row = [&](int i) {   // per-lane part of load instruction i; keys past the end of the run: its last one, masked
         const int row = RW * wave + RPI * i + lane / CH, last = run_end - 1 - rq.first;
-        rq.off[i] = (unsigned)(row < last ? row : last) * kv_row_bytes + (unsigned)(((lane % CH) ^ swz<D>(row)) << 4);
+        rq.off[i] = (unsigned)(row < last ? row : last) * kv_row_bytes + (unsigned)(((lane % CH) ^ ksa_swz<D>(row)) << 4);
     };
     auto prepare_all = [&]() {
         prepare_tile();
@@ -703,7 +697,7 @@ __global__ __launch_bounds__(NW * 64) void ksa_bwd_dkv_kernel(const BwdArgs a) {
         const int per = run == KSA_SPACE_TEXT ? a.m : a.c;
         // augmented row of idx minus that of `first`: the index distance plus the other kind's rows in between
         const int d_rows = (idx - first) + (chunk_of(run, idx) - chunk_of(run, first)) * per;
-        const unsigned col = (unsigned)(((lane % CH) ^ swz<D>(row)) << 4);
+        const unsigned col = (unsigned)(((lane % CH) ^ ksa_swz<D>(row)) << 4);
         rq.q_off[i] = (unsigned)d_rows * q_row_bytes + col;
         rq.g_off[i] = (unsigned)d_rows * g_row_bytes + col;
     };

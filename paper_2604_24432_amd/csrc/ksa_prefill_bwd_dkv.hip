@@ -71,12 +71,6 @@ __device__ __forceinline__ void lds_direct_load_4_s(const float *sbase, unsigned
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(voff_bytes), "s"(sbase), "s"(lds_addr) : "memory");
 }
 
-// LDS tile: row-major [32][D] bf16, the 16-byte piece index XORed with a function of the row that spreads both the 16 rows
-// of a plain 16-byte read and the 4 rows of a transposing read over different banks (head_dim 64:
-// two rows share the 256 bytes of all banks, so the rows of one parity have to differ).
-template <int D>
-__device__ __forceinline__ int swz(int row) { return ((D == 64 ? (row & 2) << 1 : (row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
-
 // Query rows [lo, hi) of index space q_space that see key `key` of index space `space` (Eq. 3 read from the key's side).  A
 // row's visible ranges never move backwards from one row to the next, so these are consecutive rows, and lo and hi do
 // not decrease from one key to the next.
@@ -97,7 +91,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
     constexpr int KS = D / 16, DB = D / 32, BYTES = BM * D * 2, CH = D / 8, RPI = 64 / CH, NI = RW / RPI;
     constexpr int STAGE_ROW = D * 2 + 16;
     static_assert(RW % RPI == 0 && NI >= 1, "a wave's share of a tile is a whole number of load instructions");
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES * 2 * BYTES];   // Q and G tiles
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES * 2 * BYTES];   // Q and G tiles, row-major, swizzled by ksa_swz
     __shared__ __attribute__((aligned(256))) float st[STAGES * 2 * BM];                // ... and their rows' statistics
     __shared__ __attribute__((aligned(16))) float own_lse[NW][BM];
     // the first K_LDS of a lane's K operands: kept in registers they would not fit
@@ -207,7 +201,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
             const int row = RW * wave + RPI * i + lane / CH;
             const unsigned k = min(row, end - 1 - rq_first);   // rows behind the run: its last one, masked (they may hold NaN)
             const unsigned d_rows = k + ((__umul24(k, mul) + add) >> 16) * (unsigned)other;
-            const unsigned col = (unsigned)(((lane % CH) ^ swz<D>(row)) << 4);
+            const unsigned col = (unsigned)(((lane % CH) ^ ksa_swz<D>(row)) << 4);
             q_off[i] = d_rows * q_row_bytes + col, g_off[i] = d_rows * g_row_bytes + col;
         }
     };
@@ -265,8 +259,8 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
 
     const int grp = lane >> 4, li = lane & 15;
     const int t_row = 4 * (grp >> 1) + (li >> 2), t_col = 16 * (grp & 1) + 4 * (li & 3);
-    unsigned at_r = r * (D * 2) + ((h ^ swz<D>(r)) << 4);                                               // rows
-    unsigned at_t = t_row * (D * 2) + (((t_col >> 3) ^ swz<D>(t_row)) << 4) + ((t_col & 7) << 1);       // columns
+    unsigned at_r = r * (D * 2) + ((h ^ ksa_swz<D>(r)) << 4);                                               // rows
+    unsigned at_t = t_row * (D * 2) + (((t_col >> 3) ^ ksa_swz<D>(t_row)) << 4) + ((t_col & 7) << 1);       // columns
 
     // One tile: scores | dP with the exponentials between its MFMAs | dV with dS between its MFMAs | dK.  LDS operands are
     // read AHEAD MFMAs before the one that uses them.

@@ -133,11 +133,6 @@ __device__ __forceinline__ Visible visible(const DirectArgs &a, int q_space, int
     return r;
 }
 
-// The swizzle for tiles that are read both ways (K in the dQ kernel: rows for the scores, columns for dQ): spreads the 16
-// rows of a plain 16-byte read and the 4 rows of a transposing read over different banks.
-template <int D>
-__device__ __forceinline__ int both_swz(int row) { return ((D == 64 ? (row & 2) << 1 : (row & 3) << 2) | ((row >> 2) & 3)) & (D / 8 - 1); }
-
 // GRAD = false: forward.  GRAD = true: dQ of the backward pass (see ksa_prefill_bwd.hip for the products) on the same key
 // lists: S^T = K Q^T and dP^T = V dO^T, whose accumulator starts from minus delta, dS^T = P^T o dP^T in bf16 as the B operand
 // of dQ^T += K^T dS^T.
@@ -145,8 +140,8 @@ template <int D, bool GRAD>
 __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) {
     using T = Tile<D>;
     static_assert(NW * 32 * T::STAGE_ROW <= 4 * T::BYTES, "the epilogue's staging area reuses the tile buffers");
-    auto k_swizzle = [](int row) { return GRAD ? both_swz<D>(row) : k_swz<D>(row); };
-    auto v_swizzle = [](int row) { return GRAD ? both_swz<D>(row) : v_swz<D>(row); };
+    auto k_swizzle = [](int row) { return GRAD ? ksa_swz<D>(row) : k_swz<D>(row); };
+    auto v_swizzle = [](int row) { return GRAD ? ksa_swz<D>(row) : v_swz<D>(row); };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
