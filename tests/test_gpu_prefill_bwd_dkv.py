@@ -1,6 +1,6 @@
 """GPU parity of the dK / dV kernel with 32-row query tiles (ksa_prefill_bwd_dkv.hip) and of the line to the one with 64-row
-blocks: chunks that divide a query tile, are divided by one, or neither; incomplete last tiles of either space; one to eight
-query heads per KV head; rows whose log-sum-exp is no number."""
+blocks (which layout takes which: test_layout_dkv.py): chunks that divide a query tile, are divided by one, or neither; incomplete
+last tiles of either space; one to eight query heads per KV head; rows that are no numbers, or whose log-sum-exp is none."""
 import math
 
 import numpy as np
@@ -26,7 +26,7 @@ def run(shape, flags=0, seed=0):
 # batch, heads, KV heads, d, n, c, m, C
 SHAPES = [(1, 4, 2, 128, 31, 8, 1, 2), (1, 2, 1, 128, 33, 16, 2, 1), (2, 3, 1, 64, 129, 32, 4, 0), (1, 8, 1, 128, 353, 64, 8, 1),
           (1, 2, 2, 64, 641, 96, 32, 1), (1, 4, 1, 128, 500, 128, 64, 1), (1, 2, 1, 128, 479, 48, 6, 2), (1, 2, 2, 64, 383, 1, 0, 70),
-          (1, 4, 4, 128, 417, 2, 1, 100), (1, 2, 2, 128, 510, 64, 0, 9), (1, 2, 2, 64, 300, 100, 0, 9), (1, 2, 1, 128, 385, 64, 0, 9)]
+          (1, 4, 4, 128, 417, 2, 1, 100), (1, 4, 4, 128, 900, 128, 64, 1), (1, 2, 2, 128, 510, 64, 0, 9), (1, 2, 2, 64, 300, 100, 0, 9), (1, 2, 1, 128, 385, 64, 0, 9)]
 
 
 @pytest.mark.parametrize("self_only", [0, 1])
@@ -76,9 +76,11 @@ def test_split_tiles_of_64_row_blocks_and_packed_gradients(shape, self_only, pac
 
 
 @pytest.mark.parametrize("value", [math.nan, -math.inf, math.inf])
-@pytest.mark.parametrize("shape", [(1, 2, 1, 128, 353, 64, 8, 1), (1, 2, 2, 64, 383, 1, 0, 70)], ids=["chunks", "window"])
+@pytest.mark.parametrize("shape", [(1, 2, 1, 128, 353, 64, 8, 1), (1, 2, 2, 64, 383, 1, 0, 70), (1, 2, 2, 64, 900, 128, 64, 1)],
+                         ids=["chunks", "window", "64-row blocks"])
 def test_log_sum_exp_that_is_no_number(shape, value):
-    """A weight of a row without a log-sum-exp is none (infinite: zero) for the keys that the row sees and zero for the others."""
+    """A weight of a row without a log-sum-exp is none (infinite: zero) for the keys that the row sees and zero for the others, in
+    both gradients."""
     cfg, lay, q, k, v, g = run(shape)
     o, lse = K.ksa_prefill_fwd(lay, q, k, v)
     row = 200
@@ -87,13 +89,14 @@ def test_log_sum_exp_that_is_no_number(shape, value):
     g0 = g.clone()
     g0[0, row] = 0                       # without the row's contribution
     lse[0, :, row] = math.inf
-    _, _, want = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g0)
+    _, want_dk, want_dv = K.ksa_prefill_bwd(lay, q, k, v, o, lse, g0)
     sees = torch.from_numpy(np.array(O.mask(cfg.n_text, cfg.chunk_len, cfg.n_summary, cfg.window_chunks)[row], dtype=bool)).cuda()
-    assert torch.equal(dv[0, ~sees], want[0, ~sees])
-    if value == math.inf:
-        assert bool(torch.isfinite(dv[0, sees]).all())
-    else:
-        assert not bool(torch.isfinite(dv[0, sees]).any())
+    for x, want in ((dk, want_dk), (dv, want_dv)):
+        assert torch.equal(x[0, ~sees], want[0, ~sees])
+        if value == math.inf:
+            assert torch.equal(x, want)
+        else:
+            assert not bool(torch.isfinite(x[0, sees]).any())
 
 
 @pytest.mark.parametrize("shape,space,at", [((1, 8, 2, 128, 1024, 64, 8, 1), 1, 16), ((1, 8, 2, 128, 960, 48, 6, 1), 1, 20),
