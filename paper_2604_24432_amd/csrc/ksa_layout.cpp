@@ -312,7 +312,8 @@ void dkv_steps(const ksa_params &p, DkvTiles &tiles, DkvTiles &wide) {
 // place, for comparison: 32K tokens 4.44 ms against 3.95, 64K 15.8 / 14.4, 2048 124 us / 87.  Equal pieces only: dense causal
 // 16K 3.67 ms against 3.40.  (Whole backward pass, 32/8 heads, d 128.)
 // All partial sums have to fit into the memory of dq (see ksa_launch_prefill_bwd), which holds batch * rows * query heads / 512
-// of them.
+// of them.  Every layout pays for the search: half of the 0.25 ms that one of 131072 tokens in the paper's form, 8/1 heads takes
+// (long tiles, twelve launches played through), a tenth of the 0.2 ms of the same with 32/8 heads, 4 of 7 us at 2 x 4096 tokens.
 //
 // The kernel that works on blocks of 64 rows (ksa_prefill_bwd.hip) takes the launches whose time is that of their longest
 // workgroup: alone on its compute unit a workgroup takes 0.9 us per 32 rows there, 1.1 in ksa_prefill_bwd_dkv.hip (head_dim 64

@@ -16,11 +16,14 @@
 // V 32, scores and dP of one block 32: of K's 32 the first operands come from LDS (K_LDS), read back lane by lane.  What the
 // loop needs only now and then (the keys' visibility, the parameters of another chunk row) is worked out again from opaque
 // copies of the lane number and of the argument pointer: kept in registers it pushed operands out to scratch, which costs
-// 15 % (a reload waits for the tiles in flight).
+// 15 % (a reload waits for the tiles in flight).  54 scalars (head_dim 64: 51) do not fit the scalar registers and are kept in
+// lanes of a vector register, some of them read back for every request.
 // What bounds it: 128K tokens (32/8 heads, d 128, 35.6 TFLOP executed) the board's power cap, 32.5 ms, before 35.2; 2 x 4096
 // tokens 131 us, before 205: chains of 90 and more steps of 0.9 - 1.2 us per workgroup; 20003 tokens in the paper's form 690 us,
 // before 830.  Per step of 32 MFMAs (1024 clocks) a wave alone on its SIMD takes about 2300 clocks: the four phases 1700, the
 // barrier 100, the first operands' way from LDS 250, the next request 200.
+// A workgroup alone on its unit is slower than one of ksa_bwd_dkv_kernel, which takes the launches that wait for one: build_dkv in
+// ksa_layout.cpp.
 // Tried and dropped: query tiles of 64 rows (the offsets of twice as many loads spill); four stages in flight instead of three
 // (equal); S and dP interleaved (the chain of eight dependent MFMAs costs nothing: 32 clocks each); operands read one, two or
 // four MFMAs ahead (1 - 2 %); a look at every tile's log-sum-exp for values that are no numbers (2 %; now at clipped tiles only).
