@@ -23,6 +23,8 @@
 // launches (64K, batch 32 86.7 / 87.3, 128K, batch 16 176.5 / 171.9, window 1024, batch 64 29.8 / 24.1).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <utility>
 
@@ -55,6 +57,7 @@ struct DecodeArgs {
     int32_t c, m, C, n_text;
     int32_t n_q_heads, n_kv_heads;
     float scale_log2e;
+    float q_scale, score_scale;   // scale_log2e in two factors for the matrix unit, the first a power of two that q is scaled by
 };
 
 struct Ranges {
@@ -358,6 +361,7 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const Decod
     const __bf16 *vb = a.v + b * a.cs[0] + hkv * a.cs[1] + chunk * 8;
 
     const int64_t row = a.cs[2];
+    bool scaled = false;
     for (int base = v0 + wave * (RPW * U); base < v1; base += R_IT) {
         // Nearly all blocks lie in one piece of the cache and before the end: then a scalar offset moves the lane's addresses.
         // (The shift never decreases from one visible row to the next, so equal ends mean one piece.)
@@ -385,6 +389,13 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const Decod
 #pragma unroll
         for (int u = 0; u < U; ++u) vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + v_at[u]));
         __builtin_amdgcn_sched_barrier(0);   // all loads of the block are on their way
+        if (!scaled) {   // (exact; in front of the loop it would hold up the first rows: a step of 24.3 us took 24.7)
+            scaled = true;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) qreg[s][e] = (__bf16)((float)qreg[s][e] * a.q_scale);
+        }
         f32x4 acc[KB];
 #pragma unroll
         for (int x = 0; x < KB; ++x) {
@@ -396,7 +407,7 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const Decod
         float p[U], mx = m_run;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float s = (KB == 1 || !(gi & 1) ? acc[0][u] : acc[KB - 1][u]) * a.scale_log2e;
+            const float s = (KB == 1 || !(gi & 1) ? acc[0][u] : acc[KB - 1][u]) * a.score_scale;
             p[u] = base + v_row + u < v1 ? s : -INFINITY;
             mx = fmaxf(mx, p[u]);
         }
@@ -557,6 +568,11 @@ int ksa_launch_decode(const KsaDecodeLaunch &L, void *stream) {
     a.n_q_heads = L.p.n_q_heads;
     a.n_kv_heads = L.p.n_kv_heads;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
+    // q K^T of the matrix unit is no larger than the scaled scores and at least half as large, so that it does not overflow
+    // where those would not (a scale of 1 / sqrt(128): from 2.7e39 on, unscaled products from 3.4e38)
+    int exponent = 0;
+    (void)std::frexp(a.scale_log2e, &exponent);
+    a.q_scale = std::ldexp(1.f, std::max(std::min(exponent - 1, 0), -8)), a.score_scale = a.scale_log2e / a.q_scale;
     a.batch = L.p.batch;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (L.p.head_dim == 128) return launch_all<128>(a, st);
