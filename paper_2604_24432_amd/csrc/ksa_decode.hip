@@ -57,7 +57,7 @@ struct DecodeArgs {
     int32_t c, m, C, n_text;
     int32_t n_q_heads, n_kv_heads;
     float scale_log2e;
-    float q_scale, score_scale;   // scale_log2e in two factors for the matrix unit, the first a power of two that q is scaled by
+    float q_scale, score_scale;   // scale_log2e in two factors, the first a power of two
 };
 
 struct Ranges {
@@ -351,85 +351,93 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const Decod
 #pragma unroll
         for (int s = 0; s < KS; ++s) qreg[s] = *reinterpret_cast<const bf16x8 *>(qp + s * 32);
     }
-    float m_run = -1e30f, l_run = 0.f, o[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[g][e] = 0.f;
+    float m_run, l_run, o[G][8], largest;   // largest: of the lane's products; a NaN stays
 
     const __bf16 *kb = a.k + b * a.cs[0] + hkv * a.cs[1] + (lane >> 4) * 8;
     const __bf16 *vb = a.v + b * a.cs[0] + hkv * a.cs[1] + chunk * 8;
 
     const int64_t row = a.cs[2];
-    bool scaled = false;
-    for (int base = v0 + wave * (RPW * U); base < v1; base += R_IT) {
-        // Nearly all blocks lie in one piece of the cache and before the end: then a scalar offset moves the lane's addresses.
-        // (The shift never decreases from one visible row to the next, so equal ends mean one piece.)
-        const int end = base + RPW * U, shift = row_shift(R, base);
-        const bool whole = end <= v1 && row_shift(R, end - 1) == shift;
-        int64_t k_at[KB], v_at[U];
-        if (whole) {
-            const int64_t first = (int64_t)(base + shift) * row;
+    auto walk = [&](const bf16x8 (&q)[KS], float to_score) {
+        m_run = -1e30f, l_run = 0.f, largest = 0.f;
 #pragma unroll
-            for (int x = 0; x < KB; ++x) k_at[x] = (lane & 15) * row + (first + 16 * x * row);
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int u = 0; u < U; ++u) v_at[u] = v_row * row + (first + u * row);
-        } else {
-            auto offset = [&](int v) { v = min(v, v1 - 1); return (int64_t)(v + row_shift(R, v)) * row; };
+            for (int e = 0; e < 8; ++e) o[g][e] = 0.f;
+        for (int base = v0 + wave * (RPW * U); base < v1; base += R_IT) {
+            // Nearly all blocks lie in one piece of the cache and before the end: then a scalar offset moves the lane's addresses.
+            // (The shift never decreases from one visible row to the next, so equal ends mean one piece.)
+            const int end = base + RPW * U, shift = row_shift(R, base);
+            const bool whole = end <= v1 && row_shift(R, end - 1) == shift;
+            int64_t k_at[KB], v_at[U];
+            if (whole) {
+                const int64_t first = (int64_t)(base + shift) * row;
 #pragma unroll
-            for (int x = 0; x < KB; ++x) k_at[x] = offset(base + 16 * x + (lane & 15));
+                for (int x = 0; x < KB; ++x) k_at[x] = (lane & 15) * row + (first + 16 * x * row);
 #pragma unroll
-            for (int u = 0; u < U; ++u) v_at[u] = offset(base + v_row + u);
+                for (int u = 0; u < U; ++u) v_at[u] = v_row * row + (first + u * row);
+            } else {
+                auto offset = [&](int v) { v = min(v, v1 - 1); return (int64_t)(v + row_shift(R, v)) * row; };
+#pragma unroll
+                for (int x = 0; x < KB; ++x) k_at[x] = offset(base + 16 * x + (lane & 15));
+#pragma unroll
+                for (int u = 0; u < U; ++u) v_at[u] = offset(base + v_row + u);
+            }
+            u32x4 kk[KB][KS], vv[U];
+#pragma unroll
+            for (int x = 0; x < KB; ++x)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) kk[x][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(kb + k_at[x] + s * 32));
+#pragma unroll
+            for (int u = 0; u < U; ++u) vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + v_at[u]));
+            __builtin_amdgcn_sched_barrier(0);   // all loads of the block are on their way
+            f32x4 acc[KB];
+#pragma unroll
+            for (int x = 0; x < KB; ++x) {
+                acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kk[x][s]), q[s], acc[x], 0, 0, 0);
+                largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, fabsf(acc[x][0])), fabsf(acc[x][1]));
+                largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, fabsf(acc[x][2])), fabsf(acc[x][3]));
+            }
+            float p[U], mx = m_run;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float s = (KB == 1 || !(gi & 1) ? acc[0][u] : acc[KB - 1][u]) * to_score;
+                p[u] = base + v_row + u < v1 ? s : -INFINITY;
+                mx = fmaxf(mx, p[u]);
+            }
+            if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
+                const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
+                l_run *= alpha, m_run = mx;
+                for_heads<D, G>(alpha, [&](int g, float x) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[g][e] *= x;
+                });
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                p[u] = __builtin_amdgcn_exp2f(p[u] - m_run);
+                l_run += p[u];
+                float vf[8];
+                unpack8(vv[u], vf);
+                for_heads<D, G>(p[u], [&](int g, float x) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[g][e] = fmaf(x, vf[e], o[g][e]);
+                });
+            }
         }
-        u32x4 kk[KB][KS], vv[U];
+    };
+    walk(qreg, a.scale_log2e);
+    // Products that overflow may be scores that do not: the wave's rows once more with the scale's power of two in q (exact).  A
+    // sum that was infinite at any time is so in the end, or a NaN.  (The look at the products costs the smallest launches 1 - 2 %:
+    // one span of 1500 rows, 16 workgroups 21.3 / 21.7 us; scaling every q before the loop 4 %, in it 4 %, a look per block 4 %.)
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(largest < INFINITY)) != 0, 0)) {
 #pragma unroll
-        for (int x = 0; x < KB; ++x)
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int s = 0; s < KS; ++s) kk[x][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(kb + k_at[x] + s * 32));
-#pragma unroll
-        for (int u = 0; u < U; ++u) vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vb + v_at[u]));
-        __builtin_amdgcn_sched_barrier(0);   // all loads of the block are on their way
-        if (!scaled) {   // (exact; in front of the loop it would hold up the first rows: a step of 24.3 us took 24.7)
-            scaled = true;
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) qreg[s][e] = (__bf16)((float)qreg[s][e] * a.q_scale);
-        }
-        f32x4 acc[KB];
-#pragma unroll
-        for (int x = 0; x < KB; ++x) {
-            acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kk[x][s]), qreg[s], acc[x], 0, 0, 0);
-        }
-        float p[U], mx = m_run;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float s = (KB == 1 || !(gi & 1) ? acc[0][u] : acc[KB - 1][u]) * a.score_scale;
-            p[u] = base + v_row + u < v1 ? s : -INFINITY;
-            mx = fmaxf(mx, p[u]);
-        }
-        if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
-            const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
-            l_run *= alpha, m_run = mx;
-            for_heads<D, G>(alpha, [&](int g, float x) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[g][e] *= x;
-            });
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            p[u] = __builtin_amdgcn_exp2f(p[u] - m_run);
-            l_run += p[u];
-            float vf[8];
-            unpack8(vv[u], vf);
-            for_heads<D, G>(p[u], [&](int g, float x) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[g][e] = fmaf(x, vf[e], o[g][e]);
-            });
-        }
+            for (int e = 0; e < 8; ++e) qreg[s][e] = (__bf16)((float)qreg[s][e] * a.q_scale);
+        walk(qreg, a.score_scale);
     }
 
     // ---- merge the lane groups of each wave, then the waves -----------------------------------------
@@ -568,8 +576,8 @@ int ksa_launch_decode(const KsaDecodeLaunch &L, void *stream) {
     a.n_q_heads = L.p.n_q_heads;
     a.n_kv_heads = L.p.n_kv_heads;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
-    // q K^T of the matrix unit is no larger than the scaled scores and at least half as large, so that it does not overflow
-    // where those would not (a scale of 1 / sqrt(128): from 2.7e39 on, unscaled products from 3.4e38)
+    // with the first factor in q the products are no larger than the scaled scores and at least half as large, so that they do
+    // not overflow where those would not (a scale of 1 / sqrt(128): from 2.7e39 on, unscaled products from 3.4e38)
     int exponent = 0;
     (void)std::frexp(a.scale_log2e, &exponent);
     a.q_scale = std::ldexp(1.f, std::max(std::min(exponent - 1, 0), -8)), a.score_scale = a.scale_log2e / a.q_scale;

@@ -43,10 +43,11 @@ def test_blocks_across_the_pieces_of_the_cache(form, heads, d, n_splits):
     assert np.isfinite(err).all() and (err <= 1e-4 + 2.0 ** -8 * np.abs(want)).all() and lerr.max() <= 1e-4
 
 
+@pytest.mark.parametrize("cancel", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("heads", [(2, 2), (4, 2), (8, 2), (8, 1)], ids=lambda h: "x".join(map(str, h)))
-def test_scores_whose_unscaled_products_exceed_fp32(heads, d):
-    """q . k is 1.4e39 (d 64: 6.8e38) for one row, the scaled score 1.2e38 (8.5e37): the row has all the weight."""
+def test_scores_whose_unscaled_products_exceed_fp32(heads, d, cancel):
+    """q . k of one row is beyond fp32, or a partial sum of it far below, while the scaled score is not: the row has all the weight."""
     (c, m, C), (Hq, Hkv), n = (64, 8, 1), heads, 1500
     p = K.make_params(1, n, c, m, C, Hq, Hkv, d)
     _, rows = K.cache_geometry(p)
@@ -55,9 +56,11 @@ def test_scores_whose_unscaled_products_exceed_fp32(heads, d):
     q = torch.full((1, Hq, d), 0.25, dtype=torch.bfloat16)
     r = K.ksa_decode_ranges(p, n - 1)
     row = r[2] + r[3] // 2
-    k[0, :, row] = 2.0 ** 125
+    k[0, :, row] = 2.0 ** 126 if cancel and d == 64 else 2.0 ** 125
+    if cancel:
+        k[0, :, row, :32] = -2.0 ** 125           # -2^128 so far
     for n_splits in (1, 3):
         o, lse = K.ksa_decode_fwd(p, q.cuda(), k.cuda(), v.cuda(), torch.tensor([n - 1], dtype=torch.int32).cuda(), n_splits=n_splits)
         assert torch.equal(o[0].cpu(), v[0, :, row].repeat_interleave(Hq // Hkv, 0))
-        want = d * 0.25 * 2.0 ** 125 / np.sqrt(d)
+        want = 0.25 * float(k[0, 0, row].double().sum()) / np.sqrt(d)
         assert np.abs(lse.cpu().double().numpy() / want - 1).max() <= 1e-6      # fp32: the scale, its product, the logarithm's base
