@@ -65,16 +65,20 @@ def test_pieces_are_the_steps_of_the_kernel(plan, shape, flags):
 
 @pytest.mark.parametrize("shape", [(1, 8, 1, 128, 131072, 64, 8, 1), (1, 8, 1, 64, 131072, 8, 1, 128)], ids=lambda s: "x".join(map(str, s)))
 def test_building_a_layout_stays_cheap(shape):
-    """Every caller pays for the plan, also one that only runs the forward pass.  0.2 - 0.25 ms on the machine where playing every
-    candidate launch through piece by piece took 1.9 - 2.1 ms; the bar leaves a slower one a factor of four."""
+    """Every caller pays for the plan, also one that only runs the forward pass.  A layout of one KV head has the most pieces to weigh
+    up; it takes 1.1 times as long as one of the same text with 32/8 heads, whose schedule is longer and whose plan is short
+    (playing every candidate launch through piece by piece: 3.5 - 4.2 times)."""
     import time
 
     import paper_2604_24432_amd as K
-    B, Hq, Hkv, d, n, c, m, C = shape
-    p, best = K.make_params(B, n, c, m, C, Hq, Hkv, d), 1.0
-    for _ in range(20):
-        t = time.perf_counter()
-        lay = K.ksa_build_layout(p)
-        best = min(best, time.perf_counter() - t)
-        del lay
-    assert best < 1e-3
+    B, _, _, d, n, c, m, C = shape
+    best = {}
+    for _ in range(25):
+        for heads in ((8, 1), (32, 8)):
+            p = K.make_params(B, n, c, m, C, *heads, d)
+            t = time.perf_counter()
+            lay = K.ksa_build_layout(p)
+            best[heads] = min(best.get(heads, 1.0), time.perf_counter() - t)
+            del lay
+    print({k: f"{v * 1e6:.0f} us" for k, v in best.items()})
+    assert best[8, 1] < 2.5 * best[32, 8]
