@@ -16,12 +16,16 @@
 // V 32, scores and dP of one block 32: of K's 32 the first operands come from LDS (K_LDS), read back lane by lane.  What the
 // loop needs only now and then (the keys' visibility, the parameters of another chunk row) is worked out again from opaque
 // copies of the lane number and of the argument pointer: kept in registers it pushed operands out to scratch, which costs
-// 15 % (a reload waits for the tiles in flight).  54 scalars (head_dim 64: 51) do not fit the scalar registers and are kept in
-// lanes of a vector register, some of them read back for every request.
+// 15 % (a reload waits for the tiles in flight).
+// Where the tiles lie is worked out for 64 steps at a time, one per lane, and kept in LDS.  Taken from the step before, as it was,
+// it was 100 scalar instructions with branches, 500 - 700 clocks per step, and 54 scalars that did not fit the scalar registers
+// (now 9 and 160 clocks): 20003 tokens in the paper's form 1623 -> 1596 us (forward and backward; the kernel's clocks fall by 11 %,
+// the power cap takes most of it back), 2 x 4096 345.8 -> 341.8, 6011 tokens, c 48, m 6, d 64, where a block's place was worked
+// out from the start 158.4 -> 148.7, window 1024, d 64, 2 x 1536 158.0 -> 150.4.
 // What bounds it: 128K tokens (32/8 heads, d 128, 35.6 TFLOP executed) the board's power cap, 32.5 ms, before 35.2; 2 x 4096
 // tokens 131 us, before 205: chains of 90 and more steps of 0.9 - 1.2 us per workgroup; 20003 tokens in the paper's form 690 us,
 // before 830.  Per step of 32 MFMAs (1024 clocks) a wave alone on its SIMD takes about 2300 clocks: the four phases 1700, the
-// barrier 100, the first operands' way from LDS 250, the next request 200.
+// barrier 100, the first operands' way from LDS 250, the next request 160.
 // A workgroup alone on its unit is slower than one of ksa_bwd_dkv_kernel, which takes the launches that wait for one: build_dkv in
 // ksa_layout.cpp.
 // Tried and dropped: query tiles of 64 rows (the offsets of twice as many loads spill); four stages in flight instead of three
@@ -44,6 +48,7 @@ static_assert(NW * 32 == KSA_DKV_KEYS, "the schedule counts key tiles of this si
 static_assert(BM == KSA_DKV_ROWS, "... and query tiles of this size");
 static_assert(BM == KSA_STAT_ROWS, "a tile's statistics are one 64-lane load");
 constexpr int RW = BM / NW;        // rows of a tile each wave fetches
+constexpr int PLAN = 64;           // steps per part of the request plan: one per lane of the wave that works it out
 
 // what the visibility of a key depends on
 struct KeyView {
@@ -60,8 +65,6 @@ struct DkvArgs {
     int64_t qs[3], ks[3], gs[3], dks[3];   // {batch, row, head} strides in elements
     KeyView view;
     int32_t n_q_heads, n_kv_heads, group, n_bh, sum_tiles, nt_pad, ns_pad;
-    int32_t alike_c, alike_m;      // whether chunks of c and of m rows divide a query tile, or it them
-    int32_t gap_c, gap_m;          // rows of the other kind per query tile, or per chunk if that is longer
     uint32_t small_c, small_m;     // 65536 / c and 65536 / m, rounded up (used where c, m < 64)
     KsaDivisor by_bh, by_kv_heads, by_group;
     float scale, scale_log2e;
@@ -98,7 +101,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
     __shared__ __attribute__((aligned(256))) float st[STAGES * 2 * BM];                // ... and their rows' statistics
     __shared__ __attribute__((aligned(16))) float own_lse[NW][BM];
     // the first K_LDS of a lane's K operands: kept in registers they would not fit
-    constexpr int K_LDS = D == 128 ? 6 : 2, K_REG = KS - K_LDS;
+    constexpr int K_LDS = D == 128 ? 6 : 2;
     __shared__ __attribute__((aligned(1024))) bf16x8 k_lds[K_LDS > 0 ? K_LDS : 1][NW * 64];
     static_assert(NW * 32 * STAGE_ROW <= STAGES * 2 * BYTES, "the epilogue's staging area reuses the tile buffers");
 
@@ -142,21 +145,15 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
     const int w_key0 = k0 + wave * 32;
     const bool w_any = w_key0 < n_space;
     const int key = min(w_key0 + r, n_space - 1);
-    bf16x8 kreg[K_REG], vreg[KS];
+    bf16x8 kreg[KS], vreg[KS];
     {
         const int64_t at = b * a.ks[0] + (int64_t)key_row(key) * a.ks[1] + hkv * a.ks[2] + h * 8;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(a.k + at + s * 16);
-            if (s < K_LDS) k_lds[s < K_LDS ? s : 0][tid] = x; else kreg[s < K_LDS ? 0 : s - K_LDS] = x;
+            kreg[s] = *reinterpret_cast<const bf16x8 *>(a.k + at + s * 16);
             vreg[s] = *reinterpret_cast<const bf16x8 *>(a.v + at + s * 16);
         }
     }
-    f32x16 dk[DB], dv[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) dk[db][e] = 0.f, dv[db][e] = 0.f;
 
     // ---- the sequence of query tiles: run 0 is the text rows, run 1 the summary rows, a step one head of one block ------
     int run_end[2], blk_n[2];      // rows before run_end, the last blk_n blocks of them
@@ -170,61 +167,76 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
     const int steps0 = blk_n[0] * a.group;
     const int n_steps = min(steps0 + blk_n[1] * a.group, step_end) - step_begin;   // > 0: a key is seen by its own row
 
-    // ---- the request of a tile: prepare, then issue its loads between the MFMAs of the tile in work -------------------
-    const unsigned lds0 = (unsigned)(size_t)lds, st0 = (unsigned)(size_t)&st[0];
-    const unsigned q_row_bytes = (unsigned)a.qs[1] * 2u, g_row_bytes = (unsigned)a.gs[1] * 2u;
-    const int64_t q_head_bytes = a.qs[2] * 2, g_head_bytes = a.gs[2] * 2, st_head_bytes = 8 * ((int64_t)a.nt_pad + a.ns_pad);
-    const char *rq_q, *rq_g;       // row `rq_first` of the tile
-    const char *rq_st;             // its statistics: 32 of the one kind, then 32 of the other
-    unsigned q_off[NI], g_off[NI];
-    int rq_run, rq_first, rq_head, rq_left = n_steps, run_lo;   // run_lo: first row of the run's first block
-    // Blocks whose rows lie alike in the augmented sequence (chunks that divide a block, or it them) keep the offsets of the block
-    // before and lie BM rows in front of it, or BM + gap rows where a chunk border lies in between: every gap_every rows.
-    int alike, gap, gap_every, gap_in;
-    auto open_block = [&](int x, int blk, int head) {   // block blk of run x, worked out from the start
+    // ---- the requests: one wave works out 64 of them at a time, one per lane, into LDS; a step reads the next one ---------
+    struct Request {
+        const char *q, *g;         // row `first` of the tile
+        const char *stats;         // its statistics: 32 of the one kind, then 32 of the other
+        uint32_t first;            // the tile's first row (a multiple of BM) with the run in bit 0
+        uint32_t pattern;          // what the tile's other rows' places depend on: run | last row << 1 | border << 6
+    };
+    static_assert(sizeof(Request) == 32, "two 16-byte reads");
+    __shared__ __attribute__((aligned(16))) unsigned char plan[2 * PLAN * sizeof(Request)];   // of two parts by turns
+    auto plan_part = [&](int n0) {   // requests n0 .. n0 + 63; behind the last one: it again, into a stage nobody reads
         const auto *p = args_again();
-        const int per = x ? p->view.m : p->view.c, other = x ? p->view.c : p->view.m, end = x ? run_end[1] : run_end[0];
-        rq_run = x, rq_first = blk * BM, rq_head = head;
-        run_lo = (last_block(x) + 1 - (x ? blk_n[1] : blk_n[0])) * BM;
-        const int j0 = ksa_div(rq_first, KsaDivisor{x ? p->view.by_m.mul : p->view.by_c.mul, x ? p->view.by_m.shift : p->view.by_c.shift});
-        const int phase = rq_first - j0 * per;
-        const int64_t row0 = (int64_t)rq_first + (x ? p->view.c : 0) + (int64_t)j0 * other;
-        const int hq = hkv * a.group + head;
-        rq_q = (const char *)(p->q + b * p->qs[0] + row0 * p->qs[1] + hq * p->qs[2]);
-        rq_g = (const char *)(p->g + b * p->gs[0] + row0 * p->gs[1] + hq * p->gs[2]);
-        rq_st = (const char *)(p->stats + 2 * ((int64_t)(b * p->n_q_heads + hq) * (p->nt_pad + p->ns_pad) + (x ? p->nt_pad : 0) + rq_first));
-        alike = rq_first + BM <= end ? (x ? p->alike_m : p->alike_c) : 0;
-        gap = (x ? p->gap_m : p->gap_c), gap_every = max(per - BM, 0), gap_in = per < BM ? 0 : phase;
-        // row k of the tile lies k + (chunk borders in between) * other rows behind the first: see ksa_prefill_direct.hip
-        const unsigned mul = per < 64 ? (x ? p->small_m : p->small_c) : 1024u;
-        const unsigned add = (per < 64 ? phase : 64 - min(64, per - phase)) * mul;
+        const int n = n0 + lane_again(), s = step_begin + min(n, n_steps - 1);
+        const bool x = s >= steps0;
+        const int in_run = s - (x ? steps0 : 0), ti = ksa_div(in_run, KsaDivisor{p->by_group.mul, p->by_group.shift});
+        const int hq = hkv * p->group + in_run - ti * p->group;
+        const int c = p->view.c, m = p->view.m, per = x ? m : c, other = x ? c : m, end = x ? run_end[1] : run_end[0];
+        const int first = ((int)((unsigned)(end - 1) / BM) - ti) * BM;   // the blocks of a run from its last one down
+        // (both quotients: a choice between the divisors would be a load per lane, which waits for the tiles in flight)
+        const int by_c = ksa_div(first, KsaDivisor{p->view.by_c.mul, p->view.by_c.shift});
+        const int by_m = ksa_div(first, KsaDivisor{p->view.by_m.mul, p->view.by_m.shift});
+        const int j0 = x ? by_m : by_c;
+        const int phase = first - j0 * per;
+        const int64_t row0 = (int64_t)first + (x ? c : 0) + (int64_t)j0 * other;
+        // Row k of the tile lies k + (chunk borders in between) * other rows behind the first: see ksa_prefill_direct.hip.  Chunks of
+        // 64 rows and more have at most one border, at `border` = 64 - its distance; none in the tile counts as 0.
+        int border = per < 64 ? phase : 64 - min(64, per - phase);
+        if (per >= 64 && border <= 64 - BM) border = 0;
+        Request r;
+        r.q = (const char *)(p->q + b * p->qs[0] + row0 * p->qs[1] + hq * p->qs[2]);
+        r.g = (const char *)(p->g + b * p->gs[0] + row0 * p->gs[1] + hq * p->gs[2]);
+        r.stats = (const char *)(p->stats + 2 * ((int64_t)(b * p->n_q_heads + hq) * (p->nt_pad + p->ns_pad) + (x ? p->nt_pad : 0) + first));
+        r.first = (uint32_t)first | (x ? 1u : 0u);
+        r.pattern = (x ? 1u : 0u) | (uint32_t)(min(BM, end - first) - 1) << 1 | (uint32_t)border << 6;   // (rows behind the run may hold NaN)
+        *reinterpret_cast<Request *>(plan + (n % (2 * PLAN)) * sizeof(Request)) = r;
+    };
+    if (wave < 2) plan_part(wave * PLAN);
+#pragma unroll
+    for (int s = 0; s < K_LDS; ++s) k_lds[s][tid] = kreg[s];
+    __syncthreads();
+
+    const unsigned lds0 = (unsigned)(size_t)lds, st0 = (unsigned)(size_t)&st[0];
+    u32x4 next_lo, next_hi;        // the request behind the prepared one, as read from LDS
+    auto read_request = [&](int n) {
+        const unsigned char *at = plan + (n % (2 * PLAN)) * sizeof(Request);
+        next_lo = *reinterpret_cast<const u32x4 *>(at), next_hi = *reinterpret_cast<const u32x4 *>(at + 16);
+    };
+    const char *rq_q, *rq_g, *rq_st;
+    unsigned q_off[NI], g_off[NI], rq_first, rq_pattern = ~0u;
+    auto take_request = [&]() {    // the one read last becomes the prepared one
+        auto scalar = [](unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); };
+        auto pointer = [&](unsigned lo, unsigned hi) { return (const char *)((uint64_t)scalar(hi) << 32 | scalar(lo)); };
+        rq_q = pointer(next_lo[0], next_lo[1]), rq_g = pointer(next_lo[2], next_lo[3]), rq_st = pointer(next_hi[0], next_hi[1]);
+        rq_first = scalar(next_hi[2]);
+        const unsigned pattern = scalar(next_hi[3]);
+        if (pattern == rq_pattern) return;
+        rq_pattern = pattern;
+        const auto *p = args_again();
+        const bool x = pattern & 1;
+        const int per = x ? p->view.m : p->view.c, limit = (pattern >> 1) & 31;
+        const unsigned other = (unsigned)(x ? p->view.c : p->view.m), mul = per < 64 ? (x ? p->small_m : p->small_c) : 1024u, add = (pattern >> 6) * mul;
+        const unsigned q_row_bytes = (unsigned)p->qs[1] * 2u, g_row_bytes = (unsigned)p->gs[1] * 2u;
         const int lane = lane_again();
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int row = RW * wave + RPI * i + lane / CH;
-            const unsigned k = min(row, end - 1 - rq_first);   // rows behind the run: its last one, masked (they may hold NaN)
-            const unsigned d_rows = k + ((__umul24(k, mul) + add) >> 16) * (unsigned)other;
+            const unsigned k = min(row, limit);   // rows behind the run: its last one, masked
+            const unsigned d_rows = k + ((__umul24(k, mul) + add) >> 16) * other;
             const unsigned col = (unsigned)(((lane % CH) ^ ksa_swz<D>(row)) << 4);
             q_off[i] = d_rows * q_row_bytes + col, g_off[i] = d_rows * g_row_bytes + col;
         }
-    };
-    auto advance = [&]() {   // prepares the tile behind the prepared one; none left: it is fetched again, into a stage nobody reads
-        if (--rq_left <= 0) return;
-        if (++rq_head < a.group) {
-            rq_q += q_head_bytes, rq_g += g_head_bytes, rq_st += st_head_bytes;
-            return;
-        }
-        const bool first_run_ends = rq_first == run_lo;   // (and the second one begins: there are steps left)
-        if (alike && !first_run_ends) {
-            const unsigned back = BM + (gap_in == 0 ? gap : 0);
-            gap_in = gap_in == 0 ? gap_every : gap_in - BM;
-            rq_first -= BM, rq_head = 0;
-            rq_q -= (uint64_t)back * q_row_bytes + (a.group - 1) * q_head_bytes;
-            rq_g -= (uint64_t)back * g_row_bytes + (a.group - 1) * g_head_bytes;
-            rq_st -= 8 * BM + (a.group - 1) * st_head_bytes;
-            return;
-        }
-        open_block(first_run_ends ? 1 : rq_run, first_run_ends ? last_block(1) : rq_first / BM - 1, 0);
     };
     constexpr int LOADS = 2 * NI + 1;
     auto issue = [&](int stage, int x) {   // load x of the prepared tile: Q and G by turns, then the statistics
@@ -236,19 +248,23 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
         else
             lds_direct_load_16_s((const __bf16 *)rq_g, g_off[x / 2], dst + BYTES);
     };
-    {
-        const int x = step_begin < steps0 ? 0 : 1, in_run = step_begin - (x ? steps0 : 0), ti = ksa_div(in_run, a.by_group);
-        open_block(x, last_block(x) - ti, in_run - ti * a.group);
-    }
-    int tile_first[STAGES - 1];    // first rows of the tiles that are on their way, with the run in bit 0 (rows are multiples of BM)
+    unsigned tile_first[STAGES - 1];   // `first` of the tiles that are on their way
+    f32x16 dk[DB], dv[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dk[db][e] = 0.f, dv[db][e] = 0.f;
+
     // K and V have arrived before the first request: the counted waits below are about tile requests only
     __builtin_amdgcn_s_waitcnt(0x0F70);
 #pragma unroll
-    for (int x = 0; x < STAGES - 1; ++x) {
-        tile_first[x] = rq_first | rq_run;
+    for (int x = 0; x < STAGES; ++x) {
+        read_request(x);
+        take_request();
+        if (x == STAGES - 1) break;
+        tile_first[x] = rq_first;
 #pragma unroll
         for (int y = 0; y < LOADS; ++y) issue(x, y);
-        advance();
     }
 
     // rows that see some key of the wave, and those that see every one of them, in the run of the tile in work
@@ -267,7 +283,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
 
     // One tile: scores | dP with the exponentials between its MFMAs | dV with dS between its MFMAs | dK.  LDS operands are
     // read AHEAD MFMAs before the one that uses them.
-    auto compute = [&](int stage, int req, int first) {
+    auto compute = [&](int stage, int req, int first, int step) {
         const float *const stats = &st[stage * 2 * BM + 4 * h];
         const float *lse = stats;
         const bool clip = (int)(first < all_lo) | (int)(first + BM > all_hi);
@@ -310,6 +326,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
             for (int y = half * SLOTS; y < (half + 1) * SLOTS; ++y) {
                 const int x = ph * KS + y;
                 if (x + AHEAD < NM) read_op(x + AHEAD);
+                if (x == NM - SLOTS) read_request(step + STAGES);
                 if (ph == 0 && y >= KS - 4) {   // dP starts from minus delta
                     const int g4 = y - (KS - 4);
                     const f32x4 nd = *reinterpret_cast<const f32x4 *>(stats + BM + 8 * g4);
@@ -318,7 +335,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
                 }
                 if (ph == 1 && y == 0) read_l(0);
                 KSA_FENCE();
-                if constexpr (ph == 0) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], y < K_LDS ? kop[y < K_LDS ? y : 0] : kreg[y < K_LDS ? 0 : y - K_LDS], sacc, 0, 0, 0);
+                if constexpr (ph == 0) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], y < K_LDS ? kop[y < K_LDS ? y : 0] : kreg[y], sacc, 0, 0, 0);
                 if constexpr (ph == 1) gacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], vreg[y], gacc, 0, 0, 0);
                 if constexpr (ph == 2) dv[y % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], pp[y / DB], dv[y % DB], 0, 0, 0);
                 if constexpr (ph == 3) dk[y % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], pd[y / DB], dk[y % DB], 0, 0, 0);
@@ -378,18 +395,20 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
         static_assert(YOUNGER < 16, "the low bits of the count");
         __builtin_amdgcn_s_waitcnt(0x0F70 | YOUNGER);
         __syncthreads();   // ... and everybody's; nobody reads the stage any more that the next request overwrites
-        const int first = tile_first[0] & -2, x = tile_first[0] & 1, req = stage == 0 ? STAGES - 1 : stage - 1;
+        const int first = (int)(tile_first[0] & ~1u), x = (int)(tile_first[0] & 1u), req = stage == 0 ? STAGES - 1 : stage - 1;
 #pragma unroll
         for (int y = 0; y + 1 < STAGES - 1; ++y) tile_first[y] = tile_first[y + 1];
-        tile_first[STAGES - 2] = rq_first | rq_run;
+        tile_first[STAGES - 2] = rq_first;
+        if (step % PLAN == 0 && step > 0 && wave == step / PLAN % NW) plan_part(step + PLAN);
         if (x != run) enter_run(x);
         if (first >= some_hi || first + BM <= some_lo) {   // nothing for this wave
 #pragma unroll
             for (int y = 0; y < LOADS; ++y) issue(req, y);
+            read_request(step + STAGES);
         } else {
-            compute(stage, req, first);
+            compute(stage, req, first, step);
         }
-        advance();
+        take_request();
         const int by = stage == STAGES - 1 ? -stage * 2 * BYTES : 2 * BYTES;
         at_r += by, at_t += by, stage = stage == STAGES - 1 ? 0 : stage + 1;
     }
@@ -455,8 +474,6 @@ void ksa_launch_dkv_direct(const KsaPrefillBwdLaunch &L, const float *stats, flo
     a.n_bh = p.batch * p.n_kv_heads;
     a.sum_tiles = (a.view.n_sum + KSA_DKV_KEYS - 1) / KSA_DKV_KEYS;
     a.nt_pad = (a.view.n_text + 63) / 64 * 64, a.ns_pad = (a.view.n_sum + 63) / 64 * 64;
-    a.alike_c = a.view.c % BM == 0 || BM % a.view.c == 0, a.alike_m = a.view.m > 0 && (a.view.m % BM == 0 || BM % a.view.m == 0);
-    a.gap_c = a.view.m * std::max(1, BM / a.view.c), a.gap_m = a.view.m > 0 ? a.view.c * std::max(1, BM / a.view.m) : 0;
     a.small_c = (65535 + a.view.c) / a.view.c, a.small_m = a.view.m > 0 ? (65535 + a.view.m) / a.view.m : 0;
     a.view.by_c = ksa_divisor(a.view.c), a.view.by_m = ksa_divisor(a.view.m > 0 ? a.view.m : 1);
     a.by_bh = ksa_divisor(a.n_bh), a.by_kv_heads = ksa_divisor(a.n_kv_heads), a.by_group = ksa_divisor(a.group);
