@@ -282,7 +282,7 @@ def main():
                      "frac": round(attn_tflops / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": pre_traffic,
                      "traffic_source": pre_traffic_note,
                      "frac_of_mfma_only_loop": round(attn_tflops / ach["mfma_only_tflops_1_wave_per_simd"], 4)},
-        "roofline_decode": {"bound": "hbm", "kernel": "ksa_decode_split_matrix_kernel<128, 4, 256>", "achieved": round(dec_gbs, 1),
+        "roofline_decode": {"bound": "hbm", "kernel": "ksa_decode_split_matrix_kernel<128, 4, 256, true>", "achieved": round(dec_gbs, 1),
                             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(dec_gbs / HBM_PEAK_GBS, 4),
                             "traffic": dec_traffic,
                             "frac_of_stream_read": round(dec_gbs / ach["stream_read_gbs"], 4)},

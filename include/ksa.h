@@ -231,7 +231,8 @@ size_t ksa_decode_workspace_bytes(const ksa_params *params, int32_t n_splits);
  *   q [B, Hq, d] device bf16 contiguous; k_cache, v_cache device bf16 with cache_strides = {batch, head, row}
  *   in elements (NULL = contiguous [B, Hkv, cache_rows, d]); pos: device int32 [B], text index of the new
  *   token, whose K/V must already be in the cache; o [B, Hq, d] device bf16; lse device fp32 [B, Hq] or NULL.
- *   workspace: device, at least ksa_decode_workspace_bytes(params, n_splits); n_splits = 0 picks a default.
+ *   workspace: device, at least ksa_decode_workspace_bytes(params, n_splits).  n_splits = 0: the library chooses the number of
+ *   spans, for large problems by each sequence's own length.
  * Split-K over the visible rows: each workgroup streams one span of K and V rows once for all Hq/Hkv query
  * heads of a KV head and writes a partial (max, sum, o); a second kernel merges the spans by log-sum-exp.
  * Sequences whose pos is outside [0, n_text) produce NaN rows (device-side positions cannot be validated

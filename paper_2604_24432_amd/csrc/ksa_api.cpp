@@ -2,6 +2,8 @@
 // Every argument check happens before the first HIP call.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 
@@ -168,11 +170,89 @@ int ksa_prefill_bwd(ksa_layout *lay, const void *q, const void *k, const void *v
     return ksa_launch_prefill_bwd(a, stream);
 }
 
+namespace {
+
+// a span's record per query head: head_dim partial outputs + running max + running sum, fp32
+size_t record_bytes(const ksa_params *p) { return (size_t)p->n_q_heads * (p->head_dim + 2) * sizeof(float); }
+
+// Spans of a call that leaves their number to the library.
+struct DecodePlan {
+    int32_t n_splits;   // spans per sequence; 0: n_spans per KV head dealt by the sequences' lengths
+    int32_t n_spans;    // per KV head, all sequences together
+    bool wide;          // workgroups of 1024 threads (512 with eight query heads per KV head) instead of 256
+};
+
+/*
+ * rows: the most that a sequence can read.  All times below in us, per call, the same number of spans for every sequence unless they
+ * are called dealt; w: rows in units of 256 bytes of K, "n wide" / "n": n workgroups of 1024 / 256 threads.
+ *
+ * One span per sequence has no merge kernel.  It is ahead up to w = 256 (16/16 heads, 384 rows: batch 1 6.5, 128 workgroups 5.8;
+ * 32/8 heads: batch 1 9.3, 128 7.5), with 64 and more (sequence, KV head) pairs up to 384 (32/8, 384 rows, batch 16: 10.4, 512 11.2),
+ * and where it fills the chip once (256 pairs, wide: 16/16 heads, 1128 rows 19.7, 768 22.4; 8/4 heads 21.5, 24.2) or more
+ * (512 pairs, 640 rows: 24.8, 1024 31.2).
+ *
+ * Workgroups go to the compute units evenly, so a launch of a multiple of 256 ends together (32K, batch 4, 32/8 heads: 192 23.2, 256
+ * 20.9, 320 22.8, 384 21.3, 512 19.7): the number of spans is taken near `want` where the last round is best filled.
+ * `want`: short launches want a workgroup per unit (12/12 heads, d 64, 2000 rows: 256 7.6, 512 8.9); with more rows the loads in flight count:
+ * two on each unit with four heads per KV head (batch 4, 3808 rows: 256 18.0, 512 15.4, 768 16.3), three with one or two (8/4 heads, batch
+ * 8, 2176 rows: 256 wide 11.2, 512 11.1, 768 10.7), a wide one with eight (batch 64, 1128 rows: 256 wide 12.9, 512 14.0).  Spans of
+ * 24 rows at least, and up to 64 per sequence, which the merge kernel takes at once (8/1 heads, batch 1, 3808 rows: 64 10.4, 192 13.3).
+ *
+ * From a million rows on the spans are dealt by the sequences' lengths, which costs 1 - 1.5 to work out: lengths 1 : 4, batch 64 at 128K 511 ->
+ * 457, batch 16 133 -> 118, batch 8 in the paper's form 74.5 -> 68.7; all alike 658 -> 652, 173 -> 169, 97 -> 92 (before: about 1536 workgroups, none below
+ * 768 rows).  At least three per sequence (batch 64: 512 537, 768 507, 1536 457).
+ */
+DecodePlan plan_decode(const ksa_params *p, int64_t rows) {
+    const int64_t groups = (int64_t)p->batch * p->n_kv_heads, total = groups * rows;
+    const int64_t w = rows * p->head_dim / 128;
+    const int32_t heads = p->n_q_heads / p->n_kv_heads;
+    auto wide = [&](int64_t splits) {
+        if (splits * groups > 256) return false;
+        const int64_t per = w / splits;
+        return per >= (heads == 8 ? 64 : heads == 4 ? (splits == 1 ? 900 : 280) : 300);
+    };
+    if (w <= (groups < 64 ? 256 : 384) || (groups >= 192 && groups <= 256 && rows < 1536) ||
+        (groups > 256 && rows < (groups >= 512 ? 1536 : 768)))
+        return {1, p->batch, groups <= 256 && (wide(1) || (w >= 384 && groups >= 192))};
+    int64_t want = total < 30000 ? 256 : heads <= 2 ? (total < 65000 ? 512 : heads == 2 || total < 130000 ? 768 : 1280)
+                                                    : heads == 4 || total > 250000 ? 512 : 256;
+    const bool deal = total >= 1000000 && p->batch > 1 && p->batch <= 64;
+    if (deal)
+        want = heads == 1 ? 1536 : heads == 2 ? (groups <= 256 ? 768 : 1280) : groups <= 64 ? 512 : groups <= 128 ? 768 : 1536;
+    else if (total >= 800000)
+        want = 1536;
+    want = std::max<int64_t>(std::min(want, total / 24), 1);
+    // (records no larger than the static array of ksa_decode_fwd_static, unless those of the least number are)
+    const int64_t fit = std::max<int64_t>(KSA_DECODE_STATIC_SCRATCH_BYTES / (p->batch * record_bytes(p)), ksa_decode_default_splits(p));
+    if (deal && fit > 1) {
+        const int64_t spans = std::min(std::max<int64_t>(want / p->n_kv_heads, p->batch), fit * p->batch);
+        return {0, (int32_t)spans, false};
+    }
+    int64_t best = 1;
+    double best_score = -1e30;
+    for (int64_t s = std::max<int64_t>(1, want / (2 * groups)); s <= std::max<int64_t>(1, 3 * want / (2 * groups)); ++s) {
+        const double n = (double)(s * groups), fill = n / (256.0 * std::ceil(n / 256.0)), score = fill - 0.25 * std::fabs(std::log(n / want));
+        if (score > best_score) best = s, best_score = score;
+    }
+    best = std::min({best, std::max<int64_t>(64, rows / 512), fit});
+    return {(int32_t)best, (int32_t)(p->batch * best), wide(best)};
+}
+
+int64_t most_rows(const ksa_params *p, int32_t kind) {
+    if (kind == KSA_ROW_SUMMARY) return (int64_t)p->chunk_len + p->n_summary;
+    return (int64_t)(p->n_text / p->chunk_len) * p->n_summary + (int64_t)(p->window_chunks + 1) * p->chunk_len;
+}
+
+}  // namespace
+
 size_t ksa_decode_workspace_bytes(const ksa_params *p, int32_t n_splits) {
     if (ksa_validate_params(p) != KSA_OK || n_splits < 0) return 0;
-    if (n_splits == 0) n_splits = ksa_decode_default_splits(p);
-    // per (batch, query head, split): head_dim partial outputs + running max + running sum, fp32
-    return (size_t)p->batch * p->n_q_heads * n_splits * (p->head_dim + 2) * sizeof(float);
+    int64_t spans = (int64_t)p->batch * n_splits;
+    if (n_splits == 0) {   // (no less than the least that a call accepts)
+        spans = (int64_t)p->batch * ksa_decode_default_splits(p);
+        for (const int32_t kind : {KSA_ROW_TEXT, KSA_ROW_SUMMARY}) spans = std::max<int64_t>(spans, plan_decode(p, most_rows(p, kind)).n_spans);
+    }
+    return (size_t)spans * record_bytes(p);
 }
 
 namespace {
@@ -189,18 +269,25 @@ int decode_call(const ksa_params *p, int32_t kind, const void *q, const void *k_
     if (n_splits < 0 || n_splits > 1024) return KSA_ERR_INVALID_ARG;
     if (kind == KSA_ROW_SUMMARY && p->n_summary == 0) return KSA_ERR_INVALID_ARG;
     if (p->n_q_heads / p->n_kv_heads > 8) return KSA_ERR_UNSUPPORTED;
-    const bool chosen = n_splits != 0;
-    if (!chosen) n_splits = ksa_decode_default_splits(p);
-    if (workspace_bytes < ksa_decode_workspace_bytes(p, n_splits)) return KSA_ERR_WORKSPACE_TOO_SMALL;
-    // a summary token reads at most chunk_len + n_summary rows, whatever the cache holds: one span up to 768 rows (the
-    // shortest span of the default for a text token)
-    if (!chosen && kind == KSA_ROW_SUMMARY && p->chunk_len + p->n_summary <= 768) n_splits = 1;
+    const int64_t spans = (int64_t)p->batch * (n_splits != 0 ? n_splits : ksa_decode_default_splits(p));
+    if (workspace_bytes < (size_t)spans * record_bytes(p)) return KSA_ERR_WORKSPACE_TOO_SMALL;
+    DecodePlan plan;
+    if (n_splits != 0) {
+        plan = {n_splits, (int32_t)spans, n_splits > 1 && spans * p->n_kv_heads <= 256};
+    } else {
+        plan = plan_decode(p, most_rows(p, kind));
+        const int64_t fit = (int64_t)(workspace_bytes / record_bytes(p));   // at least one per sequence
+        if (plan.n_splits == 0)
+            plan.n_spans = (int32_t)std::min<int64_t>(plan.n_spans, fit);
+        else if (plan.n_spans > fit)
+            plan.n_splits = (int32_t)(fit / p->batch), plan.n_spans = p->batch * plan.n_splits;
+    }
     KsaDecodeLaunch a;
     default_strides(a.cache_strides, cache_strides, p->n_kv_heads, rows, p->head_dim);
     if (!strides_ok(a.cache_strides)) return KSA_ERR_INVALID_ARG;
     a.q = q, a.k_cache = k_cache, a.v_cache = v_cache, a.pos = pos, a.o = o, a.lse = lse;
     a.workspace = static_cast<float *>(workspace);
-    a.n_splits = n_splits;
+    a.n_splits = plan.n_splits, a.n_spans = plan.n_spans, a.wide = plan.wide;
     a.summary_capacity = s_cap;
     a.kind = kind;
     a.p = *p;
@@ -231,7 +318,8 @@ int ksa_decode_fwd_static(const ksa_params *p, const void *q, const void *k_cach
     float *buf = nullptr;
     const int rs = ksa_decode_static_scratch(&buf);
     if (rs != KSA_OK) return rs;
-    return decode_call(p, KSA_ROW_TEXT, q, k_cache, v_cache, pos, o, lse, cache_strides, buf, need, splits, stream);
+    return decode_call(p, KSA_ROW_TEXT, q, k_cache, v_cache, pos, o, lse, cache_strides, buf, KSA_DECODE_STATIC_SCRATCH_BYTES,
+                       n_splits, stream);
 }
 
 int ksa_decode_summary_fwd(const ksa_params *p, const void *q, const void *k_cache, const void *v_cache,

@@ -7,7 +7,9 @@
 // its 8 columns of the output for all query heads of the group, and every lane group runs its own online softmax on the rows
 // it saw.  The lane groups of a wave are merged by lane swaps, the waves through LDS, into one partial (max, sum, o) per query
 // head; a second kernel merges the spans of a sequence by log-sum-exp.  With one span per sequence (a summary token's few
-// rows, small caches) the workgroup stores the result itself and there is no second kernel.
+// rows, small caches) the workgroup stores the result itself and there is no second kernel.  How many spans: plan_decode() in
+// ksa_api.cpp.  With a million rows and more they are dealt by the sequences' lengths, which only the device knows: every workgroup
+// works out its own from all positions (batch 64 at 128K, lengths 1 : 4: 511 us, dealt 457; all alike 658, 655).
 //
 // Scores: with four and eight query heads per KV head from the matrix unit, S^T = K Q^T with v_mfma_f32_16x16x32_bf16: 16 cache
 // rows by G heads (repeated over the 16 columns), fp32 sums of exact products.  Lane l receives the scores of rows
@@ -15,7 +17,8 @@
 // of the other heads are a DPP move away.  With one and two heads they are dot products on the vector unit, 8 columns per lane
 // and a 4-step DPP all-reduce over the row's lanes.
 // What bounds it: HBM reads where the launch fills the chip (batch 64 at a 128K context, 4.33 GB: 655 us, 6.6 TB/s; scores on the
-// vector unit 670).  With eight heads the vector unit was the bound: batch 32, 64K context, 8/1 heads 58.1 / 37.2 us, window
+// vector unit 670; with few rows the two launches and their chains of loads: 2000 rows, batch 1, 8/4 heads 7.5, before 16.0, when
+// spans had 768 rows at least).  With eight heads the vector unit was the bound: batch 32, 64K context, 8/1 heads 58.1 / 37.2 us, window
 // 1024 with batch 64 41.1 / 28.2; batch 3, 20K, d 64 22.3 / 16.6.  With four: 32K, batch 4 and append 26.1 / 24.7, 128K, batch 1
 // 23.9 / 22.6.  With one head the matrix unit's operand reads (64 bytes of 16 rows instead of four whole rows) lost: batch 32,
 // 32K, 16/16 heads 163.9 us on the vector unit, 169.0.  With two heads likewise where there are few spans (vector / matrix unit,
@@ -28,6 +31,7 @@
 #include <mutex>
 #include <utility>
 
+#include "ksa_device.h"
 #include "ksa_internal.h"
 
 // Scratch memory of ksa_decode_fwd_static: the partial (o, max, sum) records of the spans, which ksa_decode_fwd
@@ -38,10 +42,6 @@ static __device__ __align__(256) unsigned char scratch[KSA_DECODE_STATIC_SCRATCH
 
 namespace {
 
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int U = 4;         // row loads in flight per lane, K and V each
 
 struct DecodeArgs {
@@ -51,11 +51,13 @@ struct DecodeArgs {
     float *lse;
     float *ws;
     int64_t cs[3];   // {batch, head, row} strides of the caches in elements
-    int32_t n_splits, s_cap;
+    int32_t n_splits, s_cap;   // n_splits: spans per sequence; 0: the n_spans of a KV head are dealt by the sequences' lengths
+    int32_t n_spans;           // per KV head, all sequences together
     int32_t batch;
     int32_t kind, self_only;   // KSA_ROW_TEXT / KSA_ROW_SUMMARY query; flag bit 0 of the parameters
     int32_t c, m, C, n_text;
     int32_t n_q_heads, n_kv_heads;
+    KsaDivisor by_c, by_m, by_slots;   // chunk_len, n_summary, window_chunks + 1
     float scale_log2e;
     float q_scale, score_scale;   // scale_log2e in two factors, the first a power of two
 };
@@ -77,15 +79,15 @@ __device__ __forceinline__ Ranges visible_rows(const DecodeArgs &a, int p) {
     Ranges R = {0, 0, 0, 0, 0, 0};
     if (!valid_pos(a, p)) return R;
     if (a.kind == KSA_ROW_SUMMARY) {
-        const int j = p / a.m, slot = p - j * a.m;
+        const int j = ksa_div(p, a.by_m), slot = p - j * a.m;
         R.off0 = a.self_only ? p : j * a.m;
         R.n0 = a.self_only ? 1 : slot + 1;
-        R.off1 = a.s_cap + (j % (a.C + 1)) * a.c;
+        R.off1 = a.s_cap + (j - ksa_div(j, a.by_slots) * (a.C + 1)) * a.c;
         R.n1 = a.c;
         return R;
     }
-    const int j = p / a.c, r = p - j * a.c;
-    const int slot = j % (a.C + 1);
+    const int j = ksa_div(p, a.by_c), r = p - j * a.c;
+    const int slot = j - ksa_div(j, a.by_slots) * (a.C + 1);
     R.n0 = (j - a.C > 0 ? j - a.C : 0) * a.m;
     R.off1 = a.s_cap;
     R.n1 = slot * a.c + r + 1;
@@ -176,9 +178,99 @@ __device__ __forceinline__ float swap8(float x) {   // lane l ^ 8: row_ror 8
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xf, 0xf, false));
 }
 
+// Spans dealt by length: how the n_spans of a KV head are shared out among at most 64 sequences; lane l holds sequence l's part.
+// Sequence b takes n_b = max(1, ceil(N_b / per)) of them, `per` nearly the smallest for which they are enough.  With T rows in all,
+// per = T / (n_spans - batch) always is: sum(n_b) <= T / per + batch.  The merge kernel works the same out again from the same numbers.
+struct Deal {
+    Ranges R;
+    int n, behind;   // spans of the sequence; of it and of those in front of it
+};
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_scan(int x) { return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false); }
+__device__ __forceinline__ Deal deal_spans(const DecodeArgs &a) {
+    const int lane = threadIdx.x & 63;
+    const bool any = lane < a.batch;
+    Deal d;
+    d.R = visible_rows(a, a.pos[min(lane, a.batch - 1)]);
+    const int N = d.R.n0 + d.R.n1 + d.R.n2;
+    if (__builtin_amdgcn_ballot_w64(N != __builtin_amdgcn_readfirstlane(N)) == 0) {   // all alike (lanes without a sequence repeat the last one)
+        d.n = (int)((unsigned)a.n_spans / (unsigned)a.batch);
+        d.behind = min(lane + 1, a.batch) * d.n;
+        return d;
+    }
+    const float rows = any ? (float)N : 0.f;
+    auto total = [](float x) {
+        x = row_allreduce<16>(x);
+        x += swap16(x);
+        return x + swap32(x);
+    };
+    auto spans = [&](float per) { return any ? fmaxf(ceilf(rows * __builtin_amdgcn_rcpf(per)), 1.f) : 0.f; };
+    // (the factors keep a quotient that should be whole from being rounded up to the next number)
+    const float all = fmaxf(total(rows), 1.f), most = (float)a.n_spans;
+    float lo = all * __builtin_amdgcn_rcpf(most) * 1.0001f, hi = all * __builtin_amdgcn_rcpf(most - (float)a.batch) * 1.0002f;
+    float per = lo;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (total(spans(per)) <= most) hi = per; else lo = per;
+        per = 0.5f * (lo + hi);
+    }
+    d.n = (int)spans(hi);
+    int x = d.n;   // sums over the lanes up to this one
+    x = dpp_scan<0x111, 0xf>(x);   // row_shr 1, 2, 4, 8
+    x = dpp_scan<0x112, 0xf>(x);
+    x = dpp_scan<0x114, 0xf>(x);
+    x = dpp_scan<0x118, 0xf>(x);
+    x = dpp_scan<0x142, 0xa>(x);   // row_bcast 15: the last lane of rows 0 and 2 to rows 1 and 3
+    x = dpp_scan<0x143, 0xc>(x);   // row_bcast 31
+    d.behind = x;
+    return d;
+}
+
+// What a workgroup works on: rows [v0, v1) of the visible rows R of sequence b for KV head hkv; b < 0: nothing.  Wave-uniform.
+struct Span {
+    Ranges R;
+    int b, hkv, v0, v1;
+    int record;   // number of the span's record among those of a query head
+};
+template <bool DEAL>
+__device__ __forceinline__ Span find_span(const DecodeArgs &a) {
+    Span s;
+    const int x = blockIdx.x;
+    if constexpr (!DEAL) {
+        s.b = blockIdx.z, s.hkv = blockIdx.y, s.record = s.b * a.n_splits + x;
+        s.R = visible_rows(a, a.pos[s.b]);
+        const int N = s.R.n0 + s.R.n1 + s.R.n2, per = (N + a.n_splits - 1) / a.n_splits;
+        s.v0 = x * per, s.v1 = min(N, s.v0 + per);
+        return s;
+    }
+    // one wave deals (all of them took the launch 4 % at batch 64); workgroups by sequence, KV head, span, the last fastest
+    __shared__ int found[9];
+    if (threadIdx.x < 64) {
+        const Deal d = deal_spans(a);
+        const uint64_t from = __builtin_amdgcn_ballot_w64(d.behind * a.n_kv_heads > x);   // (lanes behind the last sequence hold the sum of all)
+        const int at = from ? __builtin_ctzll(from) : 0;
+        if ((int)threadIdx.x == at) {
+            found[0] = from ? at : -1, found[1] = d.R.off0, found[2] = d.R.n0, found[3] = d.R.off1, found[4] = d.R.n1, found[5] = d.R.off2;
+            found[6] = d.R.n2, found[7] = d.n, found[8] = d.behind;
+        }
+    }
+    __syncthreads();
+    auto get = [&](int y) { return __builtin_amdgcn_readfirstlane(found[y]); };
+    s.b = get(0);
+    s.R = {get(1), get(2), get(3), get(4), get(5), get(6)};
+    const int N = s.R.n0 + s.R.n1 + s.R.n2, n = get(7), first = get(8) - n;
+    const int in_b = x - first * a.n_kv_heads;
+    s.hkv = (int)((unsigned)in_b / (unsigned)n);
+    const int split = in_b - s.hkv * n;
+    const int per = (N + n - 1) / n;
+    s.v0 = split * per, s.v1 = min(N, s.v0 + per);
+    s.record = first + split;
+    return s;
+}
+
 // the waves' partial results -> the workgroup's: its record in the workspace, or with one span per sequence the result
 template <int D, int G, int NT>
-__device__ __forceinline__ void merge_waves(const DecodeArgs &a, int split, int hkv, int b, const float (&sh_o)[NT / 64][G][D],
+__device__ __forceinline__ void merge_waves(const DecodeArgs &a, const Span &s, const float (&sh_o)[NT / 64][G][D],
                                             const float (&sh_m)[NT / 64][G], const float (&sh_l)[NT / 64][G]) {
     constexpr int NW = NT / 64;
     __syncthreads();
@@ -193,11 +285,11 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs &a, int split, int 
             const float w = __builtin_amdgcn_exp2f(sh_m[y][g] - M);
             acc += sh_o[y][g][col] * w, den += sh_l[y][g] * w;
         }
-        const int hq = hkv * G + g;
+        const int hq = s.hkv * G + g;
         if (a.n_splits == 1) {
-            store_result<D>(a, b, hq, col, valid_pos(a, a.pos[b]), acc, den, M);
+            store_result<D>(a, s.b, hq, col, valid_pos(a, a.pos[s.b]), acc, den, M);
         } else {
-            float *rec = a.ws + (((int64_t)b * a.n_q_heads + hq) * a.n_splits + split) * (D + 2);
+            float *rec = a.ws + ((int64_t)hq * a.n_spans + s.record) * (D + 2);
             rec[col] = acc;
             if (col == 0) rec[D] = M, rec[D + 1] = den;
         }
@@ -205,21 +297,20 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs &a, int split, int 
 }
 
 // partial record in the workspace: [D] unnormalised o, then running max (log2 domain), then running sum
-template <int D, int G, int NT>
+template <int D, int G, int NT, bool DEAL>
 __global__ __launch_bounds__(NT) void ksa_decode_split_kernel(const DecodeArgs a) {
     constexpr int LPR = D / 8;          // lanes per cache row
     constexpr int RPW = 64 / LPR;       // rows per wavefront load
     constexpr int NW = NT / 64;
     constexpr int R_IT = NW * RPW * U;  // rows per workgroup iteration
 
-    const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int chunk = lane % LPR, gi = lane / LPR;
 
-    const Ranges R = visible_rows(a, a.pos[b]);
-    const int N = R.n0 + R.n1 + R.n2;
-    const int per = (N + a.n_splits - 1) / a.n_splits;
-    const int v0 = split * per, v1 = min(N, v0 + per);
+    const Span span = find_span<DEAL>(a);
+    const int b = span.b, hkv = span.hkv, v0 = span.v0, v1 = span.v1;
+    if (DEAL && b < 0) return;
+    const Ranges R = span.R;
 
     float qf[G][8];
 #pragma unroll
@@ -321,11 +412,11 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_kernel(const DecodeArgs a
             if (chunk == 0) sh_m[wave][g] = M, sh_l[wave][g] = l;
         }
     }
-    merge_waves<D, G, NT>(a, split, hkv, b, sh_o, sh_m, sh_l);
+    merge_waves<D, G, NT>(a, span, sh_o, sh_m, sh_l);
 }
 
 // the same with scores from the matrix unit: four and eight query heads per KV head
-template <int D, int G, int NT>
+template <int D, int G, int NT, bool DEAL>
 __global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const DecodeArgs a) {
     constexpr int LPR = D / 8;          // lanes per V row
     constexpr int RPW = 64 / LPR;       // V rows per wavefront load
@@ -335,15 +426,14 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const Decod
     constexpr int R_IT = NW * RPW * U;  // rows per workgroup iteration
     static_assert(KB * KS == U && U == 4, "as many loads of K as of V");
 
-    const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int chunk = lane % LPR, gi = lane / LPR;
     const int v_row = (D == 64 ? 16 * (gi & 1) : 0) + 4 * (lane >> 4);   // the lane's V rows: v_row .. v_row + 3
 
-    const Ranges R = visible_rows(a, a.pos[b]);
-    const int N = R.n0 + R.n1 + R.n2;
-    const int per = (N + a.n_splits - 1) / a.n_splits;
-    const int v0 = split * per, v1 = min(N, v0 + per);
+    const Span span = find_span<DEAL>(a);
+    const int b = span.b, hkv = span.hkv, v0 = span.v0, v1 = span.v1;
+    if (DEAL && b < 0) return;
+    const Ranges R = span.R;
 
     bf16x8 qreg[KS];
     {
@@ -462,59 +552,99 @@ __global__ __launch_bounds__(NT) void ksa_decode_split_matrix_kernel(const Decod
             if (gi == 0) sh_o[wave][g][chunk * 8 + e] = sum;
         }
     });
-    merge_waves<D, G, NT>(a, split, hkv, b, sh_o, sh_m, sh_l);
+    merge_waves<D, G, NT>(a, span, sh_o, sh_m, sh_l);
 }
 
-// one workgroup of D threads per (batch, query head): log-sum-exp merge of the spans
-template <int D>
-__global__ __launch_bounds__(D) void ksa_decode_merge_kernel(const DecodeArgs a) {
-    const int hq = blockIdx.x, b = blockIdx.y, col = threadIdx.x, lane = threadIdx.x & 63;
-    const float *rec = a.ws + ((int64_t)b * a.n_q_heads + hq) * a.n_splits * (D + 2);
+// One workgroup per (batch, query head): log-sum-exp merge of the spans.  Part y of its MP parts of D threads takes spans
+// MU y .. MU y + MU - 1 of every MP MU, whose loads travel together, the first ones beside those of the maxima and sums; the weights of
+// 64 spans live in the lanes of every wave.
+constexpr int MU = 8;
+template <int D, bool DEAL, int MP>
+__global__ __launch_bounds__(MP * D) void ksa_decode_merge_kernel(const DecodeArgs a) {
+    const int hq = blockIdx.x, b = blockIdx.y, col = threadIdx.x % D, lane = threadIdx.x & 63;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / D);
+    int first = b * a.n_splits, n = a.n_splits;
+    if constexpr (DEAL) {
+        __shared__ int found[2];
+        if (threadIdx.x < 64) {
+            const Deal d = deal_spans(a);
+            if ((int)threadIdx.x == b) found[0] = d.n, found[1] = d.behind - d.n;   // (the first wave's lane: at most 64 sequences)
+        }
+        __syncthreads();
+        n = __builtin_amdgcn_readfirstlane(found[0]), first = __builtin_amdgcn_readfirstlane(found[1]);
+    }
+    const float *rec = a.ws + ((int64_t)hq * a.n_spans + first) * (D + 2);
+    auto at = [&](int s) { return rec + (int64_t)min(s, n - 1) * (D + 2); };
+    float o[MU];
+    auto load = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < MU; ++u) o[u] = at(s + u)[col];
+    };
+    auto stats = [&](int s, float &m, float &l) { m = at(s + lane)[D], l = s + lane < n ? at(s + lane)[D + 1] : 0.f; };
+    float m, l, acc = 0.f, den = 0.f;
+    stats(0, m, l);
+    load(MU * part);
     const bool valid = valid_pos(a, a.pos[b]);
-    float M = -1e30f;
-    for (int s = lane; s < a.n_splits; s += 64) M = fmaxf(M, rec[s * (D + 2) + D]);
+    float M = m;
+    for (int s = 64; s < n; s += 64) M = fmaxf(M, at(s + lane)[D]);
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
-    float acc = 0.f, den = 0.f;
-#pragma unroll 8
-    for (int s = 0; s < a.n_splits; ++s) {   // unrolled: the loads of several spans travel together
-        const float wgt = __builtin_amdgcn_exp2f(rec[s * (D + 2) + D] - M);
-        acc += rec[s * (D + 2) + col] * wgt;
-        den += rec[s * (D + 2) + D + 1] * wgt;
+    for (int s = 0; s < n; s += 64) {
+        if (s > 0) stats(s, m, l);
+        const float w = __builtin_amdgcn_exp2f(m - M);
+        den += l * w;
+        for (int x = MU * part; x < min(64, n - s); x += MP * MU) {
+            if (s + x != MU * part) load(s + x);
+#pragma unroll
+            for (int u = 0; u < MU; ++u)
+                if (s + x + u < n) acc += o[u] * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), x + u));
+        }
     }
+    if constexpr (MP > 1) {
+        __shared__ float parts[MP][D];
+        parts[part][col] = acc;
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int y = 1; y < MP; ++y) acc += parts[y][col];
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) den += __shfl_xor(den, d);
     store_result<D>(a, b, hq, col, valid, acc, den, M);
 }
 
-template <int D, int G, int NT>
+template <int D, int G, int NT, bool DEAL>
 void launch(const DecodeArgs &a, hipStream_t st) {
-    const dim3 grid(a.n_splits, a.n_kv_heads, a.batch);
+    const dim3 grid = DEAL ? dim3(a.n_spans * a.n_kv_heads) : dim3(a.n_splits, a.n_kv_heads, a.batch);
     if constexpr (G >= 4)
-        hipLaunchKernelGGL((ksa_decode_split_matrix_kernel<D, G, NT>), grid, dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((ksa_decode_split_matrix_kernel<D, G, NT, DEAL>), grid, dim3(NT), 0, st, a);
     else
-        hipLaunchKernelGGL((ksa_decode_split_kernel<D, G, NT>), grid, dim3(NT), 0, st, a);
-    if (a.n_splits > 1) hipLaunchKernelGGL(ksa_decode_merge_kernel<D>, dim3(a.n_q_heads, a.batch), dim3(D), 0, st, a);
+        hipLaunchKernelGGL((ksa_decode_split_kernel<D, G, NT, DEAL>), grid, dim3(NT), 0, st, a);
+    if (a.n_splits == 1) return;
+    const dim3 outputs(a.n_q_heads, a.batch);
+    if (a.n_spans > 8 * a.batch)
+        hipLaunchKernelGGL((ksa_decode_merge_kernel<D, DEAL, 4>), outputs, dim3(4 * D), 0, st, a);
+    else
+        hipLaunchKernelGGL((ksa_decode_merge_kernel<D, DEAL, 1>), outputs, dim3(D), 0, st, a);
 }
 
-// 256 threads per span; with no more spans than compute units 1024 (512 with eight query heads per KV head, whose
-// accumulators take more registers), i.e. four times the loads in flight per unit.  Kernels of one step, 256 / 1024 threads, 32/8
-// heads: 128K context, batch 1 (168 spans) 24.9 / 22.7 us; 32K, batch 4 (160) 25.2 / 22.3; 16K, batch 16 (256) 30.2 / 28.7; 128K,
-// batch 2 (336) 35.3 / 39.9; 64K, d 64, batch 8 (640) 30.6 / 37.0.  8/1 heads, 256 / 512: 128K, batch 4 (84) 29.2 / 24.2; 64K,
-// batch 32 (320) 39.0 / 42.4.  16/16 heads: 64K, batch 2 (320) 27.2 / 30.0; 8/4: 64K, batch 8 (320) 31.1 / 33.0.
 template <int D, int G>
-void launch_group(const DecodeArgs &a, hipStream_t st) {
-    if (a.n_splits == 1 || (int64_t)a.batch * a.n_splits * a.n_kv_heads > 256)
-        launch<D, G, 256>(a, st);
+void launch_group(const DecodeArgs &a, bool wide, hipStream_t st) {
+    if (a.n_splits == 0)
+        launch<D, G, 256, true>(a, st);   // (a million rows and more)
+    else if (wide)
+        launch<D, G, G == 8 ? 512 : 1024, false>(a, st);
     else
-        launch<D, G, G == 8 ? 512 : 1024>(a, st);
+        launch<D, G, 256, false>(a, st);
 }
 
 template <int D>
-int launch_all(const DecodeArgs &a, hipStream_t st) {
+int launch_all(const DecodeArgs &a, bool wide, hipStream_t st) {
     switch (a.n_q_heads / a.n_kv_heads) {
-        case 1: launch_group<D, 1>(a, st); break;
-        case 2: launch_group<D, 2>(a, st); break;
-        case 4: launch_group<D, 4>(a, st); break;
-        case 8: launch_group<D, 8>(a, st); break;
+        case 1: launch_group<D, 1>(a, wide, st); break;
+        case 2: launch_group<D, 2>(a, wide, st); break;
+        case 4: launch_group<D, 4>(a, wide, st); break;
+        case 8: launch_group<D, 8>(a, wide, st); break;
         default: return KSA_ERR_UNSUPPORTED;
     }
     return hipGetLastError() == hipSuccess ? KSA_OK : KSA_ERR_HIP;
@@ -522,11 +652,8 @@ int launch_all(const DecodeArgs &a, hipStream_t st) {
 
 }  // namespace
 
-// Enough spans that the launch has about six workgroups per compute unit (1536 in all; 128K cache, 32/8 heads, batch 16:
-// 768 workgroups 172.6 us, 1024 182.3, 1536 173.7, 2048 185.3, 3072 178.4; batch 64: 1024 702, 1536 656, 2048 775, 2560 659), but
-// no span shorter than 768 rows, whose fixed costs the workgroups would repeat: 64K, batch 8, 640 workgroups 54.5, 1280 52.7;
-// 128K, batch 2, 336 35.8, 672 33.0.  With few sequences the numbers of rounds count more than the spans' length: 128K, batch 1, 168
-// workgroups 23.2, 224 20.3, 272 24.6; 32K, batch 4, 160 23.3, 256 18.1, 320 22.0.
+// The spans per sequence that the least workspace of a call without a number of its own holds records for: about 1536 workgroups, none
+// with less than 768 rows.  What such a call takes is plan_decode() in ksa_api.cpp.
 int ksa_decode_default_splits(const ksa_params *p) {
     const int64_t groups = (int64_t)p->batch * p->n_kv_heads;
     const int64_t rows = (int64_t)(p->n_text / p->chunk_len) * p->n_summary + (int64_t)(p->window_chunks + 1) * p->chunk_len;
@@ -565,7 +692,7 @@ int ksa_launch_decode(const KsaDecodeLaunch &L, void *stream) {
     a.lse = L.lse;
     a.ws = L.workspace;
     for (int x = 0; x < 3; ++x) a.cs[x] = L.cache_strides[x];
-    a.n_splits = L.n_splits;
+    a.n_splits = L.n_splits, a.n_spans = L.n_spans;
     a.s_cap = L.summary_capacity;
     a.kind = L.kind;
     a.self_only = (L.p.flags & 1u) ? 1 : 0;
@@ -573,6 +700,7 @@ int ksa_launch_decode(const KsaDecodeLaunch &L, void *stream) {
     a.m = L.p.n_summary;
     a.C = L.p.window_chunks;
     a.n_text = L.p.n_text;
+    a.by_c = ksa_divisor(a.c), a.by_m = ksa_divisor(std::max(a.m, 1)), a.by_slots = ksa_divisor(a.C + 1);
     a.n_q_heads = L.p.n_q_heads;
     a.n_kv_heads = L.p.n_kv_heads;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
@@ -583,7 +711,7 @@ int ksa_launch_decode(const KsaDecodeLaunch &L, void *stream) {
     a.q_scale = std::ldexp(1.f, std::max(std::min(exponent - 1, 0), -8)), a.score_scale = a.scale_log2e / a.q_scale;
     a.batch = L.p.batch;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (L.p.head_dim == 128) return launch_all<128>(a, st);
-    if (L.p.head_dim == 64) return launch_all<64>(a, st);
+    if (L.p.head_dim == 128) return launch_all<128>(a, L.wide, st);
+    if (L.p.head_dim == 64) return launch_all<64>(a, L.wide, st);
     return KSA_ERR_UNSUPPORTED;
 }

@@ -22,7 +22,7 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # what the benchmark workload launches (head_dim 128, four query heads per KV head)
-KERNELS = (("prefill", "ksa_prefill_kernel<128, false>"), ("decode", "ksa_decode_split_matrix_kernel<128, 4, 256>"))
+KERNELS = (("prefill", "ksa_prefill_kernel<128, false>"), ("decode", "ksa_decode_split_matrix_kernel<128, 4, 256, true>"))
 
 
 def per_kernel(folder: str, counter: str):
