@@ -8,13 +8,20 @@
 // three) and fill each other's start, barriers and end.  It reads K and V as they are: no key-major copy of V has to be
 // written first.  What it costs: every operand read from LDS feeds one MFMA instead of two, and V^T comes from
 // transposing reads.
-// What bounds it: 4K tokens (2 x 4096, 32/8 heads, d 128: 190 MB, 47 GFLOP) take 90 us (before: 135) of which about 40 are
+// What bounds it: 4K tokens (2 x 4096, 32/8 heads, d 128: 190 MB, 47 GFLOP) take 89 us (before: 135) of which about 40 are
 // the start and end of the workgroups (Q rows from HBM, stores; 1 tile per workgroup alone: 48 us) and 50 the tiles: the
 // matrix unit is busy 39 % of the time that both waves of a SIMD are there.  At 17 and more tiles per workgroup it is 55 %, at
 // 2.0 of 2.4 GHz under the board's power cap (1370 - 1385 of 1400 W), at 15 % more energy per product than the pipelined kernel
 // (64K: 1.09 against 1.18 PFLOP/s).  Neither deeper prefetch (5 stages of 32 keys), three workgroups per compute unit, nor the
 // scores of the next tile under the exponentials of this one changed the time by more than 3 %; the loads dealt between the
-// MFMAs, the row offsets kept from tile to tile and the order of the query tiles did (together 10 - 30 %).
+// MFMAs, the row offsets kept from tile to tile and the order of the query tiles did (together 10 - 30 %).  Of a workgroup's 20 us at
+// 4K tokens 2.7 pass until its first tile is requested, 2.7 until that tile is there, 13.2 in the loop (6 tiles), 1.6 in its end;
+// outside the tile loops a wave issued some 1550 of its 2620 vector instructions: row norms as dot products of pairs, the largest K norm
+// by lane moves, output rows as offsets from one address and masks by constants where every row sees a tile's beginning take 2.5 % off
+// (91.8 -> 89.2 us, window of 1024 at 16K 314.6 -> 311.2).  Workgroups that take several query tiles and request the next one's rows
+// ahead were no faster (the other workgroup of the unit fills those times already).
+// The LDS is the other limit: per tile and workgroup K takes 512 clocks of it, V 1024 (transposing reads run at half rate), the
+// loads' writes 256, two workgroups 3584; a tile takes 3560 (1.87 us at 1.9 GHz) with 17 tiles in a row.
 // The line between the two kernels: takes_direct() in ksa_layout.cpp.  dQ (three products per visible pair instead of two)
 // is ahead of ksa_bwd_dq_kernel nearly everywhere (dq_takes_direct()): 103 against 221 us at 2 x 4096 tokens.  It spills 2
 // registers (d 64: 7), outside the blocks that hold its MFMAs.
@@ -75,6 +82,7 @@ struct DirectArgs {
     int32_t mixed_tiles;                // a key tile may hold the last summaries and the first text rows of a list
     int64_t aug_len;
     float scale_log2e;
+    float static_shift;                 // 32 / scale_log2e
     // dQ only: o is dq, the others as in ksa_prefill_bwd.hip
     const __bf16 *g;                    // dLoss/dO
     int64_t gs[3];
@@ -90,7 +98,20 @@ __device__ __forceinline__ float other_half(float x) {
     return __builtin_bit_cast(float, (threadIdx.x & 32) ? r[0] : r[1]);
 }
 
+__device__ __forceinline__ float other_row(float x) {
+    // value held by lane l^16
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __builtin_bit_cast(float, (threadIdx.x & 16) ? r[0] : r[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+    return fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false)));
+}
+
 #define KSA_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 template <int D>
 struct Tile {
@@ -317,17 +338,24 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         const float *src = a.knorm_parts + (int64_t)bh * a.norm_parts;
 #pragma unroll
         for (int i = 0; i < NORM_PARTS; i += 64) kmax2 = fmaxf(kmax2, src[min(i + lane, a.norm_parts - 1)]);   // (the last one repeats)
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) kmax2 = fmaxf(kmax2, __shfl_xor(kmax2, d));
+        kmax2 = dpp_max<0xB1>(kmax2);    // quad_perm [1,0,3,2]
+        kmax2 = dpp_max<0x4E>(kmax2);    // quad_perm [2,3,0,1]
+        kmax2 = dpp_max<0x141>(kmax2);   // row_half_mirror
+        kmax2 = dpp_max<0x140>(kmax2);   // row_mirror
+        kmax2 = fmaxf(kmax2, other_row(kmax2));
+        kmax2 = fmaxf(kmax2, other_half(kmax2));
         if (rest == 0 && tid == 0) a.knorm[bh] = kmax2;
         float n2 = 0.f;
 #pragma unroll
         for (int s = 0; s < T::KS; ++s)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) n2 = fmaf((float)qreg[s][e], (float)qreg[s][e], n2);
+            for (int e = 0; e < 8; e += 2) {
+                const bf16x2 x = {qreg[s][e], qreg[s][e + 1]};
+                n2 = __builtin_amdgcn_fdot2_f32_bf16(x, x, n2, false);
+            }
         n2 += other_half(n2);
-        const float bound = __builtin_sqrtf(n2 * kmax2) * 1.002f;
-        m_static = bound - 32.f / sl;
+        const float bound = __builtin_amdgcn_sqrtf(n2 * kmax2) * 1.002f;   // (the factor covers the rounding of all this)
+        m_static = bound - a.static_shift;
         static_ok = !running_max && __builtin_amdgcn_ballot_w64(!(bound * sl <= 60.f)) == 0;
     }
 
@@ -369,10 +397,17 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 const int y0 = x0 + kb * 32, base_t = y0 + 4 * h - t_lo, base_s = y0 + 4 * h - s_lo;
                 const unsigned span_t = (unsigned)max(t_hi - t_lo, 0), span_s = (unsigned)max(s_hi - s_lo, 0);
                 if (y0 >= t_first || y0 + 32 <= n_s) {
-                    const int base = y0 >= t_first ? base_t : base_s;
-                    const unsigned span = y0 >= t_first ? span_t : span_s;
+                    const bool txt = y0 >= t_first;
+                    if (y0 >= (txt ? ft_lo : fs_lo)) {
+                        const int end = (txt ? t_hi : s_hi) - y0 - 4 * h;
 #pragma unroll
-                    for (int g = 0; g < 16; ++g) sacc[g] = (unsigned)(base + 8 * (g / 4) + g % 4) < span ? sacc[g] : -INFINITY;
+                        for (int g = 0; g < 16; ++g) sacc[g] = 8 * (g / 4) + g % 4 < end ? sacc[g] : -INFINITY;
+                    } else {
+                        const int base = txt ? base_t : base_s;
+                        const unsigned span = txt ? span_t : span_s;
+#pragma unroll
+                        for (int g = 0; g < 16; ++g) sacc[g] = (unsigned)(base + 8 * (g / 4) + g % 4) < span ? sacc[g] : -INFINITY;
+                    }
                 } else {
 #pragma unroll
                     for (int g = 0; g < 16; ++g) {
@@ -466,13 +501,22 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 const int base_t = x0 + 4 * h - t_lo, base_s = x0 + 4 * h - s_lo;
                 const unsigned span_t = (unsigned)max(t_hi - t_lo, 0), span_s = (unsigned)max(s_hi - s_lo, 0);
                 if (x0 >= t_first || x1 <= n_s) {   // one kind of key
-                    const int base = x0 >= t_first ? base_t : base_s;
-                    const unsigned span = x0 >= t_first ? span_t : span_s;
+                    const bool txt = x0 >= t_first;
+                    if (x0 >= (txt ? ft_lo : fs_lo)) {   // ... whose first one every row sees: a compare with a constant each
+                        const int end = (txt ? t_hi : s_hi) - x0 - 4 * h;
 #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
+                        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int g = 0; g < 16; ++g)
-                            sacc[kb][g] = (unsigned)(base + kb * 32 + 8 * (g / 4) + g % 4) < span ? sacc[kb][g] : -INFINITY;
+                            for (int g = 0; g < 16; ++g) sacc[kb][g] = kb * 32 + 8 * (g / 4) + g % 4 < end ? sacc[kb][g] : -INFINITY;
+                    } else {
+                        const int base = txt ? base_t : base_s;
+                        const unsigned span = txt ? span_t : span_s;
+#pragma unroll
+                        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                            for (int g = 0; g < 16; ++g)
+                                sacc[kb][g] = (unsigned)(base + kb * 32 + 8 * (g / 4) + g % 4) < span ? sacc[kb][g] : -INFINITY;
+                    }
                 } else {
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
@@ -567,13 +611,27 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 *reinterpret_cast<bf16x4 *>(stg + r * T::STAGE_ROW + (db * 32 + g4 * 8 + h * 4) * 2) = pk;
             }
         const int piece = lane % T::CH;
-        __bf16 *const obase = a.o + b * a.os[0] + hq * a.os[2] + piece * 8;
+        // Row k of the wave lies k + (chunk borders in between) * other rows behind its first: see prepare.
+        const bool txt = q_space == KSA_SPACE_TEXT;
+        const int per = txt ? a.c : a.m, other = txt ? a.m : a.c;
+        const int j0 = ksa_div(w_begin, KsaDivisor{txt ? a.by_c.mul : a.by_m.mul, txt ? a.by_c.shift : a.by_m.shift}), phase = w_begin - j0 * per;
+        const unsigned mul = per < 64 ? (txt ? a.small_c : a.small_m) : 1024u, add = (per < 64 ? phase : 64 - min(64, per - phase)) * mul;
+        __bf16 *const obase = a.o + b * a.os[0] + ((int64_t)w_begin + (txt ? 0 : a.c) + (int64_t)j0 * other) * a.os[1] + hq * a.os[2] + piece * 8;
+        u32x4 x[32 / T::RPI];
 #pragma unroll
-        for (int i = 0; i < 32 / T::RPI; ++i) {
+        for (int i = 0; i < 32 / T::RPI; ++i) x[i] = *reinterpret_cast<const u32x4 *>(stg + (T::RPI * i + lane / T::CH) * T::STAGE_ROW + piece * 16);
+        auto store = [&](int i) {
             const int row = T::RPI * i + lane / T::CH;
-            const u32x4 x = *reinterpret_cast<const u32x4 *>(stg + row * T::STAGE_ROW + piece * 16);
-            if (w_begin + row < q_end)
-                *reinterpret_cast<u32x4 *>(obase + (int64_t)row_of(a, q_space, w_begin + row) * a.os[1]) = x;
+            const unsigned d_rows = row + ((__umul24(row, mul) + add) >> 16) * (unsigned)other;   // (less than 2^30)
+            *reinterpret_cast<u32x4 *>(obase + (uint64_t)d_rows * (uint64_t)a.os[1]) = x[i];
+        };
+        if (w_begin + 32 <= q_end) {
+#pragma unroll
+            for (int i = 0; i < 32 / T::RPI; ++i) store(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 32 / T::RPI; ++i)
+                if (w_begin + T::RPI * i + lane / T::CH < q_end) store(i);
         }
         if constexpr (GRAD) return;
         if (a.lse && h == 0 && w_begin + r < q_end) {
@@ -708,6 +766,7 @@ int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_parts, flo
     a.running_text = L.running_text, a.running_sum = L.running_sum;
     a.knorm = knorm;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
+    a.static_shift = 32.f / a.scale_log2e;
     const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);
     if (n_wg >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
