@@ -54,8 +54,7 @@ struct KsaDivisor {
     uint32_t mul, shift;
 };
 inline KsaDivisor ksa_divisor(int d) {
-    uint32_t s = 0;
-    while (((int64_t)1 << s) < d) ++s;
+    const uint32_t s = d > 1 ? 32u - (uint32_t)__builtin_clz((unsigned)d - 1u) : 0u;
     return {(uint32_t)(((uint64_t)1 << (31 + s)) / (uint64_t)d + 1), s};
 }
 __device__ __forceinline__ int ksa_div(int x, const KsaDivisor &d) {
