@@ -20,8 +20,6 @@
 // by lane moves, output rows as offsets from one address and masks by constants where every row sees a tile's beginning take 2.5 % off
 // (91.8 -> 89.2 us, window of 1024 at 16K 314.6 -> 311.2).  Workgroups that take several query tiles and request the next one's rows
 // ahead were no faster (the other workgroup of the unit fills those times already).
-// The LDS is the other limit: per tile and workgroup K takes 512 clocks of it, V 1024 (transposing reads run at half rate), the
-// loads' writes 256, two workgroups 3584; a tile takes 3560 (1.87 us at 1.9 GHz) with 17 tiles in a row.
 // The line between the two kernels: takes_direct() in ksa_layout.cpp.  dQ (three products per visible pair instead of two)
 // is ahead of ksa_bwd_dq_kernel nearly everywhere (dq_takes_direct()): 103 against 221 us at 2 x 4096 tokens.  It spills 2
 // registers (d 64: 7), outside the blocks that hold its MFMAs.
