@@ -77,6 +77,7 @@ struct DirectArgs {
     int32_t text_tiles, sum_tiles;      // query tiles of the two spaces
     int32_t text_before;                // text tiles whose key lists are longer than a summary tile's
     int32_t self_only;
+    int32_t longest_list;               // about so many keys are in the longest list of a query tile
     int32_t mixed_tiles;                // a key tile may hold the last summaries and the first text rows of a list
     int64_t aug_len;
     float scale_log2e;
@@ -155,15 +156,19 @@ __device__ __forceinline__ Visible visible(const DirectArgs &a, int q_space, int
 // GRAD = false: forward.  GRAD = true: dQ of the backward pass (see ksa_prefill_bwd.hip for the products) on the same key
 // lists: S^T = K Q^T and dP^T = V dO^T, whose accumulator starts from minus delta, dS^T = P^T o dP^T in bf16 as the B operand
 // of dQ^T += K^T dS^T.
-template <int D, bool GRAD>
-__device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) {
+// TEAMS = 2: eight waves, of which the second four take every other key tile, in buffers of their own, and add what they have to
+// the first four's at the end.
+template <int D, bool GRAD, int TEAMS>
+__device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *const lds_all) {
     using T = Tile<D>;
     static_assert(NW * 32 * T::STAGE_ROW <= 4 * T::BYTES, "the epilogue's staging area reuses the tile buffers");
+    static_assert(TEAMS == 1 || NW * (32 * T::STAGE_ROW + (T::DB * 4 + 1) * 1024) <= TEAMS * 4 * T::BYTES, "... and the second team's results lie behind it");
     auto k_swizzle = [](int row) { return GRAD ? ksa_swz<D>(row) : k_swz<D>(row); };
     auto v_swizzle = [](int row) { return GRAD ? ksa_swz<D>(row) : v_swz<D>(row); };
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % NW, team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / NW;
+    unsigned char *const lds = lds_all + team * 4 * T::BYTES;
     const int r = lane & 31, h = lane >> 5;
     // Workgroup index -> (query tile, slice of the group's heads, batch and KV head), the latter fastest: workgroup ids go
     // to the XCDs round-robin, so with a multiple of 8 (batch, KV head) pairs all tiles of a head share one L2.  Longest
@@ -249,8 +254,8 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
             const unsigned mul = per < 64 ? (s ? a.small_m : a.small_c) : 1024u;
             const int chunks = (BN * mul) >> 16;   // 64 / per
             if (chunks * per == BN) {
-                fast_left = ((s ? n_s : n_keys) - x0) / BN - 1;
-                fast_step = (int64_t)(BN + chunks * other) * a.ks[1];
+                fast_left = (((s ? n_s : n_keys) - x0) / BN - 1) / TEAMS;
+                fast_step = (int64_t)(BN + chunks * other) * a.ks[1] * TEAMS;
             }
             if (renew) {
                 // Row k of the tile is k + j (rows of the other kind per chunk) rows behind the first, j = how many chunk
@@ -300,10 +305,10 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         else
             lds_direct_load_16_s(rq_v, v_off[i], dst);
     };
-    prepare(0);
+    prepare(team);
 #pragma unroll
     for (int x = 0; x < 2 * T::NI; ++x) issue(0, x);
-    prepare(1);
+    prepare(team + TEAMS);
 
     const Visible vis = visible(a, q_space, idx);
     // In list positions: the row sees [s_lo, s_hi) of the summaries and [t_lo, t_hi) of the text; some row of the wave
@@ -390,7 +395,7 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 if (kb == 0) issue(buf ^ 1, s);
                 KSA_FENCE();
             }
-            if (kb == 0) prepare(t + 2);
+            if (kb == 0) prepare(t + 2 * TEAMS);
             if (masked) {   // as in the forward tile
                 const int y0 = x0 + kb * 32, base_t = y0 + 4 * h - t_lo, base_s = y0 + 4 * h - s_lo;
                 const unsigned span_t = (unsigned)max(t_hi - t_lo, 0), span_s = (unsigned)max(s_hi - s_lo, 0);
@@ -451,15 +456,15 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         const unsigned ind1 = (lane == 0 || lane == 32 || lane == 17 || lane == 49) ? 0x3f803f80u : 0u;
         const bf16x8 ind = __builtin_bit_cast(bf16x8, u32x4{ind1, ind1, ind1, ind1});
 
-        for (int t = 0; t < n_tiles; ++t) {
-            const int buf = t & 1;
+        for (int round = 0; round * TEAMS < n_tiles; ++round) {
+            const int t = round * TEAMS + team, buf = round & 1;   // (a t behind the last tile: nothing for this wave)
             __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's pieces of tile t have landed
             __syncthreads();                      // ... and everybody's; nobody reads the other buffer any more
             const int x0 = t * BN, x1 = x0 + BN;
             if ((unsigned)(t - ws_t) >= ws_n && (unsigned)(t - wt_t) >= wt_n) {   // nothing for this wave
 #pragma unroll
                 for (int x = 0; x < 2 * T::NI; ++x) issue(buf ^ 1, x);
-                prepare(t + 2);
+                prepare(t + 2 * TEAMS);
                 continue;
             }
             const unsigned char *tile_lds = lds + buf * 2 * T::BYTES;
@@ -492,7 +497,7 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
                 issue(buf ^ 1, s);
                 KSA_FENCE();
             }
-            prepare(t + 2);
+            prepare(t + 2 * TEAMS);
             __builtin_amdgcn_s_setprio(0);
             if ((unsigned)(t - fs_t) >= fs_n && (unsigned)(t - ft_t) >= ft_n) {
                 // clip to what the row sees: score register g of block kb is position x0 + 32 kb + 4 h + 8 (g / 4) + g % 4
@@ -587,8 +592,46 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
         // ---- O = O^T / l through a per-wave staging area in the tile buffers, whole rows stored; LSE ---------------
         __builtin_amdgcn_s_waitcnt(0x0F70);   // the loads behind the last tile have landed
         __syncthreads();                      // everybody is done with the tiles
+        if constexpr (TEAMS == 2) {   // a wave of the second team holds the same rows as the one of the first, in the same lanes
+            f32x4 *const given = reinterpret_cast<f32x4 *>(lds_all + NW * 32 * T::STAGE_ROW) + wave * ((T::DB * 4 + 1) * 64) + lane;
+            if (team == 1 && w_any) {
+#pragma unroll
+                for (int x = 0; x < T::DB * 4; ++x)
+                    given[x * 64] = f32x4{oacc[x / 4][x % 4 * 4], oacc[x / 4][x % 4 * 4 + 1], oacc[x / 4][x % 4 * 4 + 2], oacc[x / 4][x % 4 * 4 + 3]};
+                if constexpr (!GRAD) given[T::DB * 4 * 64] = f32x4{l_sum[0], l_sum[1], l_exact, m_ref};
+            }
+            __syncthreads();
+            if (team == 1) return;
+            if (w_any) {
+                float mine = 1.f, theirs = 1.f;   // what the two parts are multiplied by: with running maxima their references differ
+                f32x4 more = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (!GRAD) more = given[T::DB * 4 * 64];
+                if constexpr (TRACK) {
+                    const float m_new = fmaxf(m_ref, more[3]);   // (equal references, also two infinite ones, must give exactly 1)
+                    mine = m_ref == m_new ? 1.f : __builtin_amdgcn_exp2f((m_ref - m_new) * sl);
+                    theirs = more[3] == m_new ? 1.f : __builtin_amdgcn_exp2f((more[3] - m_new) * sl);
+                    m_ref = m_new;
+                }
+#pragma unroll
+                for (int x = 0; x < T::DB * 4; ++x) {
+                    const f32x4 o = given[x * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float &acc = reinterpret_cast<float (&)[16]>(oacc[x / 4])[x % 4 * 4 + e];
+                        acc = TRACK ? fmaf(o[e], theirs, acc * mine) : acc + o[e];
+                    }
+                }
+                if constexpr (TRACK) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) l_sum[e] = fmaf(more[e], __shfl(theirs, (lane & 15) + 16 * e), l_sum[e] * __shfl(mine, (lane & 15) + 16 * e));
+                } else {
+                    l_sum[0] += more[0], l_sum[1] += more[1];
+                }
+                l_exact = l_exact * mine + more[2] * theirs;
+            }
+        }
         if (!w_any) return;
-        unsigned char *stg = lds + wave * (32 * T::STAGE_ROW);
+        unsigned char *stg = lds_all + wave * (32 * T::STAGE_ROW);
         const float s0 = __shfl(l_sum[0], r & 15), s1 = __shfl(l_sum[1], r & 15);
         float l_row = (r & 16) ? s1 : s0;
         l_exact += other_half(l_exact);
@@ -656,12 +699,23 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *lds) 
 template <int D>
 __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_prefill_direct_kernel(const DirectArgs a) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * Tile<D>::BYTES];
-    direct<D, false>(a, lds);
+    direct<D, false, 1>(a, lds);
 }
 template <int D>
 __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dq_direct_kernel(const DirectArgs a) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * Tile<D>::BYTES];
-    direct<D, true>(a, lds);
+    direct<D, true, 1>(a, lds);
+}
+// ... and with eight waves in a workgroup (two_teams())
+template <int D>
+__global__ __launch_bounds__(2 * NW * 64, 2) void ksa_prefill_teams_kernel(const DirectArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * 4 * Tile<D>::BYTES];
+    direct<D, false, 2>(a, lds);
+}
+template <int D>
+__global__ __launch_bounds__(2 * NW * 64, 2) void ksa_bwd_dq_teams_kernel(const DirectArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * 4 * Tile<D>::BYTES];
+    direct<D, true, 2>(a, lds);
 }
 
 // Largest squared K row norm of norm_run 64-key tiles of a (batch, KV head), the parts of the text space first.
@@ -697,10 +751,22 @@ __global__ __launch_bounds__(256) void ksa_knorm_parts_kernel(const DirectArgs a
         out[((int64_t)b * a.n_kv_heads + hkv) * gridDim.x + part] = fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
 }
 
+// A launch with no more workgroups than compute units takes eight waves each (TEAMS = 2), which halves the chain of tiles.  us, four waves /
+// eight, forward (backward): head_dim 64 12/4 heads, 2000 tokens, c 48, m 6 30.5 / 23.4 (78.7 / 69.2), 2 x 1024, c 64, m 8 25.3 / 21.2
+// (58.2 / 51.0), 1 head, 512 tokens 12.1 / 11.6 (29.9 / 28.3); head_dim 128 16/16 heads, 1024 tokens 31.1 / 26.7 (67.8 / 61.7), 1 head, 3000
+// tokens 17.7 / 16.8 (61.1 / 60.0), but with few tiles in a list (1 head, window of 255) 13.8 / 14.3, and with four heads per workgroup, whose
+// waves all read the same keys, 512 tokens 15.9 / 16.6 (58.2 / 59.0), 700 in the paper's form 22.6 / 22.0 (81.2 / 81.4).
+bool two_teams(const DirectArgs &a, int head_dim, int64_t n_wg) {
+    return n_wg <= 256 && (head_dim == 64 || (a.stack == 1 && a.longest_list > 8 * BN));
+}
+
 template <int D>
 void launch(const DirectArgs &a, float *parts, int batch, int64_t n_wg, hipStream_t st) {
     if (a.knorm_parts) hipLaunchKernelGGL(ksa_knorm_parts_kernel<D>, dim3(a.norm_parts, a.n_kv_heads, batch), dim3(256), 0, st, a, parts);
-    hipLaunchKernelGGL(ksa_prefill_direct_kernel<D>, dim3((unsigned)n_wg), dim3(NW * 64), 0, st, a);
+    if (two_teams(a, D, n_wg))
+        hipLaunchKernelGGL(ksa_prefill_teams_kernel<D>, dim3((unsigned)n_wg), dim3(2 * NW * 64), 0, st, a);
+    else
+        hipLaunchKernelGGL(ksa_prefill_direct_kernel<D>, dim3((unsigned)n_wg), dim3(NW * 64), 0, st, a);
 }
 
 // the parts of the arguments that describe the key lists (the strides are set); returns the number of workgroups
@@ -739,6 +805,9 @@ int64_t fill_lists(DirectArgs &a, const ksa_params &p, int32_t head_stack, int64
             if (longer(mid)) hi = mid; else lo = mid + 1;
         }
         a.text_before = a.text_tiles - lo;
+        const int64_t chunks = (a.n_text - 1) / a.c, text = (chunks > a.C ? (chunks - a.C) * a.m : 0) +
+                                                            std::min<int64_t>(a.n_text, (int64_t)(a.C + 1) * a.c + a.q_rows);
+        a.longest_list = (int32_t)std::max(text, std::min<int64_t>(sum_keys, (int64_t)a.n_text + a.n_sum));
     }
     a.self_only = (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY) ? 1 : 0;
     a.mixed_tiles = ksa_mixed_tile_rows(a.c, a.m, a.q_rows) * a.ks[1] * 2 < ((int64_t)1 << 32) ? 1 : 0;   // 32-bit byte offsets
@@ -795,10 +864,15 @@ int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *stats, void 
     if (n_wg >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
     a.nt_pad = (a.n_text + 63) / 64 * 64, a.ns_pad = (a.n_sum + 63) / 64 * 64;
     a.scale = L.p.softmax_scale, a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
-    const dim3 grid((unsigned)n_wg), block(NW * 64);
+    const bool two = two_teams(a, L.p.head_dim, n_wg);
+    const dim3 grid((unsigned)n_wg), block(NW * 64 * (two ? 2 : 1));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (L.p.head_dim == 128)
+    if (L.p.head_dim == 128 && two)
+        hipLaunchKernelGGL(ksa_bwd_dq_teams_kernel<128>, grid, block, 0, st, a);
+    else if (L.p.head_dim == 128)
         hipLaunchKernelGGL(ksa_bwd_dq_direct_kernel<128>, grid, block, 0, st, a);
+    else if (two)
+        hipLaunchKernelGGL(ksa_bwd_dq_teams_kernel<64>, grid, block, 0, st, a);
     else
         hipLaunchKernelGGL(ksa_bwd_dq_direct_kernel<64>, grid, block, 0, st, a);
     return KSA_OK;
