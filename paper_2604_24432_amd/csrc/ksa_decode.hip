@@ -103,21 +103,6 @@ __device__ __forceinline__ int phys_row(const Ranges &R, int v) {
     return R.off2 + (v - R.n1);
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float x) {
-    const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false);
-    return x + __builtin_bit_cast(float, y);
-}
-// sum over the LPR adjacent lanes that share a row; every one of them ends with the total
-template <int LPR>
-__device__ __forceinline__ float row_allreduce(float x) {
-    x = dpp_add<0xB1>(x);    // quad_perm [1,0,3,2]
-    x = dpp_add<0x4E>(x);    // quad_perm [2,3,0,1]
-    x = dpp_add<0x141>(x);   // row_half_mirror: the other quad of the 8
-    if (LPR == 16) x = dpp_add<0x140>(x);   // row_mirror: the other 8 of the 16
-    return x;
-}
-
 // how far behind its position v among the visible rows a row lies in the cache
 __device__ __forceinline__ int row_shift(const Ranges &R, int v) {
     const int ring = v < R.n0 + R.n1 ? R.off1 - R.n0 : R.off2 - R.n0 - R.n1;

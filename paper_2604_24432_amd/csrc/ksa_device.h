@@ -47,6 +47,21 @@ __device__ __forceinline__ void lds_direct_load_16_s(const __bf16 *sbase, unsign
                  : "memory");
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+    const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false);
+    return x + __builtin_bit_cast(float, y);
+}
+// sum over 8 or 16 adjacent lanes (a row of head_dim 64 or 128 in 16-byte pieces); every one of them ends with the total
+template <int LANES>
+__device__ __forceinline__ float row_allreduce(float x) {
+    x = dpp_add<0xB1>(x);    // quad_perm [1,0,3,2]
+    x = dpp_add<0x4E>(x);    // quad_perm [2,3,0,1]
+    x = dpp_add<0x141>(x);   // row_half_mirror: the other quad of the 8
+    if (LANES == 16) x = dpp_add<0x140>(x);   // row_mirror: the other 8 of the 16
+    return x;
+}
+
 // Division of an index x in [0, 2^31) by a fixed d in [1, 2^31) as one multiplication: with 2^(s-1) < d <= 2^s the
 // quotient is (x * M) >> (31 + s), M = floor(2^(31 + s) / d) + 1 < 2^32 (Granlund and Montgomery: exact for x < 2^31,
 // because M d exceeds 2^(31 + s) by at most d <= 2^s).

@@ -65,6 +65,8 @@ struct BwdArgs {
     float *scratch;                           // partial sums (the memory of dq, which is written last); NULL: no tile is split
     int64_t aug_len;
     float scale, scale_log2e;
+    int32_t stat_blocks;                      // blocks of 64 statistics slots per (batch, head)
+    KsaDivisor by_heads, by_blocks, by_c, by_m;
 };
 
 // global -> LDS, 4 bytes per lane: the wave's 64 pieces land back to back (lane order) from the wave-uniform LDS
@@ -166,37 +168,43 @@ __device__ __forceinline__ void visible_range(const BwdArgs &a, int q_space, int
 }
 
 // ---- per-row statistics: delta_i = G_i . O_i and lse_i log2(e), in compact order ------------------------------------
+// Bound by HBM reads of O and G.  A workgroup takes 64 rows of one head, all loads on their way together, and its neighbours the
+// other heads of the same rows, which lie beside them.  One row per 16 lanes, its place by 64-bit divisions, and a head's rows after one
+// another: 20003 tokens in the paper's form, 16 heads (187 MB) 46.1 us, now 35.5; 2 x 4096, 32 heads (154 MB) 25.9, now 25.4.
 template <int D>
-__global__ __launch_bounds__(256) void ksa_bwd_delta_kernel(const BwdArgs a, int64_t n_slots /* B * Hq * (nt_pad + ns_pad) */) {
-    constexpr int CH = D / 8;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int64_t slot = idx / CH;
-    const int piece = (int)(idx % CH);
-    const bool in_grid = slot < n_slots;
-    if (!in_grid) slot = n_slots - 1;
-    const int sp = a.nt_pad + a.ns_pad;
-    const int pos = (int)(slot % sp);
-    const int64_t bh = slot / sp;
-    const int hq = (int)(bh % a.n_q_heads);
-    const int64_t b = bh / a.n_q_heads;
-    const int space = pos < a.nt_pad ? KSA_SPACE_TEXT : KSA_SPACE_SUMMARY;
-    const int ci = space == KSA_SPACE_TEXT ? pos : pos - a.nt_pad;
-    const bool live = ci < (space == KSA_SPACE_TEXT ? a.n_text : a.n_sum);   // wave-uniform per group of CH lanes
-    float s = 0.f, l2 = 0.f;
-    if (live) {
-        const int64_t aq = aug_row(a, space, ci);
-        const int64_t off = b * a.os[0] + aq * a.os[1] + hq * a.os[2] + piece * 8;
-        const bf16x8 o8 = *reinterpret_cast<const bf16x8 *>(a.o + off);
-        const bf16x8 g8 = *reinterpret_cast<const bf16x8 *>(a.g + off);
+__global__ __launch_bounds__(256) void ksa_bwd_delta_kernel(const BwdArgs a) {
+    constexpr int CH = D / 8, ROWS = 256 / CH, PASSES = 64 / ROWS;
+    const int rest = ksa_div(blockIdx.x, a.by_heads), hq = blockIdx.x - rest * a.n_q_heads;
+    const int b = ksa_div(rest, a.by_blocks), block = rest - b * a.stat_blocks;
+    const int piece = threadIdx.x % CH;
+    const int text_blocks = a.nt_pad / 64;
+    const int space = block < text_blocks ? KSA_SPACE_TEXT : KSA_SPACE_SUMMARY;
+    const int first = (space == KSA_SPACE_TEXT ? block : block - text_blocks) * 64 + threadIdx.x / CH;
+    const int n = space == KSA_SPACE_TEXT ? a.n_text : a.n_sum;
+    const int64_t at = b * a.os[0] + hq * a.os[2] + piece * 8;
+    const float *const lse = a.lse + ((int64_t)b * a.n_q_heads + hq) * a.aug_len;
+    bf16x8 o8[PASSES], g8[PASSES];
+    float l[PASSES];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s += (float)o8[e] * (float)g8[e];
-        l2 = a.lse[(b * a.n_q_heads + hq) * a.aug_len + aq] * 1.4426950408889634f;
+    for (int i = 0; i < PASSES; ++i) {
+        const int ci = min(first + ROWS * i, n - 1);   // rows behind the last one: that one again, stored as zeros
+        const int aq = space == KSA_SPACE_TEXT ? ci + ksa_div(ci, a.by_c) * a.m : ci + (ksa_div(ci, a.by_m) + 1) * a.c;
+        const int64_t row = at + (int64_t)aq * a.os[1];
+        o8[i] = *reinterpret_cast<const bf16x8 *>(a.o + row), g8[i] = *reinterpret_cast<const bf16x8 *>(a.g + row);
+        l[i] = lse[aq];
     }
+    float *const out = a.stats + 2 * (((int64_t)b * a.n_q_heads + hq) * (a.nt_pad + a.ns_pad) + block * 64);
 #pragma unroll
-    for (int d = CH / 2; d > 0; d >>= 1) s += __shfl_xor(s, d);
-    if (in_grid && piece == 0) {
-        float *at = a.stats + ksa_stat_at(slot);
-        at[0] = l2, at[KSA_STAT_ROWS] = -s;
+    for (int i = 0; i < PASSES; ++i) {
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += (float)o8[i][e] * (float)g8[i][e];
+        s = row_allreduce<CH>(s);
+        if (piece == 0) {
+            const bool live = first + ROWS * i < n;
+            float *const x = out + ksa_stat_at((int)threadIdx.x / CH + ROWS * i);
+            x[0] = live ? l[i] * 1.4426950408889634f : 0.f, x[KSA_STAT_ROWS] = live ? -s : 0.f;
+        }
     }
 }
 
@@ -972,8 +980,7 @@ void launch_dkv(const KsaPrefillBwdLaunch &L, const BwdArgs &a, hipStream_t st) 
 
 template <int D, bool POW2>
 int launch_all(const KsaPrefillBwdLaunch &L, const BwdArgs &a, int64_t n_rows, hipStream_t st) {
-    const int64_t delta_blocks = (n_rows * (D / 8) + 255) / 256;
-    hipLaunchKernelGGL(ksa_bwd_delta_kernel<D>, dim3((unsigned)delta_blocks), dim3(256), 0, st, a, n_rows);
+    hipLaunchKernelGGL(ksa_bwd_delta_kernel<D>, dim3((unsigned)(n_rows / 64)), dim3(256), 0, st, a);
     // with split key tiles dq holds their partial sums until it is written itself
     if (a.scratch) launch_dkv<D, POW2>(L, a, st);
     if (L.dq_direct) {
@@ -1040,6 +1047,9 @@ int ksa_launch_prefill_bwd(const KsaPrefillBwdLaunch &L, void *stream) {
     a.sum_tiles = (a.n_sum + KEYS_PER_WG - 1) / KEYS_PER_WG;
     a.nt_pad = (int32_t)pad64(a.n_text);
     a.ns_pad = (int32_t)pad64(a.n_sum);
+    a.stat_blocks = (a.nt_pad + a.ns_pad) / 64;
+    a.by_heads = ksa_divisor(a.n_q_heads), a.by_blocks = ksa_divisor(a.stat_blocks);
+    a.by_c = ksa_divisor(a.c), a.by_m = ksa_divisor(std::max(a.m, 1));
     a.aug_len = L.aug_len;
     a.scale = L.p.softmax_scale;
     a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
