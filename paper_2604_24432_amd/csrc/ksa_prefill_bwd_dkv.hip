@@ -163,7 +163,6 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dkv_direct_
         run_end[x] = hi;
         blk_n[x] = hi > lo ? (hi + BM - 1) / BM - lo / BM : 0;
     }
-    auto last_block = [&](int x) { return (int)((unsigned)((x ? run_end[1] : run_end[0]) - 1) / BM); };   // (of a run that has rows)
     const int steps0 = blk_n[0] * a.group;
     const int n_steps = min(steps0 + blk_n[1] * a.group, step_end) - step_begin;   // > 0: a key is seen by its own row
 
