@@ -145,8 +145,8 @@ size_t ksa_prefill_workspace_bytes(const ksa_layout *layout);
  *   lse: device fp32 [B, Hq, L] contiguous, natural-log sum-exp of the scaled visible scores; may be NULL.
  *   workspace: device memory, 16-byte aligned, at least ksa_prefill_workspace_bytes(layout) bytes, owned by the
  *   caller, and needed until the work enqueued on `stream` has finished.  What the call writes there depends on the
- *   layout: a key-major copy of V and the largest K row norms (long key runs), the norms alone (short ones), or nothing
- *   (chunk shapes that are no powers of two).  From the norms the kernels derive a fixed softmax reference per row wherever
+ *   layout: a key-major copy of V and the largest K row norms (long key runs), the norms alone (short ones; of short texts
+ *   only those per (batch, KV head)), or nothing (chunk shapes that are no powers of two).  From the norms the kernels derive a fixed softmax reference per row wherever
  *   |q| max |k| * scale is small enough to rule out overflow and underflow; other rows keep a running maximum.  Calls that
  *   share a workspace must be stream-ordered.
  *   stream: hipStream_t (NULL = default stream).

@@ -61,6 +61,7 @@ struct DirectArgs {
     int64_t qs[3], ks[3], os[3];        // {batch, row, head} strides in elements
     const float *knorm_parts;           // largest squared K row norm per part of a (batch, KV head)'s rows; NULL: keep running maxima
     float *knorm;                       // ... per (batch, KV head): stored by one workgroup of each
+    int32_t own_norms;                  // every workgroup takes the norms of its head's rows itself, nothing is in knorm_parts
     int32_t running_text, running_sum;  // query tiles from these rows on keep running maxima whatever the norms say
     int32_t norm_parts;                 // parts per (batch, KV head), at most NORM_PARTS
     int32_t norm_text_parts;            // the first so many are text
@@ -123,6 +124,25 @@ struct Tile {
     static constexpr int BYTES = BN * D * 2;   // one tensor's tile; a buffer holds K, then V
     static constexpr int STAGE_ROW = D * 2 + 16;
 };
+
+// squared norm of a row whose 16-byte pieces lie in CH neighbouring lanes, in all of them
+template <int CH>
+__device__ __forceinline__ float row_norm2(const bf16x8 &x) {
+    float s2 = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const bf16x2 y = {x[e], x[e + 1]};
+        s2 = __builtin_amdgcn_fdot2_f32_bf16(y, y, s2, false);
+    }
+    return row_allreduce<CH>(s2);
+}
+// the largest value of a wave whose groups of CH lanes hold one each
+template <int CH>
+__device__ __forceinline__ float rows_max(float x) {
+    if (CH == 8) x = dpp_max<0x140>(x);   // row_mirror
+    x = fmaxf(x, other_row(x));
+    return fmaxf(x, other_half(x));
+}
 
 // LDS tile: row-major [64][D] bf16, the 16-byte piece index XORed with a function of the row: for K all rows of a
 // 16-lane phase of the plain read differ, for V the four rows of a transposing read do.  At head_dim 64 two rows share the 256
@@ -338,15 +358,31 @@ __device__ __forceinline__ void direct(const DirectArgs &a, unsigned char *const
     bool static_ok = false;
     if (!GRAD && a.knorm_parts) {
         float kmax2 = 0.f;
-        const float *src = a.knorm_parts + (int64_t)bh * a.norm_parts;
+        if (a.own_norms) {
+            constexpr int WAVES = NW * TEAMS, ROWS = WAVES * 64 / T::CH, AT_ONCE = 4;   // loads of a lane that travel together
+            __shared__ float best_of[WAVES];
+            const __bf16 *const src = kbase + tid % T::CH * 8;
+            for (int64_t row0 = tid / T::CH; row0 < a.aug_len + tid / T::CH; row0 += AT_ONCE * ROWS) {
+                bf16x8 x[AT_ONCE];
 #pragma unroll
-        for (int i = 0; i < NORM_PARTS; i += 64) kmax2 = fmaxf(kmax2, src[min(i + lane, a.norm_parts - 1)]);   // (the last one repeats)
-        kmax2 = dpp_max<0xB1>(kmax2);    // quad_perm [1,0,3,2]
-        kmax2 = dpp_max<0x4E>(kmax2);    // quad_perm [2,3,0,1]
-        kmax2 = dpp_max<0x141>(kmax2);   // row_half_mirror
-        kmax2 = dpp_max<0x140>(kmax2);   // row_mirror
-        kmax2 = fmaxf(kmax2, other_row(kmax2));
-        kmax2 = fmaxf(kmax2, other_half(kmax2));
+                for (int i = 0; i < AT_ONCE; ++i) x[i] = *reinterpret_cast<const bf16x8 *>(src + min(row0 + i * ROWS, a.aug_len - 1) * a.ks[1]);
+#pragma unroll
+                for (int i = 0; i < AT_ONCE; ++i) kmax2 = fmaxf(kmax2, row_norm2<T::CH>(x[i]));
+            }
+            kmax2 = rows_max<T::CH>(kmax2);
+            if (lane == 0) best_of[tid >> 6] = kmax2;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < WAVES; ++i) kmax2 = fmaxf(kmax2, best_of[i]);
+        } else {
+            const float *src = a.knorm_parts + (int64_t)bh * a.norm_parts;
+#pragma unroll
+            for (int i = 0; i < NORM_PARTS; i += 64) kmax2 = fmaxf(kmax2, src[min(i + lane, a.norm_parts - 1)]);   // (the last one repeats)
+            kmax2 = dpp_max<0xB1>(kmax2);    // quad_perm [1,0,3,2]
+            kmax2 = dpp_max<0x4E>(kmax2);    // quad_perm [2,3,0,1]
+            kmax2 = dpp_max<0x141>(kmax2);   // row_half_mirror
+            kmax2 = rows_max<8>(kmax2);
+        }
         if (rest == 0 && tid == 0) a.knorm[bh] = kmax2;
         float n2 = 0.f;
 #pragma unroll
@@ -737,18 +773,10 @@ __global__ __launch_bounds__(256) void ksa_knorm_parts_kernel(const DirectArgs a
         for (int i = 0; i < BN / ROWS; ++i) {
             const int key = min(k0 + BN * t + ROWS * i + tid / CH, n_space - 1);
             const bf16x8 x = *reinterpret_cast<const bf16x8 *>(kb + (int64_t)row_of(a, space, key) * a.ks[1]);
-            float s2 = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                const bf16x2 y = {x[e], x[e + 1]};
-                s2 = __builtin_amdgcn_fdot2_f32_bf16(y, y, s2, false);
-            }
-            best = fmaxf(best, row_allreduce<CH>(s2));   // the CH lanes of a row are neighbours
+            best = fmaxf(best, row_norm2<CH>(x));
         }
     }
-    if (CH == 8) best = dpp_max<0x140>(best);
-    best = fmaxf(best, other_row(best));
-    best = fmaxf(best, other_half(best));
+    best = rows_max<CH>(best);
     if ((tid & 63) == 0) wave_best[tid >> 6] = best;
     __syncthreads();
     if (tid == 0)
@@ -764,9 +792,16 @@ bool two_teams(const DirectArgs &a, int head_dim, int64_t n_wg) {
     return n_wg <= 256 && (head_dim == 64 || (a.stack == 1 && a.longest_list > 8 * BN));
 }
 
+// Short texts: a launch of its own for the K norms takes 3 - 4 us, a workgroup reads all rows of its head in less.  us, norms before / by
+// every workgroup: head_dim 64 (eight waves) 200 tokens 10.7 / 8.8, 512 11.1 / 10.0, 1500 rows 11.1 / 10.7, 3375 12.9 / 15.2; head_dim 128, eight
+// waves 787 rows 19.3 / 18.7, 1152 25.7 / 26.0, four waves 216 rows 14.6 / 13.1, 576 15.3 / 15.5.
+bool takes_own_norms(const DirectArgs &a, int head_dim, int64_t n_wg) {
+    return n_wg <= 256 && a.aug_len * head_dim <= (two_teams(a, head_dim, n_wg) ? 100 : 56) * 1024;
+}
+
 template <int D>
 void launch(const DirectArgs &a, float *parts, int batch, int64_t n_wg, hipStream_t st) {
-    if (a.knorm_parts) hipLaunchKernelGGL(ksa_knorm_parts_kernel<D>, dim3(a.norm_parts, a.n_kv_heads, batch), dim3(256), 0, st, a, parts);
+    if (a.knorm_parts && !a.own_norms) hipLaunchKernelGGL(ksa_knorm_parts_kernel<D>, dim3(a.norm_parts, a.n_kv_heads, batch), dim3(256), 0, st, a, parts);
     if (two_teams(a, D, n_wg))
         hipLaunchKernelGGL(ksa_prefill_teams_kernel<D>, dim3((unsigned)n_wg), dim3(2 * NW * 64), 0, st, a);
     else
@@ -845,6 +880,7 @@ int ksa_launch_prefill_direct(const KsaPrefillLaunch &L, float *knorm_parts, flo
     a.norm_run = std::max(1, (text_tiles + sum_tiles + NORM_PARTS - 3) / (NORM_PARTS - 2));   // (each space may add a short part)
     a.norm_text_parts = (text_tiles + a.norm_run - 1) / a.norm_run;
     a.norm_parts = a.norm_text_parts + (sum_tiles + a.norm_run - 1) / a.norm_run;
+    a.own_norms = takes_own_norms(a, L.p.head_dim, n_wg);
     if (L.p.head_dim == 128)
         launch<128>(a, knorm_parts, L.p.batch, n_wg, st);
     else if (L.p.head_dim == 64)
@@ -861,7 +897,7 @@ int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *stats, void 
     a.v = static_cast<const __bf16 *>(L.v);
     a.g = static_cast<const __bf16 *>(L.d_o);
     a.o = static_cast<__bf16 *>(L.dq);
-    a.lse = nullptr, a.knorm_parts = nullptr, a.knorm = nullptr, a.running_text = a.running_sum = a.norm_parts = a.norm_text_parts = a.norm_run = 0;
+    a.lse = nullptr, a.knorm_parts = nullptr, a.knorm = nullptr, a.own_norms = 0, a.running_text = a.running_sum = a.norm_parts = a.norm_text_parts = a.norm_run = 0;
     for (int x = 0; x < 3; ++x) a.qs[x] = L.q_strides[x], a.ks[x] = L.kv_strides[x], a.gs[x] = L.o_strides[x], a.os[x] = L.dq_strides[x];
     a.stats = stats;
     const int64_t n_wg = fill_lists(a, L.p, L.head_stack, L.aug_len);

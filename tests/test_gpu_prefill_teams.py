@@ -64,3 +64,19 @@ def test_no_number_stays_in_its_row(shape, value):
     assert bool(torch.isnan(got[:, rows].float()).all())
     # (rows beside one that is no number keep running maxima instead of a fixed reference: another rounding of the weights)
     assert (got[:, others].float() - want[:, others].float()).norm() <= 9e-3 * want[:, others].float().norm()
+
+
+@pytest.mark.parametrize("d,n", [(64, 1), (64, 8), (64, 70), (64, 1420), (64, 1600), (128, 1), (128, 33), (128, 380), (128, 410), (128, 900)])
+def test_largest_key_norm(d, n):
+    """Short texts, whose workgroups take the K norms themselves, and those just beyond: the workspace ends with the largest squared
+    norm of each KV head (exact for whole-numbered keys), whichever row it is in."""
+    B, H, c, m = 2, 2, 8, 1
+    lay = K.ksa_build_layout(K.make_params(B, n, c, m, 1, H, H, d))
+    ws = torch.empty(K.prefill_workspace_bytes(lay), dtype=torch.uint8, device="cuda")
+    q, v = (f(B, lay.aug_len, H, d, dtype=torch.bfloat16, device="cuda") for f in (torch.zeros, torch.ones))
+    for row in {0, lay.aug_len // 2, lay.aug_len - 1}:
+        k = torch.ones_like(v)
+        k[1, row, 0, d - 1] = 16
+        o, _ = K.ksa_prefill_fwd(lay, q, k, v, workspace=ws)
+        assert ws[-4 * B * H:].view(torch.float32).tolist() == [d, d, d - 1 + 256, d], row
+        assert bool((o == 1).all())
