@@ -200,9 +200,16 @@ struct DecodePlan {
  *
  * From a million rows on the spans are dealt by the sequences' lengths, which costs 1 - 1.5 to work out: lengths 1 : 4, batch 64 at 128K 511 ->
  * 457, batch 16 133 -> 118, batch 8 in the paper's form 74.5 -> 68.7; all alike 658 -> 652, 173 -> 169, 97 -> 92 (before: about 1536 workgroups, none below
- * 768 rows).  At least three per sequence (batch 64: 512 537, 768 507, 1536 457).
+ * 768 rows).  Batch 64: 512 workgroups 537, 768 507, 1536 457.  Two and more per sequence, or there is nothing to deal: with one and two heads
+ * per KV head three where it would be less than two and a half (lengths 1 : 4 / alike, batch 60, 32/16, 1600 rows, 1.3 99.9 / 126, three 88.0 /
+ * 127; batch 33, 32/16, 9000 rows, 2.4 249 / 411, three 246 / 374; but batch 64, 16/8, 6400 rows, 2.5 170 / 248, three 190 / 262), with more
+ * heads two (batch 28, 128/32, 3500 rows, 1.7 177 / 271, two 178 / 250, three 178 / 263).  From 1024 pairs on the workgroups balance each
+ * other and nothing is dealt (dealt one by one / the same number each: batch 64, 64/32 heads, 2100 rows 237 / 341, 231 / 335; batch 33,
+ * 64/32 heads, 4000 rows 252 / 366, two each 229 / 345), with two each up to 1500 pairs (batch 44, 128/32, 3500 rows 271 / 391, one 283 / 401).
+ *
+ * fit: for how many spans of a KV head there is room, one per sequence at least.
  */
-DecodePlan plan_decode(const ksa_params *p, int64_t rows) {
+DecodePlan plan_decode(const ksa_params *p, int64_t rows, int64_t fit) {
     const int64_t groups = (int64_t)p->batch * p->n_kv_heads, total = groups * rows;
     const int64_t w = rows * p->head_dim / 128;
     const int32_t heads = p->n_q_heads / p->n_kv_heads;
@@ -216,17 +223,16 @@ DecodePlan plan_decode(const ksa_params *p, int64_t rows) {
         return {1, p->batch, groups <= 256 && (wide(1) || (w >= 384 && groups >= 192))};
     int64_t want = total < 30000 ? 256 : heads <= 2 ? (total < 65000 ? 512 : heads == 2 || total < 130000 ? 768 : 1280)
                                                     : heads == 4 || total > 250000 ? 512 : 256;
-    const bool deal = total >= 1000000 && p->batch > 1 && p->batch <= 64;
+    const int64_t enough = heads <= 2 ? 5 * p->batch / 2 : 2 * p->batch;   // dealt spans per KV head
+    const bool deal = total >= 1000000 && p->batch > 1 && p->batch <= 64 && groups < 1024 && fit >= enough;
     if (deal)
         want = heads == 1 ? 1536 : heads == 2 ? (groups <= 256 ? 768 : 1280) : groups <= 64 ? 512 : groups <= 128 ? 768 : 1536;
     else if (total >= 800000)
-        want = 1536;
+        want = groups >= 1024 ? 2048 : 1536;
     want = std::max<int64_t>(std::min(want, total / 24), 1);
-    // (records no larger than the static array of ksa_decode_fwd_static, unless those of the least number are)
-    const int64_t fit = std::max<int64_t>(KSA_DECODE_STATIC_SCRATCH_BYTES / (p->batch * record_bytes(p)), ksa_decode_default_splits(p));
-    if (deal && fit > 1) {
-        const int64_t spans = std::min(std::max<int64_t>(want / p->n_kv_heads, p->batch), fit * p->batch);
-        return {0, (int32_t)spans, false};
+    if (deal) {
+        const int64_t spans = want / p->n_kv_heads;
+        return {0, (int32_t)std::min<int64_t>(spans >= enough ? spans : (heads <= 2 ? 3 : 2) * p->batch, fit), false};
     }
     int64_t best = 1;
     double best_score = -1e30;
@@ -234,8 +240,14 @@ DecodePlan plan_decode(const ksa_params *p, int64_t rows) {
         const double n = (double)(s * groups), fill = n / (256.0 * std::ceil(n / 256.0)), score = fill - 0.25 * std::fabs(std::log(n / want));
         if (score > best_score) best = s, best_score = score;
     }
-    best = std::min({best, std::max<int64_t>(64, rows / 512), fit});
+    best = std::min({best, std::max<int64_t>(64, rows / 512), fit / p->batch});
     return {(int32_t)best, (int32_t)(p->batch * best), wide(best)};
+}
+
+// records no larger than the static array of ksa_decode_fwd_static, unless those of the least number are
+int64_t most_spans(const ksa_params *p) {
+    const int64_t most = KSA_DECODE_STATIC_SCRATCH_BYTES / (p->batch * record_bytes(p));
+    return p->batch * std::max<int64_t>(most, ksa_decode_default_splits(p));
 }
 
 int64_t most_rows(const ksa_params *p, int32_t kind) {
@@ -250,7 +262,7 @@ size_t ksa_decode_workspace_bytes(const ksa_params *p, int32_t n_splits) {
     int64_t spans = (int64_t)p->batch * n_splits;
     if (n_splits == 0) {   // (no less than the least that a call accepts)
         spans = (int64_t)p->batch * ksa_decode_default_splits(p);
-        for (const int32_t kind : {KSA_ROW_TEXT, KSA_ROW_SUMMARY}) spans = std::max<int64_t>(spans, plan_decode(p, most_rows(p, kind)).n_spans);
+        for (const int32_t kind : {KSA_ROW_TEXT, KSA_ROW_SUMMARY}) spans = std::max<int64_t>(spans, plan_decode(p, most_rows(p, kind), most_spans(p)).n_spans);
     }
     return (size_t)spans * record_bytes(p);
 }
@@ -271,17 +283,9 @@ int decode_call(const ksa_params *p, int32_t kind, const void *q, const void *k_
     if (p->n_q_heads / p->n_kv_heads > 8) return KSA_ERR_UNSUPPORTED;
     const int64_t spans = (int64_t)p->batch * (n_splits != 0 ? n_splits : ksa_decode_default_splits(p));
     if (workspace_bytes < (size_t)spans * record_bytes(p)) return KSA_ERR_WORKSPACE_TOO_SMALL;
-    DecodePlan plan;
-    if (n_splits != 0) {
-        plan = {n_splits, (int32_t)spans, n_splits > 1 && spans * p->n_kv_heads <= 256};
-    } else {
-        plan = plan_decode(p, most_rows(p, kind));
-        const int64_t fit = (int64_t)(workspace_bytes / record_bytes(p));   // at least one per sequence
-        if (plan.n_splits == 0)
-            plan.n_spans = (int32_t)std::min<int64_t>(plan.n_spans, fit);
-        else if (plan.n_spans > fit)
-            plan.n_splits = (int32_t)(fit / p->batch), plan.n_spans = p->batch * plan.n_splits;
-    }
+    DecodePlan plan = {n_splits, (int32_t)spans, n_splits > 1 && spans * p->n_kv_heads <= 256};
+    if (n_splits == 0)
+        plan = plan_decode(p, most_rows(p, kind), std::min<int64_t>(most_spans(p), workspace_bytes / record_bytes(p)));
     KsaDecodeLaunch a;
     default_strides(a.cache_strides, cache_strides, p->n_kv_heads, rows, p->head_dim);
     if (!strides_ok(a.cache_strides)) return KSA_ERR_INVALID_ARG;

@@ -165,7 +165,7 @@ __device__ __forceinline__ float swap8(float x) {   // lane l ^ 8: row_ror 8
 
 // Spans dealt by length: how the n_spans of a KV head are shared out among at most 64 sequences; lane l holds sequence l's part.
 // Sequence b takes n_b = max(1, ceil(N_b / per)) of them, `per` nearly the smallest for which they are enough.  With T rows in all,
-// per = T / (n_spans - batch) always is: sum(n_b) <= T / per + batch.  The merge kernel works the same out again from the same numbers.
+// per = T / (n_spans - batch) always is: sum(n_b) <= T / per + batch (plan_decode() gives two and more per sequence).  The merge kernel works the same out again from the same numbers.
 struct Deal {
     Ranges R;
     int n, behind;   // spans of the sequence; of it and of those in front of it

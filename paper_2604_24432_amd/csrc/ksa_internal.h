@@ -125,7 +125,7 @@ struct KsaDecodeLaunch {
     int64_t cache_strides[3];
     float *workspace;
     int32_t n_splits;         // spans per sequence; 0: dealt by the sequences' lengths (batch <= 64)
-    int32_t n_spans;          // spans per KV head: batch * n_splits, or those to deal (at least one per sequence)
+    int32_t n_spans;          // spans per KV head: batch * n_splits, or those to deal (at least two per sequence)
     bool wide;                // workgroups of 1024 threads (512 with eight query heads per KV head) instead of 256
     int32_t summary_capacity;
     int32_t kind;             // KSA_ROW_TEXT: pos is a text index; KSA_ROW_SUMMARY: pos is a summary ordinal
