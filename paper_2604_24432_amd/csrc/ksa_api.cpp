@@ -196,7 +196,8 @@ struct DecodePlan {
  * `want`: short launches want a workgroup per unit (12/12 heads, d 64, 2000 rows: 256 7.6, 512 8.9); with more rows the loads in flight count:
  * two on each unit with four heads per KV head (batch 4, 3808 rows: 256 18.0, 512 15.4, 768 16.3), three with one or two (8/4 heads, batch
  * 8, 2176 rows: 256 wide 11.2, 512 11.1, 768 10.7), a wide one with eight (batch 64, 1128 rows: 256 wide 12.9, 512 14.0).  Spans of
- * 24 rows at least, and up to 64 per sequence, which the merge kernel takes at once (8/1 heads, batch 1, 3808 rows: 64 10.4, 192 13.3).
+ * about 24 rows at least (16 where that fills a round better), and up to 64 per sequence, which the merge kernel takes at once (8/1 heads,
+ * batch 1, 3808 rows: 64 10.4, 192 13.3); more have 768 rows or, within one round, 512 (2/1 heads, batch 3, 50000 rows: 255 19.4, 291 22.4).
  *
  * From a million rows on the spans are dealt by the sequences' lengths, which costs 1 - 1.5 to work out: lengths 1 : 4, batch 64 at 128K 511 ->
  * 457, batch 16 133 -> 118, batch 8 in the paper's form 74.5 -> 68.7; all alike 658 -> 652, 173 -> 169, 97 -> 92 (before: about 1536 workgroups, none below
@@ -234,13 +235,19 @@ DecodePlan plan_decode(const ksa_params *p, int64_t rows, int64_t fit) {
         const int64_t spans = want / p->n_kv_heads;
         return {0, (int32_t)std::min<int64_t>(spans >= enough ? spans : (heads <= 2 ? 3 : 2) * p->batch, fit), false};
     }
+    const int64_t most = std::max({(int64_t)64, rows / 768, std::min(rows / 512, 256 / groups)});
+    const int64_t hi = std::max<int64_t>(1, std::min({3 * want / (2 * groups), most, fit / p->batch}));
+    const int64_t lo = std::max<int64_t>(1, std::min(want / groups, hi) / 2);
     int64_t best = 1;
     double best_score = -1e30;
-    for (int64_t s = std::max<int64_t>(1, want / (2 * groups)); s <= std::max<int64_t>(1, 3 * want / (2 * groups)); ++s) {
-        const double n = (double)(s * groups), fill = n / (256.0 * std::ceil(n / 256.0)), score = fill - 0.25 * std::fabs(std::log(n / want));
+    auto look_at = [&](int64_t s) {
+        const int64_t n = s * groups, places = (n + 255) / 256 * 256;
+        const double score = (double)n / places - 0.25 * std::fabs(std::log((double)n / want));
         if (score > best_score) best = s, best_score = score;
-    }
-    best = std::min({best, std::max<int64_t>(64, rows / 512), fit / p->batch});
+    };
+    // (from 64 workgroups on the score rises up to the last number of a round; below, up to `want`)
+    for (const int64_t s : {want / groups, want / groups + 1}) look_at(std::min(std::max(s, lo), hi));
+    for (int64_t round = (lo * groups + 255) / 256; round <= (hi * groups + 255) / 256; ++round) look_at(std::min(std::max(256 * round / groups, lo), hi));
     return {(int32_t)best, (int32_t)(p->batch * best), wide(best)};
 }
 

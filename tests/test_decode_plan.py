@@ -80,3 +80,19 @@ def test_a_workspace_of_the_asked_size_changes_nothing(plans):
     for c, own, static in zip(calls, plans(calls), plans([(STATIC, *c[1:]) for c in calls])):
         if static["status"] == 0:
             assert all(own[x] == static[x] for x in ("n_splits", "n_spans", "wide")), c
+
+
+def test_spans_are_not_too_short(plans):
+    """More than 64 spans of a sequence have 768 rows each, or 512 within one round of workgroups; and none has less than 16."""
+    calls = list(random_calls(20000, 3))
+    for c, got in zip(calls, plans(calls)):
+        n, groups, rows = got["n_splits"], c[2] * c[4], rows_of(c)
+        if n > 1:
+            assert n <= max(64, rows // 768, min(rows // 512, 256 // groups)) and n * 16 <= rows, (c, got)
+
+
+@pytest.mark.parametrize("shape,workgroups", [((3, 2, 1, 50000), 255), ((3, 1, 1, 93328), 255), ((3, 2, 1, 76664), 255), ((1, 8, 8, 35000), 512)])
+def test_the_last_round_is_full_with_few_long_sequences(plans, shape, workgroups):
+    batch, heads, kv_heads, rows = shape
+    got, = plans([call(batch, heads, kv_heads, 128, rows)])
+    assert got["n_spans"] * kv_heads == workgroups
