@@ -195,13 +195,20 @@ struct DecodePlan {
  * 20.9, 320 22.8, 384 21.3, 512 19.7): the number of spans is taken near `want` where the last round is best filled.
  * `want`: short launches want a workgroup per unit (12/12 heads, d 64, 2000 rows: 256 7.6, 512 8.9); with more rows the loads in flight count:
  * two on each unit with four heads per KV head (batch 4, 3808 rows: 256 18.0, 512 15.4, 768 16.3), three with one or two (8/4 heads, batch
- * 8, 2176 rows: 256 wide 11.2, 512 11.1, 768 10.7), a wide one with eight (batch 64, 1128 rows: 256 wide 12.9, 512 14.0).  Spans of
+ * 8, 2176 rows: 256 wide 11.2, 512 11.1, 768 10.7), five with one and enough pairs (8/8 heads, batch 16, 3120 rows: 768 27.2, 1280 26.4; batch 1,
+ * 118744 rows: 768 77.8, 1280 79.1), a wide one with eight (batch 64, 1128 rows: 256 wide 12.9, 512 14.0) up to 250 000 rows (64/8 heads, batch 1,
+ * 230 000: 256 27.7, 512 29.5; batch 4 26.6, 25.9; 280 000: 30.8, 29.4).  One sequence takes no more than that however long it is (850 000
+ * rows: 64/8 heads 512 74.9, 1536 88.6; 32/8 72.0, 78.7).  Spans of
  * about 24 rows at least (16 where that fills a round better), and up to 64 per sequence, which the merge kernel takes at once (8/1 heads,
  * batch 1, 3808 rows: 64 10.4, 192 13.3); more have 768 rows or, within one round, 512 (2/1 heads, batch 3, 50000 rows: 255 19.4, 291 22.4).
  *
- * From a million rows on the spans are dealt by the sequences' lengths, which costs 1 - 1.5 to work out: lengths 1 : 4, batch 64 at 128K 511 ->
- * 457, batch 16 133 -> 118, batch 8 in the paper's form 74.5 -> 68.7; all alike 658 -> 652, 173 -> 169, 97 -> 92 (before: about 1536 workgroups, none below
- * 768 rows).  Batch 64: 512 workgroups 537, 768 507, 1536 457.  Two and more per sequence, or there is nothing to deal: with one and two heads
+ * Spans dealt by the sequences' lengths cost 1 - 1.5 to work out.  Lengths 1 : 4, batch 64 at 128K 511 -> 457, batch 16 133 -> 118, batch 8 in
+ * the paper's form 74.5 -> 68.7; all alike 658 -> 652, 173 -> 169, 97 -> 92 (before: about 1536 workgroups, none below 768 rows).  Batch 64:
+ * 512 workgroups 537, 768 507, 1536 457.  They pay from 800 000 rows on (batch 16, 16/8 heads, 850 000 rows, lengths 1 : 4 / alike: 768 the same
+ * for all 57.6 / 73.5, dealt 50.5 / 70.8), with up to 128 pairs and four or eight heads per KV head from 500 000 (batch 33, 8/2, 760 000 rows 59.3 / 68.1, 512
+ * dealt 48.2 / 69.1; batch 12, 4/1 55.3 / 64.2, 46.4 / 64.9), with two to four sequences from a million (batch 4, 32/8, 700 000 rows 47.2 / 61.0, 48.1 /
+ * 61.7); more than 64 sequences are never dealt and take 1536 workgroups from 800 000 rows on (batch 96, 16/4, 3 million rows 208, 768 224).
+ * Two and more per sequence, or there is nothing to deal: with one and two heads
  * per KV head three where it would be less than two and a half (lengths 1 : 4 / alike, batch 60, 32/16, 1600 rows, 1.3 99.9 / 126, three 88.0 /
  * 127; batch 33, 32/16, 9000 rows, 2.4 249 / 411, three 246 / 374; but batch 64, 16/8, 6400 rows, 2.5 170 / 248, three 190 / 262), with more
  * heads two (batch 28, 128/32, 3500 rows, 1.7 177 / 271, two 178 / 250, three 178 / 263).  From 1024 pairs on the workgroups balance each
@@ -222,13 +229,14 @@ DecodePlan plan_decode(const ksa_params *p, int64_t rows, int64_t fit) {
     if (w <= (groups < 64 ? 256 : 384) || (groups >= 192 && groups <= 256 && rows < 1536) ||
         (groups > 256 && rows < (groups >= 512 ? 1536 : 768)))
         return {1, p->batch, groups <= 256 && (wide(1) || (w >= 384 && groups >= 192))};
-    int64_t want = total < 30000 ? 256 : heads <= 2 ? (total < 65000 ? 512 : heads == 2 || total < 130000 ? 768 : 1280)
+    int64_t want = total < 30000 ? 256 : heads <= 2 ? (total < 65000 ? 512 : heads == 2 || groups < 16 || total < 130000 ? 768 : 1280)
                                                     : heads == 4 || total > 250000 ? 512 : 256;
     const int64_t enough = heads <= 2 ? 5 * p->batch / 2 : 2 * p->batch;   // dealt spans per KV head
-    const bool deal = total >= 1000000 && p->batch > 1 && p->batch <= 64 && groups < 1024 && fit >= enough;
+    const int64_t large = p->batch <= 4 ? 1000000 : heads >= 4 && groups <= 128 ? 500000 : 800000;
+    const bool deal = total >= large && p->batch > 1 && p->batch <= 64 && groups < 1024 && fit >= enough;
     if (deal)
-        want = heads == 1 ? 1536 : heads == 2 ? (groups <= 256 ? 768 : 1280) : groups <= 64 ? 512 : groups <= 128 ? 768 : 1536;
-    else if (total >= 800000)
+        want = heads == 1 ? 1536 : heads == 2 ? (groups <= 256 ? 768 : 1280) : groups <= 64 || total < 1000000 ? 512 : groups <= 128 ? 768 : 1536;
+    else if (total >= 800000 && p->batch > 4)
         want = groups >= 1024 ? 2048 : 1536;
     want = std::max<int64_t>(std::min(want, total / 24), 1);
     if (deal) {
@@ -237,7 +245,7 @@ DecodePlan plan_decode(const ksa_params *p, int64_t rows, int64_t fit) {
     }
     const int64_t most = std::max({(int64_t)64, rows / 768, std::min(rows / 512, 256 / groups)});
     const int64_t hi = std::max<int64_t>(1, std::min({3 * want / (2 * groups), most, fit / p->batch}));
-    const int64_t lo = std::max<int64_t>(1, std::min(want / groups, hi) / 2);
+    const int64_t lo = std::max<int64_t>(1, std::min({want / (2 * groups), hi, std::max<int64_t>(64, hi / 2)}));
     int64_t best = 1;
     double best_score = -1e30;
     auto look_at = [&](int64_t s) {

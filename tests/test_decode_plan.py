@@ -66,7 +66,8 @@ def test_dealt_spans_are_several_per_sequence(plans):
 # batch, heads, KV heads, rows -> spans per sequence (0: dealt) that were the fastest or level with them; see the comment at plan_decode
 @pytest.mark.parametrize("shape,n_splits,n_spans", [((64, 32, 32, 1600), 1, 64), ((64, 64, 32, 2096), 1, 64), ((33, 64, 32, 4000), 2, 66), ((44, 128, 32, 3500), 2, 88),
                                                     ((64, 16, 16, 1600), 2, 128), ((33, 32, 16, 9000), 0, 99), ((60, 32, 16, 1600), 0, 180),
-                                                    ((64, 16, 8, 6400), 0, 160),
+                                                    ((64, 16, 8, 6400), 0, 160), ((33, 8, 2, 11496), 0, 256), ((8, 32, 8, 9352), 0, 64),
+                                                    ((16, 16, 8, 6640), 0, 96), ((96, 16, 4, 7808), 4, 384), ((4, 32, 8, 21872), 16, 64),
                                                     ((28, 128, 32, 3500), 0, 56), ((64, 32, 8, 16504), 0, 192), ((8, 32, 8, 17000), 0, 64)],
                          ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else None)
 def test_many_sequences_and_heads(plans, shape, n_splits, n_spans):
@@ -91,7 +92,8 @@ def test_spans_are_not_too_short(plans):
             assert n <= max(64, rows // 768, min(rows // 512, 256 // groups)) and n * 16 <= rows, (c, got)
 
 
-@pytest.mark.parametrize("shape,workgroups", [((3, 2, 1, 50000), 255), ((3, 1, 1, 93328), 255), ((3, 2, 1, 76664), 255), ((1, 8, 8, 35000), 512)])
+@pytest.mark.parametrize("shape,workgroups", [((3, 2, 1, 50000), 255), ((3, 1, 1, 93328), 255), ((3, 2, 1, 76664), 255),
+                                              ((1, 64, 8, 118744), 512), ((1, 32, 8, 118744), 512), ((3, 1, 1, 316664), 768), ((1, 8, 8, 35000), 512)])
 def test_the_last_round_is_full_with_few_long_sequences(plans, shape, workgroups):
     batch, heads, kv_heads, rows = shape
     got, = plans([call(batch, heads, kv_heads, 128, rows)])
