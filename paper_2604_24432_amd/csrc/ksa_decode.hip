@@ -165,7 +165,10 @@ __device__ __forceinline__ float swap8(float x) {   // lane l ^ 8: row_ror 8
 
 // Spans dealt by length: how the n_spans of a KV head are shared out among at most 64 sequences; lane l holds sequence l's part.
 // Sequence b takes n_b = max(1, ceil(N_b / per)) of them, `per` nearly the smallest for which they are enough.  With T rows in all,
-// per = T / (n_spans - batch) always is: sum(n_b) <= T / per + batch (plan_decode() gives two and more per sequence).  The merge kernel works the same out again from the same numbers.
+// per = T / (n_spans - batch) always is: sum(n_b) <= T / per + batch (plan_decode() gives two and more per sequence).
+// The merge kernel works the same out again, and every instantiation of both has to come to the same numbers: one span more or less for
+// one sequence and the merge would read the records of others.  So nothing here is left to the compiler's choice: sums in a given order,
+// and no product fused into a sum.
 struct Deal {
     Ranges R;
     int n, behind;   // spans of the sequence; of it and of those in front of it
@@ -173,6 +176,7 @@ struct Deal {
 template <int CTRL, int ROWS>
 __device__ __forceinline__ int dpp_scan(int x) { return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false); }
 __device__ __forceinline__ Deal deal_spans(const DecodeArgs &a) {
+#pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
     const bool any = lane < a.batch;
     Deal d;
