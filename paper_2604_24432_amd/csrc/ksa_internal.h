@@ -2,6 +2,8 @@
 #ifndef KSA_INTERNAL_H_
 #define KSA_INTERNAL_H_
 
+#include <algorithm>
+#include <numeric>
 #include <vector>
 
 #include "ksa.h"
@@ -78,6 +80,28 @@ inline int64_t ksa_mixed_tile_rows(int64_t c, int64_t m, int64_t q_rows) {
     auto chunks = [&](int64_t rows, int64_t per) { return (rows + per - 1) / per; };
     const int64_t text = chunks(63, m) + chunks(63, c) + chunks(q_rows, c), sums = chunks(q_rows, m) + chunks(63, c);
     return ((text > sums ? text : sums) + 1) * (c + m);
+}
+
+// About how many keys the longest list of one of its query tiles holds, none less.  A text tile's text begins C chunks before the chunk of
+// its first row, whose place in that chunk is a multiple of gcd(c, q_rows); a summary tile sees the chunks of its rows and their summaries.
+inline int64_t ksa_longest_list(int64_t c, int64_t m, int64_t C, int64_t n_text, int64_t n_sum, int64_t q_rows) {
+    const int64_t chunks = (n_text - 1) / c;
+    const int64_t text = (chunks > C ? (chunks - C) * m : 0) + std::min(n_text, C * c + q_rows + c - std::gcd(c, q_rows));
+    if (m <= 0) return text;
+    const int64_t rows = std::min(n_sum, q_rows + m - std::gcd(m, q_rows));
+    return std::max(text, std::min((rows + m - 1) / m * c, n_text) + rows);
+}
+// Whether a launch of that kernel (grad: of the one for dQ) takes eight waves per workgroup, the second four every other key tile.  With no
+// more workgroups than compute units that halves the chain of tiles.  us, four waves / eight, forward (backward): head_dim 64 12/4 heads,
+// 2000 tokens, c 48, m 6 30.5 / 23.4 (78.7 / 69.2), 2 x 1024, c 64, m 8 25.3 / 21.2 (58.2 / 51.0), 1 head, 512 tokens 12.1 / 11.6 (29.9 /
+// 28.3); head_dim 128 16/16 heads, 1024 tokens 31.1 / 26.7 (67.8 / 61.7), 1 head, 3000 tokens 17.7 / 16.8 (61.1 / 60.0), but with few tiles
+// in a list (1 head, window of 255) 13.8 / 14.3, and with four heads per workgroup, whose waves all read the same keys, 512 tokens 15.9 /
+// 16.6 (58.2 / 59.0), 700 in the paper's form 22.6 / 22.0 (81.2 / 81.4).  Lists of one key tile leave nothing to the second four (head_dim 64,
+// 32/8 heads, 48 tokens, c 48 5.56 / 6.52 (23.6 / 24.0), c 8, window of 128 6.11 / 7.12 (19.8 / 20.3)), a few keys more hardly anything forward
+// (70 keys 6.38 / 6.77 (28.4 / 28.0), but 80 keys, 700 tokens, 12/4 heads, c 16, window of 32 8.80 / 8.27 (28.1 / 27.1)).
+inline bool ksa_two_teams(int head_dim, int64_t n_wg, int head_stack, int64_t longest_list, bool grad) {
+    if (n_wg > 256) return false;
+    return head_dim == 64 ? longest_list > (grad ? 64 : 72) : head_stack == 1 && longest_list > 8 * 64;
 }
 
 struct KsaPrefillBwdLaunch {

@@ -78,7 +78,7 @@ struct DirectArgs {
     int32_t text_tiles, sum_tiles;      // query tiles of the two spaces
     int32_t text_before;                // text tiles whose key lists are longer than a summary tile's
     int32_t self_only;
-    int32_t longest_list;               // about so many keys are in the longest list of a query tile
+    int32_t longest_list;               // keys in the longest list of a query tile
     int32_t mixed_tiles;                // a key tile may hold the last summaries and the first text rows of a list
     int64_t aug_len;
     float scale_log2e;
@@ -742,7 +742,7 @@ __global__ __launch_bounds__(NW * 64, D == 128 ? 2 : 3) void ksa_bwd_dq_direct_k
     __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * Tile<D>::BYTES];
     direct<D, true, 1>(a, lds);
 }
-// ... and with eight waves in a workgroup (two_teams())
+// ... and with eight waves in a workgroup (ksa_two_teams() in ksa_internal.h)
 template <int D>
 __global__ __launch_bounds__(2 * NW * 64, 2) void ksa_prefill_teams_kernel(const DirectArgs a) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * 4 * Tile<D>::BYTES];
@@ -783,26 +783,20 @@ __global__ __launch_bounds__(256) void ksa_knorm_parts_kernel(const DirectArgs a
         out[((int64_t)b * a.n_kv_heads + hkv) * gridDim.x + part] = fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
 }
 
-// A launch with no more workgroups than compute units takes eight waves each (TEAMS = 2), which halves the chain of tiles.  us, four waves /
-// eight, forward (backward): head_dim 64 12/4 heads, 2000 tokens, c 48, m 6 30.5 / 23.4 (78.7 / 69.2), 2 x 1024, c 64, m 8 25.3 / 21.2
-// (58.2 / 51.0), 1 head, 512 tokens 12.1 / 11.6 (29.9 / 28.3); head_dim 128 16/16 heads, 1024 tokens 31.1 / 26.7 (67.8 / 61.7), 1 head, 3000
-// tokens 17.7 / 16.8 (61.1 / 60.0), but with few tiles in a list (1 head, window of 255) 13.8 / 14.3, and with four heads per workgroup, whose
-// waves all read the same keys, 512 tokens 15.9 / 16.6 (58.2 / 59.0), 700 in the paper's form 22.6 / 22.0 (81.2 / 81.4).
-bool two_teams(const DirectArgs &a, int head_dim, int64_t n_wg) {
-    return n_wg <= 256 && (head_dim == 64 || (a.stack == 1 && a.longest_list > 8 * BN));
-}
+bool two_teams(const DirectArgs &a, int head_dim, int64_t n_wg, bool grad) { return ksa_two_teams(head_dim, n_wg, a.stack, a.longest_list, grad); }
 
 // Short texts: a launch of its own for the K norms takes 3 - 4 us, a workgroup reads all rows of its head in less.  us, norms before / by
 // every workgroup: head_dim 64 (eight waves) 200 tokens 10.7 / 8.8, 512 11.1 / 10.0, 1500 rows 11.1 / 10.7, 3375 12.9 / 15.2; head_dim 128, eight
-// waves 787 rows 19.3 / 18.7, 1152 25.7 / 26.0, four waves 216 rows 14.6 / 13.1, 576 15.3 / 15.5.
+// waves 787 rows 19.3 / 18.7, 1152 25.7 / 26.0, four waves 216 rows 14.6 / 13.1, 576 15.3 / 15.5; head_dim 64, four waves (lists of one key tile)
+// 900 rows 8.2 / 7.2, 1280 8.2 / 8.0.
 bool takes_own_norms(const DirectArgs &a, int head_dim, int64_t n_wg) {
-    return n_wg <= 256 && a.aug_len * head_dim <= (two_teams(a, head_dim, n_wg) ? 100 : 56) * 1024;
+    return n_wg <= 256 && a.aug_len * head_dim <= (two_teams(a, head_dim, n_wg, false) ? 100 : head_dim == 64 ? 80 : 56) * 1024;
 }
 
 template <int D>
 void launch(const DirectArgs &a, float *parts, int batch, int64_t n_wg, hipStream_t st) {
     if (a.knorm_parts && !a.own_norms) hipLaunchKernelGGL(ksa_knorm_parts_kernel<D>, dim3(a.norm_parts, a.n_kv_heads, batch), dim3(256), 0, st, a, parts);
-    if (two_teams(a, D, n_wg))
+    if (two_teams(a, D, n_wg, false))
         hipLaunchKernelGGL(ksa_prefill_teams_kernel<D>, dim3((unsigned)n_wg), dim3(2 * NW * 64), 0, st, a);
     else
         hipLaunchKernelGGL(ksa_prefill_direct_kernel<D>, dim3((unsigned)n_wg), dim3(NW * 64), 0, st, a);
@@ -844,9 +838,7 @@ int64_t fill_lists(DirectArgs &a, const ksa_params &p, int32_t head_stack, int64
             if (longer(mid)) hi = mid; else lo = mid + 1;
         }
         a.text_before = a.text_tiles - lo;
-        const int64_t chunks = (a.n_text - 1) / a.c, text = (chunks > a.C ? (chunks - a.C) * a.m : 0) +
-                                                            std::min<int64_t>(a.n_text, (int64_t)(a.C + 1) * a.c + a.q_rows);
-        a.longest_list = (int32_t)std::max(text, std::min<int64_t>(sum_keys, (int64_t)a.n_text + a.n_sum));
+        a.longest_list = (int32_t)ksa_longest_list(a.c, a.m, a.C, a.n_text, a.n_sum, a.q_rows);
     }
     a.self_only = (p.flags & KSA_FLAG_SUMMARY_SELF_ONLY) ? 1 : 0;
     a.mixed_tiles = ksa_mixed_tile_rows(a.c, a.m, a.q_rows) * a.ks[1] * 2 < ((int64_t)1 << 32) ? 1 : 0;   // 32-bit byte offsets
@@ -904,7 +896,7 @@ int ksa_launch_dq_direct(const KsaPrefillBwdLaunch &L, const float *stats, void 
     if (n_wg >= (int64_t)1 << 30) return KSA_ERR_UNSUPPORTED;
     a.nt_pad = (a.n_text + 63) / 64 * 64, a.ns_pad = (a.n_sum + 63) / 64 * 64;
     a.scale = L.p.softmax_scale, a.scale_log2e = L.p.softmax_scale * 1.4426950408889634f;
-    const bool two = two_teams(a, L.p.head_dim, n_wg);
+    const bool two = two_teams(a, L.p.head_dim, n_wg, true);
     const dim3 grid((unsigned)n_wg), block(NW * 64 * (two ? 2 : 1));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (L.p.head_dim == 128 && two)
