@@ -80,3 +80,29 @@ def test_dealt_spans(shape, alike):
     assert bool(torch.isnan(o2[1:B - 1]).all()) and bool(torch.isnan(lse2[1:B - 1]).all())
     for b in (0, B - 1):
         compare(f"  sequence {b} beside invalid ones", o2[b], lse2[b], ref[b], ref_lse[b])
+
+
+@pytest.mark.parametrize("shape", [
+    # B, Hq, Hkv, d, rows: spans that the library deals
+    (9, 8, 2, 128, 31000),      # four query heads per KV head: 256 for 9 sequences
+    (6, 4, 4, 128, 35000),      # one
+    (7, 16, 2, 128, 40000),     # eight
+    (33, 32, 16, 64, 1600),     # 99 for 33
+    (50, 16, 16, 64, 1600),     # 150 for 50
+    (64, 16, 8, 64, 1600),      # 160 for 64
+], ids=lambda s: "x".join(map(str, s)))
+def test_dealt_spans_of_ragged_batches(shape):
+    """Lengths from one row to a full cache, with the workspace of the asked size and of the least one, and sequences that read nothing."""
+    B, Hq, Hkv, d, rows = shape
+    c, m, C = 64, 8, 1
+    n = (rows - 128) // m * c
+    pos = [min(n - 1, (n - 1) * (b + 1) // B + 17 * (b % 3)) for b in range(B)]
+    pos[1], pos[B // 2] = 0, 70
+    p, q, kc, vc, pos_t, ref, ref_lse = inputs(B, Hq, Hkv, d, n, c, m, C, pos, seed=B)
+    compare(f"{shape}", *K.ksa_decode_fwd(p, q, kc, vc, pos_t), ref, ref_lse)
+    compare("  least workspace", *K.ksa_decode_fwd(p, q, kc, vc, pos_t, workspace=least_workspace(p)), ref, ref_lse)
+    pos_t[2:4] = -1
+    o, lse = K.ksa_decode_fwd(p, q, kc, vc, pos_t)
+    assert bool(torch.isnan(o[2:4]).all()) and bool(torch.isnan(lse[2:4]).all())
+    rest = [b for b in range(B) if b not in (2, 3)]
+    compare("  beside invalid ones", o[rest], lse[rest], ref[rest], ref_lse[rest])
