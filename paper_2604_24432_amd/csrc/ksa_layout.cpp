@@ -328,8 +328,10 @@ void dkv_steps(const ksa_params &p, DkvTiles &tiles, DkvTiles &wide) {
 // 32-row kernel: window 1024 over 2048 tokens, 16/4 heads, d 64 115 / 141, 8/1 heads, d 128 162 / 186; paper's form 2048 tokens
 // 16/4 heads 211 / 226, dense causal 4096 tokens 358 / 379; 8192 tokens in chunks, gradients packed into one tensor, 32/8
 // heads 1049 / 1168, d 64 703 / 856; but chunks of 64, 1000 tokens, 16/16 heads 84 / 70, 2 x 4096, 32/8 347 / 292, 20003 in the
-// paper's form 1460 / 1318.  Over 848 layouts, each dense and packed (200 - 32K tokens, ten chunk shapes, of one to eight heads
-// per KV head), the choice costs 0.1 % against the better kernel of each, 5.7 % at most.
+// paper's form 1460 / 1318.  Those figures, and the ratios, are from before the 32-row kernel planned its requests in LDS, which takes
+// a tenth off its steps: now 114 / 129, 160 / 175, 208 / 213, dense causal 344 / 345, packed 1022 / 1060, 686 / 780, 1000 tokens 79.5 / 62,
+// 2 x 4096 322 / 254, 20003 1373 / 1184.  Over 180 layouts (200 - 16K tokens) the choice costs 1.5 % against the better kernel of
+// each, all of it where the 64-row kernel is taken, 18 % at most (4/4 heads, d 64, 3 x 231 tokens, c 48, m 6, 29.1 / 24.6).
 constexpr int64_t DKV_STEPS_PER_START = 8, DKV_STEPS_OF_SUMS = 12, DKV_MIN_STEPS = 16;
 void build_dkv(ksa_layout &lay) {
     const ksa_params &p = lay.p;

@@ -17,7 +17,7 @@
 // MFMAs, the row offsets kept from tile to tile and the order of the query tiles did (together 10 - 30 %).  Of a workgroup's 20 us at
 // 4K tokens 2.7 pass until its first tile is requested, 2.7 until that tile is there, 13.2 in the loop (6 tiles), 1.6 in its end;
 // outside the tile loops a wave issued some 1550 of its 2620 vector instructions: row norms as dot products of pairs, the largest K norm
-// by lane moves, output rows as offsets from one address and masks by constants where every row sees a tile's beginning take 2.5 % off
+// by lane moves, output rows as offsets from one address and masks by constants where every row sees a tile's beginning take 2.8 % off
 // (91.8 -> 89.2 us, window of 1024 at 16K 314.6 -> 311.2).  Workgroups that take several query tiles and request the next one's rows
 // ahead were no faster (the other workgroup of the unit fills those times already).
 // The line between the two kernels: takes_direct() in ksa_layout.cpp.  dQ (three products per visible pair instead of two)
@@ -25,8 +25,9 @@
 // registers (d 64: 7), outside the blocks that hold its MFMAs.
 //
 // The work of a workgroup follows from its index in closed form (Eq. 3): no schedule is read from memory.  The keys of
-// its query tile form one list (summaries, then text) cut into tiles of 64; tile t sits in LDS buffer t % 2, and tile
-// t + 1 is requested behind the barrier that publishes tile t.  Layout of scores, weights and operands: as in
+// its query tile form one list (summaries, then text) cut into tiles of 64; a team's tiles sit in its two LDS buffers by
+// turns, and its next one is requested behind the barrier that publishes the one before (with two teams: the one after the
+// other team's).  Layout of scores, weights and operands: as in
 // ksa_prefill.hip.
 #include <hip/hip_runtime.h>
 

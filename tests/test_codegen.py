@@ -81,7 +81,8 @@ TILE_LOOPS = [
     ("ksa_prefill.hip", {"ksa_prefill_kernel": 4}, MFMA_STREAM),
     ("ksa_prefill_bwd.hip", {"ksa_bwd_dq_kernel": 1, "ksa_bwd_dkv_kernel": 4}, MFMA_STREAM),
     # (these wait for all their loads; a spill inside the loop would cost time only)
-    ("ksa_prefill_direct.hip", {"ksa_prefill_direct_kernel": 2, "ksa_bwd_dq_direct_kernel": 2}, 8),
+    ("ksa_prefill_direct.hip", {"ksa_prefill_direct_kernel": 2, "ksa_bwd_dq_direct_kernel": 2, "ksa_prefill_teams_kernel": 2,
+                                "ksa_bwd_dq_teams_kernel": 2}, 8),
 ]
 
 

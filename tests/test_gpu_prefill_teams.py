@@ -1,5 +1,5 @@
 """GPU parity of the forward and dQ kernels for short key runs in launches with no more workgroups than compute units, where eight
-waves share a query tile's keys: lists of one tile (nothing for the second four), of an even and an odd number, both softmax
+waves share a query tile's keys: lists of one tile (a launch of its own, or nothing for the second four), of an even and an odd number, both softmax
 references, waves without rows, and rows that are no numbers."""
 import numpy as np
 import pytest
