@@ -197,7 +197,9 @@ struct DecodePlan {
  * two on each unit with four heads per KV head (batch 4, 3808 rows: 256 18.0, 512 15.4, 768 16.3), three with one or two (8/4 heads, batch
  * 8, 2176 rows: 256 wide 11.2, 512 11.1, 768 10.7), five with one and enough pairs (8/8 heads, batch 16, 3120 rows: 768 27.2, 1280 26.4; batch 1,
  * 118744 rows: 768 77.8, 1280 79.1), a wide one with eight (batch 64, 1128 rows: 256 wide 12.9, 512 14.0) up to 250 000 rows (64/8 heads, batch 1,
- * 230 000: 256 27.7, 512 29.5; batch 4 26.6, 25.9; 280 000: 30.8, 29.4).  One sequence takes no more than that however long it is (850 000
+ * 230 000: 256 27.7, 512 29.5; batch 4 26.6, 25.9; 280 000: 30.8, 29.4).  The other lines, both sides: 30 000 rows, 8/8 heads, batch 1,
+ * 24 000 256 8.5, 512 8.8, 4/1, batch 3 13.6, 14.6, 32/8, batch 4, 36 000 12.5, 11.5; 65 000, 8/8, batch 4, 55 000 512 9.5, 768 10.0, 75 000
+ * 11.1, 10.8; 130 000, the same, 110 000 768 12.6, 1280 13.5, 150 000 15.9, 15.2.  One sequence takes no more than that however long it is (850 000
  * rows: 64/8 heads 512 74.9, 1536 88.6; 32/8 72.0, 78.7).  Spans of
  * about 24 rows at least (16 where that fills a round better), and up to 64 per sequence, which the merge kernel takes at once (8/1 heads,
  * batch 1, 3808 rows: 64 10.4, 192 13.3); more have 768 rows or, within one round, 512 (2/1 heads, batch 3, 50000 rows: 255 19.4, 291 22.4).
